@@ -375,13 +375,13 @@ typedef struct still_bwd_ws_layout {
   size_t dq32;     /* float [B, Hq, N, d]                                                                     */
   size_t dk32, dv32; /* float [B, Hkv, N, d]                                                                  */
   size_t cxq, cxk; /* float [B, Hq, N]        coefficient of x in its own gradient (the norm |x| of Sec. 3.2)   */
-  size_t qt, dot;  /* dtype [B, Hq, d, Npad]  q and dout transposed, zero padded                              */
-  size_t kt;       /* dtype [B, Hkv, d, Npad] k transposed                                                    */
+  size_t qt, dot;  /* float [B, Hq, cap, d]   gradients of the retained keys and values, in routing order     */
+  size_t kt;       /* uint64 [B, Hq, cap/64]  bit = the retained entry is a token                             */
   size_t kret;     /* dtype [B, Hq, cap, d]   retained keys in routing order                                  */
-  size_t krett;    /* dtype [B, Hq, d, cap]   the same, transposed                                            */
+  size_t krett;    /* dtype [B, Hq, cap, d]   retained values                                                 */
   size_t total;
-  int32_t n_pad_t; /* Npad of the three transposed copies above (64 more than the forward workspace's)         */
-  int32_t cap_t;   /* cap of the two retained-key copies (likewise)                                           */
+  int32_t n_pad_t; /* Npad of the forward workspace                                                           */
+  int32_t cap_t;   /* cap of the two retained copies (64 more than the forward workspace's)                   */
 } still_bwd_ws_layout_t;
 STILL_API size_t still_bwd_workspace_bytes(const still_params_t* p);
 STILL_API still_status_t still_bwd_workspace_layout(const still_params_t* p, still_bwd_ws_layout_t* layout);

@@ -851,16 +851,15 @@ void compute_bwd_layout(const still_params_t* p, still_bwd_ws_layout_t* L) {
   L->dv32 = take(kvrows * d * 4);
   L->cxq = take(rows * 4);
   L->cxk = take(rows * 4);
-  // transposed copies with a row stride that is no power of two: their readers fetch 16 bytes from each of 32 rows
-  // at once, and rows a power of two apart would all fall into one memory channel
-  const size_t npt = (size_t)F.n_pad + 64, capt = (size_t)F.cap + 64;
-  L->qt = take(U * d * npt * es);
-  L->dot = take(U * d * npt * es);
-  L->kt = take((size_t)p->B * p->Hkv * d * npt * es);
-  L->kret = take(F.cap ? U * capt * d * es : 0);
-  L->krett = take(F.cap ? U * capt * d * es : 0);
-  L->n_pad_t = (int32_t)npt;
-  L->cap_t = (int32_t)(F.cap ? capt : 0);
+  // retained rows, 64 more than the forward workspace's: the last tile of 128 entries may reach past its capacity
+  const size_t capt = F.cap ? (size_t)F.cap + 64 : 0;
+  L->qt = take(U * capt * d * 4);
+  L->dot = take(U * capt * d * 4);
+  L->kt = take(U * (capt / 64) * 8);
+  L->kret = take(U * capt * d * es);
+  L->krett = take(U * capt * d * es);
+  L->n_pad_t = F.n_pad;
+  L->cap_t = (int32_t)capt;
   L->total = off;
 }
 
@@ -957,31 +956,22 @@ still_status_t bwd_impl(const still_params_t* p, const void* q, const void* k, c
   ra.U = U; ra.N = N; ra.Hq = Hq; ra.d = d;
   if ((e = still::launch_bwd_row_prep(ra, dt, stream)) != hipSuccess) return hip_fail("bwd_row_prep", e);
 
-  // ---- softmax branch: dq (owned rows), dk / dv (atomic adds per key tile).  Its products over rows and keys read
-  // transposed copies: q^T, dout^T, k^T of the sequence, and the retained keys both ways (the prefill's gather
-  // kernel with k in the place of v too).
-  still::TransposeVArgs tq{q, p->q_sb, p->q_st, p->q_sh, bws + BL.qt, nullptr, N, BL.n_pad_t, Hq, d, C, nullptr};
-  still::TransposeVArgs td{dout, p->o_sb, p->o_st, p->o_sh, bws + BL.dot, nullptr, N, BL.n_pad_t, Hq, d, C, nullptr};
-  still::TransposeVArgs tk{k, p->k_sb, p->k_st, p->k_sh, bws + BL.kt, nullptr, N, BL.n_pad_t, Hkv, d, C, nullptr};
-  if ((e = still::launch_transpose_v(tq, dt, B, stream)) != hipSuccess ||
-      (e = still::launch_transpose_v(td, dt, B, stream)) != hipSuccess ||
-      (e = still::launch_transpose_v(tk, dt, B, stream)) != hipSuccess)
-    return hip_fail("bwd transposes", e);
-  still::GatherArgs ga{};
-  ga.k = k; ga.v = k;
+  // ---- softmax branch: dq (owned rows), dk / dv (the local span's, and the retained entries' in routing order)
+  still::BwdGatherArgs ga{};
+  ga.k = k; ga.v = v;
   ga.k_sb = p->k_sb; ga.k_st = p->k_st; ga.k_sh = p->k_sh;
-  ga.v_sb = p->k_sb; ga.v_st = p->k_st; ga.v_sh = p->k_sh;
-  ga.map = map;
-  ga.sel = sel_idx;
+  ga.v_sb = p->v_sb; ga.v_st = p->v_st; ga.v_sh = p->v_sh;
+  ga.map = map; ga.sel = sel_idx;
   ga.nsel = have_sel ? still::retained_rows(ncf, p->lambda, budget) : 0;
   ga.sel_stride = ncf * p->lambda;
-  ga.C = C; ga.lam = p->lambda; ga.rcap = budget; ga.seq_len = nullptr;
-  ga.cap = BL.cap_t; ga.Hq = Hq; ga.d = d; ga.N = N;
-  ga.kret = bws + BL.kret; ga.vrett = bws + BL.krett;
-  if ((e = still::launch_gather(ga, dt, B, stream)) != hipSuccess) return hip_fail("bwd gather", e);
+  ga.cap = BL.cap_t; ga.C = C; ga.lam = have_sel ? p->lambda : 0; ga.Hq = Hq; ga.d = d; ga.N = N;
+  ga.kret = bws + BL.kret; ga.vret = bws + BL.krett;
+  ga.rvalid = reinterpret_cast<unsigned long long*>(bws + BL.kt);
+  if ((e = still::launch_bwd_gather(ga, dt, U, stream)) != hipSuccess) return hip_fail("bwd gather", e);
   still::BwdSaArgs sa{};
-  sa.qt = bws + BL.qt; sa.dot = bws + BL.dot; sa.kt = bws + BL.kt; sa.kret = bws + BL.kret; sa.krett = bws + BL.krett;
-  sa.Np = BL.n_pad_t; sa.cap = BL.cap_t;
+  sa.kret = ga.kret; sa.vret = ga.vret; sa.rvalid = ga.rvalid;
+  sa.cap = BL.cap_t;
+  sa.dkret = f32p(BL.qt); sa.dvret = f32p(BL.dot);
   sa.q = q; sa.k = k; sa.v = v; sa.dout = dout;
   sa.q_sb = p->q_sb; sa.q_st = p->q_st; sa.q_sh = p->q_sh;
   sa.k_sb = p->k_sb; sa.k_st = p->k_st; sa.k_sh = p->k_sh;
@@ -990,10 +980,10 @@ still_status_t bwd_impl(const still_params_t* p, const void* q, const void* k, c
   sa.sel = sel_idx; sa.lse = lse; sa.delta = ra.delta;
   sa.dq32 = f32p(BL.dq32); sa.dk32 = f32p(BL.dk32); sa.dv32 = f32p(BL.dv32);
   sa.map = map;
-  sa.N = N; sa.C = C; sa.lam = have_sel ? p->lambda : 0; sa.rcap = budget; sa.Hq = Hq; sa.Hkv = Hkv; sa.nc = nc;
+  sa.N = N; sa.C = C; sa.lam = have_sel ? p->lambda : 0; sa.rcap = budget; sa.U = U; sa.Hq = Hq; sa.Hkv = Hkv;
   sa.sel_stride = ncf * p->lambda;
-  sa.n_row_tiles = (N + 63) / 64;
-  sa.n_ret_tiles = (still::retained_rows(nc >= 2 ? nc - 2 : 0, sa.lam, budget) + 63) / 64;
+  sa.n_row_tiles = (N + 127) / 128;
+  sa.n_ret_tiles = (still::retained_rows(nc >= 2 ? nc - 2 : 0, sa.lam, budget) + 127) / 128;
   sa.scale = p->scale;
   if ((e = still::launch_bwd_sa(sa, dt, d, B, stream)) != hipSuccess) return hip_fail("bwd_sparse_attention", e);
 
@@ -1098,9 +1088,18 @@ still_status_t bwd_impl(const still_params_t* p, const void* q, const void* k, c
   }
 
   // ---- fp32 sums -> the caller's tensors
-  still::BwdFinishArgs fq{f32p(BL.dq32), dq, q, p->q_sb, p->q_st, p->q_sh, f32p(BL.cxq), 0, map, B, Hq, Hq, N, d};
-  still::BwdFinishArgs fk{f32p(BL.dk32), dk, k, p->k_sb, p->k_st, p->k_sh, f32p(BL.cxk), 1, map, B, Hkv, Hq, N, d};
-  still::BwdFinishArgs fv{f32p(BL.dv32), dv, v, p->v_sb, p->v_st, p->v_sh, nullptr, 0, map, B, Hkv, Hq, N, d};
+  still::BwdFinishArgs fq{};
+  fq.map = map; fq.B = B; fq.Hq = Hq; fq.N = N; fq.d = d; fq.C = C; fq.lam = sa.lam; fq.ncf = ncf;
+  fq.cap = BL.cap_t; fq.sel_stride = sa.sel_stride; fq.n_ret = still::retained_rows(nc >= 2 ? nc - 2 : 0, sa.lam, budget);
+  fq.kmask = la.kmask; fq.sel = sel_idx;
+  still::BwdFinishArgs fk = fq, fv = fq;
+  fq.src = f32p(BL.dq32); fq.dst = dq; fq.x = q; fq.H = Hq; fq.cx = f32p(BL.cxq);
+  fq.s_b = p->q_sb; fq.s_t = p->q_st; fq.s_h = p->q_sh;
+  fk.src = f32p(BL.dk32); fk.dst = dk; fk.x = k; fk.H = Hkv; fk.cx = f32p(BL.cxk); fk.per_kv = 1;
+  fk.s_b = p->k_sb; fk.s_t = p->k_st; fk.s_h = p->k_sh;
+  fv.src = f32p(BL.dv32); fv.dst = dv; fv.x = v; fv.H = Hkv; fv.per_kv = 1;
+  fv.s_b = p->v_sb; fv.s_t = p->v_st; fv.s_h = p->v_sh;
+  if (fq.n_ret > 0) fk.dret = sa.dkret, fv.dret = sa.dvret;
   if ((e = still::launch_bwd_finish(fq, dt, stream)) != hipSuccess ||
       (e = still::launch_bwd_finish(fk, dt, stream)) != hipSuccess ||
       (e = still::launch_bwd_finish(fv, dt, stream)) != hipSuccess)

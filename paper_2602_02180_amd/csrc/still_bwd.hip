@@ -16,10 +16,8 @@
 //        du = phi+ (dphi+ - <phi+, dphi+>) - phi- (dphi- - <phi-, dphi->)
 //        df = (|x| / |f|) (du - fh <fh, du>),  fh = f / |f|;   dx = df W^T + <fh, du> x / |x|;   dW = x^T df
 //
-// This first version keeps every step a separate, simple kernel: the sparse branch as tile kernels (one that owns
-// query rows and produces dq, one that owns key tiles and produces dk, dv), the linear branch as a sequence of
-// batched products on one generic MFMA tile kernel with row-wise kernels between them, intermediates in the
-// workspace.  All sums are fp32; operands of the matrix core are in the storage type.
+// The softmax branch is in still_bwd_sa.hip.  The linear branch is a sequence of batched products on one generic MFMA
+// tile kernel with row-wise kernels between them, intermediates in the workspace.  All sums are fp32; operands of the matrix core are in the storage type.
 #include "still_kernels.h"
 
 namespace still {
@@ -503,8 +501,8 @@ __global__ __launch_bounds__(256) void bwd_dg_kernel(BwdRowArgs a) {
   store8_t<T>(static_cast<T*>(a.dg) + go, r);
 }
 
-// fp32 gradient rows (+ coefficient * x for the |x| path of the NP-Map, summed over the query heads that read the
-// row's head) -> the caller's strided tensors in the storage type
+// fp32 gradient rows (+ coefficient * x for the |x| path of the NP-Map and the rows of the retained entries, both
+// summed over the query heads that read the row's head) -> the caller's strided tensors in the storage type
 template <typename T>
 __global__ __launch_bounds__(256) void bwd_finish_kernel(BwdFinishArgs a) {
   int64_t row;
@@ -528,279 +526,28 @@ __global__ __launch_bounds__(256) void bwd_finish_kernel(BwdFinishArgs a) {
 #pragma unroll
     for (int e = 0; e < 8; ++e) x[e] += coef * xv[e];
   }
+  const int c = t / a.C;
+  if (a.dret != nullptr && c < a.ncf) {
+    // the query heads of the group that retained this token: its entry is its rank among the list's tokens
+    for (int hq = 0; hq < a.Hq; ++hq) {
+      if (a.map.kv[hq] != h) continue;
+      const int64_t unit = (int64_t)b * a.Hq + hq;
+      const int w = t % a.C;
+      const uint32_t* m = a.kmask + (unit * a.ncf + c) * (a.C / 32);
+      if (!((m[w / 32] >> (w & 31)) & 1u)) continue;
+      int e = c * a.lam + __popc(m[w / 32] & ((1u << (w & 31)) - 1u));
+      for (int j = 0; j < w / 32; ++j) e += __popc(m[j]);
+      const int32_t* list = a.sel + unit * a.sel_stride;
+      if (list[e] != t)            // (a list with foreign entries between its tokens)
+        for (e = c * a.lam; list[e] != t; ++e) {}
+      if (e >= a.n_ret) continue;
+      float xr[8];
+      load8_f32(xr, a.dret + (unit * a.cap + e) * a.d + e0);
+#pragma unroll
+      for (int i = 0; i < 8; ++i) x[i] += xr[i];
+    }
+  }
   store8_t<T>(static_cast<T*>(a.dst) + b * a.s_b + (int64_t)t * a.s_t + h * a.s_h + e0, x);
-}
-
-// ---------------------------------------------------------------------------------------------------------
-// Sparse (softmax) branch.  Tiles of 64 query rows x 64 keys, four waves, one 32 x 32 block of logits each.
-// A key tile is either 64 consecutive entries of the head's retained list (routing order) or 64 consecutive tokens of
-// the local span.  Row t of chunk c sees retained entry e when e < n_vis(c) = min((c-1) lambda, budget), and local
-// token j when (c-1) C <= j <= t.
-// Every matrix operand is read from global memory directly in fragment form (a lane's 8 consecutive contraction
-// entries are 16 contiguous bytes): rows of q, k, v, dout for the products that contract over the head dimension,
-// and transposed copies (q^T, dout^T, k^T of the local span, k^T of the retained rows, all [d][tokens], zero padded)
-// for those that contract over rows or keys.  LDS only carries P and dS from the accumulator layout of one product
-// to the operand layout of the next.
-// ---------------------------------------------------------------------------------------------------------
-template <typename T>
-struct BwdTile {
-  static constexpr int PAD = sizeof(T) == 2 ? 8 : 4;
-  static constexpr int LT = 64 + PAD;       // row stride of a [64][64] tile
-};
-
-// acc += sum over 64 contraction entries of X[m][k] Y[n][k]: X an LDS tile [..][LT] (rows xr0 + m), Y rows in global
-// memory (row n of the block at yrow, contraction entries contiguous)
-template <typename T>
-__device__ __forceinline__ void acc64_lds_global(floatx16& acc, const T* X, int xr0, const T* yrow, int l31, int g) {
-  typedef Mma<T> M;
-#pragma unroll
-  for (int s = 0; s < 64 / M::KK; ++s)
-    acc = M::mma(M::load(X + (xr0 + l31) * BwdTile<T>::LT + s * M::KK + g * M::KPL),
-                 M::load(yrow + s * M::KK + g * M::KPL), acc);
-}
-
-template <typename T, int D>
-__global__ __launch_bounds__(256) void bwd_sa_dq_kernel(BwdSaArgs a) {
-  typedef Mma<T> M;
-  constexpr int LT = BwdTile<T>::LT, KS = D / M::KK, DX = D / 64;
-  __shared__ __attribute__((aligned(16))) T dSs[64 * LT];
-  __shared__ float Ls[64], dls[64];
-  __shared__ int toks[64];
-
-  const int unit = blockIdx.y, rt = a.n_row_tiles - 1 - blockIdx.x;   // long rows first
-  const int b = unit / a.Hq, h = unit % a.Hq, kvh = a.map.kv[h];
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int l31 = lane & 31, g = lane >> 5, wr = wave >> 1, wc = wave & 1;
-  const int N = a.N, C = a.C, r0 = rt * 64;
-  const int c = r0 / C;
-  const int n_vis = retained_rows(c >= 1 ? c - 1 : 0, a.lam, a.rcap);
-  const int lo = (c >= 1 ? c - 1 : 0) * C;
-  const int last = min(N - 1, r0 + 63);
-  const int n_ret_tiles = (n_vis + 63) / 64, n_tiles = n_ret_tiles + (last + 1 - lo + 63) / 64;
-
-  const T* kb = static_cast<const T*>(a.k) + b * a.k_sb + kvh * a.k_sh;
-  const T* vb = static_cast<const T*>(a.v) + b * a.v_sb + kvh * a.v_sh;
-  const T* kret = static_cast<const T*>(a.kret) + (int64_t)unit * a.cap * D;
-  const T* krett = static_cast<const T*>(a.krett) + (int64_t)unit * D * a.cap;
-  const T* kt = static_cast<const T*>(a.kt) + ((int64_t)b * a.Hkv + kvh) * D * a.Np;
-  const int32_t* sel = a.sel + (int64_t)unit * a.sel_stride;
-  if (tid < 64) {
-    const int t = r0 + tid;
-    Ls[tid] = t < N ? a.lse[(int64_t)unit * N + t] * kLog2e : 0.f;
-    dls[tid] = t < N ? a.delta[(int64_t)unit * N + t] : 0.f;
-  }
-  // this wave's 32 query rows as A operands, for the whole kernel
-  typename M::frag qf[KS], dof[KS];
-  {
-    const int t = min(r0 + 32 * wr + l31, N - 1);
-    const T* qp = static_cast<const T*>(a.q) + b * a.q_sb + (int64_t)t * a.q_st + h * a.q_sh + g * M::KPL;
-    const T* dp = static_cast<const T*>(a.dout) + b * a.o_sb + (int64_t)t * a.o_st + h * a.o_sh + g * M::KPL;
-#pragma unroll
-    for (int s = 0; s < KS; ++s) {
-      qf[s] = M::load(qp + s * M::KK);
-      dof[s] = M::load(dp + s * M::KK);
-    }
-  }
-  floatx16 dq[DX];
-#pragma unroll
-  for (int j = 0; j < DX; ++j) dq[j] = zero16();
-  const float sc2 = a.scale * kLog2e;
-  const int kcol = 32 * wc + l31;
-
-  for (int ti = 0; ti < n_tiles; ++ti) {
-    const bool ret = ti < n_ret_tiles;
-    const int k0 = ret ? ti * 64 : lo + (ti - n_ret_tiles) * 64;
-    __syncthreads();   // the previous tile's products have read dSs and toks (first trip: Ls, dls are written)
-    if (tid < 64) {
-      int tok;
-      if (ret) {
-        const int e = k0 + tid;
-        tok = e < n_vis ? sel[e] : -1;
-        if (tok < 0 || tok >= N || tok / C != e / a.lam) tok = -1;   // lists are never trusted for addressing
-      } else {
-        tok = k0 + tid < N ? k0 + tid : -1;
-      }
-      toks[tid] = tok;
-    }
-    __syncthreads();
-    const int tok = toks[kcol];
-    const int tokc = tok < 0 ? 0 : tok;
-    const T* krow = (ret ? kret + (int64_t)(k0 + kcol) * D : kb + (int64_t)tokc * a.k_st) + g * M::KPL;
-    const T* vrow = vb + (int64_t)tokc * a.v_st + g * M::KPL;
-    floatx16 s = zero16(), dp = zero16();
-#pragma unroll
-    for (int st = 0; st < KS; ++st) {
-      s = M::mma(qf[st], M::load(krow + st * M::KK), s);
-      dp = M::mma(dof[st], M::load(vrow + st * M::KK), dp);
-    }
-#pragma unroll
-    for (int i = 0; i < 16; ++i) {
-      const int r = 32 * wr + c_row(i, g);
-      const int t = r0 + r;
-      const bool vis = tok >= 0 && t < N && (ret || (tok >= lo && tok <= t));
-      const float p = vis ? fast_exp2(fmaf(s[i], sc2, -Ls[r])) : 0.f;
-      dSs[r * LT + kcol] = from_f32<T>(p * (dp[i] - dls[r]) * a.scale);
-    }
-    __syncthreads();
-    const T* ktile = ret ? krett + k0 : kt + k0;
-    const int64_t kstride = ret ? a.cap : a.Np;
-#pragma unroll
-    for (int j = 0; j < DX; ++j)
-      acc64_lds_global<T>(dq[j], dSs, 32 * wr, ktile + (int64_t)(32 * (wc * DX + j) + l31) * kstride, l31, g);
-  }
-  float* out = a.dq32 + ((int64_t)unit * N) * D;
-#pragma unroll
-  for (int j = 0; j < DX; ++j)
-#pragma unroll
-    for (int i = 0; i < 16; ++i) {
-      const int t = r0 + 32 * wr + c_row(i, g);
-      if (t < N) out[(int64_t)t * D + 32 * (wc * DX + j) + l31] = dq[j][i];
-    }
-}
-
-// LOCAL: one workgroup per (batch, kv head, tile of 64 tokens); it walks the query heads that read this kv head one
-// after the other, so the sums over the group stay in its accumulators and every row of the fp32 gradients is written
-// once, with plain stores (no zero fill is needed before, and the atomic adds of every other step come after).
-// !LOCAL: one workgroup per (batch, query head, tile of 64 retained entries), added atomically at the entries' tokens.
-template <typename T, int D, bool LOCAL>
-__global__ __launch_bounds__(256) void bwd_sa_dkv_kernel(BwdSaArgs a) {
-  typedef Mma<T> M;
-  constexpr int LT = BwdTile<T>::LT, KS = D / M::KK, DX = D / 64;
-  __shared__ __attribute__((aligned(16))) T PTs[64 * LT];     // [key][row]
-  __shared__ __attribute__((aligned(16))) T dSTs[64 * LT];
-  __shared__ float Ls[64], dls[64];
-  __shared__ int toks[64];
-
-  const int ti = blockIdx.x;
-  int b, kvh, h_lo, h_hi;
-  if (LOCAL) {
-    b = blockIdx.y / a.Hkv;
-    kvh = blockIdx.y % a.Hkv;
-    h_lo = 0;
-    h_hi = a.Hq - 1;
-  } else {
-    b = blockIdx.y / a.Hq;
-    h_lo = h_hi = blockIdx.y % a.Hq;
-    kvh = a.map.kv[h_lo];
-  }
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int l31 = lane & 31, g = lane >> 5, wr = wave >> 1, wc = wave & 1;
-  const int N = a.N, C = a.C;
-  const int k0 = ti * 64;
-  int row_lo, row_hi;   // rows that may see a key of this tile: [row_lo, row_hi)
-  if (!LOCAL) {
-    if (a.lam <= 0 || k0 >= retained_rows(a.nc >= 2 ? a.nc - 2 : 0, a.lam, a.rcap)) return;
-    row_lo = (k0 / a.lam + 2) * C;
-    row_hi = N;
-  } else {
-    row_lo = k0;
-    row_hi = min(N, (k0 / C + 2) * C);
-  }
-  if (row_lo >= row_hi) return;
-  const T* kb = static_cast<const T*>(a.k) + b * a.k_sb + kvh * a.k_sh;
-  const T* vb = static_cast<const T*>(a.v) + b * a.v_sb + kvh * a.v_sh;
-  if (tid < 64) {
-    int tok;
-    if (!LOCAL) {
-      const int e = k0 + tid;
-      tok = e < a.sel_stride ? a.sel[((int64_t)b * a.Hq + h_lo) * a.sel_stride + e] : -1;
-      if (tok < 0 || tok >= N || tok / C != e / a.lam) tok = -1;   // lists are never trusted for addressing
-    } else {
-      tok = k0 + tid < N ? k0 + tid : -1;
-    }
-    toks[tid] = tok;
-  }
-  __syncthreads();
-  const int kcol = 32 * wc + l31;
-  const int tok = toks[kcol];
-  // this wave's 32 keys as B operands of the logits and of dy.v, for the whole kernel
-  typename M::frag kf[KS], vf[KS];
-  {
-    const int tokc = tok < 0 ? 0 : tok;
-    const T* kp = kb + (int64_t)tokc * a.k_st + g * M::KPL;
-    const T* vp = vb + (int64_t)tokc * a.v_st + g * M::KPL;
-#pragma unroll
-    for (int s = 0; s < KS; ++s) {
-      kf[s] = M::load(kp + s * M::KK);
-      vf[s] = M::load(vp + s * M::KK);
-    }
-  }
-  floatx16 dk[DX], dv[DX];
-#pragma unroll
-  for (int j = 0; j < DX; ++j) dk[j] = dv[j] = zero16();
-  const float sc2 = a.scale * kLog2e;
-  const int e = k0 + kcol;
-
-  for (int h = h_lo; h <= h_hi; ++h) {
-    if (LOCAL && a.map.kv[h] != kvh) continue;   // uniform
-    const int unit = b * a.Hq + h;
-    const T* qb = static_cast<const T*>(a.q) + b * a.q_sb + h * a.q_sh;
-    const T* dob = static_cast<const T*>(a.dout) + b * a.o_sb + h * a.o_sh;
-    const T* qt = static_cast<const T*>(a.qt) + (int64_t)unit * D * a.Np;
-    const T* dot = static_cast<const T*>(a.dot) + (int64_t)unit * D * a.Np;
-    for (int r0 = row_lo / 64 * 64; r0 < row_hi; r0 += 64) {
-      __syncthreads();   // the previous trip's products have read PTs, dSTs, Ls, dls
-      if (tid < 64) {
-        const int t = r0 + tid;
-        Ls[tid] = t < N ? a.lse[(int64_t)unit * N + t] * kLog2e : 0.f;
-        dls[tid] = t < N ? a.delta[(int64_t)unit * N + t] : 0.f;
-      }
-      floatx16 s = zero16(), dp = zero16();
-      {
-        const int t = min(r0 + 32 * wr + l31, N - 1);
-        const T* qp = qb + (int64_t)t * a.q_st + g * M::KPL;
-        const T* dp_ = dob + (int64_t)t * a.o_st + g * M::KPL;
-#pragma unroll
-        for (int st = 0; st < KS; ++st) {
-          s = M::mma(M::load(qp + st * M::KK), kf[st], s);
-          dp = M::mma(M::load(dp_ + st * M::KK), vf[st], dp);
-        }
-      }
-      __syncthreads();   // Ls, dls visible
-#pragma unroll
-      for (int i4 = 0; i4 < 4; ++i4) {
-        const int rbase = 32 * wr + c_row(4 * i4, g);   // four consecutive rows
-#pragma unroll
-        for (int j = 0; j < 4; ++j) {
-          const int i = 4 * i4 + j;
-          const int r = rbase + j;
-          const int t = r0 + r;
-          const int c = t / C;
-          bool vis = tok >= 0 && t < N;
-          if (!LOCAL) vis = vis && e < retained_rows(c >= 1 ? c - 1 : 0, a.lam, a.rcap);
-          else vis = vis && tok <= t && tok >= (c >= 1 ? c - 1 : 0) * C;
-          const float p = vis ? fast_exp2(fmaf(s[i], sc2, -Ls[r])) : 0.f;
-          PTs[kcol * LT + r] = from_f32<T>(p);
-          dSTs[kcol * LT + r] = from_f32<T>(p * (dp[i] - dls[r]) * a.scale);
-        }
-      }
-      __syncthreads();
-#pragma unroll
-      for (int j = 0; j < DX; ++j) {
-        const int64_t xrow = (int64_t)(32 * (wc * DX + j) + l31) * a.Np + r0;
-        acc64_lds_global<T>(dv[j], PTs, 32 * wr, dot + xrow, l31, g);    // dV[key][x] += P^T dO
-        acc64_lds_global<T>(dk[j], dSTs, 32 * wr, qt + xrow, l31, g);    // dK[key][x] += dS^T Q
-      }
-    }
-  }
-  float* dkb = a.dk32 + ((int64_t)b * a.Hkv + kvh) * N * D;
-  float* dvb = a.dv32 + ((int64_t)b * a.Hkv + kvh) * N * D;
-#pragma unroll
-  for (int j = 0; j < DX; ++j)
-#pragma unroll
-    for (int i = 0; i < 16; ++i) {
-      const int tk = toks[32 * wr + c_row(i, g)];
-      if (tk >= 0) {
-        const int x = 32 * (wc * DX + j) + l31;
-        if (LOCAL) {
-          dkb[(int64_t)tk * D + x] = dk[j][i];
-          dvb[(int64_t)tk * D + x] = dv[j][i];
-        } else {
-          atomicAdd(dkb + (int64_t)tk * D + x, dk[j][i]);
-          atomicAdd(dvb + (int64_t)tk * D + x, dv[j][i]);
-        }
-      }
-    }
 }
 
 // ---------------------------------------------------------------------------------------------------------
@@ -887,19 +634,6 @@ __global__ __launch_bounds__(256) void map_dw_kernel(MapDwArgs a) {
     if (!kept) val = (a.dA[row * a.N + j] - a.rowdot[row]) * __expf(-a.lse[row]);
   }
   static_cast<T*>(a.dw)[((int64_t)unit * a.N + t) * a.Np8 + j] = from_f32<T>(val);
-}
-
-template <typename T, int D>
-hipError_t launch_sa_t(const BwdSaArgs& a, int B, hipStream_t s) {
-  hipLaunchKernelGGL((bwd_sa_dq_kernel<T, D>), dim3(a.n_row_tiles, B * a.Hq), dim3(256), 0, s, a);
-  hipError_t e = hipGetLastError();
-  if (e != hipSuccess) return e;
-  // the local tiles first: they store, everything after them adds
-  hipLaunchKernelGGL((bwd_sa_dkv_kernel<T, D, true>), dim3(a.n_row_tiles, B * a.Hkv), dim3(256), 0, s, a);
-  e = hipGetLastError();
-  if (e != hipSuccess || a.n_ret_tiles == 0) return e;
-  hipLaunchKernelGGL((bwd_sa_dkv_kernel<T, D, false>), dim3(a.n_ret_tiles, B * a.Hq), dim3(256), 0, s, a);
-  return hipGetLastError();
 }
 
 }  // namespace
@@ -1008,12 +742,6 @@ hipError_t launch_attn_map(const AttnMapArgs& a, int dtype, int d, int U, hipStr
     else hipLaunchKernelGGL((attn_map_kernel<float, 64>), grid, dim3(256), 0, s, a);
   }
   return hipGetLastError();
-}
-
-hipError_t launch_bwd_sa(const BwdSaArgs& a, int dtype, int d, int B, hipStream_t s) {
-  if (dtype == 1) return d == 128 ? launch_sa_t<bf16, 128>(a, B, s) : launch_sa_t<bf16, 64>(a, B, s);
-  if (d == 64) return launch_sa_t<float, 64>(a, B, s);
-  return hipErrorInvalidValue;   // fp32 at d = 128 does not fit the tiles in LDS (refused by the host checks)
 }
 
 }  // namespace still

@@ -357,8 +357,12 @@ struct BwdFinishArgs {
   int64_t s_b, s_t, s_h;
   const float* cx;         // nullable [B, Hq, N]: dst += coefficient * x
   int per_kv;              // 1: H counts kv heads, the coefficients of the query heads of a kv head are added up
+  const float* dret;       // nullable [B * Hq, cap, d]: the retained entries' part (per_kv), entry c * lam + slot
+  const uint32_t* kmask;   // [B, Hq, ncf, C/32]: with dret, the tokens of every list
+  const int32_t* sel;      // [B, Hq, sel_stride]
   HeadMap map;
-  int B, H, Hq, N, d;
+  int B, H, Hq, N, d, cap, C, lam, ncf, sel_stride;
+  int n_ret;               // entries that have a gradient (some row sees them)
 };
 struct BwdSaArgs {
   const void* q;
@@ -366,20 +370,33 @@ struct BwdSaArgs {
   const void* v;
   const void* dout;
   int64_t q_sb, q_st, q_sh, k_sb, k_st, k_sh, v_sb, v_st, v_sh, o_sb, o_st, o_sh;
-  const void* qt;          // [U, d, Np]: q transposed, zero padded
-  const void* dot;         // [U, d, Np]: dout transposed
-  const void* kt;          // [B, Hkv, d, Np]: k transposed
   const void* kret;        // [U, cap, d]: retained keys in routing order, zero rows where no token is retained
-  const void* krett;       // [U, d, cap]: the same, transposed
+  const void* vret;        // [U, cap, d]: retained values
+  const unsigned long long* rvalid;   // [U, cap / 64]: bit = the retained entry is a token
   const int32_t* sel;      // [U, sel_stride]: retained entry e is token sel[e] (chunk e / lam)
   const float* lse;        // [U, N]
   const float* delta;      // [U, N]
   float* dq32;             // [U, N, d]
-  float* dk32;             // [B, Hkv, N, d]: stored by the local key tiles, added to by the retained ones
+  float* dk32;             // [B, Hkv, N, d]: the local key tiles' part
   float* dv32;
+  float* dkret;            // [U, cap, d]: gradients of the retained entries
+  float* dvret;
   HeadMap map;
-  int N, Np, cap, C, lam, rcap, Hq, Hkv, nc, sel_stride, n_row_tiles, n_ret_tiles;
+  int N, cap, C, lam, rcap, U, Hq, Hkv, sel_stride;
+  int n_row_tiles, n_ret_tiles;   // tiles of 128 rows / of 128 retained entries that some row sees
   float scale;
+};
+// retained keys and values of every (batch, query head) as rows, for the backward pass
+struct BwdGatherArgs {
+  const void* k;
+  const void* v;
+  int64_t k_sb, k_st, k_sh, v_sb, v_st, v_sh;
+  const int32_t* sel;      // [U, sel_stride]; the first nsel entries are used
+  void* kret;              // [U, cap, d]
+  void* vret;
+  unsigned long long* rvalid;   // [U, cap / 64]
+  HeadMap map;
+  int nsel, sel_stride, cap, C, lam, Hq, d, N;
 };
 struct RopeArgs {
   void* q;                 // nullable [B, N, Hq, d], rotated in place
@@ -401,6 +418,7 @@ hipError_t launch_bwd_np(const BwdNpArgs& a, int dtype, bool backward, hipStream
 hipError_t launch_bwd_colsum(const BwdColsumArgs& a, int dtype, int U, hipStream_t stream);
 hipError_t launch_bwd_revcumsum(float* X, int U, int nc, int64_t L, hipStream_t stream);
 hipError_t launch_bwd_finish(const BwdFinishArgs& a, int dtype, hipStream_t stream);
+hipError_t launch_bwd_gather(const BwdGatherArgs& a, int dtype, int U, hipStream_t stream);
 hipError_t launch_bwd_sa(const BwdSaArgs& a, int dtype, int d, int B, hipStream_t stream);
 struct AttnMapArgs {
   const void* q;

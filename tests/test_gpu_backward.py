@@ -132,6 +132,18 @@ def test_backward_bf16(kw):
     check_backward(w, inp, 63)
 
 
+@pytest.mark.parametrize("kw", [
+    dict(dtype="bf16", d=128, N=31, lam=4),                          # one ragged 32-row tile
+    dict(dtype="bf16", d=128, N=129, lam=4, Hq=4),                   # one row past a 128-row / 128-key workgroup
+    dict(dtype="bf16", d=64, N=64 * 21 + 33, lam=7),                 # 133 visible entries: just past a 128-entry tile
+    dict(dtype="f32", N=64 * 10, lam=16, Hq=3),                      # exactly 128 visible entries
+    dict(dtype="bf16", d=128, C=128, N=128 * 5 - 1, lam=128),        # every token retained, last chunk ragged
+], ids=["n31", "n129", "entries133", "entries128", "all-kept-ragged"])
+def test_backward_at_the_edges_of_the_softmax_tiles(kw):
+    w = small("bwd-edge-" + "-".join(f"{k}{v}" for k, v in kw.items()), **kw)
+    check_backward(w, synth.make_inputs(w, seed=71, with_gate=True), 72)
+
+
 def test_backward_at_the_training_shape_sampled_units():
     """Config c6 (the shape bench.py --backward times: 16 sequences of 1024 tokens, 32 query heads over 8 kv heads,
     d = 128, bf16), in the launch configuration the benchmark uses.  The oracle covers what it can reach in seconds:
