@@ -352,7 +352,7 @@ STILL_API still_status_t still_selection_overlap(const still_params_t* p, const 
  *   workspace      device scratch of at least still_bwd_workspace_bytes(p) bytes
  *
  * Covers budget_policy 0 (with or without max_retained), both selection modes, both gate modes; d = 64 or 128 in
- * bf16, d = 64 in fp32; not right-padded batches (seq_len must be NULL).  dk, dv and the parameter gradients are
+ * bf16, d = 64 in fp32; not right-padded batches (seq_len must be NULL).  The parameter gradients are
  * accumulated with floating-point atomic adds: results are reproducible to rounding, not bit for bit.
  * Validation on the host before any launch, as everywhere.
  */
@@ -363,18 +363,18 @@ typedef struct still_bwd_ws_layout {
   size_t ed;       /* float [B, Hq, N]        E_t * delta_t                                                   */
   size_t a;        /* dtype [B, Hq, N, d]     E_t (gate_t * dout_t)                                           */
   size_t phi_q;    /* dtype [B, Hq, N, 2*d_f] feature map of the queries                                      */
-  size_t phi_k;    /* dtype [B, Hq, N, 2*d_f] feature map of the keys, zero for the selected tokens           */
-  size_t uq, uk;   /* float [B, Hq, N, d_f]   rescaled pre-activations u of Sec. 3.2                          */
-  size_t stq, stk; /* float [B, Hq, N, 2]     |x|, |f(x)|                                                     */
-  size_t nraw;     /* float [B, Hq, N, d]     phi_q S (the ungated linear numerator)                          */
-  size_t gq;       /* float [B, Hq, N, 2*d_f] S A_t                                                           */
-  size_t dphi_k;   /* float [B, Hq, N, 2*d_f] dS v_j                                                          */
-  size_t ds;       /* dtype [B, Hq, ceil(N/C), 2*d_f, d]  gradient of the state the rows of chunk c+2 and later read */
+  size_t phi_k;    /* dtype [B, Hq, N, 2*d_f] feature map of the keys, zero for the selected tokens (maps)    */
+  size_t uq, uk;   /* float [B, Hq, N, d_f]   rescaled pre-activations u of Sec. 3.2 (maps)                   */
+  size_t stq, stk; /* float [B, Hq, N, 2]     |x|, |f(x)| (maps)                                              */
+  size_t nraw;     /* float [B, Hq, N, d]     not used                                                        */
+  size_t gq;       /* float [B, Hq, N, 2*d_f] gradient of phi_q (maps)                                        */
+  size_t dphi_k;   /* float [B, Hq, N, 2*d_f] gradient of phi_k (maps)                                        */
+  size_t ds;       /* dtype [B, Hq, ceil(N/C), d, 2*d_f]  gradient of the state the rows of chunk c+2 and later read */
   size_t dz;       /* float [B, Hq, ceil(N/C), 2*d_f]     likewise for z                                       */
   size_t dfq, dfk; /* dtype [B, Hq, N, d_f]   gradient of f(x)                                                */
   size_t dq32;     /* float [B, Hq, N, d]                                                                     */
   size_t dk32, dv32; /* float [B, Hkv, N, d]                                                                  */
-  size_t cxq, cxk; /* float [B, Hq, N]        coefficient of x in its own gradient (the norm |x| of Sec. 3.2)   */
+  size_t cxq, cxk; /* float [B, Hq, N]        coefficient of x in its own gradient (maps)                       */
   size_t qt, dot;  /* float [B, Hq, cap, d]   gradients of the retained keys and values, in routing order     */
   size_t kt;       /* uint64 [B, Hq, cap/64]  bit = the retained entry is a token                             */
   size_t kret;     /* dtype [B, Hq, cap, d]   retained keys in routing order                                  */

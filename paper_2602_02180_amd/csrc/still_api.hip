@@ -835,8 +835,9 @@ void compute_bwd_layout(const still_params_t* p, still_bwd_ws_layout_t* L) {
   L->a = take(rows * d * es);
   L->phi_q = take(rows * DP * es);
   L->phi_k = take(rows * DP * es);
-  L->uq = take(rows * df * 4);
-  L->uk = take(rows * df * 4);
+  const size_t wimg = (size_t)p->Hq * d * df * es;   // (the backward pass keeps the weights' operand order here)
+  L->uq = take(rows * df * 4 > wimg ? rows * df * 4 : wimg);
+  L->uk = take(rows * df * 4 > wimg ? rows * df * 4 : wimg);
   L->stq = take(rows * 2 * 4);
   L->stk = take(rows * 2 * 4);
   L->nraw = take(rows * d * 4);
@@ -914,18 +915,13 @@ still_status_t bwd_impl(const still_params_t* p, const void* q, const void* k, c
   };
   auto f32p = [&](size_t off) { return reinterpret_cast<float*>(bws + off); };
 
-  // ---- outputs and accumulators that are added into
-  if ((e = still::launch_fill_f32(dWq, (int64_t)Hq * d * F, 0.f, stream)) != hipSuccess ||
-      (e = still::launch_fill_f32(dWk, (int64_t)Hq * d * F, 0.f, stream)) != hipSuccess ||
-      (dbq && (e = still::launch_fill_f32(dbq, (int64_t)Hq * F, 0.f, stream)) != hipSuccess) ||
-      (dbk && (e = still::launch_fill_f32(dbk, (int64_t)Hq * F, 0.f, stream)) != hipSuccess))
-    return hip_fail("fill", e);
+  // ---- the weights in operand order, the parameter gradients (sums are added into them) cleared
+  still::BwdWeightsArgs wa{Wq, Wk, ws + L.wqt, ws + L.wkf, bws + BL.uq, bws + BL.uk, dWq, dWk, dbq, dbk, d};
+  if ((e = still::launch_bwd_weights(wa, dt, Hq, stream)) != hipSuccess) return hip_fail("bwd_weights", e);
 
   // ---- the forward pass's linear-attention states, rebuilt from the index lists (same kernels as the prefill)
   still::TransposeVArgs tv{v, p->v_sb, p->v_st, p->v_sh, ws + L.vt, ws + L.vfr, N, L.n_pad, Hkv, d, C, nullptr};
   if ((e = still::launch_transpose_v(tv, dt, B, stream)) != hipSuccess) return hip_fail("transpose_v", e);
-  still::TransposeWArgs twk{Wk, ws + L.wkf, Hq, d, F, 1};
-  if ((e = still::launch_transpose_w(twk, dt, stream)) != hipSuccess) return hip_fail("transpose_w", e);
   still::KeepMaskArgs km{sel_idx, reinterpret_cast<uint32_t*>(ws + L.kmask), Hq, ncf, C, have_sel ? p->lambda : 0,
                          budget};
   if ((e = still::launch_keep_mask(km, B, stream)) != hipSuccess) return hip_fail("keep_mask", e);
@@ -947,12 +943,10 @@ still_status_t bwd_impl(const still_params_t* p, const void* q, const void* k, c
   if ((e = still::launch_la_states(la, dt, d, B, stream)) != hipSuccess) return hip_fail("la_states", e);
   if ((e = still::launch_la_prefix(la, dt, d, B, stream)) != hipSuccess) return hip_fail("la_prefix", e);
 
-  // ---- per-row scalars and A_t = E_t (gate_t * dy_t)
+  // ---- per-row scalars
   still::BwdRowArgs ra{};
   ra.out = out; ra.dout = dout; ra.o_sb = p->o_sb; ra.o_st = p->o_st; ra.o_sh = p->o_sh;
-  ra.g = g; ra.g_sb = p->g_sb; ra.g_st = p->g_st; ra.g_sh = p->g_sh; ra.gate_act = p->gate_activation != 0;
   ra.lse = lse; ra.e_row = f32p(BL.e_row); ra.delta = f32p(BL.delta); ra.ed = f32p(BL.ed);
-  ra.A = bws + BL.a; ra.nraw = f32p(BL.nraw); ra.dg = dg;
   ra.U = U; ra.N = N; ra.Hq = Hq; ra.d = d;
   if ((e = still::launch_bwd_row_prep(ra, dt, stream)) != hipSuccess) return hip_fail("bwd_row_prep", e);
 
@@ -987,123 +981,41 @@ still_status_t bwd_impl(const still_params_t* p, const void* q, const void* k, c
   sa.scale = p->scale;
   if ((e = still::launch_bwd_sa(sa, dt, d, B, stream)) != hipSuccess) return hip_fail("bwd_sparse_attention", e);
 
-  // ---- NP-Map of q and k again: f = x W on the matrix core, then phi, u and the norms per token
-  still::GemmArgs gm{};
-  gm.Hq = Hq; gm.map = map;
-  auto product = [&](const still::GemmOperand& A_, const still::GemmOperand& B_, float* Cp, int64_t c_b, int64_t c_h,
-                     int64_t c_c, int64_t c_r, int c_kv, int M_, int Nn_, int K_, int m_total, int k_total, int mode,
-                     int n_c, const still::GemmOperand* B2_ = nullptr) -> hipError_t {
-    gm.A = A_; gm.B = B_; gm.C = Cp;
-    gm.B2 = B2_ != nullptr ? *B2_ : still::GemmOperand{}; gm.c_b = c_b; gm.c_h = c_h; gm.c_c = c_c; gm.c_r = c_r; gm.c_kv = c_kv;
-    gm.M = M_; gm.Nn = Nn_; gm.K = K_; gm.m_total = m_total; gm.k_total = k_total; gm.mode = mode;
-    return still::launch_bgemm(gm, dt, U, n_c, stream);
-  };
-  const int64_t NF = (int64_t)N * F, NDP = (int64_t)N * DP, ND = (int64_t)N * d;
-  const still::GemmOperand q_rows = operand(q, p->q_sb, p->q_sh, (int64_t)C * p->q_st, p->q_st, 1);
-  const still::GemmOperand k_rows = operand(k, p->k_sb, p->k_sh, (int64_t)C * p->k_st, p->k_st, 1, 1);
-  const still::GemmOperand v_rows = operand(v, p->v_sb, p->v_sh, (int64_t)C * p->v_st, p->v_st, 1, 1);
-  const still::GemmOperand wq_fx = operand(Wq, 0, (int64_t)d * F, 0, 1, F);   // (n = feature, k = x)
-  const still::GemmOperand wk_fx = operand(Wk, 0, (int64_t)d * F, 0, 1, F);
-  const still::GemmOperand wq_xf = operand(Wq, 0, (int64_t)d * F, 0, F, 1);   // (n = x, k = feature)
-  const still::GemmOperand wk_xf = operand(Wk, 0, (int64_t)d * F, 0, F, 1);
-  if ((e = product(q_rows, wq_fx, f32p(BL.uq), Hq * NF, NF, (int64_t)C * F, F, 0, C, F, d, N, 0, 0, nc)) != hipSuccess ||
-      (e = product(k_rows, wk_fx, f32p(BL.uk), Hq * NF, NF, (int64_t)C * F, F, 0, C, F, d, N, 0, 0, nc)) != hipSuccess)
-    return hip_fail("bwd f = x W", e);
-  still::BwdNpArgs nq{};
-  nq.x = q; nq.x_sb = p->q_sb; nq.x_st = p->q_st; nq.x_sh = p->q_sh; nq.x_kv = 0;
-  nq.bias = bq; nq.u = f32p(BL.uq); nq.st = f32p(BL.stq); nq.phi = bws + BL.phi_q; nq.kmask = nullptr;
-  nq.dphi = f32p(BL.gq); nq.coef = ra.ed; nq.z1 = la.zsnap; nq.z2 = la.zpre;
-  nq.df = bws + BL.dfq; nq.cx = f32p(BL.cxq);
-  nq.map = map; nq.U = U; nq.N = N; nq.Hq = Hq; nq.Hkv = Hkv; nq.d = d; nq.F = F; nq.C = C; nq.nc = nc; nq.ncf = ncf;
-  nq.nseg = L.nseg; nq.seg_chunks = L.seg_chunks;
-  still::BwdNpArgs nk = nq;
-  nk.x = k; nk.x_sb = p->k_sb; nk.x_st = p->k_st; nk.x_sh = p->k_sh; nk.x_kv = 1;
-  nk.bias = bk; nk.u = f32p(BL.uk); nk.st = f32p(BL.stk); nk.phi = bws + BL.phi_k; nk.kmask = la.kmask;
-  nk.dphi = f32p(BL.dphi_k); nk.coef = nullptr; nk.z1 = f32p(BL.dz); nk.z2 = nullptr;
-  nk.df = bws + BL.dfk; nk.cx = f32p(BL.cxk);
-  if ((e = still::launch_bwd_np(nq, dt, false, stream)) != hipSuccess ||
-      (e = still::launch_bwd_np(nk, dt, false, stream)) != hipSuccess)
-    return hip_fail("bwd_np_fwd", e);
-
-  // ---- query side of the linear branch: phi_q S (for dg) and S A (for dphi_q), against both state images
-  const still::GemmOperand phiq_rows = operand(bws + BL.phi_q, Hq * NDP, NDP, (int64_t)C * DP, DP, 1);
-  const still::GemmOperand a_rows = operand(bws + BL.a, Hq * ND, ND, (int64_t)C * d, d, 1);
-  const int64_t img = (int64_t)d * DP;
-  const still::GemmOperand snap_xf = operand(la.snap, Hq * nc * img, nc * img, img, DP, 1);        // (n = x, k = f)
-  const still::GemmOperand pimg_xf = operand(la.pimg, Hq * L.nseg * img, L.nseg * img, img, DP, 1, 0, 0, L.seg_chunks);
-  const still::GemmOperand snap_fx = operand(la.snap, Hq * nc * img, nc * img, img, 1, DP);        // (n = f, k = x)
-  const still::GemmOperand pimg_fx = operand(la.pimg, Hq * L.nseg * img, L.nseg * img, img, 1, DP, 0, 0, L.seg_chunks);
-  if ((e = product(phiq_rows, snap_xf, f32p(BL.nraw), Hq * ND, ND, (int64_t)C * d, d, 0, C, d, DP, N, 0, 0, nc, &pimg_xf)) != hipSuccess ||
-      (e = product(a_rows, snap_fx, f32p(BL.gq), Hq * NDP, NDP, (int64_t)C * DP, DP, 0, C, DP, d, N, 0, 0, nc, &pimg_fx)) != hipSuccess)
-    return hip_fail("bwd query-side products", e);
-  if (g != nullptr && (e = still::launch_bwd_dg(ra, dt, stream)) != hipSuccess) return hip_fail("bwd_dg", e);
-
-  // ---- gradient of the states: the per-chunk contributions phi_q^T A summed over the chunks two and more ahead
-  const still::GemmOperand phiq_ft = operand(bws + BL.phi_q, Hq * NDP, NDP, (int64_t)C * DP, 1, DP);   // (m = f, k = token)
-  const still::GemmOperand a_xt = operand(bws + BL.a, Hq * ND, ND, (int64_t)C * d, 1, d);              // (n = x, k = token)
-  const int64_t simg = (int64_t)DP * d;
-  gm.A = phiq_ft; gm.B = a_xt; gm.B2 = still::GemmOperand{};
-  gm.C = f32p(BL.ds);   // written in the storage type by the scan
-  gm.c_b = Hq * nc * simg; gm.c_h = nc * simg; gm.c_c = simg; gm.c_r = d; gm.c_kv = 0;
-  gm.M = DP; gm.Nn = d; gm.K = C; gm.m_total = 0; gm.k_total = N; gm.mode = 0;
-  if ((e = still::launch_bgemm_revscan(gm, dt, U, nc, stream)) != hipSuccess)
-    return hip_fail("bwd state gradient", e);
-  still::BwdColsumArgs cz{bws + BL.phi_q, ra.ed, f32p(BL.dz), N, C, nc, DP, Hq, 0};
-  if ((e = still::launch_bwd_colsum(cz, dt, U, stream)) != hipSuccess) return hip_fail("bwd_colsum", e);
-  if ((e = still::launch_bwd_revcumsum(f32p(BL.dz), U, nc, DP, stream)) != hipSuccess)
-    return hip_fail("bwd_revcumsum", e);
-
-  // ---- key side: dphi_k = v dS^T (- dz, in the NP-Map kernel), dv += phi_k dS
-  const still::GemmOperand ds_fx = operand(bws + BL.ds, Hq * nc * simg, nc * simg, simg, d, 1);   // (n = f, k = x)
-  const still::GemmOperand ds_xf = operand(bws + BL.ds, Hq * nc * simg, nc * simg, simg, 1, d);   // (n = x, k = f)
-  const still::GemmOperand phik_rows = operand(bws + BL.phi_k, Hq * NDP, NDP, (int64_t)C * DP, DP, 1);
-  if ((e = product(v_rows, ds_fx, f32p(BL.dphi_k), Hq * NDP, NDP, (int64_t)C * DP, DP, 0, C, DP, d, N, 0, 0, nc)) != hipSuccess ||
-      (e = product(phik_rows, ds_xf, f32p(BL.dv32), Hkv * ND, ND, (int64_t)C * d, d, 1, C, d, DP, N, 0, 2, nc)) != hipSuccess)
-    return hip_fail("bwd key-side products", e);
-
-  // ---- NP-Map backwards (df, and the |x| path of dx), then dx += df W^T and dW += x^T df
-  if ((e = still::launch_bwd_np(nq, dt, true, stream)) != hipSuccess ||
-      (e = still::launch_bwd_np(nk, dt, true, stream)) != hipSuccess)
-    return hip_fail("bwd_np_bwd", e);
-  const still::GemmOperand dfq_rows = operand(bws + BL.dfq, Hq * NF, NF, (int64_t)C * F, F, 1);
-  const still::GemmOperand dfk_rows = operand(bws + BL.dfk, Hq * NF, NF, (int64_t)C * F, F, 1);
-  if ((e = product(dfq_rows, wq_xf, f32p(BL.dq32), Hq * ND, ND, (int64_t)C * d, d, 0, C, d, F, N, 0, 1, nc)) != hipSuccess ||
-      (e = product(dfk_rows, wk_xf, f32p(BL.dk32), Hkv * ND, ND, (int64_t)C * d, d, 1, C, d, F, N, 0, 2, nc)) != hipSuccess)
-    return hip_fail("bwd dx += df W^T", e);
-  const int KS = 256, nsplit = (N + KS - 1) / KS;   // tokens per split of the sum over tokens
-  const still::GemmOperand q_xt = operand(q, p->q_sb, p->q_sh, (int64_t)KS * p->q_st, 1, p->q_st);       // (m = x, k = token)
-  const still::GemmOperand k_xt = operand(k, p->k_sb, p->k_sh, (int64_t)KS * p->k_st, 1, p->k_st, 1);
-  const still::GemmOperand dfq_ft = operand(bws + BL.dfq, Hq * NF, NF, (int64_t)KS * F, 1, F);           // (n = f, k = token)
-  const still::GemmOperand dfk_ft = operand(bws + BL.dfk, Hq * NF, NF, (int64_t)KS * F, 1, F);
-  if ((e = product(q_xt, dfq_ft, dWq, 0, (int64_t)d * F, 0, F, 0, d, F, KS, 0, N, 2, nsplit)) != hipSuccess ||
-      (e = product(k_xt, dfk_ft, dWk, 0, (int64_t)d * F, 0, F, 0, d, F, KS, 0, N, 2, nsplit)) != hipSuccess)
-    return hip_fail("bwd dW += x^T df", e);
-  if (dbq != nullptr) {
-    still::BwdColsumArgs cb{bws + BL.dfq, nullptr, dbq, N, C, nc, F, Hq, 1};
-    if ((e = still::launch_bwd_colsum(cb, dt, U, stream)) != hipSuccess) return hip_fail("bwd db", e);
-  }
-  if (dbk != nullptr) {
-    still::BwdColsumArgs cb{bws + BL.dfk, nullptr, dbk, N, C, nc, F, Hq, 1};
-    if ((e = still::launch_bwd_colsum(cb, dt, U, stream)) != hipSuccess) return hip_fail("bwd db", e);
-  }
-
-  // ---- fp32 sums -> the caller's tensors
-  still::BwdFinishArgs fq{};
-  fq.map = map; fq.B = B; fq.Hq = Hq; fq.N = N; fq.d = d; fq.C = C; fq.lam = sa.lam; fq.ncf = ncf;
-  fq.cap = BL.cap_t; fq.sel_stride = sa.sel_stride; fq.n_ret = still::retained_rows(nc >= 2 ? nc - 2 : 0, sa.lam, budget);
-  fq.kmask = la.kmask; fq.sel = sel_idx;
-  still::BwdFinishArgs fk = fq, fv = fq;
-  fq.src = f32p(BL.dq32); fq.dst = dq; fq.x = q; fq.H = Hq; fq.cx = f32p(BL.cxq);
-  fq.s_b = p->q_sb; fq.s_t = p->q_st; fq.s_h = p->q_sh;
-  fk.src = f32p(BL.dk32); fk.dst = dk; fk.x = k; fk.H = Hkv; fk.cx = f32p(BL.cxk); fk.per_kv = 1;
-  fk.s_b = p->k_sb; fk.s_t = p->k_st; fk.s_h = p->k_sh;
-  fv.src = f32p(BL.dv32); fv.dst = dv; fv.x = v; fv.H = Hkv; fv.per_kv = 1;
-  fv.s_b = p->v_sb; fv.s_t = p->v_st; fv.s_h = p->v_sh;
-  if (fq.n_ret > 0) fk.dret = sa.dkret, fv.dret = sa.dvret;
-  if ((e = still::launch_bwd_finish(fq, dt, stream)) != hipSuccess ||
-      (e = still::launch_bwd_finish(fk, dt, stream)) != hipSuccess ||
-      (e = still::launch_bwd_finish(fv, dt, stream)) != hipSuccess)
-    return hip_fail("bwd_finish", e);
+  // ---- linear branch: query side (dq, dg, and what the state gradient is made of), state gradient, key side, then the
+  // parameter gradients
+  still::BwdLinArgs lq{};
+  lq.x = q; lq.x_sb = p->q_sb; lq.x_st = p->q_st; lq.x_sh = p->q_sh;
+  lq.dout = dout; lq.o_sb = p->o_sb; lq.o_st = p->o_st; lq.o_sh = p->o_sh;
+  lq.gate = g; lq.g_sb = p->g_sb; lq.g_st = p->g_st; lq.g_sh = p->g_sh; lq.gate_act = p->gate_activation != 0;
+  lq.wf = wa.wqf; lq.wr = wa.wqr; lq.bias = bq;
+  lq.snap = la.snap; lq.zsnap = la.zsnap; lq.pimg = la.pimg; lq.zpre = la.zpre;
+  lq.e_row = ra.e_row; lq.ed = ra.ed;
+  lq.a_rows = bws + BL.a; lq.phi = bws + BL.phi_q; lq.df = bws + BL.dfq;
+  lq.dx32 = sa.dq32; lq.dx = dq; lq.dg = dg;
+  lq.map = map; lq.n_units = U;
+  lq.N = N; lq.C = C; lq.Hq = Hq; lq.Hkv = Hkv; lq.nc = nc; lq.ncf = ncf; lq.nseg = L.nseg; lq.seg_chunks = L.seg_chunks;
+  if ((e = still::launch_bwd_lin(lq, dt, d, false, stream)) != hipSuccess) return hip_fail("bwd_lin (queries)", e);
+  still::BwdRevscanArgs rs{lq.a_rows, lq.phi, ra.ed, bws + BL.ds, f32p(BL.dz), N, C, nc};
+  if ((e = still::launch_bwd_revscan(rs, dt, d, U, stream)) != hipSuccess) return hip_fail("bwd_revscan", e);
+  still::BwdLinArgs lk{};
+  lk.x = k; lk.x_sb = p->k_sb; lk.x_st = p->k_st; lk.x_sh = p->k_sh;
+  lk.v = v; lk.v_sb = p->v_sb; lk.v_st = p->v_st; lk.v_sh = p->v_sh;
+  lk.wf = wa.wkf; lk.wr = wa.wkr; lk.bias = bk;
+  lk.snap = rs.ds; lk.zsnap = rs.dz; lk.kmask = la.kmask;
+  lk.df = bws + BL.dfk;
+  lk.dx32 = sa.dk32; lk.dv32 = sa.dv32; lk.dx = dk; lk.dv = dv;
+  lk.sel = sel_idx; lk.lam = sa.lam; lk.cap = BL.cap_t; lk.sel_stride = sa.sel_stride;
+  lk.n_ret = still::retained_rows(nc >= 2 ? nc - 2 : 0, sa.lam, budget);
+  if (lk.n_ret > 0) lk.dkret = sa.dkret, lk.dvret = sa.dvret;
+  lk.map = map; lk.n_units = B * Hkv;
+  lk.N = N; lk.C = C; lk.Hq = Hq; lk.Hkv = Hkv; lk.nc = nc; lk.ncf = ncf;
+  if ((e = still::launch_bwd_lin(lk, dt, d, true, stream)) != hipSuccess) return hip_fail("bwd_lin (keys)", e);
+  still::BwdDwArgs dw{};
+  dw.q = q; dw.q_sb = p->q_sb; dw.q_st = p->q_st; dw.q_sh = p->q_sh;
+  dw.k = k; dw.k_sb = p->k_sb; dw.k_st = p->k_st; dw.k_sh = p->k_sh;
+  dw.dfq = lq.df; dw.dfk = lk.df; dw.dwq = dWq; dw.dwk = dWk; dw.dbq = dbq; dw.dbk = dbk;
+  dw.map = map; dw.B = B; dw.N = N; dw.Hq = Hq;
+  if ((e = still::launch_bwd_dw(dw, dt, d, stream)) != hipSuccess) return hip_fail("bwd_dw", e);
   g_err[0] = 0;
   return STILL_OK;
 }

@@ -16,8 +16,9 @@
 //        du = phi+ (dphi+ - <phi+, dphi+>) - phi- (dphi- - <phi-, dphi->)
 //        df = (|x| / |f|) (du - fh <fh, du>),  fh = f / |f|;   dx = df W^T + <fh, du> x / |x|;   dW = x^T df
 //
-// The softmax branch is in still_bwd_sa.hip.  The linear branch is a sequence of batched products on one generic MFMA
-// tile kernel with row-wise kernels between them, intermediates in the workspace.  All sums are fp32; operands of the matrix core are in the storage type.
+// The softmax branch is in still_bwd_sa.hip, the linear branch in still_bwd_lin.hip.  Here: the per-row scalars both start
+// from, and the attention map with its backward pass, whose linear branch is a sequence of batched products on one generic
+// MFMA tile kernel with row-wise kernels between them.  All sums are fp32; operands of the matrix core are in the storage type.
 #include "still_kernels.h"
 
 namespace still {
@@ -146,62 +147,6 @@ __global__ __launch_bounds__(256) void bgemm_kernel(GemmArgs a) {
   }
 }
 
-// The state gradient as a running sum: dS(c) = sum over c' >= c + 2 of A(c')^T-products.  One workgroup owns a 64 x BN
-// tile of the state for one (batch, head) and walks the chunks from the last one down, keeping the sum in its
-// accumulators: after adding the contribution of chunk c' the accumulators ARE dS(c' - 2), which is stored in the
-// storage type (it is only ever a matrix-core operand again).  The two last chunks' dS is zero.  Operands as in
-// bgemm_kernel (item index = chunk, contraction over the chunk's tokens, cut short in a ragged last chunk).
-template <typename T, int BN>
-__global__ __launch_bounds__(256) void bgemm_revscan_kernel(GemmArgs a, int n_c) {
-  typedef Mma<T> M;
-  constexpr int BK = 64, NT = BN / 64;
-  constexpr int LDK = BK + (sizeof(T) == 2 ? 8 : 4);
-  __shared__ __attribute__((aligned(16))) T As[64 * LDK];
-  __shared__ __attribute__((aligned(16))) T Bs[BN * LDK];
-  const int unit = blockIdx.z;
-  const int ntn = a.Nn / BN;
-  const int mt = blockIdx.x / ntn, nt = blockIdx.x % ntn;
-  const int b = unit / a.Hq, h = unit % a.Hq, kvh = a.map.kv[h];
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int l31 = lane & 31, g = lane >> 5;
-  const int wr = wave >> 1, wc = wave & 1;
-  floatx16 acc[NT];
-#pragma unroll
-  for (int j = 0; j < NT; ++j) acc[j] = zero16();
-  T* cbase = reinterpret_cast<T*>(a.C) + b * a.c_b + (a.c_kv ? kvh : h) * a.c_h;
-  auto store = [&](int c) {
-    T* cp = cbase + (int64_t)c * a.c_c;
-#pragma unroll
-    for (int j = 0; j < NT; ++j) {
-      const int n = nt * BN + 32 * (wc * NT + j) + l31;
-#pragma unroll
-      for (int i = 0; i < 16; ++i) cp[(int64_t)(mt * 64 + 32 * wr + c_row(i, g)) * a.c_r + n] = from_f32<T>(acc[j][i]);
-    }
-  };
-  if (n_c >= 1) store(n_c - 1);
-  if (n_c >= 2) store(n_c - 2);
-  for (int c = n_c - 1; c >= 2; --c) {
-    int k_valid = a.K;
-    if (a.k_total > 0) k_valid = min(a.K, a.k_total - c * a.K);
-    const int64_t a_off = b * a.A.s_b + (a.A.kv ? kvh : h) * a.A.s_h + (int64_t)c * a.A.s_c;
-    const int64_t b_off = b * a.B.s_b + (a.B.kv ? kvh : h) * a.B.s_h + (int64_t)c * a.B.s_c;
-    for (int k0 = 0; k0 < k_valid; k0 += BK) {
-      load_operand<T, 64, LDK>(As, a.A, a_off, mt * 64, a.M, k0, k_valid, tid);
-      load_operand<T, BN, LDK>(Bs, a.B, b_off, nt * BN, a.Nn, k0, k_valid, tid);
-      __syncthreads();
-#pragma unroll
-      for (int s = 0; s < BK / M::KK; ++s) {
-        const typename M::frag af = M::load(As + (32 * wr + l31) * LDK + s * M::KK + g * M::KPL);
-#pragma unroll
-        for (int j = 0; j < NT; ++j)
-          acc[j] = M::mma(af, M::load(Bs + (32 * (wc * NT + j) + l31) * LDK + s * M::KK + g * M::KPL), acc[j]);
-      }
-      __syncthreads();
-    }
-    store(c - 2);
-  }
-}
-
 // ---------------------------------------------------------------------------------------------------------
 // Element-wise kernels
 // ---------------------------------------------------------------------------------------------------------
@@ -250,7 +195,7 @@ __device__ __forceinline__ bool row_of_lane(int64_t n_rows, int width, int64_t& 
   return row < n_rows;
 }
 
-// delta_t = dy_t . y_t, E_t = exp(-L_t), A_t = E_t (gate_t * dy_t)
+// delta_t = dy_t . y_t, E_t = exp(-L_t)
 template <typename T>
 __global__ __launch_bounds__(256) void bwd_row_prep_kernel(BwdRowArgs a) {
   int64_t row;
@@ -260,28 +205,15 @@ __global__ __launch_bounds__(256) void bwd_row_prep_kernel(BwdRowArgs a) {
   const int unit = (int)(rowc / a.N), t = (int)(rowc % a.N);
   const int b = unit / a.Hq, h = unit % a.Hq;
   const int64_t oo = b * a.o_sb + (int64_t)t * a.o_st + h * a.o_sh + e0;
-  float y[8], dy[8], gate[8];
+  float y[8], dy[8];
   load8_t<T>(y, static_cast<const T*>(a.out) + oo);
   load8_t<T>(dy, static_cast<const T*>(a.dout) + oo);
-#pragma unroll
-  for (int e = 0; e < 8; ++e) gate[e] = 1.f;
-  if (a.g) {
-    load8_t<T>(gate, static_cast<const T*>(a.g) + b * a.g_sb + (int64_t)t * a.g_st + h * a.g_sh + e0);
-    if (a.gate_act) {
-#pragma unroll
-      for (int e = 0; e < 8; ++e) gate[e] = 1.f / (1.f + __expf(-gate[e]));
-    }
-  }
   const float E = __expf(-a.lse[rowc]);
-  float dot = 0.f, av[8];
+  float dot = 0.f;
 #pragma unroll
-  for (int e = 0; e < 8; ++e) {
-    dot += dy[e] * y[e];
-    av[e] = E * gate[e] * dy[e];
-  }
+  for (int e = 0; e < 8; ++e) dot += dy[e] * y[e];
   dot = group_sum(dot, lpr);
   if (!live) return;
-  store8_t<T>(static_cast<T*>(a.A) + row * a.d + e0, av);
   if (e0 == 0) {
     a.e_row[row] = E;
     a.delta[row] = dot;
@@ -460,96 +392,6 @@ __global__ __launch_bounds__(256) void bwd_colsum_kernel(BwdColsumArgs a) {
   }
 }
 
-// X[unit][c][l] <- sum over c' >= c + 2 of X[unit][c'][l]  (the rows of chunk c' see the state through chunk c'-2)
-__global__ __launch_bounds__(256) void bwd_revcumsum_kernel(float* X, int nc, int64_t L) {
-  const int64_t l = blockIdx.x * 256ll + threadIdx.x;
-  if (l >= L) return;
-  float* p = X + (int64_t)blockIdx.y * nc * L + l;
-  float s1 = 0.f, s2 = 0.f;
-  for (int c = nc - 1; c >= 0; --c) {
-    const float v = p[(int64_t)c * L];
-    p[(int64_t)c * L] = s2;
-    s2 = s1;
-    s1 += v;
-  }
-}
-
-// dg = E_t dy_t * (phi_q S)_t  (times the logistic function's slope when the gate is activated here)
-template <typename T>
-__global__ __launch_bounds__(256) void bwd_dg_kernel(BwdRowArgs a) {
-  int64_t row;
-  int e0, lpr;
-  if (!row_of_lane((int64_t)a.U * a.N, a.d, row, e0, lpr)) return;
-  const int unit = (int)(row / a.N), t = (int)(row % a.N);
-  const int b = unit / a.Hq, h = unit % a.Hq;
-  float dy[8], nr[8], r[8];
-  load8_t<T>(dy, static_cast<const T*>(a.dout) + b * a.o_sb + (int64_t)t * a.o_st + h * a.o_sh + e0);
-  load8_f32(nr, a.nraw + row * a.d + e0);
-  const float E = a.e_row[row];
-  const int64_t go = b * a.g_sb + (int64_t)t * a.g_st + h * a.g_sh + e0;
-#pragma unroll
-  for (int e = 0; e < 8; ++e) r[e] = E * dy[e] * nr[e];
-  if (a.gate_act) {
-    float gv[8];
-    load8_t<T>(gv, static_cast<const T*>(a.g) + go);
-#pragma unroll
-    for (int e = 0; e < 8; ++e) {
-      const float sg = 1.f / (1.f + __expf(-gv[e]));
-      r[e] *= sg * (1.f - sg);
-    }
-  }
-  store8_t<T>(static_cast<T*>(a.dg) + go, r);
-}
-
-// fp32 gradient rows (+ coefficient * x for the |x| path of the NP-Map and the rows of the retained entries, both
-// summed over the query heads that read the row's head) -> the caller's strided tensors in the storage type
-template <typename T>
-__global__ __launch_bounds__(256) void bwd_finish_kernel(BwdFinishArgs a) {
-  int64_t row;
-  int e0, lpr;
-  if (!row_of_lane((int64_t)a.B * a.H * a.N, a.d, row, e0, lpr)) return;
-  const int t = (int)(row % a.N);
-  const int bh = (int)(row / a.N);
-  const int b = bh / a.H, h = bh % a.H;
-  float x[8];
-  load8_f32(x, a.src + row * a.d + e0);
-  if (a.cx != nullptr) {
-    float coef = 0.f;
-    if (a.per_kv) {
-      for (int hq = 0; hq < a.Hq; ++hq)
-        if (a.map.kv[hq] == h) coef += a.cx[((int64_t)b * a.Hq + hq) * a.N + t];
-    } else {
-      coef = a.cx[row];
-    }
-    float xv[8];
-    load8_t<T>(xv, static_cast<const T*>(a.x) + b * a.s_b + (int64_t)t * a.s_t + h * a.s_h + e0);
-#pragma unroll
-    for (int e = 0; e < 8; ++e) x[e] += coef * xv[e];
-  }
-  const int c = t / a.C;
-  if (a.dret != nullptr && c < a.ncf) {
-    // the query heads of the group that retained this token: its entry is its rank among the list's tokens
-    for (int hq = 0; hq < a.Hq; ++hq) {
-      if (a.map.kv[hq] != h) continue;
-      const int64_t unit = (int64_t)b * a.Hq + hq;
-      const int w = t % a.C;
-      const uint32_t* m = a.kmask + (unit * a.ncf + c) * (a.C / 32);
-      if (!((m[w / 32] >> (w & 31)) & 1u)) continue;
-      int e = c * a.lam + __popc(m[w / 32] & ((1u << (w & 31)) - 1u));
-      for (int j = 0; j < w / 32; ++j) e += __popc(m[j]);
-      const int32_t* list = a.sel + unit * a.sel_stride;
-      if (list[e] != t)            // (a list with foreign entries between its tokens)
-        for (e = c * a.lam; list[e] != t; ++e) {}
-      if (e >= a.n_ret) continue;
-      float xr[8];
-      load8_f32(xr, a.dret + (unit * a.cap + e) * a.d + e0);
-#pragma unroll
-      for (int i = 0; i < 8; ++i) x[i] += xr[i];
-    }
-  }
-  store8_t<T>(static_cast<T*>(a.dst) + b * a.s_b + (int64_t)t * a.s_t + h * a.s_h + e0, x);
-}
-
 // ---------------------------------------------------------------------------------------------------------
 // Attention map of the operator: A[t][j] = weight of v_j in row t under the shared normaliser (what the first
 // training stage of Sec. 4.1 compares with the teacher's softmax map).  One workgroup per (64 rows, 64 keys) at or
@@ -651,19 +493,6 @@ hipError_t launch_bgemm(const GemmArgs& a, int dtype, int U, int n_c, hipStream_
   return hipGetLastError();
 }
 
-hipError_t launch_bgemm_revscan(const GemmArgs& a, int dtype, int U, int n_c, hipStream_t s) {
-  const int bn = a.Nn % 128 == 0 ? 128 : 64;
-  const dim3 grid((a.Nn / bn) * (a.M / 64), 1, U);
-  if (dtype == 1) {
-    if (bn == 128) hipLaunchKernelGGL((bgemm_revscan_kernel<bf16, 128>), grid, dim3(256), 0, s, a, n_c);
-    else hipLaunchKernelGGL((bgemm_revscan_kernel<bf16, 64>), grid, dim3(256), 0, s, a, n_c);
-  } else {
-    if (bn == 128) hipLaunchKernelGGL((bgemm_revscan_kernel<float, 128>), grid, dim3(256), 0, s, a, n_c);
-    else hipLaunchKernelGGL((bgemm_revscan_kernel<float, 64>), grid, dim3(256), 0, s, a, n_c);
-  }
-  return hipGetLastError();
-}
-
 hipError_t launch_fill_f32(float* p, int64_t n, float x, hipStream_t s) {
   if (n <= 0) return hipSuccess;
   const int blocks = (int)((n + 255) / 256 < 4096 ? (n + 255) / 256 : 4096);
@@ -676,14 +505,6 @@ hipError_t launch_bwd_row_prep(const BwdRowArgs& a, int dtype, hipStream_t s) {
   const int blocks = (int)(((int64_t)a.U * a.N + rpb - 1) / rpb);
   if (dtype == 1) hipLaunchKernelGGL((bwd_row_prep_kernel<bf16>), dim3(blocks), dim3(256), 0, s, a);
   else hipLaunchKernelGGL((bwd_row_prep_kernel<float>), dim3(blocks), dim3(256), 0, s, a);
-  return hipGetLastError();
-}
-
-hipError_t launch_bwd_dg(const BwdRowArgs& a, int dtype, hipStream_t s) {
-  const int rpb = 256 / (a.d / 8);
-  const int blocks = (int)(((int64_t)a.U * a.N + rpb - 1) / rpb);
-  if (dtype == 1) hipLaunchKernelGGL((bwd_dg_kernel<bf16>), dim3(blocks), dim3(256), 0, s, a);
-  else hipLaunchKernelGGL((bwd_dg_kernel<float>), dim3(blocks), dim3(256), 0, s, a);
   return hipGetLastError();
 }
 
@@ -704,19 +525,6 @@ hipError_t launch_bwd_colsum(const BwdColsumArgs& a, int dtype, int U, hipStream
   const dim3 grid(a.nc, U);
   if (dtype == 1) hipLaunchKernelGGL((bwd_colsum_kernel<bf16>), grid, dim3(256), 0, s, a);
   else hipLaunchKernelGGL((bwd_colsum_kernel<float>), grid, dim3(256), 0, s, a);
-  return hipGetLastError();
-}
-
-hipError_t launch_bwd_revcumsum(float* X, int U, int nc, int64_t L, hipStream_t s) {
-  hipLaunchKernelGGL(bwd_revcumsum_kernel, dim3((unsigned)((L + 255) / 256), U), dim3(256), 0, s, X, nc, L);
-  return hipGetLastError();
-}
-
-hipError_t launch_bwd_finish(const BwdFinishArgs& a, int dtype, hipStream_t s) {
-  const int rpb = 256 / (a.d / 8);
-  const int blocks = (int)(((int64_t)a.B * a.H * a.N + rpb - 1) / rpb);
-  if (dtype == 1) hipLaunchKernelGGL((bwd_finish_kernel<bf16>), dim3(blocks), dim3(256), 0, s, a);
-  else hipLaunchKernelGGL((bwd_finish_kernel<float>), dim3(blocks), dim3(256), 0, s, a);
   return hipGetLastError();
 }
 

@@ -314,18 +314,90 @@ struct BwdRowArgs {
   const void* out;         // y of the forward pass, strided like dout
   const void* dout;
   int64_t o_sb, o_st, o_sh;
-  const void* g;           // nullable gate
-  int64_t g_sb, g_st, g_sh;
-  int gate_act;
   const float* lse;        // [U, N]
   float* e_row;            // [U, N]: E_t = exp(-L_t)
   float* delta;            // [U, N]: dy_t . y_t
   float* ed;               // [U, N]: E_t delta_t
-  void* A;                 // [U, N, d] storage type: E_t (gate_t * dy_t)
-  const float* nraw;       // [U, N, d]: phi_q S (dg kernel)
-  void* dg;                // strided like g (dg kernel)
   int U, N, Hq, d;
 };
+// both weight matrices in the two operand orders of the linear branch, and cleared parameter gradients
+struct BwdWeightsArgs {
+  const void* wq;          // [Hq, d, d]
+  const void* wk;
+  void* wqf;               // [Hq, d, d]: operand order of f^T = W^T x^T (wfrag_offset)
+  void* wkf;
+  void* wqr;               // [Hq, d, d]: operand order of dx = df W^T
+  void* wkr;
+  float* dwq;
+  float* dwk;
+  float* dbq;              // nullable
+  float* dbk;
+  int d;
+};
+// linear branch of one side (still_bwd_lin.hip); "q:" / "k:" = query / key side
+struct BwdLinArgs {
+  const void* x;           // q: q; k: k
+  int64_t x_sb, x_st, x_sh;
+  const void* v;           // k: v
+  int64_t v_sb, v_st, v_sh;
+  const void* dout;        // q
+  int64_t o_sb, o_st, o_sh;
+  const void* gate;        // q: nullable
+  int64_t g_sb, g_st, g_sh;
+  int gate_act;
+  const void* wf;          // this side's weights in operand order (BwdWeightsArgs)
+  const void* wr;
+  const void* bias;        // nullable [Hq, d]
+  const void* snap;        // q: LaArgs::snap; k: the state gradient, same layout
+  const float* zsnap;
+  const void* pimg;        // q: LaArgs::pimg, zpre
+  const float* zpre;
+  const float* e_row;      // q: [U, N]
+  const float* ed;         // q: [U, N]
+  const uint32_t* kmask;   // k: [B, Hq, ncf, C/32]
+  void* a_rows;            // q: [U, N, d] written: A_t (tokens of chunks >= 2)
+  void* phi;               // q: [U, N, 2d] written (tokens of chunks >= 2)
+  void* df;                // [U, N, d] written
+  const float* dx32;       // the softmax branch's part: q: [U, N, d]; k: [B, Hkv, N, d]
+  const float* dv32;       // k
+  void* dx;                // strided like x
+  void* dv;                // k: strided like v
+  void* dg;                // q: nullable, strided like gate
+  const float* dkret;      // k: nullable [U, cap, d]: the retained entries' part, entry c * lam + slot
+  const float* dvret;
+  const int32_t* sel;      // k: [U, sel_stride]
+  HeadMap map;
+  int n_units;             // q: B * Hq; k: B * Hkv
+  int N, C, Hq, Hkv, nc, ncf, nseg, seg_chunks;
+  int lam, cap, sel_stride;
+  int n_ret;               // entries that have a gradient (some row sees them)
+};
+struct BwdRevscanArgs {
+  const void* a_rows;      // [U, N, d]
+  const void* phi;         // [U, N, 2d]
+  const float* ed;         // [U, N]
+  void* ds;                // [U, nc, d, 2d] storage type: dS(c) as [x][feature], chunks <= nc - 3
+  float* dz;               // [U, nc, 2d]
+  int N, C, nc;
+};
+struct BwdDwArgs {
+  const void* q;
+  const void* k;
+  int64_t q_sb, q_st, q_sh, k_sb, k_st, k_sh;
+  const void* dfq;         // [U, N, d]
+  const void* dfk;
+  float* dwq;              // [Hq, d, d], added into
+  float* dwk;
+  float* dbq;              // nullable [Hq, d], added into
+  float* dbk;
+  HeadMap map;
+  int B, N, Hq;
+  int tiles_per_block;     // set by the launcher
+};
+hipError_t launch_bwd_weights(const BwdWeightsArgs& a, int dtype, int Hq, hipStream_t stream);
+hipError_t launch_bwd_lin(const BwdLinArgs& a, int dtype, int d, bool key, hipStream_t stream);
+hipError_t launch_bwd_revscan(const BwdRevscanArgs& a, int dtype, int d, int U, hipStream_t stream);
+hipError_t launch_bwd_dw(BwdDwArgs a, int dtype, int d, hipStream_t stream);
 struct BwdNpArgs {
   const void* x;           // q or k
   int64_t x_sb, x_st, x_sh;
@@ -349,20 +421,6 @@ struct BwdColsumArgs {
   const float* w;          // nullable [U, N]
   float* out;              // [U, nc, L], or (per_head) [Hq, L] added atomically
   int N, C, nc, L, Hq, per_head;
-};
-struct BwdFinishArgs {
-  const float* src;        // [B, H, N, d]
-  void* dst;               // strided, storage type
-  const void* x;           // the tensor the gradient belongs to (same strides as dst); read when cx is given
-  int64_t s_b, s_t, s_h;
-  const float* cx;         // nullable [B, Hq, N]: dst += coefficient * x
-  int per_kv;              // 1: H counts kv heads, the coefficients of the query heads of a kv head are added up
-  const float* dret;       // nullable [B * Hq, cap, d]: the retained entries' part (per_kv), entry c * lam + slot
-  const uint32_t* kmask;   // [B, Hq, ncf, C/32]: with dret, the tokens of every list
-  const int32_t* sel;      // [B, Hq, sel_stride]
-  HeadMap map;
-  int B, H, Hq, N, d, cap, C, lam, ncf, sel_stride;
-  int n_ret;               // entries that have a gradient (some row sees them)
 };
 struct BwdSaArgs {
   const void* q;
@@ -408,16 +466,10 @@ struct RopeArgs {
 };
 hipError_t launch_rope(const RopeArgs& a, int dtype, hipStream_t stream);
 hipError_t launch_bgemm(const GemmArgs& a, int dtype, int U, int n_c, hipStream_t stream);
-// the same product summed over the items c' >= c + 2 for every item c, written in the storage type (C is then a T*;
-// M a multiple of 64, m_total unused)
-hipError_t launch_bgemm_revscan(const GemmArgs& a, int dtype, int U, int n_c, hipStream_t stream);
 hipError_t launch_fill_f32(float* p, int64_t n, float x, hipStream_t stream);
 hipError_t launch_bwd_row_prep(const BwdRowArgs& a, int dtype, hipStream_t stream);
-hipError_t launch_bwd_dg(const BwdRowArgs& a, int dtype, hipStream_t stream);
 hipError_t launch_bwd_np(const BwdNpArgs& a, int dtype, bool backward, hipStream_t stream);
 hipError_t launch_bwd_colsum(const BwdColsumArgs& a, int dtype, int U, hipStream_t stream);
-hipError_t launch_bwd_revcumsum(float* X, int U, int nc, int64_t L, hipStream_t stream);
-hipError_t launch_bwd_finish(const BwdFinishArgs& a, int dtype, hipStream_t stream);
 hipError_t launch_bwd_gather(const BwdGatherArgs& a, int dtype, int U, hipStream_t stream);
 hipError_t launch_bwd_sa(const BwdSaArgs& a, int dtype, int d, int B, hipStream_t stream);
 struct AttnMapArgs {

@@ -297,3 +297,16 @@ def test_attention_map_against_the_oracle(kw):
         err = float(np.max(np.abs(x - ref[n])))
         print(f"[{w.name}] map backward {n}: max |ref| {scale_:.3e}  max-abs err {err:.3e}")
         assert np.all(np.isfinite(x)) and err <= BAR[w.dtype] * max(scale_, 1e-30), (n, err, scale_)
+
+
+@pytest.mark.parametrize("kw,gate", [
+    (dict(dtype="bf16", d=128, C=128, N=128 * 9 + 70, Hq=8, Hkv=2, lam=8), True),   # two 64-token tiles per image, prefix images
+    (dict(dtype="bf16", d=128, C=64, N=64 * 3, Hq=8, Hkv=8, lam=5), False),         # one chunk with a state behind it, no gate
+    (dict(dtype="bf16", d=64, C=64, N=64 * 7 + 1, Hq=6, Hkv=2, lam=16), True),      # a last tile of one token
+    (dict(dtype="f32", C=64, N=64 * 5 + 63, Hq=8, Hkv=4, lam=3), False),            # a last tile short of one token
+    (dict(dtype="f32", C=128, W=128, N=128 * 6 - 64, Hq=2, Hkv=2, lam=16), True),   # the last chunk is half a chunk
+], ids=["bf16-d128-C128", "bf16-no-gate-3-chunks", "bf16-d64-one-token-tail", "f32-no-gate", "f32-C128-half-chunk"])
+def test_backward_linear_branch_tiles(kw, gate):
+    """The linear branch works in tiles of 64 tokens (several kv groups and their head maps, both image sources)."""
+    w = small("bwd-lin-" + "-".join(f"{k}{v}" for k, v in kw.items()), **kw)
+    check_backward(w, with_bias(w, synth.make_inputs(w, seed=81, with_gate=gate), 82), 83)
