@@ -7,6 +7,7 @@
 #include <stdio.h>
 #include <string.h>
 
+#include <algorithm>
 #include <mutex>
 
 #include "still_kernels.h"
@@ -185,19 +186,13 @@ void fill_map(const still_params_t* p, still::HeadMap* m) {
   for (int h = 0; h < p->Hq; ++h) m->kv[h] = p->kv_head_of_q ? p->kv_head_of_q[h] : h / (p->Hq / p->Hkv);
 }
 
-void compute_layout(const still_params_t* p, still_ws_layout_t* L) {
+void layout_with_segments(const still_params_t* p, int64_t G, still_ws_layout_t* L) {
   const size_t es = esize(p->dtype);
   const int64_t B = p->B, N = p->N, Hq = p->Hq, Hkv = p->Hkv, d = p->d, df = p->d_f;
   const int64_t nc = (N + p->C - 1) / p->C, ncf = N / p->C;
   const int64_t npad = (N + 127) / 128 * 128;
   const bool evict = p->budget_policy == 1;   // then the retained rows of the workspace are ALL offers, under masks
   const int64_t cap = ((int64_t)still::retained_rows((int)ncf, p->lambda, evict ? still::kNoBudget : retained_budget(p)) + 63) / 64 * 64;
-  int64_t G = (nc * B * Hq + 255) / 256;   // one workgroup per CU at the size of the chip
-  if (G < 2) G = 2;
-  if (G > nc) G = nc;
-  // the scan walks in rounds of RT tokens: a segment is a whole number of rounds
-  const int64_t per_round = still::la_round_tokens((int)es, (int)d) / p->C;
-  if (per_round > 1) G = (G + per_round - 1) / per_round * per_round;
   const int64_t nseg = (nc + G - 1) / G;
   size_t off = 0;
   auto take = [&](size_t bytes) {
@@ -232,6 +227,35 @@ void compute_layout(const still_params_t* p, still_ws_layout_t* L) {
   L->cap = (int32_t)cap;
   L->nseg = (int32_t)nseg;
   L->seg_chunks = (int32_t)G;
+}
+
+// Chunks per segment of the scan.  The scan walks in rounds of RT tokens, a segment is a whole number of rounds, and the
+// device holds one of its workgroups per CU at a time.  A workgroup costs its rounds and about one more (its weights, its
+// total); the cheapest number of passes over the CUs wins, the smaller number of segments among equals.  (Cutting for one
+// workgroup per CU, whatever that leaves, put 5 sequences of 3001 tokens, 32 heads, into 320 workgroups, i.e. two
+// passes of twelve chunks: call 505 us; three segments, two passes of eight: 446 us.  Counting two workgroups per CU at
+// d = 64, where two fit, was 2 % slower at 4 x 4096 tokens.)
+void compute_layout(const still_params_t* p, still_ws_layout_t* L) {
+  constexpr int64_t kCus = 256;
+  const int64_t nc = ((int64_t)p->N + p->C - 1) / p->C, units = (int64_t)p->B * p->Hq;
+  const int64_t rt = still::la_round_tokens((int)esize(p->dtype), p->d), per_round = rt > p->C ? rt / p->C : 1;
+  auto whole_rounds = [&](int64_t g) { return (g + per_round - 1) / per_round * per_round; };
+  int64_t G = 0, best = 0;
+  for (int64_t ns = 1; ns <= nc && (ns == 1 || units * ns <= 4 * kCus); ++ns) {
+    int64_t g = (nc + ns - 1) / ns;
+    g = whole_rounds(g < 2 ? 2 : g);
+    const int64_t groups = units * ((nc + g - 1) / g);
+    const int64_t cost = (groups + kCus - 1) / kCus * ((g * p->C + rt - 1) / rt + 1);
+    if (G == 0 || cost < best) G = g, best = cost;
+  }
+  layout_with_segments(p, G, L);
+  // More segments take more workspace: a problem that only fits the built-in scratch array with fewer keeps fewer.
+  const int64_t g_few = whole_rounds(std::min(nc, std::max<int64_t>(2, (nc * units + kCus - 1) / kCus)));
+  if (g_few > G && L->total > (size_t)STILL_STATIC_WORKSPACE_BYTES) {
+    still_ws_layout_t F;
+    layout_with_segments(p, g_few, &F);
+    if (F.total <= (size_t)STILL_STATIC_WORKSPACE_BYTES) *L = F;
+  }
 }
 
 still_status_t validate_state_params(const still_params_t* p) {

@@ -216,7 +216,9 @@ __global__ __launch_bounds__(256, 2) void bwd_lin_kernel(BwdLinArgs a) {
     }
     for (int i = tid; i < DP; i += 256) {
       float z = a.zsnap[(unit * a.nc + c) * DP + i];
-      if constexpr (!KEY) z += a.zpre[(unit * a.nseg + c / a.seg_chunks) * DP + i];
+      if constexpr (!KEY) {
+        if (c >= a.seg_chunks) z += a.zpre[(unit * a.nseg + c / a.seg_chunks) * DP + i];   // (segment 0 has no prefix)
+      }
       zl[i] = z;
     }
     const float coef = KEY ? 1.f : a.ed[unit * N + t];

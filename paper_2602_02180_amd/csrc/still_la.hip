@@ -88,12 +88,16 @@ __device__ __forceinline__ void la_body(const LaArgs& a) {
   const int r = lane & 31, g = lane >> 5;
   const int kvh = a.map.kv[hq];
   const int N = seq_tokens(a.seq_len, b, a.N);   // this sequence's tokens (a right-padded batch has shorter ones)
-  const int nc_b = (N + C - 1) / C, ncf_b = N / C;
+  const int nc_b = (N + C - 1) / C;
   const int G = a.seg_chunks;
   if (seg * G >= nc_b) return;                   // the whole segment is padding (uniform over the workgroup)
 
-  const int seg_tok0 = (seg * G - 1) * C;        // first token of the segment's first chunk (chunk -1 for segment 0)
-  const int R = G * C / RT;                      // rounds; G * C is a multiple of RT by construction of G
+  // Chunks [c_beg, c_end) are walked: those of the segment that exist and that some row's state holds (the last two
+  // chunks of a sequence are never behind any row).  A round that reaches past c_end meets zero features there.
+  const int c_beg = seg > 0 ? seg * G - 1 : 0;
+  const int c_end = (seg + 1) * G - 1 < nc_b - 2 ? (seg + 1) * G - 1 : nc_b - 2;
+  const int seg_tok0 = c_beg * C;
+  const int R = c_end > c_beg ? ((c_end - c_beg) * C + RT - 1) / RT : 0;   // rounds
   const int64_t unit = (int64_t)b * a.Hq + hq;
   float* __restrict__ segp = a.seg + (unit * a.nseg + seg) * (int64_t)(DP * (D + 1));
 
@@ -133,7 +137,7 @@ __device__ __forceinline__ void la_body(const LaArgs& a) {
     // goes to the state)
     auto load_keep = [&](int tokw) __attribute__((always_inline)) {
       const int cc = floor_div(tokw, C);
-      const bool valid = cc >= 0 && cc < ncf_b;          // only full chunks are ever routed
+      const bool valid = cc < c_end;                     // (c_end never exceeds the number of full chunks)
       if constexpr (SUB) kw = valid ? 0u : 0xffffffffu;  // (which positions carry nothing comes with the rows)
       else kw = valid ? a.kmask[(unit * a.ncf + cc) * (C / 32) + (tokw - cc * C) / 32] : 0xffffffffu;
     };
@@ -296,14 +300,17 @@ __device__ __forceinline__ void la_body(const LaArgs& a) {
   auto emit = [&](int oc) __attribute__((always_inline)) {
     if (oc >= nc_b) return;
     const int lane_now = fresh_lane_id(), rr = lane_now & 31, gg = lane_now >> 5;
-    T* sp = static_cast<T*>(a.snap) + (unit * a.nc + oc) * (int64_t)(D * DP) + (int64_t)(32 * wave + rr) * DP;
+    // (nobody reads the image of a segment's first chunk, which would be empty, nor of the first two chunks)
+    if (oc % G != 0 && oc >= 2) {
+      T* sp = static_cast<T*>(a.snap) + (unit * a.nc + oc) * (int64_t)(D * DP) + (int64_t)(32 * wave + rr) * DP;
 #pragma unroll
-    for (int ft = 0; ft < PT; ++ft)
+      for (int ft = 0; ft < PT; ++ft)
 #pragma unroll
-      for (int s = 0; s < SPT; ++s) {
-        if constexpr (M::KPL == 1) sp[32 * ft + M::pos_of_reg(s, gg)] = M::from_acc(S[ft], s);
-        else *reinterpret_cast<typename M::frag*>(sp + 32 * ft + s * M::KK + gg * M::KPL) = M::from_acc(S[ft], s);
-      }
+        for (int s = 0; s < SPT; ++s) {
+          if constexpr (M::KPL == 1) sp[32 * ft + M::pos_of_reg(s, gg)] = M::from_acc(S[ft], s);
+          else *reinterpret_cast<typename M::frag*>(sp + 32 * ft + s * M::KK + gg * M::KPL) = M::from_acc(S[ft], s);
+        }
+    }
     a.zsnap[(unit * a.nc + oc) * DP + 64 * wave + lane_now] = z;
     if (a.s_final != nullptr && oc == nc_b - 1) {
       float* dst = a.s_final + unit * (int64_t)(DP * (D + 1));
@@ -371,6 +378,7 @@ __device__ __forceinline__ void la_body(const LaArgs& a) {
   };
 
   emit(seg * G);                                 // the prefix itself is the state of the segment's first chunk
+  if (seg == 0 && G > 1) emit(1);                // (and nothing is behind the rows of chunk 1)
   {
     VFrag va, vb;
     load_v(0, va);
@@ -380,8 +388,9 @@ __device__ __forceinline__ void la_body(const LaArgs& a) {
       if (gp + 1 < NP) part_step(gp + 1, vb, va);
     }
   }
-  // the segment's total, as [x][feature] like the snapshots (written once per workgroup)
-  {
+  // the segment's total, as [x][feature] like the snapshots (written once per workgroup).  The sequence's last segment
+  // has nobody behind it: its total is not needed.
+  if ((seg + 1) * G < nc_b) {
     const int lane_now = fresh_lane_id(), rr = lane_now & 31, gg = lane_now >> 5;
     float* tp = segp + (int64_t)(32 * wave + rr) * DP;
 #pragma unroll
@@ -399,32 +408,64 @@ __global__ __launch_bounds__((LaCfg<T, D, C>::NCW + LaCfg<T, D, C>::NPW) * 64) v
 }
 
 // Exclusive prefix over the segments of one (batch, head), elementwise over the state as [x][feature] (+ z):
-// pimg[s] / zpre[s] = sum of the totals of the segments before s, i.e. the state through chunk s*G-2; the fp32
-// state of the decode hand-over (written by the scan as a local part, laid out [feature][x]) receives the prefix
-// of the segment of the sequence's last chunk.
+// pimg[s] / zpre[s] = sum of the totals of the segments before s, i.e. the state through chunk s*G-2, for
+// s = 1 .. the segment of the sequence's last chunk (segment 0 has no prefix and its consumers read none; a scan of one
+// segment needs no launch); the fp32 state of the decode hand-over (written by the scan as a local part, laid out
+// [feature][x]) receives the prefix of the segment of the sequence's last chunk.
+// Bound: memory (totals once, images once).  A workgroup takes 32 rows x of 64 features, so that the totals and images
+// move in pieces of 256 and 128 bytes; the hand-over's transposed sum passes through LDS and is skipped where the
+// prefix is empty.  With one element per thread and the transposed sum in place (4 bytes per line, also where it added
+// zero) this took 131 us at 8 x 2048 tokens, 32 heads, d = 128 with a hand-over (one segment: now not launched), and
+// 30 us at 5 x 3001 tokens.
 template <typename T>
 __global__ __launch_bounds__(256) void la_prefix_kernel(LaArgs a, int D) {
+  constexpr int XT = 32, FT = 64;
+  __shared__ float tile[FT][XT + 1];
   const int DP = 2 * D;
   const int64_t elems = (int64_t)DP * (D + 1);
-  const int64_t idx = (int64_t)blockIdx.x * 256 + threadIdx.x;
-  if (idx >= elems) return;
   const int64_t unit = blockIdx.y;
-  const int b = (int)(unit / a.Hq);
+  const int b = (int)(unit / a.Hq), tid = threadIdx.x;
   const int N = seq_tokens(a.seq_len, b, a.N);
   const int seg_last = ((N + a.C - 1) / a.C - 1) / a.seg_chunks;     // segment of the sequence's last chunk
-  const float* tot = a.seg + unit * a.nseg * elems + idx;
-  const bool is_z = idx >= (int64_t)D * DP;
-  float run = 0.f;
-  for (int s = 0; s < a.nseg; ++s) {
-    if (is_z) a.zpre[(unit * a.nseg + s) * DP + (idx - (int64_t)D * DP)] = run;
-    else static_cast<T*>(a.pimg)[(unit * a.nseg + s) * (int64_t)(D * DP) + idx] = from_f32<T>(run);
-    if (s == seg_last && a.s_final != nullptr) {
-      float* sf = a.s_final + unit * elems;
-      if (is_z) sf[idx] += run;                                       // z sits behind S in both layouts
-      else sf[(idx % DP) * D + idx / DP] += run;                      // [x][feature] -> [feature][x]
+  const float* tot = a.seg + unit * a.nseg * elems;
+  float* sf = a.s_final != nullptr && seg_last > 0 ? a.s_final + unit * elems : nullptr;
+  const int n_ft = DP / FT;
+  if ((int)blockIdx.x == n_ft * (D / XT)) {                          // z
+    if (tid >= DP) return;
+    float run = 0.f;
+    for (int s = 1; s <= seg_last; ++s) {
+      run += tot[(s - 1) * elems + (int64_t)D * DP + tid];
+      a.zpre[(unit * a.nseg + s) * DP + tid] = run;
     }
-    if (s <= seg_last && s + 1 < a.nseg) run += tot[(int64_t)s * elems];   // later segments were never walked
+    if (sf != nullptr) sf[(int64_t)D * DP + tid] += run;             // z sits behind S in both layouts
+    return;
   }
+  const int f0 = (blockIdx.x % n_ft) * FT, x0 = (blockIdx.x / n_ft) * XT;
+  const int fl = (tid % 16) * 4, xl = tid / 16;                      // four features of rows xl and xl + 16
+  floatx4 run[2] = {{0.f, 0.f, 0.f, 0.f}, {0.f, 0.f, 0.f, 0.f}};
+#pragma unroll 4
+  for (int s = 1; s <= seg_last; ++s)
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+      const int64_t at = (int64_t)(x0 + xl + 16 * h) * DP + f0 + fl;
+      run[h] += *reinterpret_cast<const floatx4*>(tot + (s - 1) * elems + at);
+      T* dst = static_cast<T*>(a.pimg) + (unit * a.nseg + s) * (int64_t)(D * DP) + at;
+      if constexpr (sizeof(T) == 2) {
+        bf16x4 v;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) v[e] = static_cast<bf16>(run[h][e]);
+        *reinterpret_cast<bf16x4*>(dst) = v;
+      } else {
+        *reinterpret_cast<floatx4*>(dst) = run[h];
+      }
+    }
+  if (sf == nullptr) return;                                         // (uniform over the workgroup)
+#pragma unroll
+  for (int h = 0; h < 2; ++h)
+#pragma unroll
+    for (int e = 0; e < 4; ++e) tile[fl + e][xl + 16 * h] = run[h][e];
+  __syncthreads();
+  for (int i = tid; i < FT * XT; i += 256) sf[(int64_t)(f0 + i / XT) * D + x0 + i % XT] += tile[i / XT][i % XT];
 }
 
 template <typename T, int D, int C>
@@ -455,8 +496,8 @@ hipError_t launch_la_states(const LaArgs& a, int dtype, int d, int B, hipStream_
 }
 
 hipError_t launch_la_prefix(const LaArgs& a, int dtype, int d, int B, hipStream_t stream) {
-  const int64_t elems = (int64_t)2 * d * (d + 1);
-  dim3 grid((unsigned)((elems + 255) / 256), B * a.Hq), block(256);
+  if (a.nseg <= 1) return hipSuccess;
+  dim3 grid((2 * d / 64) * (d / 32) + 1, B * a.Hq), block(256);
   if (dtype == 1) hipLaunchKernelGGL(la_prefix_kernel<bf16>, grid, block, 0, stream, a, d);
   else hipLaunchKernelGGL(la_prefix_kernel<float>, grid, block, 0, stream, a, d);
   return hipGetLastError();

@@ -402,7 +402,9 @@ __device__ __forceinline__ void sa_body(const SaArgs& a) {
       request_pair(0);
       for (int i = tid; i < (la_hi - la_lo + 1) * DP; i += Cf::NW * 64) {
         const int cc = la_lo + i / DP, fz = i % DP;
-        zl[i] = a.zsnap[(unit * a.nc + cc) * DP + fz] + a.zpre[(unit * a.nseg + cc / Gs) * DP + fz];
+        float z = a.zsnap[(unit * a.nc + cc) * DP + fz];
+        if (cc >= Gs) z += a.zpre[(unit * a.nseg + cc / Gs) * DP + fz];   // (segment 0 has no prefix)
+        zl[i] = z;
       }
 #pragma unroll
       for (int s = 0; s < KS; ++s) asm volatile("" ::"v"(qf[s]));

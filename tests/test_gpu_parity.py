@@ -661,3 +661,41 @@ def test_rope_pre_pass_matches_the_oracle_and_composes_with_the_prefill(dtype):
     inp2 = dict(inp)
     inp2["q"], inp2["k"] = synth.from_torch(q), synth.from_torch(k)
     run_case(w, inp2)
+
+
+# ------------------------------------------------------------------ the cut of the chunk scan is invisible
+@pytest.mark.parametrize("kw,N,lens", [
+    (dict(d=64, C=64, W=64, Hq=16, Hkv=4), 64 * 37 + 11, [64 * 37 + 11, 1, 64, 129, 64 * 20, 64 * 13 + 5, 64 * 37]),
+    (dict(d=128, C=128, W=128, Hq=32, Hkv=8), 128 * 24 - 71, [128 * 24 - 71, 128 * 8, 128 * 8 + 1, 128 * 17, 200]),
+    (dict(d=128, C=64, W=64, Hq=8, Hkv=8), 64 * 9, [64 * 9, 64 * 2, 64 * 3 + 1]),
+], ids=["d64C64", "d128C128", "d128C64"])
+def test_segments_of_the_scan_give_the_same_rows_and_state(kw, N, lens):
+    """A right-padded batch and each of its sequences alone are cut differently (other segment lengths, segments that end
+    early, one segment); fp32 rows and the exported fp32 state may differ by the order of the sums only: a few
+    roundings of 2^-24 over at most N terms, bound 3e-5 of the largest element."""
+    import torch
+    dev, B, d, Hq, Hkv = "cuda", len(lens), kw["d"], kw["Hq"], kw["Hkv"]
+    g = torch.Generator(device=dev).manual_seed(5)
+    q, k, v = (torch.randn(B, N, h, d, generator=g, device=dev) for h in (Hq, Hkv, Hkv))
+    Wq, Wk = (torch.randn(Hq, d, d, generator=g, device=dev) / d ** 0.5 for _ in range(2))
+
+    def run(q, k, v, seq_len):
+        b, n = q.shape[0], q.shape[1]
+        out = torch.zeros_like(q)
+        p = S.make_params(B=b, N=n, lam=16, scale=d ** -0.5, eps=1e-6, dtype="f32", max_tokens=N + 64, q=q, k=k, v=v,
+                            out=out, seq_len=seq_len, **kw)
+        state = torch.zeros(S.still_state_bytes(p), dtype=torch.uint8, device=dev)
+        ws = torch.full((S.still_fwd_workspace_bytes(p),), 0x7f, dtype=torch.uint8, device=dev)   # (nothing starts at zero)
+        S.still_hybrid_attn_fwd(p, q, k, v, None, Wq, None, Wk, None, out, state_out=state, workspace=ws)
+        n_s = b * Hq * 2 * d * (d + 1)
+        off = S.still_state_layout(p).S
+        return out, state[off:off + 4 * n_s].view(torch.float32).view(b, Hq, -1), S.still_fwd_workspace_layout(p).nseg
+
+    out, S_all, nseg = run(q, k, v, torch.tensor(lens, dtype=torch.int32, device=dev))
+    cuts = {nseg}
+    for b, n in enumerate(lens):
+        one, S_one, ns = run(*(x[b:b + 1, :n].contiguous() for x in (q, k, v)), None)
+        cuts.add(ns)
+        for got, want in ((out[b, :n], one[0]), (S_all[b], S_one[0])):
+            assert (got - want).abs().max() <= 3e-5 * max(1.0, float(want.abs().max())), (b, n, nseg, ns)
+    assert len(cuts) > 1

@@ -227,3 +227,13 @@ def test_public_header_is_plain_c_and_matches_the_binding(tmp_path):
     got = [int(x) for x in subprocess.run([str(exe)], check=True, capture_output=True, text=True).stdout.split()]
     assert got == [ctypes.sizeof(S.StillParams), ctypes.sizeof(S.StillWsLayout), ctypes.sizeof(S.StillStateLayout),
                    S.StillParams.q_sb.offset, S.StillParams.seq_len.offset]
+
+
+@pytest.mark.parametrize("kw", [
+    dict(B=1, Hq=8, N=2432, dtype="f32"), dict(B=2, Hq=16, N=1280), dict(B=3, Hq=8, N=1664), dict(B=5, Hq=4, N=2048),
+    dict(B=8, Hq=4, N=1280), dict(B=3, Hq=4, N=1344, d=128, C=128), dict(B=5, Hq=8, N=192, d=128, C=128),
+    dict(B=4, Hq=4, N=576, d=128), dict(B=1, Hq=32, N=448, d=128, C=128)])
+def test_the_cut_of_the_scan_never_outgrows_the_builtin_scratch_array(kw):
+    """Problems that fill the array when the scan is cut into few segments: more segments may not push them out."""
+    kw = dict(dict(Hkv=kw["Hq"]), **kw)
+    assert S.still_fwd_workspace_bytes(params(**kw)) <= 32 << 20
