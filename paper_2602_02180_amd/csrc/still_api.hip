@@ -750,7 +750,7 @@ still_status_t decode_step(const still_params_t* p, void* state, int32_t t, cons
   const int rows = still::retained_rows(c >= 1 ? c - 1 : 0, p->lambda, a.rcap) + (t - (c >= 1 ? c - 1 : 0) * p->C + 1);
   const int units = p->B * (p->shared_selection ? p->Hkv : p->Hq);   // workgroups per split
   int nsplit = (1024 + units - 1) / units;
-  if (nsplit > 32) nsplit = 32;
+  if (nsplit > still::kMaxSplits) nsplit = still::kMaxSplits;
   if (nsplit > (rows + 63) / 64) nsplit = (rows + 63) / 64;
   if (nsplit < 1) nsplit = 1;
   a.nsplit = nsplit;

@@ -3,13 +3,16 @@
 //
 // One step is bandwidth-bound: every (batch, query head) reads all its retained keys/values plus the local
 // span once.  Kernels of a step, all on the caller's stream:
-//   append   : (k_t, v_t) into the ring of recent tokens (slot = t mod R)
-//   score    : Self-Saliency Score of token t over its window (Sec. 3.1), one thread per window key
 //   route    : only when t opens chunk c >= 2: Top-lambda of chunk c-2 (ties to the lower index), selected
 //              rows appended to the retained cache, the others folded into (S, z) through the NP-Map
-//   attend   : split over the rows of the salient cache: per split an online-softmax partial (m, l, acc)
-//   finish   : NP-Map of q_t, N_LA = phi_q S, D_LA = phi_q z, merge of the split partials,
-//              y = (N_SA + g*N_LA) / (D_SA + D_LA) with both branches scaled by exp(-max(m, 0))
+//   step     : everything that reads the state, as workgroups of one launch that do not depend on each other:
+//     attend : split over the rows of the salient cache: per split an online-softmax partial (m, l, acc)
+//     linear : NP-Map of q_t, N_LA = phi_q S, D_LA = phi_q z
+//     score  : Self-Saliency Score of token t over its window (Sec. 3.1), one thread per window key
+//     append : (k_t, v_t) into the ring of recent tokens (slot = t mod R)
+//   merge    : y = (N_SA + g*N_LA) / (D_SA + D_LA) over the partials, both branches scaled by exp(-max(m, 0))
+// The token's own key and value are read from the caller's rows, so nobody waits for the ring; its ring slot (that of
+// token t - R) lies outside every window and local span (W <= R, the span is at most 2C rows, R = 4C).
 // Everything is plain vector-ALU code with fp32 accumulation: there is no contraction here that could
 // feed a matrix core (one query row per head).
 #include "still_kernels.h"
@@ -84,22 +87,10 @@ __device__ __forceinline__ void decode_append(const DecArgs& a, int h, int b, in
   }
 }
 
-// ---------------------------------------------------------------- score of the new token (+ append)
-// Workgroups 0 .. Hq-1 of a sequence score the new token for one query head each; workgroups Hq .. Hq+Hkv-1 copy
-// the new key/value rows of one kv head into the ring.  The two do not depend on each other within the step: the
-// score reads the new key from the caller's k_t, and the ring slot being overwritten (token t - R) lies outside
-// every window (W <= R).  One thread per window key: 128 threads, or 256 for a window of more than 128 keys.
+// ---------------------------------------------------------------- score of the new token
+// One thread per window key (256 threads, W <= 256).
 template <typename T, int D>
-__global__ __launch_bounds__(256) void decode_score_kernel(DecArgs a) {
-  __shared__ float sh[16];
-  const int b = blockIdx.y;
-  const int t = step_index(a, b);
-  if (t < 0) return;
-  if ((int)blockIdx.x >= a.Hq) {
-    decode_append<T>(a, blockIdx.x - a.Hq, b, t, D);
-    return;
-  }
-  const int hq = blockIdx.x;
+__device__ __forceinline__ void decode_score(const DecArgs& a, int hq, int b, int t, float* sh) {
   const int kvh = a.map.kv[hq];
   const int j = threadIdx.x;              // window key t - j
   const int pj = t - j;
@@ -122,7 +113,7 @@ __global__ __launch_bounds__(256) void decode_score_kernel(DecArgs a) {
   }
   const float x2 = valid ? dot * (a.scale * kLog2e) : -INFINITY;
   float s0 = 0.f, s1 = 0.f, mx = x2, mn = 0.f;
-  const int nwaves = blockDim.x >> 6;
+  constexpr int nwaves = 4;
   block_reduce4(s0, s1, mx, mn, sh, nwaves);
   const float e = valid ? fast_exp2(x2 - mx) : 0.f;
   float d_all = e, d_no = j == 0 ? 0.f : e;
@@ -507,24 +498,27 @@ constexpr size_t decode_route_smem() {
 }
 
 // ---------------------------------------------------------------- attention over the salient cache (split)
-// Four workgroups per CU (one wave per SIMD each) rather than the eight the registers would allow: every workgroup
-// streams its own two rows-of-cache sequences, and with half as many sequences open at a time the memory system
-// delivers 1.5 % more (measured at B Hq = 2048 units of 4 K retained rows; more resident waves do not help a
-// kernel that is bound by bandwidth, not latency: unrolling the row loop with all loads up front changes nothing).
+// LDS tables of the row groups' partials, for GH query heads
+template <typename T, int D, int GH>
+struct AttendLds {
+  static constexpr int NG = 4 * 64 / (D * (int)sizeof(T) / 16);
+  float m[GH][NG], l[GH][NG], acc[GH][NG][D];
+};
+
 template <typename T, int D>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4, 4))) void decode_attend_kernel(DecArgs a) {
+__device__ __forceinline__ void decode_attend(const DecArgs& a, int split, int hq, int b, int t, AttendLds<T, D, 1>& lds) {
   constexpr int EPV = 16 / sizeof(T);
   constexpr int LPR = D / EPV;        // lanes per row
   constexpr int RPW = 64 / LPR;       // rows per wave step
   constexpr int NG = 4 * RPW;         // row groups per block
-  __shared__ float s_m[NG], s_l[NG], s_acc[NG][D];
-  const int split = blockIdx.x, hq = blockIdx.y, b = blockIdx.z, tid = threadIdx.x;
+  auto& s_m = lds.m[0];
+  auto& s_l = lds.l[0];
+  auto& s_acc = lds.acc[0];
+  const int tid = threadIdx.x;
   const int lane = tid & 63, wave = tid >> 6;
   const int sub = lane % LPR, grp = lane / LPR;
   const int kvh = a.map.kv[hq];
   const int64_t unit = (int64_t)b * a.Hq + hq;
-  const int t = step_index(a, b);
-  if (t < 0) return;
   const int c = t / a.C;
   const int n_ret = retained_rows(c >= 1 ? c - 1 : 0, a.lam, a.rcap);
   const int lo = (c >= 1 ? c - 1 : 0) * a.C;
@@ -555,6 +549,9 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4, 4))) voi
       const int rr = valid ? row : 0;
       kp = kret + (int64_t)rr * D;
       vp = vret + (int64_t)rr * D;
+    } else if (row == nr - 1) {          // the new token itself
+      kp = static_cast<const T*>(a.k) + ((int64_t)b * a.Hkv + kvh) * D;
+      vp = static_cast<const T*>(a.v) + ((int64_t)b * a.Hkv + kvh) * D;
     } else {
       const int slot = (lo + (row - n_ret)) % a.R;
       kp = kring + (int64_t)slot * D;
@@ -613,18 +610,19 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4, 4))) voi
 // (split, kv head, sequence) reads every key/value row once and serves up to GH query heads from it (a larger
 // group takes another pass over the rows).  Partials are written per query head, as above.
 template <typename T, int D>
-__global__ __launch_bounds__(256) void decode_attend_shared_kernel(DecArgs a) {
+__device__ __forceinline__ void decode_attend_shared(const DecArgs& a, int split, int kvh, int b, int t,
+                                                     AttendLds<T, D, 4>& lds) {
   constexpr int GH = 4;
   constexpr int EPV = 16 / sizeof(T);
   constexpr int LPR = D / EPV;        // lanes per row
   constexpr int RPW = 64 / LPR;       // rows per wave step
   constexpr int NG = 4 * RPW;         // row groups per block
-  __shared__ float s_m[GH][NG], s_l[GH][NG], s_acc[GH][NG][D];
-  const int split = blockIdx.x, kvh = blockIdx.y, b = blockIdx.z, tid = threadIdx.x;
+  auto& s_m = lds.m;
+  auto& s_l = lds.l;
+  auto& s_acc = lds.acc;
+  const int tid = threadIdx.x;
   const int lane = tid & 63, wave = tid >> 6;
   const int sub = lane % LPR, grp = lane / LPR;
-  const int t = step_index(a, b);
-  if (t < 0) return;
   const int c = t / a.C;
   const int n_ret = retained_rows(c >= 1 ? c - 1 : 0, a.lam, a.rcap);
   const int lo = (c >= 1 ? c - 1 : 0) * a.C;
@@ -666,6 +664,9 @@ __global__ __launch_bounds__(256) void decode_attend_shared_kernel(DecArgs a) {
         const int rr = valid ? row : 0;
         kp = kret + (int64_t)rr * D;
         vp = vret + (int64_t)rr * D;
+      } else if (row == nr - 1) {          // the new token itself
+        kp = static_cast<const T*>(a.k) + ((int64_t)b * a.Hkv + kvh) * D;
+        vp = static_cast<const T*>(a.v) + ((int64_t)b * a.Hkv + kvh) * D;
       } else {
         const int slot = (lo + (row - n_ret)) % a.R;
         kp = kring + (int64_t)slot * D;
@@ -731,103 +732,206 @@ __global__ __launch_bounds__(256) void decode_attend_shared_kernel(DecArgs a) {
   }
 }
 
-// ---------------------------------------------------------------- NP-Map of q_t, linear terms, merge
+// ---------------------------------------------------------------- NP-Map of q_t, linear terms
+// Latency decides here at small batches, so nothing waits that need not: the state rows a thread multiplies are
+// requested before the feature map starts (what the registers hold at four waves per SIMD), W_q comes in 16-byte pieces, and
+// every wave takes the feature map of all features by itself (one exchange through LDS between f = q W and the state).
 template <typename T, int D>
-__global__ __launch_bounds__(256) void decode_finish_kernel(DecArgs a) {
-  constexpr int DF = D, DP = 2 * D;
-  constexpr int CG = D / 4, RP = 256 / CG;         // column groups of 4 floats, row parts (8 or 16)
-  __shared__ float qs[D], phi[DP], sh[16], fpart[2][DF];
-  __shared__ __attribute__((aligned(16))) float red[RP][D];
+struct LinearLds {
+  static constexpr int EPV = 16 / (int)sizeof(T), XP = 256 / (D / EPV), RP = 256 / (D / 4);
+  float f[XP][D], red[RP][D], phi[4][2 * D];
+};
+
+template <typename T, int D>
+__device__ __forceinline__ void decode_linear(const DecArgs& a, int hq, int b, LinearLds<T, D>& lds) {
+  typedef LinearLds<T, D> L;
+  constexpr int DF = D, DP = 2 * D, EPV = L::EPV;
+  constexpr int NX = D / L::XP;                    // rows of W per thread
+  constexpr int NR = DP / L::RP, PRE = NR <= 8 ? NR : (EPV == 8 ? 16 : 8);   // rows of S per thread,
+                                                                            // requested at the start
+  constexpr int NL = D / 64;                       // features per lane
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int64_t unit = (int64_t)b * a.Hq + hq;
+  const T* q = static_cast<const T*>(a.q) + unit * D;
+  const float* Sg = a.S + unit * (int64_t)(DP * (D + 1));
+  const int cg = tid % (D / 4), rp = tid / (D / 4);        // four columns of S; rows rp, rp + RP, ...
+  // f = q W_q: thread (xp, fg) has EPV features and NX rows
+  const int fg = tid % (DF / EPV), xp = tid / (DF / EPV);
+  float fp[EPV];
+#pragma unroll
+  for (int e = 0; e < EPV; ++e) fp[e] = 0.f;
+  {
+    const T* wq = static_cast<const T*>(a.wq) + ((int64_t)hq * D + xp * NX) * DF + fg * EPV;
+    Vec<T> w[NX];
+    float qx[NX], ql[NL], zv[2 * NL];
+#pragma unroll
+    for (int x = 0; x < NX; ++x) w[x] = *reinterpret_cast<const Vec<T>*>(wq + (int64_t)x * DF);
+#pragma unroll
+    for (int x = 0; x < NX; ++x) qx[x] = to_f32(q[xp * NX + x]);
+#pragma unroll
+    for (int i = 0; i < NL; ++i) ql[i] = to_f32(q[64 * i + lane]);
+#pragma unroll
+    for (int i = 0; i < 2 * NL; ++i) zv[i] = Sg[DP * D + 64 * i + lane];
+    floatx4 sv[PRE];
+#pragma unroll
+    for (int i = 0; i < PRE; ++i) sv[i] = *reinterpret_cast<const floatx4*>(Sg + (int64_t)(rp + i * L::RP) * D + 4 * cg);
+#pragma unroll
+    for (int x = 0; x < NX; ++x)
+#pragma unroll
+      for (int e = 0; e < EPV; ++e) fp[e] = fmaf(qx[x], to_f32(w[x].v[e]), fp[e]);
+#pragma unroll
+    for (int e = 0; e < EPV; e += 4)
+      *reinterpret_cast<floatx4*>(&lds.f[xp][fg * EPV + e]) = floatx4{fp[e], fp[e + 1], fp[e + 2], fp[e + 3]};
+    __syncthreads();
+    float f[NL], nx2 = 0.f, nf2 = 0.f, fmx = -INFINITY, fmn = INFINITY;
+#pragma unroll
+    for (int i = 0; i < NL; ++i) {
+      f[i] = a.bq != nullptr ? to_f32(static_cast<const T*>(a.bq)[(int64_t)hq * DF + 64 * i + lane]) : 0.f;
+#pragma unroll
+      for (int x = 0; x < L::XP; ++x) f[i] += lds.f[x][64 * i + lane];
+      nx2 = fmaf(ql[i], ql[i], nx2);
+      nf2 = fmaf(f[i], f[i], nf2);
+      fmx = fmaxf(fmx, f[i]);
+      fmn = fminf(fmn, f[i]);
+    }
+    nx2 = wave_sum(nx2);
+    nf2 = wave_sum(nf2);
+    fmx = wave_max(fmx);
+    fmn = -wave_max(-fmn);
+    const float ratio = nf2 > 0.f ? sqrtf(nx2 / nf2) : 0.f;
+    const float a1 = ratio * kLog2e;
+    float ep[NL], en[NL], sp = 0.f, sn = 0.f, dl = 0.f;
+#pragma unroll
+    for (int i = 0; i < NL; ++i) {
+      ep[i] = fast_exp2(fmaf(f[i], a1, -fmx * a1));
+      en[i] = fast_exp2(fmaf(f[i], -a1, fmn * a1));
+      sp += ep[i];
+      sn += en[i];
+    }
+    sp = wave_sum(sp);
+    sn = wave_sum(sn);
+    float* phi = lds.phi[wave];                    // (each wave reads its own copy: no barrier)
+#pragma unroll
+    for (int i = 0; i < NL; ++i) {
+      const float pp = round_to<T>(ep[i] / sp), pn = round_to<T>(en[i] / sn);
+      phi[64 * i + lane] = pp;
+      phi[DF + 64 * i + lane] = pn;
+      dl = fmaf(pp, zv[i], dl);
+      dl = fmaf(pn, zv[NL + i], dl);
+    }
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    dl = wave_sum(dl);
+    // N_LA[x] = sum_f phi[f] S[f][x]
+    floatx4 n4 = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int i = 0; i < PRE; ++i) {
+      const float pw = phi[rp + i * L::RP];
+#pragma unroll
+      for (int e = 0; e < 4; ++e) n4[e] = fmaf(pw, sv[i][e], n4[e]);
+    }
+#pragma unroll
+    for (int i = PRE; i < NR; ++i) {
+      const floatx4 s4 = *reinterpret_cast<const floatx4*>(Sg + (int64_t)(rp + i * L::RP) * D + 4 * cg);
+      const float pw = phi[rp + i * L::RP];
+#pragma unroll
+      for (int e = 0; e < 4; ++e) n4[e] = fmaf(pw, s4[e], n4[e]);
+    }
+    *reinterpret_cast<floatx4*>(&lds.red[rp][4 * cg]) = n4;
+    __syncthreads();
+    float* part = a.part + (unit * 32 + kMaxSplits) * (int64_t)(D + 2);
+    if (tid < D) {
+      float nla = 0.f;
+#pragma unroll
+      for (int i = 0; i < L::RP; ++i) nla += lds.red[i][tid];
+      part[2 + tid] = nla;
+    }
+    if (tid == 0) part[1] = dl;
+  }
+}
+
+// ---------------------------------------------------------------- one launch of everything that reads the state
+// Workgroups: the splits of the salient cache (the long ones) first, then linear terms, scores, ring copies, which fill
+// what the splits leave idle.  As launches of their own (score + append, attend, linear terms and merge in the last)
+// each of them paid its own start and tail.  Before -> now: one sequence behind 4 K tokens, 32 heads, d = 128, 27 us
+// (6.0 + 6.2 + 12.7 in the kernels) -> 11.2 us; 24 sequences with 896 retained rows, d = 64, 59 us (5.7 + 32 + 10) -> 48
+// us; 64 sequences behind 32 K tokens 782 (16 + 714 + 54) -> 755 us, 4.69 GB at 6.2 TB/s.
+template <typename T, int D, bool SHARED>
+__device__ __forceinline__ void decode_step_body(const DecArgs& a) {
+  __shared__ __attribute__((aligned(16))) union {
+    AttendLds<T, D, SHARED ? 4 : 1> att;
+    LinearLds<T, D> lin;
+    float sh[16];
+  } lds;
+  int i = blockIdx.x;
+  const int heads = SHARED ? a.Hkv : a.Hq, n_att = a.nsplit * heads * a.B, n_q = a.Hq * a.B;
+  if (i < n_att) {
+    const int split = i % a.nsplit, h = (i / a.nsplit) % heads, b = i / (a.nsplit * heads);
+    const int t = step_index(a, b);
+    if (t < 0) return;
+    if constexpr (SHARED) decode_attend_shared<T, D>(a, split, h, b, t, lds.att);
+    else decode_attend<T, D>(a, split, h, b, t, lds.att);
+    return;
+  }
+  i -= n_att;
+  const int kind = i < n_q ? 0 : (i < 2 * n_q ? 1 : 2);
+  i -= kind * n_q;
+  const int nh = kind == 2 ? a.Hkv : a.Hq, h = i % nh, b = i / nh;
+  const int t = step_index(a, b);
+  if (t < 0) return;
+  if (kind == 0) decode_linear<T, D>(a, h, b, lds.lin);
+  else if (kind == 1) decode_score<T, D>(a, h, b, t, lds.sh);
+  else decode_append<T>(a, h, b, t, D);
+}
+
+// Four workgroups per CU (one wave per SIMD each) rather than the eight the registers would allow: every workgroup
+// streams its own two rows-of-cache sequences, and with half as many sequences open at a time the memory system
+// delivers 1.5 % more (measured at B Hq = 2048 units of 4 K retained rows; more resident waves do not help a
+// kernel that is bound by bandwidth, not latency: unrolling the row loop with all loads up front changes nothing).
+template <typename T, int D>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4, 4))) void decode_step_kernel(DecArgs a) {
+  decode_step_body<T, D, false>(a);
+}
+template <typename T, int D>
+__global__ __launch_bounds__(256) void decode_step_shared_kernel(DecArgs a) {
+  decode_step_body<T, D, true>(a);
+}
+
+// ---------------------------------------------------------------- merge of the partials
+template <typename T, int D>
+__global__ __launch_bounds__(D) void decode_merge_kernel(DecArgs a) {
   const int hq = blockIdx.x, b = blockIdx.y, tid = threadIdx.x;
   if (step_index(a, b) < 0) return;
   const int64_t unit = (int64_t)b * a.Hq + hq;
-  const T* q = static_cast<const T*>(a.q) + unit * D;
-  if (tid < D) qs[tid] = to_f32(q[tid]);
-  __syncthreads();
-  // f = q W_q: feature tid % DF, the head dimension split between the block's two halves when d_f = 128
-  float f = 0.f;
-  {
-    constexpr int XP = 256 / DF;                   // 2 (d=128) or 4 (d=64) partial sums per feature
-    const int fi = tid % DF, xp = tid / DF;
-    const T* wq = static_cast<const T*>(a.wq) + (int64_t)hq * D * DF + fi;
-    float fp = 0.f;
-#pragma unroll 8
-    for (int x = xp * (D / XP); x < (xp + 1) * (D / XP); ++x) fp = fmaf(qs[x], to_f32(wq[(int64_t)x * DF]), fp);
-    if (xp >= XP - 2) fpart[xp - (XP - 2)][fi] = fp;
-    __syncthreads();
-    if (XP == 4) {
-      if (xp < 2) fpart[xp][fi] += fp;             // distinct (xp, fi) per thread
-      __syncthreads();
-    }
-    if (tid < DF) {
-      f = fpart[0][tid] + fpart[1][tid];
-      if (a.bq != nullptr) f += to_f32(static_cast<const T*>(a.bq)[(int64_t)hq * DF + tid]);
-    }
-  }
-  float nx2 = tid < D ? qs[tid] * qs[tid] : 0.f;
-  float nf2 = tid < DF ? f * f : 0.f;
-  float fmx = tid < DF ? f : -INFINITY, fmn = tid < DF ? f : INFINITY;
-  block_reduce4(nx2, nf2, fmx, fmn, sh, 4);
-  const float ratio = nf2 > 0.f ? sqrtf(nx2 / nf2) : 0.f;
-  const float a1 = ratio * kLog2e;
-  float ep = tid < DF ? fast_exp2(fmaf(f, a1, -fmx * a1)) : 0.f;
-  float en = tid < DF ? fast_exp2(fmaf(f, -a1, fmn * a1)) : 0.f;
-  float sp = ep, sn = en, u0 = 0.f, u1 = 0.f;
-  block_reduce4(sp, sn, u0, u1, sh, 4);
-  if (tid < DF) {
-    phi[tid] = round_to<T>(ep / sp);
-    phi[DF + tid] = round_to<T>(en / sn);
-  }
-  __syncthreads();
-  // N_LA[x] = sum_f phi[f] S[f][x]: thread (rp, cg) sums rows rp, rp + RP, ... of four columns with 16-byte
-  // loads (the state is the bulk of this kernel's traffic), the row parts are added through LDS
-  const float* Sg = a.S + unit * (int64_t)(DP * (D + 1));
-  {
-    const int cg = tid % CG, rp = tid / CG;
-    floatx4 n4 = {0.f, 0.f, 0.f, 0.f};
-#pragma unroll 8
-    for (int ff = rp; ff < DP; ff += RP) {
-      const floatx4 sv = *reinterpret_cast<const floatx4*>(Sg + (int64_t)ff * D + 4 * cg);
-      const float pw = phi[ff];
-#pragma unroll
-      for (int e = 0; e < 4; ++e) n4[e] = fmaf(pw, sv[e], n4[e]);
-    }
-    *reinterpret_cast<floatx4*>(&red[rp][4 * cg]) = n4;
-    __syncthreads();
-  }
-  float dl = tid < DP ? phi[tid] * Sg[DP * D + tid] : 0.f;
-  float d1 = 0.f, d2 = 0.f, d3 = 0.f;
-  block_reduce4(dl, d1, d2, d3, sh, 4);
-  // merge the split partials
   const float* part = a.part + unit * 32 * (int64_t)(D + 2);
-  float M = -INFINITY;
-  for (int s = 0; s < a.nsplit; ++s) M = fmaxf(M, part[(int64_t)s * (D + 2)]);
-  if (tid < D) {
-    float L = 0.f, acc = 0.f;
-    for (int s = 0; s < a.nsplit; ++s) {
-      const float ms = part[(int64_t)s * (D + 2)];
-      const float w = ms == -INFINITY ? 0.f : fast_exp2(ms - M);
-      L = fmaf(w, part[(int64_t)s * (D + 2) + 1], L);
-      acc = fmaf(w, part[(int64_t)s * (D + 2) + 2 + tid], acc);
-    }
-    float fs, fl;
-    if (M >= 0.f) {
-      fs = 1.f;
-      fl = fast_exp2(-M);
-    } else {
-      fs = fast_exp2(M);
-      fl = 1.f;
-    }
-    float nla = 0.f;
-#pragma unroll
-    for (int rp = 0; rp < RP; ++rp) nla += red[rp][tid];
-    if (a.g != nullptr) {
-      const float gx = to_f32(static_cast<const T*>(a.g)[unit * D + tid]);
-      nla *= a.gate_act ? fast_sigmoid(gx) : gx;
-    }
-    const float y = (fs * acc + fl * nla) / (fs * L + fl * dl);
-    static_cast<T*>(a.out)[unit * D + tid] = from_f32<T>(y);
+  const float* lin = part + kMaxSplits * (D + 2);
+  float nla = lin[2 + tid];
+  const float dl = lin[1];
+  if (a.g != nullptr) {
+    const float gx = to_f32(static_cast<const T*>(a.g)[unit * D + tid]);
+    nla *= a.gate_act ? fast_sigmoid(gx) : gx;
   }
+  float M = -INFINITY;
+#pragma unroll 4
+  for (int s = 0; s < a.nsplit; ++s) M = fmaxf(M, part[s * (D + 2)]);
+  float L = 0.f, acc = 0.f;
+#pragma unroll 4
+  for (int s = 0; s < a.nsplit; ++s) {
+    const float ms = part[s * (D + 2)];
+    const float w = ms == -INFINITY ? 0.f : fast_exp2(ms - M);
+    L = fmaf(w, part[s * (D + 2) + 1], L);
+    acc = fmaf(w, part[s * (D + 2) + 2 + tid], acc);
+  }
+  float fs, fl;
+  if (M >= 0.f) {
+    fs = 1.f;
+    fl = fast_exp2(-M);
+  } else {
+    fs = fast_exp2(M);
+    fl = 1.f;
+  }
+  const float y = (fs * acc + fl * nla) / (fs * L + fl * dl);
+  static_cast<T*>(a.out)[unit * D + tid] = from_f32<T>(y);
 }
 
 // ---------------------------------------------------------------- state export from the prefill
@@ -886,8 +990,6 @@ __global__ void state_fill_retained_kernel(StateFillArgs a) {
   }
 
 hipError_t launch_decode_step(const DecArgs& a, int dtype, int d, bool route, hipStream_t stream) {
-#define CALL_SCORE(TT, DD) hipLaunchKernelGGL((decode_score_kernel<TT, DD>), dim3(a.Hq + a.Hkv, a.B), dim3(a.W > 128 ? 256 : 128), 0, stream, a);
-  STILL_DISPATCH(dtype, d, CALL_SCORE)
   if (route) {
     const int cr = a.t / a.C - 2;
 #define CALL_ROUTE(TT, DD)                                                                              \
@@ -901,15 +1003,16 @@ hipError_t launch_decode_step(const DecArgs& a, int dtype, int d, bool route, hi
   }
     STILL_DISPATCH(dtype, d, CALL_ROUTE)
   }
-#define CALL_ATT(TT, DD) hipLaunchKernelGGL((decode_attend_kernel<TT, DD>), dim3(a.nsplit, a.Hq, a.B), dim3(256), 0, stream, a);
-#define CALL_ATT_SHARED(TT, DD) hipLaunchKernelGGL((decode_attend_shared_kernel<TT, DD>), dim3(a.nsplit, a.Hkv, a.B), dim3(256), 0, stream, a);
+  const dim3 grid((unsigned)((a.nsplit * (a.shared ? a.Hkv : a.Hq) + 2 * a.Hq + a.Hkv) * a.B));
+#define CALL_STEP(TT, DD) hipLaunchKernelGGL((decode_step_kernel<TT, DD>), grid, dim3(256), 0, stream, a);
+#define CALL_STEP_SHARED(TT, DD) hipLaunchKernelGGL((decode_step_shared_kernel<TT, DD>), grid, dim3(256), 0, stream, a);
   if (a.shared) {
-    STILL_DISPATCH(dtype, d, CALL_ATT_SHARED)
+    STILL_DISPATCH(dtype, d, CALL_STEP_SHARED)
   } else {
-    STILL_DISPATCH(dtype, d, CALL_ATT)
+    STILL_DISPATCH(dtype, d, CALL_STEP)
   }
-#define CALL_FIN(TT, DD) hipLaunchKernelGGL((decode_finish_kernel<TT, DD>), dim3(a.Hq, a.B), dim3(256), 0, stream, a);
-  STILL_DISPATCH(dtype, d, CALL_FIN)
+#define CALL_MERGE(TT, DD) hipLaunchKernelGGL((decode_merge_kernel<TT, DD>), dim3(a.Hq, a.B), dim3(DD), 0, stream, a);
+  STILL_DISPATCH(dtype, d, CALL_MERGE)
   return hipGetLastError();
 }
 

@@ -202,6 +202,7 @@ struct SaArgs {
   int AW;              //   all offers, each under its chunk's mask; AW = words per row = cap / 64)
 };
 
+constexpr int kMaxSplits = 31;   // of the salient cache in a decode step
 struct DecArgs {
   float* S;            // [B, Hq, DP*(D+1)]
   void* kret;          // [B, Hq, cap, d]
@@ -210,7 +211,7 @@ struct DecArgs {
   void* kring;         // [B, Hkv, R, d]
   void* vring;
   float* score;        // [B, Hq, R]
-  float* part;         // [B, Hq, 32, d+2]
+  float* part;         // [B, Hq, 32, d+2]: (m, l, acc) of every split, in the last slot (-, D_LA, N_LA)
   const void* q;       // [B, Hq, d]
   const void* k;       // [B, Hkv, d]
   const void* v;

@@ -544,3 +544,41 @@ def test_decode_in_the_benchmark_launch_configuration():
     y = ref["out"][n_prefill:n_total]
     assert np.all(np.isfinite(x))
     U.assert_bf16_bar(x, y, "decode B=64")
+
+
+# ------------------------------------------------------------------ the splits of one step
+@pytest.mark.parametrize("d,dtype,shared,N", [
+    (64, "f32", 0, 64 * 70 + 5),       # the largest number of splits, one head
+    (128, "f32", 0, 64 * 70),          # the same; the step also routes a chunk
+    (64, "bf16", 1, 64 * 70 + 63),
+    (128, "bf16", 0, 64 * 3 + 1),      # few rows
+    (64, "f32", 0, 1),                 # no state, two rows
+], ids=str)
+def test_a_step_equals_the_last_row_of_a_longer_prefill(d, dtype, shared, N):
+    """Prefill N tokens, decode token N: the row a prefill of N + 1 tokens gives (fp32: sums in another order over a few
+    thousand terms, 2e-5; bf16: operands of either side are rounded to 8 bits, 3e-2 of the largest)."""
+    import torch
+    dev, T = "cuda", {"f32": torch.float32, "bf16": torch.bfloat16}[dtype]
+    g = torch.Generator(device=dev).manual_seed(7)
+    Hq = 2 if shared else 1
+    q, k, v = (torch.randn(1, N + 1, h, d, generator=g, device=dev).to(T) for h in (Hq, 1, 1))
+    Wq, Wk = ((torch.randn(Hq, d, d, generator=g, device=dev) / d ** 0.5).to(T) for _ in range(2))
+    base = dict(B=1, Hq=Hq, Hkv=1, d=d, C=64, W=64, lam=32, scale=d ** -0.5, eps=1e-6, dtype=dtype, shared_selection=shared)
+
+    def prefill(n):
+        x = [t[:, :n].contiguous() for t in (q, k, v)]
+        out = torch.zeros_like(x[0])
+        p = S.make_params(N=n, max_tokens=N + 64, q=x[0], k=x[1], v=x[2], out=out, **base)
+        state = torch.full((S.still_state_bytes(p),), 0x7f, dtype=torch.uint8, device=dev)
+        ws = torch.full((S.still_fwd_workspace_bytes(p),), 0x7f, dtype=torch.uint8, device=dev)
+        S.still_hybrid_attn_fwd(p, *x, None, Wq, None, Wk, None, out, state_out=state, workspace=ws)
+        return out, state
+
+    want = prefill(N + 1)[0][:, N].float()
+    _, state = prefill(N)
+    y = torch.zeros(1, Hq, d, dtype=T, device=dev)
+    p = S.make_params(N=1, max_tokens=N + 64, **base)
+    S.still_hybrid_attn_decode_step(p, state, N, q[:, N].contiguous(), k[:, N].contiguous(), v[:, N].contiguous(), None,
+                                    Wq, None, Wk, None, y)
+    tol = 2e-5 if dtype == "f32" else 3e-2
+    assert (y.float() - want).abs().max() <= tol * max(1.0, float(want.abs().max()))
