@@ -364,17 +364,17 @@ typedef struct still_bwd_ws_layout {
   size_t a;        /* dtype [B, Hq, N, d]     E_t (gate_t * dout_t)                                           */
   size_t phi_q;    /* dtype [B, Hq, N, 2*d_f] feature map of the queries                                      */
   size_t phi_k;    /* dtype [B, Hq, N, 2*d_f] feature map of the keys, zero for the selected tokens (maps)    */
-  size_t uq, uk;   /* float [B, Hq, N, d_f]   rescaled pre-activations u of Sec. 3.2 (maps)                   */
-  size_t stq, stk; /* float [B, Hq, N, 2]     |x|, |f(x)| (maps)                                              */
+  size_t uq, uk;   /* float [B, Hq, N, d_f]   the weights in operand order (backward pass)                        */
+  size_t stq, stk; /* float [B, Hq, N, 2]     not used                                                        */
   size_t nraw;     /* float [B, Hq, N, d]     not used                                                        */
-  size_t gq;       /* float [B, Hq, N, 2*d_f] gradient of phi_q (maps)                                        */
-  size_t dphi_k;   /* float [B, Hq, N, 2*d_f] gradient of phi_k (maps)                                        */
+  size_t gq;       /* float [B, Hq, N, 2*d_f] not used                                                        */
+  size_t dphi_k;   /* float [B, Hq, N, 2*d_f] not used                                                        */
   size_t ds;       /* dtype [B, Hq, ceil(N/C), d, 2*d_f]  gradient of the state the rows of chunk c+2 and later read */
   size_t dz;       /* float [B, Hq, ceil(N/C), 2*d_f]     likewise for z                                       */
   size_t dfq, dfk; /* dtype [B, Hq, N, d_f]   gradient of f(x)                                                */
   size_t dq32;     /* float [B, Hq, N, d]                                                                     */
   size_t dk32, dv32; /* float [B, Hkv, N, d]                                                                  */
-  size_t cxq, cxk; /* float [B, Hq, N]        coefficient of x in its own gradient (maps)                       */
+  size_t cxq, cxk; /* float [B, Hq, N]        not used                                                          */
   size_t qt, dot;  /* float [B, Hq, cap, d]   gradients of the retained keys and values, in routing order     */
   size_t kt;       /* uint64 [B, Hq, cap/64]  bit = the retained entry is a token                             */
   size_t kret;     /* dtype [B, Hq, cap, d]   retained keys in routing order                                  */
@@ -415,8 +415,8 @@ STILL_API still_status_t still_attention_map(const still_params_t* p, const void
  * bq, bk are), with q, k and the routing held fixed: what the first training stage of Sec. 4.1 updates (q and k come
  * from the frozen teacher there).  map_tj = a_tj / s_t with s_t the row's sum, so da_tj = (dmap_tj - <dmap_t, map_t>)
  * / s_t, and only the pairs owned by the linear branch depend on the parameters, through phi_q(q_t) . phi_k(k_j).
- * workspace: at least still_attention_map_bwd_workspace_bytes(p) bytes (a backward workspace plus one [B, Hq, N, N]
- * matrix in the storage type).  Same coverage and validation as the backward pass; sums with atomic adds.
+ * workspace: at least still_attention_map_bwd_workspace_bytes(p) bytes (a backward workspace plus one float per row).
+ * Same coverage and validation as the backward pass; sums with atomic adds.
  */
 STILL_API size_t still_attention_map_bwd_workspace_bytes(const still_params_t* p);
 STILL_API still_status_t still_attention_map_bwd(const still_params_t* p, const void* q, const void* k,

@@ -56,8 +56,10 @@ __global__ __launch_bounds__(256) void bwd_weights_kernel(BwdWeightsArgs a) {
   if ((which & 1) == 0) {
     static_cast<T*>(which == 0 ? a.wqf : a.wkf)[ho + idx] = w[(int64_t)k * d + 32 * tile + M::kappa(lane & 31)];
   } else {
-    static_cast<T*>(which == 1 ? a.wqr : a.wkr)[ho + idx] = w[(int64_t)(32 * tile + (lane & 31)) * d + k];
-    (which == 1 ? a.dwq : a.dwk)[ho + idx] = 0.f;
+    T* wr = static_cast<T*>(which == 1 ? a.wqr : a.wkr);
+    float* dw = which == 1 ? a.dwq : a.dwk;
+    if (wr != nullptr) wr[ho + idx] = w[(int64_t)(32 * tile + (lane & 31)) * d + k];
+    if (dw != nullptr) dw[ho + idx] = 0.f;
     float* db = which == 1 ? a.dbq : a.dbk;
     if (db != nullptr && idx < d) db[(int64_t)h * d + idx] = 0.f;
   }
@@ -88,25 +90,6 @@ __device__ __forceinline__ void store_elems(T* p, const float (&x)[8]) {
     for (int e = 0; e < 4; ++e) u[e] = x[e], v[e] = x[4 + e];
     *reinterpret_cast<floatx4*>(p) = u;
     *reinterpret_cast<floatx4*>(p + 4) = v;
-  }
-}
-
-// one lane's 16 accumulator entries of a (feature x token) product -> its token's row of an LDS row tile, columns c0 ..
-template <typename T, int W>
-__device__ __forceinline__ void put_row(T* tile, int row, int c0, const float (&x)[16], int g) {
-  typedef Mma<T> M;
-  typedef RowTile<T, W> RT;
-  if constexpr (sizeof(T) == 2) {
-#pragma unroll
-    for (int s = 0; s < 2; ++s) {
-      bf16x8 v;
-#pragma unroll
-      for (int e = 0; e < 8; ++e) v[e] = static_cast<bf16>(x[8 * s + e]);
-      *reinterpret_cast<bf16x8*>(tile + RT::off(row, c0 + M::pos_of_reg(8 * s, g))) = v;
-    }
-  } else {
-#pragma unroll
-    for (int i = 0; i < 16; ++i) tile[RT::off(row, c0 + M::pos_of_reg(i, g))] = x[i];
   }
 }
 

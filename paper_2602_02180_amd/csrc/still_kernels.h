@@ -292,25 +292,6 @@ hipError_t launch_state_fill_evict(const StateFillEvictArgs& a, int dtype, int B
 size_t evict_plan_smem(int M, int lam, int AW);
 
 // ---- backward pass (still_bwd.hip) ----
-// One operand of the generic batched product: element (row, k) of batch item (b, head, c) sits at
-// base[b*s_b + head*s_h + (c / c_div)*s_c + row*s_r + k*s_k]; head is the query head or, with kv = 1, its kv head.
-struct GemmOperand {
-  const void* base;
-  int64_t s_b, s_h, s_c, s_r, s_k;
-  int kv, c_div, f32;      // f32 = 1: the elements are float whatever the storage type
-};
-struct GemmArgs {
-  GemmOperand A, B;        // C[m][n] = sum_k A(m, k) B(n, k)
-  GemmOperand B2;          // base != nullptr: ... + sum_k A(m, k) B2(n, k), the same A against a second operand
-  float* C;                // element (m, n) of item (b, head, c) at C[b*c_b + head*c_h + c*c_c + m*c_r + n]
-  int64_t c_b, c_h, c_c, c_r;
-  int c_kv;
-  int M, Nn, K;            // per item; Nn and K multiples of 64 (a K cut short by k_total reads as zeros)
-  int m_total, k_total;    // > 0: item c holds only min(M, m_total - c*M) rows / min(K, k_total - c*K) contraction entries
-  int Hq;
-  HeadMap map;
-  int mode;                // 0: store, 1: add, 2: atomic add
-};
 struct BwdRowArgs {
   const void* out;         // y of the forward pass, strided like dout
   const void* dout;
@@ -321,15 +302,16 @@ struct BwdRowArgs {
   float* ed;               // [U, N]: E_t delta_t
   int U, N, Hq, d;
 };
-// both weight matrices in the two operand orders of the linear branch, and cleared parameter gradients
+// both weight matrices in the two operand orders of the linear branch, and cleared parameter gradients (each where a
+// destination is given)
 struct BwdWeightsArgs {
   const void* wq;          // [Hq, d, d]
   const void* wk;
   void* wqf;               // [Hq, d, d]: operand order of f^T = W^T x^T (wfrag_offset)
   void* wkf;
-  void* wqr;               // [Hq, d, d]: operand order of dx = df W^T
+  void* wqr;               // nullable [Hq, d, d]: operand order of dx = df W^T
   void* wkr;
-  float* dwq;
+  float* dwq;              // nullable
   float* dwk;
   float* dbq;              // nullable
   float* dbk;
@@ -399,30 +381,6 @@ hipError_t launch_bwd_weights(const BwdWeightsArgs& a, int dtype, int Hq, hipStr
 hipError_t launch_bwd_lin(const BwdLinArgs& a, int dtype, int d, bool key, hipStream_t stream);
 hipError_t launch_bwd_revscan(const BwdRevscanArgs& a, int dtype, int d, int U, hipStream_t stream);
 hipError_t launch_bwd_dw(BwdDwArgs a, int dtype, int d, hipStream_t stream);
-struct BwdNpArgs {
-  const void* x;           // q or k
-  int64_t x_sb, x_st, x_sh;
-  int x_kv;                // 1: x is read (and its gradient accumulated) at the kv head of the query head
-  const void* bias;        // nullable [Hq, F]
-  float* u;                // [U, N, F]: f = x W on entry of the forward kernel, u afterwards
-  float* st;               // [U, N, 2]: |x|, |f|
-  void* phi;               // [U, N, 2F] storage type (forward kernel)
-  const uint32_t* kmask;   // nullable [B, Hq, ncf, C/32]: tokens the softmax branch keeps have phi = 0, df = 0
-  const float* dphi;       // [U, N, 2F] (backward kernel)
-  const float* coef;       // nullable [U, N]: dphi -= coef * (z1 + z2)
-  const float* z1;         // nullable [U, nc, 2F]
-  const float* z2;         // nullable [U, nseg, 2F], indexed by chunk / seg_chunks
-  void* df;                // [U, N, F] storage type
-  float* cx;               // [U, N]: coefficient of x in dx (the |x| path), 0 for tokens without a gradient
-  HeadMap map;
-  int U, N, Hq, Hkv, d, F, C, nc, ncf, nseg, seg_chunks;
-};
-struct BwdColsumArgs {
-  const void* X;           // [U, N, L] storage type
-  const float* w;          // nullable [U, N]
-  float* out;              // [U, nc, L], or (per_head) [Hq, L] added atomically
-  int N, C, nc, L, Hq, per_head;
-};
 struct BwdSaArgs {
   const void* q;
   const void* k;
@@ -466,35 +424,32 @@ struct RopeArgs {
   int B, N, Hq, Hkv, d;
 };
 hipError_t launch_rope(const RopeArgs& a, int dtype, hipStream_t stream);
-hipError_t launch_bgemm(const GemmArgs& a, int dtype, int U, int n_c, hipStream_t stream);
-hipError_t launch_fill_f32(float* p, int64_t n, float x, hipStream_t stream);
 hipError_t launch_bwd_row_prep(const BwdRowArgs& a, int dtype, hipStream_t stream);
-hipError_t launch_bwd_np(const BwdNpArgs& a, int dtype, bool backward, hipStream_t stream);
-hipError_t launch_bwd_colsum(const BwdColsumArgs& a, int dtype, int U, hipStream_t stream);
 hipError_t launch_bwd_gather(const BwdGatherArgs& a, int dtype, int U, hipStream_t stream);
 hipError_t launch_bwd_sa(const BwdSaArgs& a, int dtype, int d, int B, hipStream_t stream);
-struct AttnMapArgs {
+// attention map and its backward pass (still_map.hip)
+struct MapArgs {
   const void* q;
   const void* k;
   int64_t q_sb, q_st, q_sh, k_sb, k_st, k_sh;
-  const void* phi_q;       // [U, N, 2d] storage type
-  const void* phi_k;       // [U, N, 2d], zero rows' worth for selected tokens
+  const void* wqf;         // [Hq, d, d]: operand order of f^T = W^T x^T (BwdWeightsArgs)
+  const void* wkf;
+  const void* bq;          // nullable [Hq, d]
+  const void* bk;
+  void* phi_q;             // [U, N, 2d] storage type
+  void* phi_k;             // [U, N, 2d], zero for selected tokens
   const uint32_t* kmask;   // [U, ncf, C/32]: bit = token selected (within its chunk's quota)
   const float* lse;        // [U, N]
-  float* map_out;          // [U, N, N]
+  float* map_out;          // forward: [U, N, N]
+  const float* map_in;     // backward: the map, its gradient (at and below the diagonal)
+  const float* dmap;
+  float* rowdot;           // backward: [U, N], rows of chunks >= 2
+  void* dfq;               // backward: [U, N, d] storage type
+  void* dfk;
   HeadMap map;
-  int N, C, Hq, ncf;
+  int U, N, C, Hq, nc, ncf;
   float scale;
 };
-struct MapDwArgs {
-  const float* dA;         // [U, N, N]
-  const float* lse;        // [U, N]
-  const uint32_t* kmask;   // [U, ncf, C/32]
-  float* rowdot;           // [U, N]
-  void* dw;                // [U, N, Np8] storage type
-  int N, Np8, C, ncf;
-};
-hipError_t launch_map_dw(const MapDwArgs& a, const float* A, int dtype, int U, hipStream_t stream);
-hipError_t launch_attn_map(const AttnMapArgs& a, int dtype, int d, int U, hipStream_t stream);
+hipError_t launch_map(const MapArgs& a, int dtype, int d, bool backward, hipStream_t stream);
 
 }  // namespace still

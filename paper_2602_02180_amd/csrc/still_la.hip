@@ -273,7 +273,6 @@ __device__ __forceinline__ void la_body(const LaArgs& a) {
   }
 
   // -------------------------------------------------------------------- consumer wave: x columns [32 wave, +32)
-  const int col = 32 * wave + r;
   floatx16 S[PT];
   float z;                                       // feature row 64 wave + lane
 #pragma unroll

@@ -53,6 +53,25 @@ struct RowTile {
   }
 };
 
+// one lane's 16 accumulator entries of a (feature x token) product -> its token's row of an LDS row tile, columns c0 ..
+template <typename T, int W>
+__device__ __forceinline__ void put_row(T* tile, int row, int c0, const float (&x)[16], int g) {
+  typedef Mma<T> M;
+  typedef RowTile<T, W> RT;
+  if constexpr (sizeof(T) == 2) {
+#pragma unroll
+    for (int s = 0; s < 2; ++s) {
+      bf16x8 v;
+#pragma unroll
+      for (int e = 0; e < 8; ++e) v[e] = static_cast<bf16>(x[8 * s + e]);
+      *reinterpret_cast<bf16x8*>(tile + RT::off(row, c0 + M::pos_of_reg(8 * s, g))) = v;
+    }
+  } else {
+#pragma unroll
+    for (int i = 0; i < 16; ++i) tile[RT::off(row, c0 + M::pos_of_reg(i, g))] = x[i];
+  }
+}
+
 // N products with the streamed operand read DEPTH products ahead of its use (the scheduling barriers pin that order:
 // left alone the compiler puts every read right before its product and waits for it).  a_at(IDX) reads operand IDX,
 // mm(IDX, operand) issues product IDX; both get the index as a compile-time constant.

@@ -310,3 +310,14 @@ def test_backward_linear_branch_tiles(kw, gate):
     """The linear branch works in tiles of 64 tokens (several kv groups and their head maps, both image sources)."""
     w = small("bwd-lin-" + "-".join(f"{k}{v}" for k, v in kw.items()), **kw)
     check_backward(w, with_bias(w, synth.make_inputs(w, seed=81, with_gate=gate), 82), 83)
+
+
+@pytest.mark.parametrize("kw", [
+    dict(dtype="f32", C=64, N=64 * 5 + 1, Hq=4, Hkv=2, lam=8),                   # rows that start on any 4-byte boundary, a tile of one row
+    dict(dtype="f32", C=128, W=128, N=128 * 4 + 62, Hq=8, Hkv=8, lam=16),        # two tiles per chunk, eight units (XCD order)
+    dict(dtype="bf16", d=128, C=64, N=64 * 3, Hq=2, Hkv=1, lam=4, B=4),          # one chunk of pairs: a single tile either side
+    dict(dtype="bf16", d=128, C=128, W=128, N=128 * 5 - 3, Hq=3, Hkv=3, lam=0),  # nothing selected, a last chunk short of three
+], ids=["f32-one-row-tail", "f32-C128", "bf16-one-tile", "bf16-none-selected"])
+def test_attention_map_tiles(kw):
+    """The map and its backward pass work in tiles of 64 rows and 64 keys."""
+    test_attention_map_against_the_oracle(kw)
