@@ -470,6 +470,9 @@ still_status_t fwd_impl(const still_params_t* p, const void* q, const void* k, c
   sa.score = score;
   const bool group_sel = p->shared_selection != 0;
   sa.sel = (have_sel && !sel_idx_is_input && !group_sel) ? sel : nullptr;
+  sa.seq_len = p->seq_len;
+  const bool mask_done = sa.sel != nullptr && !evict;
+  if (mask_done) sa.kmask = reinterpret_cast<uint32_t*>(ws + L.kmask);
   const bool need_scores = !sel_idx_is_input || score_out != nullptr;
   if (need_scores) {
     if ((e = still::launch_score(sa, p->dtype, d, B, nc, stream)) != hipSuccess)
@@ -546,7 +549,7 @@ still_status_t fwd_impl(const still_params_t* p, const void* q, const void* k, c
     if ((e = still::launch_vfr_gather(vg, p->dtype, B, stream)) != hipSuccess) return hip_fail("vfr_gather", e);
     la.src = ep.src;
     la.vfr = ws + L.ev_vfr;
-  } else {   // (also budget_policy 1 with lambda = 0 or without a full chunk: nothing is ever offered)
+  } else if (!mask_done) {   // lists that do not come from the score kernel (also budget_policy 1 without any offers)
     still::KeepMaskArgs km{sel, reinterpret_cast<uint32_t*>(ws + L.kmask), p->Hq, ncf, C, have_sel ? p->lambda : 0,
                            retained_budget(p)};
     if ((e = still::launch_keep_mask(km, B, stream)) != hipSuccess)

@@ -854,7 +854,7 @@ __device__ __forceinline__ void decode_linear(const DecArgs& a, int hq, int b, L
 // Workgroups: the splits of the salient cache (the long ones) first, then linear terms, scores, ring copies, which fill
 // what the splits leave idle.  As launches of their own (score + append, attend, linear terms and merge in the last)
 // each of them paid its own start and tail.  Before -> now: one sequence behind 4 K tokens, 32 heads, d = 128, 27 us
-// (6.0 + 6.2 + 12.7 in the kernels) -> 11.2 us; 24 sequences with 896 retained rows, d = 64, 59 us (5.7 + 32 + 10) -> 48
+// (6.0 + 6.2 + 12.7 in the kernels) -> 10.5 us; 24 sequences with 896 retained rows, d = 64, 59 us (5.7 + 32 + 10) -> 48
 // us; 64 sequences behind 32 K tokens 782 (16 + 714 + 54) -> 755 us, 4.69 GB at 6.2 TB/s.
 template <typename T, int D, bool SHARED>
 __device__ __forceinline__ void decode_step_body(const DecArgs& a) {
@@ -911,17 +911,21 @@ __global__ __launch_bounds__(D) void decode_merge_kernel(DecArgs a) {
     const float gx = to_f32(static_cast<const T*>(a.g)[unit * D + tid]);
     nla *= a.gate_act ? fast_sigmoid(gx) : gx;
   }
-  float M = -INFINITY;
-#pragma unroll 4
-  for (int s = 0; s < a.nsplit; ++s) M = fmaxf(M, part[s * (D + 2)]);
-  float L = 0.f, acc = 0.f;
-#pragma unroll 4
-  for (int s = 0; s < a.nsplit; ++s) {
-    const float ms = part[s * (D + 2)];
-    const float w = ms == -INFINITY ? 0.f : fast_exp2(ms - M);
-    L = fmaf(w, part[s * (D + 2) + 1], L);
-    acc = fmaf(w, part[s * (D + 2) + 2 + tid], acc);
-  }
+  // lane s of every wave has split s's maximum and sum; the accumulators are asked for before the weights are known
+  const int lane = tid & 63, ns = a.nsplit;
+  const float ms = lane < ns ? part[lane * (D + 2)] : -INFINITY, ls = lane < ns ? part[lane * (D + 2) + 1] : 0.f;
+  constexpr int PRE = 8;
+  float pre[PRE];
+#pragma unroll
+  for (int s = 0; s < PRE; ++s) pre[s] = s < ns ? part[s * (D + 2) + 2 + tid] : 0.f;
+  const float M = wave_max(ms);
+  const float w = ms == -INFINITY ? 0.f : fast_exp2(ms - M);
+  const float L = wave_sum(w * ls);
+  float acc = 0.f;
+#pragma unroll
+  for (int s = 0; s < PRE; ++s) acc = fmaf(__shfl(w, s, 64), pre[s], acc);
+#pragma unroll 8
+  for (int s = PRE; s < ns; ++s) acc = fmaf(__shfl(w, s, 64), part[s * (D + 2) + 2 + tid], acc);
   float fs, fl;
   if (M >= 0.f) {
     fs = 1.f;
@@ -936,49 +940,52 @@ __global__ __launch_bounds__(D) void decode_merge_kernel(DecArgs a) {
 
 // ---------------------------------------------------------------- state export from the prefill
 // ring and score ring <- the last min(N, R) tokens; retained K/V rows and sel <- chunks 0 .. n_routed-1
+// Rows move as 16-byte pieces, a row per d / EPV lanes: d/8 or d/4 lanes, 8 to 32 rows per workgroup.  (One workgroup of
+// 64 threads per row, element by element, took 35 + 29 us at 8 x 2048 tokens, 32 / 8 heads, d = 128.)
 template <typename T>
-__global__ void state_fill_ring_kernel(StateFillArgs a) {
-  const int h = blockIdx.y, b = blockIdx.z;     // grid.y = max(Hq, Hkv)
-  const int n_tok = seq_tokens(a.seq_len, b, a.N);
-  const int first = n_tok > a.R ? n_tok - a.R : 0;
-  const int tok = first + blockIdx.x;
-  if (tok >= n_tok) return;
-  const int slot = tok % a.R;
-  if (h < a.Hkv) {
-    const T* k = static_cast<const T*>(a.k) + (int64_t)b * a.k_sb + (int64_t)tok * a.k_st + (int64_t)h * a.k_sh;
-    const T* v = static_cast<const T*>(a.v) + (int64_t)b * a.v_sb + (int64_t)tok * a.v_st + (int64_t)h * a.v_sh;
-    T* kr = static_cast<T*>(a.kring) + (((int64_t)b * a.Hkv + h) * a.R + slot) * a.d;
-    T* vr = static_cast<T*>(a.vring) + (((int64_t)b * a.Hkv + h) * a.R + slot) * a.d;
-    for (int x = threadIdx.x; x < a.d; x += blockDim.x) {
-      kr[x] = k[x];
-      vr[x] = v[x];
-    }
-  }
-  if (h < a.Hq && threadIdx.x == 0)
-    a.score_ring[((int64_t)b * a.Hq + h) * a.R + slot] = a.score[((int64_t)b * a.Hq + h) * a.N + tok];
+__device__ __forceinline__ void copy_row(T* dst, const T* src, int piece) {
+  reinterpret_cast<Vec16*>(dst)[piece] = reinterpret_cast<const Vec16*>(src)[piece];
 }
 
 template <typename T>
-__global__ void state_fill_retained_kernel(StateFillArgs a) {
-  const int row = blockIdx.x, hq = blockIdx.y, b = blockIdx.z;   // row < n_routed * lam
+__global__ __launch_bounds__(256) void state_fill_ring_kernel(StateFillArgs a) {
+  const int b = blockIdx.z, tid = threadIdx.x;     // grid.y = Hkv (keys and values), then Hq (scores)
+  const int n_tok = seq_tokens(a.seq_len, b, a.N);
+  const int first = n_tok > a.R ? n_tok - a.R : 0;
+  if ((int)blockIdx.y < a.Hkv) {
+    const int h = blockIdx.y, lpr = a.d / (16 / (int)sizeof(T));
+    const int tok = first + blockIdx.x * (256 / lpr) + tid / lpr;
+    if (tok >= n_tok) return;
+    const int64_t row = ((int64_t)b * a.Hkv + h) * a.R + tok % a.R;
+    copy_row(static_cast<T*>(a.kring) + row * a.d,
+             static_cast<const T*>(a.k) + (int64_t)b * a.k_sb + (int64_t)tok * a.k_st + (int64_t)h * a.k_sh, tid % lpr);
+    copy_row(static_cast<T*>(a.vring) + row * a.d,
+             static_cast<const T*>(a.v) + (int64_t)b * a.v_sb + (int64_t)tok * a.v_st + (int64_t)h * a.v_sh, tid % lpr);
+  } else {
+    const int h = blockIdx.y - a.Hkv, tok = first + blockIdx.x * 256 + tid;
+    if (tok >= n_tok) return;
+    a.score_ring[((int64_t)b * a.Hq + h) * a.R + tok % a.R] = a.score[((int64_t)b * a.Hq + h) * a.N + tok];
+  }
+}
+
+template <typename T>
+__global__ __launch_bounds__(256) void state_fill_retained_kernel(StateFillArgs a) {
+  const int lpr = a.d / (16 / (int)sizeof(T)), piece = threadIdx.x % lpr;
+  const int row = blockIdx.x * (256 / lpr) + threadIdx.x / lpr, hq = blockIdx.y, b = blockIdx.z;
   const int64_t unit = (int64_t)b * a.Hq + hq;
   const int kvh = a.map.kv[hq];
   const int cr = row / a.lam, pos = row % a.lam;
   if (cr >= (seq_tokens(a.seq_len, b, a.N) + a.C - 1) / a.C - 2) return;   // not yet routed in this sequence
   int tok = a.sel[(unit * a.ncf + cr) * a.lam + pos];
   const bool used = pos < chunk_quota(cr, a.lam, a.rcap);   // the budget on retained tokens leaves later slots empty
-  if (threadIdx.x == 0) a.sel_state[(unit * a.nchunks + cr) * a.lam + pos] = used ? tok : -1;
+  if (piece == 0) a.sel_state[(unit * a.nchunks + cr) * a.lam + pos] = used ? tok : -1;
   if (!used || a.lists_only || !writes_retained(a.shared != 0, a.map, hq)) return;
   if (tok < 0 || tok >= a.N) tok = 0;
-  const T* k = static_cast<const T*>(a.k) + (int64_t)b * a.k_sb + (int64_t)tok * a.k_st + (int64_t)kvh * a.k_sh;
-  const T* v = static_cast<const T*>(a.v) + (int64_t)b * a.v_sb + (int64_t)tok * a.v_st + (int64_t)kvh * a.v_sh;
   const int64_t slice = retained_slice(a.shared != 0, b, hq, kvh, a.Hq, a.Hkv);
-  T* kr = static_cast<T*>(a.kret) + (slice * a.cap + row) * a.d;
-  T* vr = static_cast<T*>(a.vret) + (slice * a.cap + row) * a.d;
-  for (int x = threadIdx.x; x < a.d; x += blockDim.x) {
-    kr[x] = k[x];
-    vr[x] = v[x];
-  }
+  copy_row(static_cast<T*>(a.kret) + (slice * a.cap + row) * a.d,
+           static_cast<const T*>(a.k) + (int64_t)b * a.k_sb + (int64_t)tok * a.k_st + (int64_t)kvh * a.k_sh, piece);
+  copy_row(static_cast<T*>(a.vret) + (slice * a.cap + row) * a.d,
+           static_cast<const T*>(a.v) + (int64_t)b * a.v_sb + (int64_t)tok * a.v_st + (int64_t)kvh * a.v_sh, piece);
 }
 
 // ---------------------------------------------------------------- launchers
@@ -1018,16 +1025,13 @@ hipError_t launch_decode_step(const DecArgs& a, int dtype, int d, bool route, hi
 
 hipError_t launch_state_fill(const StateFillArgs& a, int dtype, int B, int n_routed, hipStream_t stream) {
   const int ntok = a.N < a.R ? a.N : a.R;
-  const int hy = a.Hq > a.Hkv ? a.Hq : a.Hkv;
-  if (dtype == 1)
-    hipLaunchKernelGGL(state_fill_ring_kernel<bf16>, dim3(ntok, hy, B), dim3(64), 0, stream, a);
-  else
-    hipLaunchKernelGGL(state_fill_ring_kernel<float>, dim3(ntok, hy, B), dim3(64), 0, stream, a);
+  const int rpb = 256 / (a.d * (dtype == 1 ? 2 : 4) / 16);   // rows per workgroup
+  const dim3 ring((ntok + rpb - 1) / rpb, a.Hkv + a.Hq, B), ret((n_routed * a.lam + rpb - 1) / rpb, a.Hq, B);
+  if (dtype == 1) hipLaunchKernelGGL(state_fill_ring_kernel<bf16>, ring, dim3(256), 0, stream, a);
+  else hipLaunchKernelGGL(state_fill_ring_kernel<float>, ring, dim3(256), 0, stream, a);
   if (n_routed > 0 && a.lam > 0) {
-    if (dtype == 1)
-      hipLaunchKernelGGL(state_fill_retained_kernel<bf16>, dim3(n_routed * a.lam, a.Hq, B), dim3(64), 0, stream, a);
-    else
-      hipLaunchKernelGGL(state_fill_retained_kernel<float>, dim3(n_routed * a.lam, a.Hq, B), dim3(64), 0, stream, a);
+    if (dtype == 1) hipLaunchKernelGGL(state_fill_retained_kernel<bf16>, ret, dim3(256), 0, stream, a);
+    else hipLaunchKernelGGL(state_fill_retained_kernel<float>, ret, dim3(256), 0, stream, a);
   }
   return hipGetLastError();
 }

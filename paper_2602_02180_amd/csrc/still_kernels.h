@@ -15,6 +15,8 @@ struct ScoreArgs {
   float scale, eps;
   float* score;   // [B, Hq, N]
   int32_t* sel;   // [B, Hq, ncf, lam] or nullptr (no selection)
+  uint32_t* kmask;          // nullable, with sel: [B, Hq, ncf, C/32], bit = token selected
+  const int32_t* seq_len;   // nullable, device [B]: chunks that are all padding are left empty
 };
 
 // Tokens that chunk c keeps when at most rcap tokens may be retained in total and chunks are served in order:

@@ -312,29 +312,36 @@ __global__ __launch_bounds__(256, 2) void map_bwd_kernel(MapArgs a) {
   request_rows<T, 2 * D>(po, 2 * D, 64 * o_beg, N, phi, wave);
 
   float rho = 0.f, E = 0.f;              // query side: of this lane's row
-  if constexpr (!KEY) {                  // rho_t over the keys up to t, one wave per row, two rows at a time
+  if constexpr (!KEY) {                  // rho_t over the keys up to t: four rows of a wave at a time, all their loads in flight
     const float* A = a.map_in + unit * N * (int64_t)N;
 #pragma unroll 1
-    for (int i2 = 0; i2 < 8; ++i2) {
-      const int r0 = 16 * wave + 2 * i2;
-      float acc[2] = {0.f, 0.f};
-      const int tl[2] = {min(t0 + r0, N - 1), min(t0 + r0 + 1, N - 1)};
+    for (int r0 = 16 * wave; r0 < 16 * wave + 16; r0 += 4) {
+      const int t_lo = min(t0 + r0, N - 1), full = (t_lo + 1) & ~255;   // columns all four rows have, in pieces of 256
+      float acc[4] = {0.f, 0.f, 0.f, 0.f};
+      const float *pa[4], *pd[4];
+#pragma unroll
+      for (int h = 0; h < 4; ++h) {
+        const int64_t o = (int64_t)min(t_lo + h, N - 1) * N;
+        pa[h] = A + o;
+        pd[h] = dA + o;
+      }
 #pragma unroll 2
-      for (int j = 4 * lane; j <= tl[1]; j += 256)
+      for (int j = 4 * lane; j < full; j += 256)
 #pragma unroll
-        for (int h = 0; h < 2; ++h) {
-          const float *pa = A + (int64_t)tl[h] * N + j, *pd = dA + (int64_t)tl[h] * N + j;
-          if (j + 3 <= tl[h]) {
-            const floatx4u xa = *reinterpret_cast<const floatx4u*>(pa), xd = *reinterpret_cast<const floatx4u*>(pd);
+        for (int h = 0; h < 4; ++h) {
+          const floatx4u xa = *reinterpret_cast<const floatx4u*>(pa[h] + j), xd = *reinterpret_cast<const floatx4u*>(pd[h] + j);
 #pragma unroll
-            for (int e = 0; e < 4; ++e) acc[h] = fmaf(xa[e], xd[e], acc[h]);
-          } else {
-            for (int e = 0; e < 4; ++e)
-              if (j + e <= tl[h]) acc[h] = fmaf(pa[e], pd[e], acc[h]);
-          }
+          for (int e = 0; e < 4; ++e) acc[h] = fmaf(xa[e], xd[e], acc[h]);
         }
 #pragma unroll
-      for (int h = 0; h < 2; ++h) {
+      for (int e = 0; e < 5; ++e) {      // (at most 255 + 4 columns are left)
+        const int j = full + 64 * e + lane;
+#pragma unroll
+        for (int h = 0; h < 4; ++h)
+          if (j <= min(t_lo + h, N - 1)) acc[h] = fmaf(pa[h][j], pd[h][j], acc[h]);
+      }
+#pragma unroll
+      for (int h = 0; h < 4; ++h) {
 #pragma unroll
         for (int o = 32; o >= 1; o >>= 1) acc[h] += __shfl_xor(acc[h], o, 64);
         if (lane == 0) {

@@ -10,7 +10,8 @@
 // the B operand, from registers).  In C layout every lane then holds the logits of ONE query, so
 // the two softmaxes and the score reduce inside a lane plus one exchange with the other lane group.
 // Scores go to an LDS array; each thread ranks one token by counting (score higher, or equal with a
-// lower index) and the selected tokens are written in ascending order.
+// lower index) and the selected tokens are written in ascending order, and once more as a bit per token for the state
+// scan (a launch of its own over the lists took 5-6 us of every prefill).
 #include "still_kernels.h"
 
 namespace still {
@@ -30,6 +31,16 @@ __global__ __launch_bounds__(256, NT > 5 ? 2 : 3) void score_select_kernel(Score
   const int kvh = a.map.kv[hq];
   const int t0 = c * C + 32 * wave;
   const int t = t0 + r;
+
+  if (c * C >= seq_tokens(a.seq_len, b, N)) {     // all padding (uniform over the workgroup): scores of zero, nothing kept
+    if (g == 0 && t < N) a.score[((int64_t)b * a.Hq + hq) * N + t] = 0.f;
+    if (a.sel != nullptr && c < a.ncf) {
+      const int64_t chunk = ((int64_t)b * a.Hq + hq) * a.ncf + c;
+      for (int i = threadIdx.x; i < a.lam; i += 2 * C) a.sel[chunk * a.lam + i] = -1;
+      if (a.kmask != nullptr && (int)threadIdx.x < C / 32) a.kmask[chunk * (C / 32) + threadIdx.x] = 0u;
+    }
+    return;
+  }
 
   __shared__ __attribute__((aligned(16))) float s_score[128];
   __shared__ int s_rank[256];
@@ -205,11 +216,14 @@ __global__ __launch_bounds__(256, NT > 5 ? 2 : 3) void score_select_kernel(Score
     const unsigned long long bal = __ballot(chosen);
     if (lane == 0) s_ball[wave] = bal;
     __syncthreads();
-    if (chosen) {
-      int pos = __popcll(bal & ((1ull << lane) - 1ull));
-      for (int w = 0; w < wave; ++w) pos += __popcll(s_ball[w]);
-      if (pos < quota)  // NaN scores can flag more tokens than the quota; never write past the chunk's slots
-        selc[pos] = c * C + threadIdx.x;
+    int pos = __popcll(bal & ((1ull << lane) - 1ull));
+    for (int w = 0; w < wave; ++w) pos += __popcll(s_ball[w]);
+    const bool kept = chosen && pos < quota;   // NaN scores can flag more tokens than the quota; never write past the slots
+    if (kept) selc[pos] = c * C + threadIdx.x;
+    if (a.kmask != nullptr) {
+      const unsigned long long m = __ballot(kept);
+      if (lane < 2 && (int)threadIdx.x < C)    // a wave below C holds 64 of the chunk's tokens
+        a.kmask[(((int64_t)b * a.Hq + hq) * a.ncf + c) * (C / 32) + 2 * wave + lane] = (uint32_t)(m >> (32 * lane));
     }
   }
 }

@@ -699,3 +699,38 @@ def test_segments_of_the_scan_give_the_same_rows_and_state(kw, N, lens):
         for got, want in ((out[b, :n], one[0]), (S_all[b], S_one[0])):
             assert (got - want).abs().max() <= 3e-5 * max(1.0, float(want.abs().max())), (b, n, nseg, ns)
     assert len(cuts) > 1
+
+
+@pytest.mark.parametrize("C,lam,budget,lens", [
+    (64, 16, 0, None), (128, 128, 0, None), (128, 7, 40, None), (64, 1, 0, [64 * 9 + 3, 64 * 4, 63, 1, 64 * 5 + 1])], ids=str)
+def test_the_keep_mask_is_the_index_lists_as_bits(C, lam, budget, lens):
+    """Bit for bit, on every full chunk of a sequence's own length; padding leaves lists and masks empty."""
+    import torch
+    dev, d, Hq, N = "cuda", 64, 3, C * 9 + 3
+    B = len(lens) if lens else 2
+    g = torch.Generator(device=dev).manual_seed(9)
+    q, k, v = (torch.randn(B, N, h, d, generator=g, device=dev).bfloat16() for h in (Hq, 1, 1))
+    W = (torch.randn(Hq, d, d, generator=g, device=dev) / 8).bfloat16()
+    seq = torch.tensor(lens, dtype=torch.int32, device=dev) if lens else None
+    out = torch.zeros_like(q)
+    p = S.make_params(B=B, N=N, Hq=Hq, Hkv=1, d=d, C=C, W=64, lam=lam, scale=0.125, eps=1e-6, dtype="bf16", q=q, k=k, v=v,
+                      out=out, max_retained=budget, seq_len=seq)
+    sel = torch.full((B, Hq, N // C, lam), -7, dtype=torch.int32, device=dev)
+    ws = torch.full((S.still_fwd_workspace_bytes(p),), 0x7f, dtype=torch.uint8, device=dev)
+    S.still_hybrid_attn_fwd(p, q, k, v, None, W, None, W, None, out, sel_idx=sel, workspace=ws)
+    off, n = S.still_fwd_workspace_layout(p).kmask, B * Hq * (N // C) * (C // 32)
+    words = ws[off:off + 4 * n].view(torch.int32).cpu().numpy().view(np.uint32).reshape(B, Hq, N // C, C // 32)
+    bits = np.unpackbits(words.view(np.uint8), axis=-1, bitorder="little").reshape(B, Hq, N // C, C)
+    lists = sel.cpu().numpy()
+    for b in range(B):
+        n_b = lens[b] if lens else N
+        for c in range(N // C):
+            quota = lam if not budget else max(0, min(lam, budget - c * lam))
+            for h in range(Hq):
+                want = np.zeros(C, dtype=np.uint8)
+                if c * C < n_b:
+                    want[lists[b, h, c, :quota] - c * C] = 1
+                    assert want.sum() == quota and np.all(lists[b, h, c, quota:] == -1)
+                else:
+                    assert np.all(lists[b, h, c] == -1)
+                assert np.array_equal(bits[b, h, c], want), (b, h, c)
