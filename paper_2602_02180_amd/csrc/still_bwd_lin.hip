@@ -12,8 +12,8 @@
 // state image S^T [x][2 d_f] passes through LDS in slabs of 64 features, and one copy of a slab serves both products:
 // read along its rows for phi S, down its columns (transposing LDS reads) for a S^T.
 // Least traffic: the images (2 d d_f elements per chunk, four times the chunk's rows at C = 64), rows and gradients once.
-// Measured at 16 sequences of 1024 tokens, 32 / 8 heads, d = 128, C = 64, bf16: query side 0.60 ms, key side 0.66 ms, state
-// gradient 0.20 ms, parameter gradients 0.12 ms; as batched products through memory (f, u, dphi, phi S and their
+// Measured at 16 sequences of 1024 tokens, 32 / 8 heads, d = 128, C = 64, bf16: query side 0.58 ms, key side 0.63 ms, state
+// gradient 0.175 ms, parameter gradients 0.12 ms; as batched products through memory (f, u, dphi, phi S and their
 // fp32 sums each written and read) 4.2 ms.
 #include "still_kernels.h"
 #include "still_tile.h"
@@ -238,15 +238,16 @@ __global__ __launch_bounds__(256, 2) void bwd_lin_kernel(BwdLinArgs a) {
       nx2 = sum32((n4[0] + n4[1]) + (n4[2] + n4[3]));
     }
     lds_barrier();                       // every wave has its fragments: the slabs may be overwritten
+    // (piece j of a wave lies 4 RPI rows, a divisor of 32, behind piece j - 1: the lane's part of the offset and the
+    // swizzle are the same for all of them)
     auto request = [&](const T* im, int f0, T* dst) __attribute__((always_inline)) {
-      constexpr int INSTR = Cf::SE * (int)sizeof(T) / 1024 / 4;
-      const int lane_now = fresh_lane_id();
+      constexpr int INSTR = Cf::SE * (int)sizeof(T) / 1024 / 4, RPI = 64 / RS::PPR;
+      static_assert(32 % (4 * RPI) == 0, "no carry between a lane's row and its piece's");
+      const int lane_now = fresh_lane_id(), sr = RPI * wave + lane_now / RS::PPR;
+      const T* src = im + state_image_offset(0, f0, DP) + state_image_offset(sr, ((lane_now % RS::PPR) ^ RS::swz(sr)) * EPV, DP);
 #pragma unroll
-      for (int j = 0; j < INSTR; ++j) {
-        const int piece = (wave + 4 * j) * 64 + lane_now;
-        const int sr = piece / RS::PPR, col = ((piece % RS::PPR) ^ RS::swz(sr)) * EPV;
-        async_copy16(im + (int64_t)sr * DP + f0 + col, lds_address(dst + (wave + 4 * j) * 64 * EPV));
-      }
+      for (int j = 0; j < INSTR; ++j)
+        async_copy16(src + state_image_offset(4 * RPI * j, 0, DP), lds_address(dst + (wave + 4 * j) * 64 * EPV));
     };
     request(img0, 0, slab0);
 
@@ -336,9 +337,9 @@ __global__ __launch_bounds__(256, 2) void bwd_lin_kernel(BwdLinArgs a) {
         }
         const int lane_now = fresh_lane_id(), rr = lane_now & 31, gg = lane_now >> 5;
         if (need_y) {
-          typename M::frag pf[SK];
-#pragma unroll
-          for (int s = 0; s < SK; ++s) pf[s] = RP::along(phi, 32 * rg + rr, SK * j + s, gg);
+          // (phi's operands are read one step ahead: all of them at once would not fit the register file)
+          typename M::frag pf[2];
+          pf[0] = RP::along(phi, 32 * rg + rr, SK * j, gg);
           piped<typename M::frag, 2 * KS, 4>(
               [&](auto I) __attribute__((always_inline)) {
                 constexpr int i = decltype(I)::value, q = i >> 1;
@@ -348,8 +349,11 @@ __global__ __launch_bounds__(256, 2) void bwd_lin_kernel(BwdLinArgs a) {
               [&](auto I, const typename M::frag& f) __attribute__((always_inline)) {
                 constexpr int i = decltype(I)::value, q = i >> 1;
                 if constexpr ((i & 1) == 0) dp[j] = M::mma(f, af[q], dp[j]);
-                else if constexpr (KEY) ya[q % NX] = M::mma(pf[q / NX], f, ya[q % NX]);
-                else yq[q % NX] = M::mma(pf[q / NX], f, yq[q % NX]);
+                else {
+                  if constexpr (q % NX == 0 && q / NX + 1 < SK) pf[(q / NX + 1) & 1] = RP::along(phi, 32 * rg + rr, SK * j + q / NX + 1, gg);
+                  if constexpr (KEY) ya[q % NX] = M::mma(pf[(q / NX) & 1], f, ya[q % NX]);
+                  else yq[q % NX] = M::mma(pf[(q / NX) & 1], f, yq[q % NX]);
+                }
               });
         } else {
           piped<typename M::frag, KS, 6>(
@@ -591,11 +595,11 @@ __global__ __launch_bounds__(256, 2) void bwd_revscan_kernel(BwdRevscanArgs a) {
     T* cp = static_cast<T*>(a.ds) + ((int64_t)unit * a.nc + c) * (int64_t)(D * DP);
 #pragma unroll
     for (int j = 0; j < NT; ++j) {
-      T* rowp = cp + (int64_t)(64 * xt + 32 * (NT == 2 ? j : xw) + M::kappa(r)) * DP + BF * ft + 32 * fw;
+      const int x = 64 * xt + 32 * (NT == 2 ? j : xw) + M::kappa(r), f0 = BF * ft + 32 * fw;
 #pragma unroll
       for (int s = 0; s < SPT; ++s) {
-        if constexpr (M::KPL == 1) rowp[M::pos_of_reg(s, g)] = M::from_acc(acc[j], s);
-        else *reinterpret_cast<typename M::frag*>(rowp + s * M::KK + g * M::KPL) = M::from_acc(acc[j], s);
+        const int f = f0 + (M::KPL == 1 ? M::pos_of_reg(s, g) : s * M::KK + g * M::KPL);
+        *reinterpret_cast<typename M::frag*>(cp + state_image_offset(x, f, DP)) = M::from_acc(acc[j], s);
       }
     }
     if (xt == 0 && 2 * pair < BF) {

@@ -9,7 +9,7 @@
 // The scan over chunks is sequential per (batch, head); it is cut into segments of G chunks so that one long
 // sequence still fills the chip, and every segment is walked ONCE, starting from an empty state.  Segment s covers
 // chunks [s*G-1, (s+1)*G-1).  What is produced, for every (batch, head):
-//   snap [chunk c] = S^T_local as [d][2 d_f] in the storage type: the sum over the chunks s*G-1 .. c-2 of c's own
+//   snap [chunk c] = S^T_local as [d][2 d_f] in the storage type (state_image_offset): the sum over the chunks s*G-1 .. c-2 of c's own
 //                    segment s = c / G (the operand layout of the product phi_q S),
 //   zsnap[chunk c] = z_local as [2 d_f] float,
 //   seg  [s]       = the segment's total, fp32, which la_prefix turns into the exclusive prefix over segments,
@@ -301,13 +301,13 @@ __device__ __forceinline__ void la_body(const LaArgs& a) {
     const int lane_now = fresh_lane_id(), rr = lane_now & 31, gg = lane_now >> 5;
     // (nobody reads the image of a segment's first chunk, which would be empty, nor of the first two chunks)
     if (oc % G != 0 && oc >= 2) {
-      T* sp = static_cast<T*>(a.snap) + (unit * a.nc + oc) * (int64_t)(D * DP) + (int64_t)(32 * wave + rr) * DP;
+      T* sp = static_cast<T*>(a.snap) + (unit * a.nc + oc) * (int64_t)(D * DP);
 #pragma unroll
       for (int ft = 0; ft < PT; ++ft)
 #pragma unroll
         for (int s = 0; s < SPT; ++s) {
-          if constexpr (M::KPL == 1) sp[32 * ft + M::pos_of_reg(s, gg)] = M::from_acc(S[ft], s);
-          else *reinterpret_cast<typename M::frag*>(sp + 32 * ft + s * M::KK + gg * M::KPL) = M::from_acc(S[ft], s);
+          const int f = 32 * ft + (M::KPL == 1 ? M::pos_of_reg(s, gg) : s * M::KK + gg * M::KPL);
+          *reinterpret_cast<typename M::frag*>(sp + state_image_offset(32 * wave + rr, f, DP)) = M::from_acc(S[ft], s);
         }
     }
     a.zsnap[(unit * a.nc + oc) * DP + 64 * wave + lane_now] = z;
@@ -412,7 +412,7 @@ __global__ __launch_bounds__((LaCfg<T, D, C>::NCW + LaCfg<T, D, C>::NPW) * 64) v
 // segment needs no launch); the fp32 state of the decode hand-over (written by the scan as a local part, laid out
 // [feature][x]) receives the prefix of the segment of the sequence's last chunk.
 // Bound: memory (totals once, images once).  A workgroup takes 32 rows x of 64 features, so that the totals and images
-// move in pieces of 256 and 128 bytes; the hand-over's transposed sum passes through LDS and is skipped where the
+// move in pieces of 256 and 32 bytes (a wave's rows of one block are contiguous); the hand-over's transposed sum passes through LDS and is skipped where the
 // prefix is empty.  With one element per thread and the transposed sum in place (4 bytes per line, also where it added
 // zero) this took 131 us at 8 x 2048 tokens, 32 heads, d = 128 with a hand-over (one segment: now not launched), and
 // 30 us at 5 x 3001 tokens.
@@ -448,7 +448,7 @@ __global__ __launch_bounds__(256) void la_prefix_kernel(LaArgs a, int D) {
     for (int h = 0; h < 2; ++h) {
       const int64_t at = (int64_t)(x0 + xl + 16 * h) * DP + f0 + fl;
       run[h] += *reinterpret_cast<const floatx4*>(tot + (s - 1) * elems + at);
-      T* dst = static_cast<T*>(a.pimg) + (unit * a.nseg + s) * (int64_t)(D * DP) + at;
+      T* dst = static_cast<T*>(a.pimg) + (unit * a.nseg + s) * (int64_t)(D * DP) + state_image_offset(x0 + xl + 16 * h, f0 + fl, DP);
       if constexpr (sizeof(T) == 2) {
         bf16x4 v;
 #pragma unroll

@@ -355,16 +355,16 @@ __device__ __forceinline__ void sa_body(const SaArgs& a) {
         for (int j = 0; j < Cf::K_INSTR; ++j)
           async_copy16(base + k_off_ret[j], lds_address(dst + Cf::NW * j * 64 * Cf::EPV));
       };
-      // columns [64 jt, +64) of a state image [D][DP]: like a V^T tile, row stride DP
+      // columns [64 jt, +64) of a state image: like a V^T tile
       auto request_t = [&](const T* img, int jt, T* slot) {
-        const T* base = img + 64 * jt;
+        const T* base = img + state_image_offset(0, 64 * jt, DP);
         T* dst = slot + wave_s * 64 * Cf::EPV;
         const int lane_now = fresh_lane_id();
 #pragma unroll
         for (int j = 0; j < Cf::V_INSTR; ++j) {
           int lrow, col;
           v_lane(lane_now, j, lrow, col);
-          async_copy16(base + (lrow * DP + col), lds_address(dst + Cf::NW * j * 64 * Cf::EPV));
+          async_copy16(base + state_image_offset(lrow, col, DP), lds_address(dst + Cf::NW * j * 64 * Cf::EPV));
         }
       };
       // The state through chunk cc-2 is the sum of two images: the running sums of cc's own segment (operand 0;
