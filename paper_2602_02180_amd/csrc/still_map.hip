@@ -12,7 +12,7 @@
 // features of both sides, one that writes the map, one per side of the backward pass, in which w goes from dA to operand
 // registers and f, u, dphi and df stay on the chip.
 // Measured at 4 sequences of 1024 tokens, 32 / 8 heads, d = 128, C = 64, bf16 (forward call included): as batched products
-// through memory, with w as a matrix of its own and the operands fetched 32 cache lines per instruction, 2.95 ms; now 1.15
+// through memory, with w as a matrix of its own and the operands fetched 32 cache lines per instruction, 2.95 ms; now 1.12
 // ms (features 0.06 twice, map 0.21: 2.6 TB/s of stores, query side 0.34, key side 0.21, parameter gradients 0.07).
 #include "still_kernels.h"
 #include "still_tile.h"
