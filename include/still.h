@@ -351,6 +351,8 @@ STILL_API still_status_t still_selection_overlap(const still_params_t* p, const 
  *   dWq, dWk       device FLOAT [Hq, d, d_f]; dbq, dbk device FLOAT [Hq, d_f], given exactly when bq, bk are.
  *                  Parameter gradients are sums over every token of the batch and are returned in fp32
  *   workspace      device scratch of at least still_bwd_workspace_bytes(p) bytes
+ * dq, dk, dv and dg may share memory with the tensors above them in this list (dq over q, say): every input is read
+ * before it is written over, at the price of one more pass over the results.
  *
  * Covers budget_policy 0 (with or without max_retained), both selection modes, both gate modes; d = 64 or 128 in
  * bf16, d = 64 in fp32; not right-padded batches (seq_len must be NULL).  The parameter gradients are
@@ -364,7 +366,8 @@ typedef struct still_bwd_ws_layout {
   size_t ed;       /* float [B, Hq, N]        E_t * delta_t                                                   */
   size_t a;        /* dtype [B, Hq, N, d]     E_t (gate_t * dout_t)                                           */
   size_t phi_q;    /* dtype [B, Hq, N, 2*d_f] feature map of the queries                                      */
-  size_t phi_k;    /* dtype [B, Hq, N, 2*d_f] feature map of the keys, zero for the selected tokens (maps)    */
+  size_t phi_k;    /* dtype [B, Hq, N, 2*d_f] feature map of the keys, zero for the selected tokens (maps);
+                      float [B, Hq, N, d] dg of a call whose results lie over its inputs (backward pass)      */
   size_t uq, uk;   /* float [B, Hq, N, d_f]   the weights in operand order (backward pass)                        */
   size_t stq, stk; /* float [B, Hq, N, 2]     not used                                                        */
   size_t nraw;     /* float [B, Hq, N, d]     not used                                                        */

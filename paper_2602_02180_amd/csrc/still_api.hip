@@ -891,6 +891,17 @@ void compute_bwd_layout(const still_params_t* p, still_bwd_ws_layout_t* L) {
   L->total = off;
 }
 
+// The bytes from a tensor's first element to its last (strides are never negative), and whether two such ranges meet.
+struct Span {
+  uintptr_t lo, hi;
+};
+Span strided_span(const still_params_t* p, const void* x, int64_t s_b, int64_t s_t, int64_t s_h, int H) {
+  const int64_t elems = (p->B - 1) * s_b + (int64_t)(p->N - 1) * s_t + (H - 1) * s_h + p->d;
+  const uintptr_t lo = reinterpret_cast<uintptr_t>(x);
+  return {lo, x != nullptr ? lo + (uintptr_t)elems * esize(p->dtype) : lo};
+}
+bool meet(const Span& a, const Span& b) { return a.lo < b.hi && b.lo < a.hi; }
+
 still_status_t bwd_impl(const still_params_t* p, const void* q, const void* k, const void* v, const void* g,
                         const void* Wq, const void* bq, const void* Wk, const void* bk, const void* out,
                         const void* dout, const float* lse, const int32_t* sel_idx, void* dq, void* dk, void* dv,
@@ -933,6 +944,25 @@ still_status_t bwd_impl(const still_params_t* p, const void* q, const void* k, c
     return fail(STILL_ERR_HIP, "%s: %s", what, hipGetErrorString(err));
   };
   auto f32p = [&](size_t off) { return reinterpret_cast<float*>(bws + off); };
+
+  // The linear branch's kernels write results while later ones still read inputs.  A caller whose gradients lie over an
+  // input gets them in fp32 inside the workspace first and rounded into place after the last read.  (out, lse and the
+  // weights have been read by then; dg over g is written element by element by the thread that read it.)
+  const Span in_q = strided_span(p, q, p->q_sb, p->q_st, p->q_sh, Hq), in_k = strided_span(p, k, p->k_sb, p->k_st, p->k_sh, Hkv),
+             in_v = strided_span(p, v, p->v_sb, p->v_st, p->v_sh, Hkv), in_g = strided_span(p, g, p->g_sb, p->g_st, p->g_sh, Hq),
+             in_do = strided_span(p, dout, p->o_sb, p->o_st, p->o_sh, Hq);
+  auto flat = [](const void* x, size_t bytes) -> Span {
+    const uintptr_t lo = reinterpret_cast<uintptr_t>(x);
+    return {lo, x != nullptr ? lo + bytes : lo};
+  };
+  const size_t bias_bytes = (size_t)Hq * p->d_f * esize(p->dtype);
+  const Span inputs[] = {in_q, in_k, in_v, in_g, in_do, flat(bq, bias_bytes), flat(bk, bias_bytes),
+                         flat(sel_idx, (size_t)U * ncf * p->lambda * 4)};
+  const Span results[] = {strided_span(p, dq, p->q_sb, p->q_st, p->q_sh, Hq), strided_span(p, dk, p->k_sb, p->k_st, p->k_sh, Hkv),
+                          strided_span(p, dv, p->v_sb, p->v_st, p->v_sh, Hkv), strided_span(p, dg, p->g_sb, p->g_st, p->g_sh, Hq)};
+  bool over = false;
+  for (const Span& r : results)
+    for (const Span& i : inputs) over = over || (meet(r, i) && !(g != nullptr && dg == g && r.lo == in_g.lo && i.lo == in_g.lo));
 
   // ---- the weights in operand order, the parameter gradients (sums are added into them) cleared
   still::BwdWeightsArgs wa{Wq, Wk, ws + L.wqt, ws + L.wkf, bws + BL.uq, bws + BL.uk, dWq, dWk, dbq, dbk, d};
@@ -1011,6 +1041,7 @@ still_status_t bwd_impl(const still_params_t* p, const void* q, const void* k, c
   lq.e_row = ra.e_row; lq.ed = ra.ed;
   lq.a_rows = bws + BL.a; lq.phi = bws + BL.phi_q; lq.df = bws + BL.dfq;
   lq.dx32 = sa.dq32; lq.dx = dq; lq.dg = dg;
+  lq.in_fp32 = over; lq.dg32 = f32p(BL.phi_k);
   lq.map = map; lq.n_units = U;
   lq.N = N; lq.C = C; lq.Hq = Hq; lq.Hkv = Hkv; lq.nc = nc; lq.ncf = ncf; lq.nseg = L.nseg; lq.seg_chunks = L.seg_chunks;
   if ((e = still::launch_bwd_lin(lq, dt, d, false, stream)) != hipSuccess) return hip_fail("bwd_lin (queries)", e);
@@ -1023,6 +1054,7 @@ still_status_t bwd_impl(const still_params_t* p, const void* q, const void* k, c
   lk.snap = rs.ds; lk.zsnap = rs.dz; lk.kmask = la.kmask;
   lk.df = bws + BL.dfk;
   lk.dx32 = sa.dk32; lk.dv32 = sa.dv32; lk.dx = dk; lk.dv = dv;
+  lk.in_fp32 = over;
   lk.sel = sel_idx; lk.lam = sa.lam; lk.cap = BL.cap_t; lk.sel_stride = sa.sel_stride;
   lk.n_ret = still::retained_rows(nc >= 2 ? nc - 2 : 0, sa.lam, budget);
   if (lk.n_ret > 0) lk.dkret = sa.dkret, lk.dvret = sa.dvret;
@@ -1035,6 +1067,14 @@ still_status_t bwd_impl(const still_params_t* p, const void* q, const void* k, c
   dw.dfq = lq.df; dw.dfk = lk.df; dw.dwq = dWq; dw.dwk = dWk; dw.dbq = dbq; dw.dbk = dbk;
   dw.map = map; dw.B = B; dw.N = N; dw.Hq = Hq;
   if ((e = still::launch_bwd_dw(dw, dt, d, stream)) != hipSuccess) return hip_fail("bwd_dw", e);
+  if (over) {
+    const still::BwdRoundArgs ro[] = {{lq.dx32, dq, p->q_sb, p->q_st, p->q_sh, B, Hq, N, d},
+                                      {lk.dx32, dk, p->k_sb, p->k_st, p->k_sh, B, Hkv, N, d},
+                                      {lk.dv32, dv, p->v_sb, p->v_st, p->v_sh, B, Hkv, N, d},
+                                      {lq.dg32, dg, p->g_sb, p->g_st, p->g_sh, B, Hq, N, d}};
+    for (const still::BwdRoundArgs& r : ro)
+      if (r.dst != nullptr && (e = still::launch_bwd_round(r, dt, stream)) != hipSuccess) return hip_fail("bwd_round", e);
+  }
   g_err[0] = 0;
   return STILL_OK;
 }

@@ -79,7 +79,32 @@ __global__ __launch_bounds__(256) void bwd_row_prep_kernel(BwdRowArgs a) {
   }
 }
 
+// fp32 rows -> the caller's strided tensor in the storage type: the last step for results that lie over an input
+template <typename T>
+__global__ __launch_bounds__(256) void bwd_round_kernel(BwdRoundArgs a) {
+  int64_t row;
+  int e0, lpr;
+  if (!row_of_lane((int64_t)a.B * a.H * a.N, a.d, row, e0, lpr)) return;
+  const int t = (int)(row % a.N), bh = (int)(row / a.N);
+  float x[8];
+  load8_t<float>(x, a.src + row * a.d + e0);
+  T* dst = static_cast<T*>(a.dst) + bh / a.H * a.s_b + (int64_t)t * a.s_t + bh % a.H * a.s_h + e0;
+  __attribute__((aligned(16))) T y[8];
+#pragma unroll
+  for (int e = 0; e < 8; ++e) y[e] = from_f32<T>(x[e]);
+#pragma unroll
+  for (int i = 0; i < (int)sizeof(y) / 16; ++i) reinterpret_cast<Vec16*>(dst)[i] = reinterpret_cast<const Vec16*>(y)[i];
+}
+
 }  // namespace
+
+hipError_t launch_bwd_round(const BwdRoundArgs& a, int dtype, hipStream_t s) {
+  const int rpb = 256 / (a.d / 8);   // rows per workgroup
+  const unsigned blocks = (unsigned)(((int64_t)a.B * a.H * a.N + rpb - 1) / rpb);
+  if (dtype == 1) hipLaunchKernelGGL((bwd_round_kernel<bf16>), dim3(blocks), dim3(256), 0, s, a);
+  else hipLaunchKernelGGL((bwd_round_kernel<float>), dim3(blocks), dim3(256), 0, s, a);
+  return hipGetLastError();
+}
 
 hipError_t launch_bwd_row_prep(const BwdRowArgs& a, int dtype, hipStream_t s) {
   const int rpb = 256 / (a.d / 8);   // rows per workgroup

@@ -428,7 +428,8 @@ __global__ __launch_bounds__(256, 2) void bwd_lin_kernel(BwdLinArgs a) {
               dy[e] *= sg * (1.f - sg);
             }
           }
-          store_elems<T>(static_cast<T*>(a.dg) + go, dy);
+          if (a.in_fp32) store_elems<float>(a.dg32 + (unit * N + tt) * D + e0, dy);
+          else store_elems<T>(static_cast<T*>(a.dg) + go, dy);
         }
       }
     }
@@ -468,7 +469,7 @@ __global__ __launch_bounds__(256, 2) void bwd_lin_kernel(BwdLinArgs a) {
   }
 
   // ---- results: the softmax branch's part, this branch's, and (keys) the retained entries', in the storage type
-  auto emit = [&](const floatx16 (&acc)[NX], const float* src, T* dst, int64_t s_b, int64_t s_t, int64_t s_h, bool with_x,
+  auto emit = [&](const floatx16 (&acc)[NX], float* src, T* dst, int64_t s_b, int64_t s_t, int64_t s_h, bool with_x,
                   const float* dret) __attribute__((always_inline)) {
     if (linear) {
 #pragma unroll
@@ -513,13 +514,16 @@ __global__ __launch_bounds__(256, 2) void bwd_lin_kernel(BwdLinArgs a) {
           for (int k = 0; k < 8; ++k) x[k] += xr[k];
         }
       }
-      store_elems<T>(dst + b * s_b + (int64_t)tt * s_t + hx * s_h + e0, x);
+      if (a.in_fp32) store_elems<float>(src + ((int64_t)bh * N + tt) * D + e0, x);
+      else store_elems<T>(dst + b * s_b + (int64_t)tt * s_t + hx * s_h + e0, x);
     }
   };
   if (!KEY && !linear && a.dg != nullptr) {
     Vec16 z16;
     z16.w[0] = z16.w[1] = z16.w[2] = z16.w[3] = 0u;
-    for (int i = tid; i < 64 * RX::PPR; i += 256)
+    for (int i = tid; i < 64 * D / 4 && a.in_fp32; i += 256)
+      if (t0 + i / (D / 4) < N) *reinterpret_cast<Vec16*>(a.dg32 + ((int64_t)bh * N + t0) * D + 4 * i) = z16;
+    for (int i = tid; i < 64 * RX::PPR && !a.in_fp32; i += 256)
       if (t0 + i / RX::PPR < N)
         *reinterpret_cast<Vec16*>(static_cast<T*>(a.dg) + b * a.g_sb + (int64_t)(t0 + i / RX::PPR) * a.g_st + hx * a.g_sh +
                                   (i % RX::PPR) * EPV) = z16;

@@ -312,6 +312,13 @@ struct BwdRowArgs {
   float* ed;               // [U, N]: E_t delta_t
   int U, N, Hq, d;
 };
+// fp32 rows -> a strided tensor in the storage type
+struct BwdRoundArgs {
+  const float* src;        // [B, H, N, d]
+  void* dst;
+  int64_t s_b, s_t, s_h;
+  int B, H, N, d;
+};
 // both weight matrices in the two operand orders of the linear branch, and cleared parameter gradients (each where a
 // destination is given)
 struct BwdWeightsArgs {
@@ -351,11 +358,13 @@ struct BwdLinArgs {
   void* a_rows;            // q: [U, N, d] written: A_t (tokens of chunks >= 2)
   void* phi;               // q: [U, N, 2d] written (tokens of chunks >= 2)
   void* df;                // [U, N, d] written
-  const float* dx32;       // the softmax branch's part: q: [U, N, d]; k: [B, Hkv, N, d]
-  const float* dv32;       // k
+  float* dx32;             // the softmax branch's part: q: [U, N, d]; k: [B, Hkv, N, d]
+  float* dv32;             // k
   void* dx;                // strided like x
   void* dv;                // k: strided like v
   void* dg;                // q: nullable, strided like gate
+  int in_fp32;             // 1: the results stay fp32 (dx and dv over dx32 and dv32, dg in dg32) for a BwdRoundArgs launch
+  float* dg32;             // q: [U, N, d]
   const float* dkret;      // k: nullable [U, cap, d]: the retained entries' part, entry c * lam + slot
   const float* dvret;
   const int32_t* sel;      // k: [U, sel_stride]
@@ -435,6 +444,7 @@ struct RopeArgs {
 };
 hipError_t launch_rope(const RopeArgs& a, int dtype, hipStream_t stream);
 hipError_t launch_bwd_row_prep(const BwdRowArgs& a, int dtype, hipStream_t stream);
+hipError_t launch_bwd_round(const BwdRoundArgs& a, int dtype, hipStream_t stream);
 hipError_t launch_bwd_gather(const BwdGatherArgs& a, int dtype, int U, hipStream_t stream);
 hipError_t launch_bwd_sa(const BwdSaArgs& a, int dtype, int d, int B, hipStream_t stream);
 // attention map and its backward pass (still_map.hip)

@@ -321,3 +321,46 @@ def test_backward_linear_branch_tiles(kw, gate):
 def test_attention_map_tiles(kw):
     """The map and its backward pass work in tiles of 64 rows and 64 keys."""
     test_attention_map_against_the_oracle(kw)
+
+
+@pytest.mark.parametrize("over", [
+    dict(dq="q", dk="k", dv="v"), dict(dk="v", dv="k"), dict(dq="k"), dict(dq="dout", dg="g"), dict(dg="dout"), dict(dk="out", dv="q"),
+], ids=lambda o: "-".join(f"{a}_over_{b}" for a, b in o.items()))
+@pytest.mark.parametrize("kw", [dict(dtype="f32", N=64 * 9 + 5), dict(dtype="bf16", d=128, C=128, W=128, N=128 * 6 + 40)],
+                         ids=["f32", "bf16-C128"])
+def test_backward_results_may_lie_over_its_inputs(kw, over):
+    """The call reads every input before it writes over one, so gradients may share memory with inputs.  dq, dk, dv and dg
+    are sums in a fixed order, rounded once: bit for bit those of a call with separate tensors; the parameter gradients
+    are added atomically (1e-5 of the largest)."""
+    import torch
+
+    w = small("bwd-over", **dict(dict(Hq=4, Hkv=4, lam=8, B=2), **kw))
+    inp = synth.make_inputs(w, seed=121, with_gate=True)
+    t = {n: synth.to_torch(inp[n], w.dtype, "cuda") for n in ("q", "k", "v", "g", "Wq", "Wk")}
+    t["dout"], t["out"] = synth.to_torch(make_dy(w, inp, 122), w.dtype, "cuda"), torch.empty_like(t["q"])
+    p = S.make_params(B=w.B, N=w.N, Hq=w.Hq, Hkv=w.Hkv, d=w.d, C=w.C, W=w.W, lam=w.lam, scale=w.scale, eps=w.eps,
+                      dtype=w.dtype, q=t["q"], k=t["k"], v=t["v"], out=t["out"], g=t["g"])
+    sel = torch.zeros(w.B, w.Hq, w.N // w.C, w.lam, dtype=torch.int32, device="cuda")
+    ws = torch.empty(S.still_fwd_workspace_bytes(p), dtype=torch.uint8, device="cuda")
+    S.still_hybrid_attn_fwd(p, t["q"], t["k"], t["v"], t["g"], t["Wq"], None, t["Wk"], None, t["out"], sel_idx=sel, workspace=ws)
+    off = S.still_fwd_workspace_layout(p).lse
+    lse = ws[off:off + w.B * w.Hq * w.N * 4].view(torch.float32)
+
+    def backward(over):
+        x = {n: y.clone() for n, y in t.items()}
+        res = {a: x[over[a]] if a in over else torch.full_like(t[b], float("nan"))
+               for a, b in (("dq", "q"), ("dk", "k"), ("dv", "v"), ("dg", "g"))}
+        res.update({n: torch.full((w.Hq, w.d, w.d), float("nan"), dtype=torch.float32, device="cuda") for n in ("dWq", "dWk")})
+        bws = torch.full((S.still_bwd_workspace_bytes(p),), 0x7f, dtype=torch.uint8, device="cuda")
+        S.still_hybrid_attn_bwd(p, x["q"], x["k"], x["v"], x["g"], x["Wq"], None, x["Wk"], None, x["out"], x["dout"], lse, sel,
+                                res["dq"], res["dk"], res["dv"], res["dg"], res["dWq"], None, res["dWk"], None, bws)
+        torch.cuda.synchronize()
+        return res
+
+    want, got = backward({}), backward(over)
+    for n in ("dq", "dk", "dv", "dg"):
+        differ = int((got[n] != want[n]).sum())
+        assert differ == 0, n
+    for n in ("dWq", "dWk"):
+        err = float((got[n] - want[n]).abs().max()) / float(want[n].abs().max())
+        assert err <= 1e-5, n
