@@ -883,7 +883,7 @@ void compute_bwd_layout(const still_params_t* p, still_bwd_ws_layout_t* L) {
   const size_t capt = F.cap ? (size_t)F.cap + 64 : 0;
   L->qt = take(U * capt * d * 4);
   L->dot = take(U * capt * d * 4);
-  L->kt = take(U * (capt / 64) * 8);
+  L->kt = take(U * (capt / 64) * 8 + U * capt * 4);
   L->kret = take(U * capt * d * es);
   L->krett = take(U * capt * d * es);
   L->n_pad_t = F.n_pad;
@@ -1010,9 +1010,10 @@ still_status_t bwd_impl(const still_params_t* p, const void* q, const void* k, c
   ga.cap = BL.cap_t; ga.C = C; ga.lam = have_sel ? p->lambda : 0; ga.Hq = Hq; ga.d = d; ga.N = N;
   ga.kret = bws + BL.kret; ga.vret = bws + BL.krett;
   ga.rvalid = reinterpret_cast<unsigned long long*>(bws + BL.kt);
+  ga.times = reinterpret_cast<int32_t*>(ga.rvalid + (size_t)U * (BL.cap_t / 64));
   if ((e = still::launch_bwd_gather(ga, dt, U, stream)) != hipSuccess) return hip_fail("bwd gather", e);
   still::BwdSaArgs sa{};
-  sa.kret = ga.kret; sa.vret = ga.vret; sa.rvalid = ga.rvalid;
+  sa.kret = ga.kret; sa.vret = ga.vret; sa.rvalid = ga.rvalid; sa.times = ga.times;
   sa.cap = BL.cap_t;
   sa.dkret = f32p(BL.qt); sa.dvret = f32p(BL.dot);
   sa.q = q; sa.k = k; sa.v = v; sa.dout = dout;
@@ -1020,11 +1021,10 @@ still_status_t bwd_impl(const still_params_t* p, const void* q, const void* k, c
   sa.k_sb = p->k_sb; sa.k_st = p->k_st; sa.k_sh = p->k_sh;
   sa.v_sb = p->v_sb; sa.v_st = p->v_st; sa.v_sh = p->v_sh;
   sa.o_sb = p->o_sb; sa.o_st = p->o_st; sa.o_sh = p->o_sh;
-  sa.sel = sel_idx; sa.lse = lse; sa.delta = ra.delta;
+  sa.lse = lse; sa.delta = ra.delta;
   sa.dq32 = f32p(BL.dq32); sa.dk32 = f32p(BL.dk32); sa.dv32 = f32p(BL.dv32);
   sa.map = map;
   sa.N = N; sa.C = C; sa.lam = have_sel ? p->lambda : 0; sa.rcap = budget; sa.U = U; sa.Hq = Hq; sa.Hkv = Hkv;
-  sa.sel_stride = ncf * p->lambda;
   sa.n_row_tiles = (N + 127) / 128;
   sa.n_ret_tiles = (still::retained_rows(nc >= 2 ? nc - 2 : 0, sa.lam, budget) + 127) / 128;
   sa.scale = p->scale;
@@ -1055,7 +1055,7 @@ still_status_t bwd_impl(const still_params_t* p, const void* q, const void* k, c
   lk.df = bws + BL.dfk;
   lk.dx32 = sa.dk32; lk.dv32 = sa.dv32; lk.dx = dk; lk.dv = dv;
   lk.in_fp32 = over;
-  lk.sel = sel_idx; lk.lam = sa.lam; lk.cap = BL.cap_t; lk.sel_stride = sa.sel_stride;
+  lk.sel = sel_idx; lk.lam = sa.lam; lk.cap = BL.cap_t; lk.sel_stride = ga.sel_stride;
   lk.n_ret = still::retained_rows(nc >= 2 ? nc - 2 : 0, sa.lam, budget);
   if (lk.n_ret > 0) lk.dkret = sa.dkret, lk.dvret = sa.dvret;
   lk.map = map; lk.n_units = B * Hkv;

@@ -505,8 +505,11 @@ __global__ __launch_bounds__(256, 2) void bwd_lin_kernel(BwdLinArgs a) {
           int en = c * a.lam + __popc(m[w / 32] & ((1u << (w & 31)) - 1u));
           for (int j = 0; j < w / 32; ++j) en += __popc(m[j]);
           const int32_t* list = a.sel + unit * a.sel_stride;
-          if (list[en] != tt)            // (a list with foreign entries between its tokens)
-            for (en = c * a.lam; list[en] != tt; ++en) {}
+          if (list[en] != tt) {          // (a list with foreign or repeated entries, or in another order)
+            const int end = (c + 1) * a.lam;
+            for (en = c * a.lam; en < end && list[en] != tt; ++en) {}
+            if (en == end) continue;
+          }
           if (en >= a.n_ret) continue;
           float xr[8];
           load_elems<float>(xr, dret + (unit * a.cap + en) * D + e0);

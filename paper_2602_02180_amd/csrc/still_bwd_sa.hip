@@ -31,6 +31,14 @@ __global__ __launch_bounds__(256) void bwd_gather_kernel(BwdGatherArgs a) {
     int tok = e < a.nsel ? a.sel[(int64_t)unit * a.sel_stride + e] : -1;
     if (tok < 0 || tok >= a.N || tok / a.C != e / a.lam) tok = -1;
     s_tok[threadIdx.x] = tok;
+    int times = 0;                       // entries of the chunk's list that name this token (more than one: the same key again)
+    if (tok >= 0) {
+      const int first = e / a.lam * a.lam, last = min(first + a.lam, a.nsel);
+      const int32_t* list = a.sel + (int64_t)unit * a.sel_stride;
+#pragma unroll 8
+      for (int i = first; i < last; ++i) times += list[i] == tok;
+    }
+    a.times[(int64_t)unit * a.cap + e] = times;
     const unsigned long long bits = __ballot(tok >= 0);
     if (threadIdx.x == 0) a.rvalid[(int64_t)unit * (a.cap / 64) + blockIdx.x] = bits;
   }
@@ -298,7 +306,7 @@ __global__ __launch_bounds__(256, 2) void bwd_sa_dkv_kernel(BwdSaArgs a) {
     row_hi = N;
   }
   const int64_t unit0 = (int64_t)b * a.Hq + h_first;                  // (!LOCAL: the unit)
-  int tok;                                                            // -1: no key here
+  int tok;                                                            // LOCAL: token, !LOCAL: its other occurrences; -1: no key here
   const T *kp, *vbase;
   int64_t v_row;
   if (LOCAL) {
@@ -307,8 +315,7 @@ __global__ __launch_bounds__(256, 2) void bwd_sa_dkv_kernel(BwdSaArgs a) {
     vbase = static_cast<const T*>(a.v) + b * a.v_sb + kvh * a.v_sh;
     v_row = a.v_st;
   } else {
-    const bool ok = (a.rvalid[unit0 * (a.cap / 64) + key / 64] >> (key & 63)) & 1ull;
-    tok = ok ? a.sel[unit0 * a.sel_stride + key] : -1;
+    tok = a.times[unit0 * a.cap + key] - 1;
     kp = static_cast<const T*>(a.kret) + (unit0 * a.cap + key) * D;
     vbase = static_cast<const T*>(a.vret) + unit0 * a.cap * D;
     v_row = D;
@@ -457,8 +464,9 @@ __global__ __launch_bounds__(256, 2) void bwd_sa_dkv_kernel(BwdSaArgs a) {
     }
   } else {
     const int64_t o = (unit0 * a.cap + key) * D;   // (the capacity covers the last tile)
-    store_row<T, D>(a.dkret + o, dk, a.scale, g);
-    store_row<T, D>(a.dvret + o, dv, 1.f, g);
+    const float times = (float)(tok + 1);          // equal keys have equal gradients, and one of them is added per token
+    store_row<T, D>(a.dkret + o, dk, a.scale * times, g);
+    store_row<T, D>(a.dvret + o, dv, times, g);
   }
 }
 

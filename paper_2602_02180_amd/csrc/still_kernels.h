@@ -409,16 +409,16 @@ struct BwdSaArgs {
   const void* kret;        // [U, cap, d]: retained keys in routing order, zero rows where no token is retained
   const void* vret;        // [U, cap, d]: retained values
   const unsigned long long* rvalid;   // [U, cap / 64]: bit = the retained entry is a token
-  const int32_t* sel;      // [U, sel_stride]: retained entry e is token sel[e] (chunk e / lam)
+  const int32_t* times;    // [U, cap]: entries of its chunk's list that name the entry's token; 0: no token
   const float* lse;        // [U, N]
   const float* delta;      // [U, N]
   float* dq32;             // [U, N, d]
   float* dk32;             // [B, Hkv, N, d]: the local key tiles' part
   float* dv32;
-  float* dkret;            // [U, cap, d]: gradients of the retained entries
+  float* dkret;            // [U, cap, d]: gradients of the retained entries, each as often as its list names the token
   float* dvret;
   HeadMap map;
-  int N, cap, C, lam, rcap, U, Hq, Hkv, sel_stride;
+  int N, cap, C, lam, rcap, U, Hq, Hkv;
   int n_row_tiles, n_ret_tiles;   // tiles of 128 rows / of 128 retained entries that some row sees
   float scale;
 };
@@ -431,6 +431,7 @@ struct BwdGatherArgs {
   void* kret;              // [U, cap, d]
   void* vret;
   unsigned long long* rvalid;   // [U, cap / 64]
+  int32_t* times;          // [U, cap]
   HeadMap map;
   int nsel, sel_stride, cap, C, lam, Hq, d, N;
 };

@@ -364,3 +364,55 @@ def test_backward_results_may_lie_over_its_inputs(kw, over):
     for n in ("dWq", "dWk"):
         err = float((got[n] - want[n]).abs().max()) / float(want[n].abs().max())
         assert err <= 1e-5, n
+
+
+@pytest.mark.parametrize("slots", [[5, 5, 9, 20, 20, 63], [63, 5, 9, 5, 20, 20], [40, 2, 31, 33, 0, 7]],
+                         ids=["repeated", "repeated-unordered", "unordered"])
+def test_backward_counts_every_entry_of_a_list(slots):
+    """Lists that name a token twice, or not in ascending order: the softmax branch sees every entry, so every entry has a
+    gradient.  Against torch's autograd on the output equation in float64 with the entries written out."""
+    import torch
+
+    w = small("bwd-entries", N=64 * 5 + 10, Hq=2, Hkv=1, lam=len(slots))
+    inp = synth.make_inputs(w, seed=131)
+    t = {n: synth.to_torch(inp[n], w.dtype, "cuda") for n in ("q", "k", "v", "Wq", "Wk")}
+    dy = make_dy(w, inp, 132)
+    dout, out = synth.to_torch(dy, w.dtype, "cuda"), torch.empty_like(t["q"])
+    p = S.make_params(B=1, N=w.N, Hq=w.Hq, Hkv=w.Hkv, d=w.d, C=w.C, W=w.W, lam=w.lam, scale=w.scale, eps=w.eps,
+                      dtype=w.dtype, q=t["q"], k=t["k"], v=t["v"], out=out)
+    lists = torch.tensor([[c * w.C + x for x in slots] for c in range(w.N // w.C)], dtype=torch.int32)
+    sel = lists.expand(1, w.Hq, *lists.shape).contiguous().cuda()
+    ws = torch.empty(S.still_fwd_workspace_bytes(p), dtype=torch.uint8, device="cuda")
+    S.still_hybrid_attn_fwd(p, t["q"], t["k"], t["v"], None, t["Wq"], None, t["Wk"], None, out, sel_idx=sel, workspace=ws,
+                            sel_idx_is_input=1)
+    off = S.still_fwd_workspace_layout(p).lse
+    lse = ws[off:off + w.Hq * w.N * 4].view(torch.float32)
+    got = {"d" + n: torch.full_like(t[n], float("nan"), dtype=torch.float32) for n in t}
+    bws = torch.empty(S.still_bwd_workspace_bytes(p), dtype=torch.uint8, device="cuda")
+    S.still_hybrid_attn_bwd(p, t["q"], t["k"], t["v"], None, t["Wq"], None, t["Wk"], None, out, dout, lse, sel, got["dq"],
+                            got["dk"], got["dv"], None, got["dWq"], None, got["dWk"], None, bws)
+
+    x = {n: y.detach().cpu().double().requires_grad_() for n, y in t.items()}
+
+    def features(a, W):
+        f = a @ W
+        u = f / f.norm(dim=-1, keepdim=True) * a.norm(dim=-1, keepdim=True)
+        return torch.cat([u.softmax(-1), (-u).softmax(-1)], -1)
+
+    # how often every row sees every key through exp; what it does not see of the routed chunks goes through phi
+    tok = torch.arange(w.N)
+    c, j = tok[:, None] // w.C, tok[None, :]
+    count = torch.bincount(lists.flatten().long(), minlength=w.N).double()
+    routed = j // w.C <= c - 2
+    seen = torch.where(routed, count[None, :], ((j // w.C >= c - 1) & (j <= tok[:, None])).double())
+    k, v = x["k"][0, :, 0], x["v"][0, :, 0]
+    y = []
+    for h in range(w.Hq):
+        q = x["q"][0, :, h]
+        a = seen * torch.exp(w.scale * (q @ k.T)) + (routed & (count == 0)) * (features(q, x["Wq"][h]) @ features(k, x["Wk"][h]).T)
+        y.append(a @ v / a.sum(-1, keepdim=True))
+    torch.stack(y, 1)[None].backward(torch.from_numpy(dy).double())
+    for n in t:
+        ref = x[n].grad
+        err = float((got["d" + n].cpu().double() - ref).abs().max()) / float(ref.abs().max())
+        assert err <= BAR["f32"], ("d" + n, err)
