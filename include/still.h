@@ -368,21 +368,20 @@ typedef struct still_bwd_ws_layout {
   size_t phi_q;    /* dtype [B, Hq, N, 2*d_f] feature map of the queries                                      */
   size_t phi_k;    /* dtype [B, Hq, N, 2*d_f] feature map of the keys, zero for the selected tokens (maps);
                       float [B, Hq, N, d] dg of a call whose results lie over its inputs (backward pass)      */
-  size_t uq, uk;   /* float [B, Hq, N, d_f]   the weights in operand order (backward pass)                        */
-  size_t stq, stk; /* float [B, Hq, N, 2]     not used                                                        */
-  size_t nraw;     /* float [B, Hq, N, d]     not used                                                        */
-  size_t gq;       /* float [B, Hq, N, 2*d_f] not used                                                        */
-  size_t dphi_k;   /* float [B, Hq, N, 2*d_f] not used                                                        */
-  size_t ds;       /* dtype [B, Hq, ceil(N/C), d, 2*d_f]  gradient of the state the rows of chunk c+2 and later read */
+  size_t wqr, wkr; /* dtype [Hq, d * d_f]     Wq, Wk in the operand order of dx = df W^T                      */
+  size_t stq, stk, nraw, gq, dphi_k; /* empty, as cxq and cxk below (kept for the places of the others)       */
+  size_t ds;       /* dtype [B, Hq, ceil(N/C), d, 2*d_f]  gradient of the state that the rows of chunk c+2 and later
+                      read, in the blocks of still_ws_layout_t's snap                                         */
   size_t dz;       /* float [B, Hq, ceil(N/C), 2*d_f]     likewise for z                                       */
   size_t dfq, dfk; /* dtype [B, Hq, N, d_f]   gradient of f(x)                                                */
-  size_t dq32;     /* float [B, Hq, N, d]                                                                     */
+  size_t dq32;     /* float [B, Hq, N, d]     the softmax branch's part of dq; dk32, dv32: of dk, dv (local span) */
   size_t dk32, dv32; /* float [B, Hkv, N, d]                                                                  */
-  size_t cxq, cxk; /* float [B, Hq, N]        not used                                                          */
-  size_t qt, dot;  /* float [B, Hq, cap, d]   gradients of the retained keys and values, in routing order     */
-  size_t kt;       /* uint64 [B, Hq, cap/64]  bit = the retained entry is a token                             */
+  size_t cxq, cxk; /* empty                                                                                   */
+  size_t dkret, dvret; /* float [B, Hq, cap, d] gradients of the retained keys and values, in routing order   */
+  size_t rvalid;   /* uint64 [B, Hq, cap/64]  bit = the retained entry is a token, then int32 [B, Hq, cap] how often the
+                      chunk's list names that token (0: no token)                                             */
   size_t kret;     /* dtype [B, Hq, cap, d]   retained keys in routing order                                  */
-  size_t krett;    /* dtype [B, Hq, cap, d]   retained values                                                 */
+  size_t vret;     /* dtype [B, Hq, cap, d]   retained values                                                 */
   size_t total;
   int32_t n_pad_t; /* Npad of the forward workspace                                                           */
   int32_t cap_t;   /* cap of the two retained copies (64 more than the forward workspace's)                   */

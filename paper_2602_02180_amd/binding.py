@@ -50,8 +50,9 @@ class StillStateLayout(ct.Structure):
 
 class StillBwdWsLayout(ct.Structure):
     _fields_ = [(n, ct.c_size_t) for n in
-                ("fwd", "e_row", "delta", "ed", "a", "phi_q", "phi_k", "uq", "uk", "stq", "stk", "nraw", "gq",
-                 "dphi_k", "ds", "dz", "dfq", "dfk", "dq32", "dk32", "dv32", "cxq", "cxk", "qt", "dot", "kt", "kret", "krett", "total")] + \
+                ("fwd", "e_row", "delta", "ed", "a", "phi_q", "phi_k", "wqr", "wkr", "stq", "stk", "nraw", "gq",
+                 "dphi_k", "ds", "dz", "dfq", "dfk", "dq32", "dk32", "dv32", "cxq", "cxk", "dkret", "dvret", "rvalid", "kret",
+                 "vret", "total")] + \
                [(n, ct.c_int32) for n in ("n_pad_t", "cap_t")]
 
 

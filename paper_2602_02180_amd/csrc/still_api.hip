@@ -300,7 +300,8 @@ void compute_state_layout(const still_params_t* p, still_state_layout_t* L) {
 extern "C" {
 
 // 0.3.0: budget_policy in the params, more regions in both layouts
-int32_t still_version(void) { return 400; }   // 0.4.0: backward pass, attention map, rotary pre-pass
+// 0.4.0: backward pass, attention map, rotary pre-pass
+int32_t still_version(void) { return 500; }   // 0.5.0: state images in blocks, other regions in the backward workspace
 
 const char* still_last_error(void) { return g_err; }
 
@@ -862,14 +863,10 @@ void compute_bwd_layout(const still_params_t* p, still_bwd_ws_layout_t* L) {
   L->a = take(rows * d * es);
   L->phi_q = take(rows * DP * es);
   L->phi_k = take(rows * DP * es);
-  const size_t wimg = (size_t)p->Hq * d * df * es;   // (the backward pass keeps the weights' operand order here)
-  L->uq = take(rows * df * 4 > wimg ? rows * df * 4 : wimg);
-  L->uk = take(rows * df * 4 > wimg ? rows * df * 4 : wimg);
-  L->stq = take(rows * 2 * 4);
-  L->stk = take(rows * 2 * 4);
-  L->nraw = take(rows * d * 4);
-  L->gq = take(rows * DP * 4);
-  L->dphi_k = take(rows * DP * 4);
+  const size_t wimg = (size_t)p->Hq * d * df * es;
+  L->wqr = take(wimg);
+  L->wkr = take(wimg);
+  L->stq = L->stk = L->nraw = L->gq = L->dphi_k = off;   // (empty)
   L->ds = take(U * nc * DP * d * es);
   L->dz = take(U * nc * DP * 4);
   L->dfq = take(rows * df * es);
@@ -877,15 +874,14 @@ void compute_bwd_layout(const still_params_t* p, still_bwd_ws_layout_t* L) {
   L->dq32 = take(rows * d * 4);
   L->dk32 = take(kvrows * d * 4);
   L->dv32 = take(kvrows * d * 4);
-  L->cxq = take(rows * 4);
-  L->cxk = take(rows * 4);
+  L->cxq = L->cxk = off;                                 // (empty)
   // retained rows, 64 more than the forward workspace's: the last tile of 128 entries may reach past its capacity
   const size_t capt = F.cap ? (size_t)F.cap + 64 : 0;
-  L->qt = take(U * capt * d * 4);
-  L->dot = take(U * capt * d * 4);
-  L->kt = take(U * (capt / 64) * 8 + U * capt * 4);
+  L->dkret = take(U * capt * d * 4);
+  L->dvret = take(U * capt * d * 4);
+  L->rvalid = take(U * (capt / 64) * 8 + U * capt * 4);
   L->kret = take(U * capt * d * es);
-  L->krett = take(U * capt * d * es);
+  L->vret = take(U * capt * d * es);
   L->n_pad_t = F.n_pad;
   L->cap_t = (int32_t)capt;
   L->total = off;
@@ -965,7 +961,7 @@ still_status_t bwd_impl(const still_params_t* p, const void* q, const void* k, c
     for (const Span& i : inputs) over = over || (meet(r, i) && !(g != nullptr && dg == g && r.lo == in_g.lo && i.lo == in_g.lo));
 
   // ---- the weights in operand order, the parameter gradients (sums are added into them) cleared
-  still::BwdWeightsArgs wa{Wq, Wk, ws + L.wqt, ws + L.wkf, bws + BL.uq, bws + BL.uk, dWq, dWk, dbq, dbk, d};
+  still::BwdWeightsArgs wa{Wq, Wk, ws + L.wqt, ws + L.wkf, bws + BL.wqr, bws + BL.wkr, dWq, dWk, dbq, dbk, d};
   if ((e = still::launch_bwd_weights(wa, dt, Hq, stream)) != hipSuccess) return hip_fail("bwd_weights", e);
 
   // ---- the forward pass's linear-attention states, rebuilt from the index lists (same kernels as the prefill)
@@ -1008,14 +1004,14 @@ still_status_t bwd_impl(const still_params_t* p, const void* q, const void* k, c
   ga.nsel = have_sel ? still::retained_rows(ncf, p->lambda, budget) : 0;
   ga.sel_stride = ncf * p->lambda;
   ga.cap = BL.cap_t; ga.C = C; ga.lam = have_sel ? p->lambda : 0; ga.Hq = Hq; ga.d = d; ga.N = N;
-  ga.kret = bws + BL.kret; ga.vret = bws + BL.krett;
-  ga.rvalid = reinterpret_cast<unsigned long long*>(bws + BL.kt);
+  ga.kret = bws + BL.kret; ga.vret = bws + BL.vret;
+  ga.rvalid = reinterpret_cast<unsigned long long*>(bws + BL.rvalid);
   ga.times = reinterpret_cast<int32_t*>(ga.rvalid + (size_t)U * (BL.cap_t / 64));
   if ((e = still::launch_bwd_gather(ga, dt, U, stream)) != hipSuccess) return hip_fail("bwd gather", e);
   still::BwdSaArgs sa{};
   sa.kret = ga.kret; sa.vret = ga.vret; sa.rvalid = ga.rvalid; sa.times = ga.times;
   sa.cap = BL.cap_t;
-  sa.dkret = f32p(BL.qt); sa.dvret = f32p(BL.dot);
+  sa.dkret = f32p(BL.dkret); sa.dvret = f32p(BL.dvret);
   sa.q = q; sa.k = k; sa.v = v; sa.dout = dout;
   sa.q_sb = p->q_sb; sa.q_st = p->q_st; sa.q_sh = p->q_sh;
   sa.k_sb = p->k_sb; sa.k_st = p->k_st; sa.k_sh = p->k_sh;

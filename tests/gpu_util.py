@@ -190,8 +190,7 @@ def assert_bf16_bar(x: np.ndarray, ref: np.ndarray, what: str = "") -> Dict[str,
 # backward pass
 # ---------------------------------------------------------------------------------------------------------------
 def run_hip_backward(w: synth.Workload, inp: Dict[str, np.ndarray], dy: np.ndarray,
-                     kv_map: Optional[np.ndarray] = None, gate_activation: int = 0,
-                     want_intermediates: bool = False) -> Dict[str, np.ndarray]:
+                     kv_map: Optional[np.ndarray] = None, gate_activation: int = 0) -> Dict[str, np.ndarray]:
     """still_hybrid_attn_fwd followed by still_hybrid_attn_bwd with the forward call's index lists and log
     normalisers.  Returns the forward's out / sel / lse and every gradient as float arrays."""
     import torch
@@ -229,19 +228,4 @@ def run_hip_backward(w: synth.Workload, inp: Dict[str, np.ndarray], dy: np.ndarr
            "dWq": dWq.cpu().numpy(), "dWk": dWk.cpu().numpy(),
            "dbq": dbq.cpu().numpy() if dbq is not None else None,
            "dbk": dbk.cpu().numpy() if dbk is not None else None}
-    if want_intermediates:
-        BL = S.still_bwd_workspace_layout(p)
-        U_, DP = B * w.Hq, 2 * w.df
-        nc = (N + w.C - 1) // w.C
-
-        def f32_region(off, shape):
-            n = int(np.prod(shape)) * 4
-            return bws[off:off + n].view(torch.float32).reshape(*shape).cpu().numpy()
-
-        res["nraw"] = f32_region(BL.nraw, (B, w.Hq, N, w.d))
-        res["gq"] = f32_region(BL.gq, (B, w.Hq, N, DP))
-        res["dz"] = f32_region(BL.dz, (B, w.Hq, nc, DP))
-        res["dphi_k"] = f32_region(BL.dphi_k, (B, w.Hq, N, DP))
-        res["uq"] = f32_region(BL.uq, (B, w.Hq, N, w.df))
-        res["dq32"] = f32_region(BL.dq32, (B, w.Hq, N, w.d))
     return res

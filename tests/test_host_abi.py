@@ -237,3 +237,18 @@ def test_the_cut_of_the_scan_never_outgrows_the_builtin_scratch_array(kw):
     """Problems that fill the array when the scan is cut into few segments: more segments may not push them out."""
     kw = dict(dict(Hkv=kw["Hq"]), **kw)
     assert S.still_fwd_workspace_bytes(params(**kw)) <= 32 << 20
+
+
+def test_the_backward_workspace_holds_what_the_kernels_use_and_no_more():
+    """The training shape (16 sequences of 1024 tokens, 32 / 8 heads, d = 128, C = 64, bf16): the forward workspace, per query
+    head and token three scalars, A, phi of either side, df of either side and a fp32 row, the state gradients, per kv head and
+    token two fp32 rows, per retained entry (64 more than the lists hold) two rows, two fp32 rows, four bytes and a bit,
+    and two copies of the weights; every region is rounded up to 256 bytes."""
+    B, N, Hq, Hkv, d, C, lam = 16, 1024, 32, 8, 128, 64, 16
+    p = params(B=B, N=N, Hq=Hq, Hkv=Hkv, d=d, C=C, W=128, lam=lam)
+    rows, entries = B * Hq * N, B * Hq * (N // C * lam + 64)
+    want = S.still_fwd_workspace_bytes(p) + rows * (12 + 2 * d + 2 * 4 * d + 2 * 2 * d + 4 * d) \
+        + B * Hq * (N // C) * 2 * d * (2 * d + 4) + 2 * 4 * B * Hkv * N * d + entries * (2 * 2 * d + 2 * 4 * d + 4) \
+        + entries // 8 + 4 * Hq * d * d
+    assert want <= S.still_bwd_workspace_bytes(p) <= want + 64 * 256
+    assert S.still_attention_map_bwd_workspace_bytes(p) <= S.still_bwd_workspace_bytes(p) + 4 * rows + 256
