@@ -249,7 +249,9 @@ void compute_layout(const still_params_t* p, still_ws_layout_t* L) {
     if (G == 0 || cost < best) G = g, best = cost;
   }
   layout_with_segments(p, G, L);
-  // More segments take more workspace: a problem that only fits the built-in scratch array with fewer keeps fewer.
+  // More segments take more workspace: a problem that only fits the built-in scratch array with fewer keeps fewer (d = 64,
+  // C = 128, bf16, 512 to 1024 tokens and 129 or more heads over the batch, for instance 5 x 768 tokens with 26 heads).  The
+  // rule does not ask which entry point called: both give the same bits, so both cut alike.
   const int64_t g_few = whole_rounds(std::min(nc, std::max<int64_t>(2, (nc * units + kCus - 1) / kCus)));
   if (g_few > G && L->total > (size_t)STILL_STATIC_WORKSPACE_BYTES) {
     still_ws_layout_t F;

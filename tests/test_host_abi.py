@@ -230,13 +230,18 @@ def test_public_header_is_plain_c_and_matches_the_binding(tmp_path):
 
 
 @pytest.mark.parametrize("kw", [
-    dict(B=1, Hq=8, N=2432, dtype="f32"), dict(B=2, Hq=16, N=1280), dict(B=3, Hq=8, N=1664), dict(B=5, Hq=4, N=2048),
-    dict(B=8, Hq=4, N=1280), dict(B=3, Hq=4, N=1344, d=128, C=128), dict(B=5, Hq=8, N=192, d=128, C=128),
-    dict(B=4, Hq=4, N=576, d=128), dict(B=1, Hq=32, N=448, d=128, C=128)])
+    dict(B=5, N=768, Hq=26, Hkv=2, lam=8), dict(B=2, N=768, Hq=66, Hkv=1, lam=4), dict(B=6, N=763, Hq=22, Hkv=2, lam=4),
+    dict(B=2, N=768, Hq=72, Hkv=6, lam=0), dict(B=7, N=512, Hq=37, Hkv=1, lam=0)], ids=lambda k: f"{k['B']}x{k['N']}x{k['Hq']}")
 def test_the_cut_of_the_scan_never_outgrows_the_builtin_scratch_array(kw):
-    """Problems that fill the array when the scan is cut into few segments: more segments may not push them out."""
-    kw = dict(dict(Hkv=kw["Hq"]), **kw)
-    assert S.still_fwd_workspace_bytes(params(**kw)) <= 32 << 20
+    """Problems that fit the built-in scratch array only when the scan is cut into few segments keep the few.  That the
+    cheapest cut is another one shows with emit_terms, which takes more than the array either way: more segments, and
+    that many more would not have fitted."""
+    kw = dict(kw, d=64, C=128)
+    few, cheap = S.still_fwd_workspace_layout(params(**kw)), S.still_fwd_workspace_layout(params(emit_terms=1, **kw))
+    assert few.total <= 32 << 20 < cheap.total
+    assert few.seg_chunks > cheap.seg_chunks and few.nseg < cheap.nseg
+    per_segment = kw["B"] * kw["Hq"] * (2 * 64 * 65 * 4 + 64 * 2 * 64 * 2 + 2 * 64 * 4)   # totals, image and z of one segment
+    assert few.total + (cheap.nseg - few.nseg) * per_segment > 32 << 20
 
 
 def test_the_backward_workspace_holds_what_the_kernels_use_and_no_more():
