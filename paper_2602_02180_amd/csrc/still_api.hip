@@ -967,7 +967,7 @@ still_status_t bwd_impl(const still_params_t* p, const void* q, const void* k, c
   if ((e = still::launch_bwd_weights(wa, dt, Hq, stream)) != hipSuccess) return hip_fail("bwd_weights", e);
 
   // ---- the forward pass's linear-attention states, rebuilt from the index lists (same kernels as the prefill)
-  still::TransposeVArgs tv{v, p->v_sb, p->v_st, p->v_sh, ws + L.vt, ws + L.vfr, N, L.n_pad, Hkv, d, C, nullptr};
+  still::TransposeVArgs tv{v, p->v_sb, p->v_st, p->v_sh, nullptr, ws + L.vfr, N, L.n_pad, Hkv, d, C, nullptr};
   if ((e = still::launch_transpose_v(tv, dt, B, stream)) != hipSuccess) return hip_fail("transpose_v", e);
   still::KeepMaskArgs km{sel_idx, reinterpret_cast<uint32_t*>(ws + L.kmask), Hq, ncf, C, have_sel ? p->lambda : 0,
                          budget};

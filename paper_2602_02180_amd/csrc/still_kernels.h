@@ -55,7 +55,7 @@ struct GScoreArgs {
 struct TransposeVArgs {
   const void* v;
   int64_t v_sb, v_st, v_sh;
-  void* vt;       // [B, Hkv, d, Np]
+  void* vt;       // nullable [B, Hkv, d, Np]
   void* vfr;      // nullable: the same values in MFMA-fragment order, see vfr_offset()
   int N, Np, Hkv, d, C;
   const int32_t* seq_len;   // nullable, device [B]: see seq_tokens()

@@ -38,7 +38,7 @@ __global__ __launch_bounds__(256) void transpose_v_kernel(TransposeVArgs a) {
     for (int e = 0; e < EPV; ++e) tile[i][x0 + e] = pe[e];
   }
   __syncthreads();
-  for (int q = threadIdx.x; q < 64 * VPR; q += 256) {
+  for (int q = threadIdx.x; q < 64 * VPR && vt != nullptr; q += 256) {
     const int i = q / VPR, t0 = (q % VPR) * EPV;               // column d0 + i, tokens tok0 + t0 ..
     Vec16 pk;
     E* pe = reinterpret_cast<E*>(&pk);

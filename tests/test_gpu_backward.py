@@ -416,3 +416,25 @@ def test_backward_counts_every_entry_of_a_list(slots):
         ref = x[n].grad
         err = float((got["d" + n].cpu().double() - ref).abs().max()) / float(ref.abs().max())
         assert err <= BAR["f32"], ("d" + n, err)
+
+
+@pytest.mark.parametrize("dtype,d", [("f32", 64), ("bf16", 128)])
+def test_backward_makes_no_transposed_copy_of_v(dtype, d):
+    """The state scan reads v in operand order only: region `vt` of the workspace keeps what it held."""
+    import torch
+
+    w = small("bwd-vt", dtype=dtype, d=d, N=450, Hq=2, Hkv=2, lam=4)
+    inp = synth.make_inputs(w, seed=141)
+    q, k, v, Wq, Wk = (synth.to_torch(inp[n], w.dtype, "cuda") for n in ("q", "k", "v", "Wq", "Wk"))
+    out, lse = torch.zeros_like(q), torch.zeros(w.Hq * w.N, dtype=torch.float32, device="cuda")
+    p = S.make_params(B=1, N=w.N, Hq=w.Hq, Hkv=w.Hkv, d=d, C=w.C, W=w.W, lam=w.lam, scale=w.scale, eps=w.eps, dtype=dtype,
+                      q=q, k=k, v=v, out=out)
+    sel = torch.arange(w.N // w.C, device="cuda", dtype=torch.int32)[:, None] * w.C + torch.arange(w.lam, device="cuda", dtype=torch.int32)
+    sel = sel.expand(1, w.Hq, *sel.shape).contiguous()
+    bws = torch.full((S.still_bwd_workspace_bytes(p),), 0x5a, dtype=torch.uint8, device="cuda")
+    dq, dk, dv = (torch.empty_like(x) for x in (q, k, v))
+    dWq, dWk = (torch.empty(w.Hq, d, d, dtype=torch.float32, device="cuda") for _ in range(2))
+    S.still_hybrid_attn_bwd(p, q, k, v, None, Wq, None, Wk, None, out, out, lse, sel, dq, dk, dv, None, dWq, None, dWk, None, bws)
+    L = S.still_fwd_workspace_layout(p)
+    untouched = bool((bws[L.vt:L.kret] == 0x5a).all())
+    assert untouched
