@@ -93,7 +93,9 @@ __device__ __forceinline__ void store_elems(T* p, const float (&x)[8]) {
   }
 }
 
-template <typename T, int D, bool KEY>
+// IN_FP32: the results stay fp32, dx and dv over dx32 and dv32, dg in dg32.  (An instance of its own: as a run-time choice it
+// cost the ordinary ones a per cent, 577 -> 582 and 619 -> 626 us at the shape above.)
+template <typename T, int D, bool KEY, bool IN_FP32>
 __global__ __launch_bounds__(256, 2) void bwd_lin_kernel(BwdLinArgs a) {
   typedef Mma<T> M;
   typedef LinCfg<T, D> Cf;
@@ -428,7 +430,7 @@ __global__ __launch_bounds__(256, 2) void bwd_lin_kernel(BwdLinArgs a) {
               dy[e] *= sg * (1.f - sg);
             }
           }
-          if (a.in_fp32) store_elems<float>(a.dg32 + (unit * N + tt) * D + e0, dy);
+          if constexpr (IN_FP32) store_elems<float>(a.dg32 + (unit * N + tt) * D + e0, dy);
           else store_elems<T>(static_cast<T*>(a.dg) + go, dy);
         }
       }
@@ -517,16 +519,16 @@ __global__ __launch_bounds__(256, 2) void bwd_lin_kernel(BwdLinArgs a) {
           for (int k = 0; k < 8; ++k) x[k] += xr[k];
         }
       }
-      if (a.in_fp32) store_elems<float>(src + ((int64_t)bh * N + tt) * D + e0, x);
+      if constexpr (IN_FP32) store_elems<float>(src + ((int64_t)bh * N + tt) * D + e0, x);
       else store_elems<T>(dst + b * s_b + (int64_t)tt * s_t + hx * s_h + e0, x);
     }
   };
   if (!KEY && !linear && a.dg != nullptr) {
     Vec16 z16;
     z16.w[0] = z16.w[1] = z16.w[2] = z16.w[3] = 0u;
-    for (int i = tid; i < 64 * D / 4 && a.in_fp32; i += 256)
+    for (int i = tid; IN_FP32 && i < 64 * D / 4; i += 256)
       if (t0 + i / (D / 4) < N) *reinterpret_cast<Vec16*>(a.dg32 + ((int64_t)bh * N + t0) * D + 4 * i) = z16;
-    for (int i = tid; i < 64 * RX::PPR && !a.in_fp32; i += 256)
+    for (int i = tid; !IN_FP32 && i < 64 * RX::PPR; i += 256)
       if (t0 + i / RX::PPR < N)
         *reinterpret_cast<Vec16*>(static_cast<T*>(a.dg) + b * a.g_sb + (int64_t)(t0 + i / RX::PPR) * a.g_st + hx * a.g_sh +
                                   (i % RX::PPR) * EPV) = z16;
@@ -775,7 +777,8 @@ hipError_t allow_lds(K kern, size_t smem) {
 
 template <typename T, int D>
 hipError_t launch_lin_t(const BwdLinArgs& a, bool key, hipStream_t s) {
-  auto kern = key ? bwd_lin_kernel<T, D, true> : bwd_lin_kernel<T, D, false>;
+  auto kern = a.in_fp32 ? (key ? bwd_lin_kernel<T, D, true, true> : bwd_lin_kernel<T, D, false, true>)
+                        : (key ? bwd_lin_kernel<T, D, true, false> : bwd_lin_kernel<T, D, false, false>);
   const hipError_t e = allow_lds(kern, LinCfg<T, D>::smem);
   if (e != hipSuccess) return e;
   hipLaunchKernelGGL(kern, dim3((unsigned)((a.N + 63) / 64) * a.n_units), dim3(256), (LinCfg<T, D>::smem), s, a);

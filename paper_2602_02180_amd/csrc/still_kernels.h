@@ -363,7 +363,7 @@ struct BwdLinArgs {
   void* dx;                // strided like x
   void* dv;                // k: strided like v
   void* dg;                // q: nullable, strided like gate
-  int in_fp32;             // 1: the results stay fp32 (dx and dv over dx32 and dv32, dg in dg32) for a BwdRoundArgs launch
+  bool in_fp32;            // the results stay fp32 (dx and dv over dx32 and dv32, dg in dg32) for a BwdRoundArgs launch
   float* dg32;             // q: [U, N, d]
   const float* dkret;      // k: nullable [U, cap, d]: the retained entries' part, entry c * lam + slot
   const float* dvret;
