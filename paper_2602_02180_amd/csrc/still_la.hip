@@ -66,8 +66,6 @@ struct LaCfg {
   static_assert(DP / NCW == 64, "one feature row of z per consumer lane");
 };
 
-__device__ __forceinline__ int floor_div(int a, int b) { return a >= 0 ? a / b : -((-a + b - 1) / b); }
-
 // SUB: the budget policy that evicts (still_evict.hip): every token position carries the key and value of the token
 // a.src names (-1: nothing), and the operand-order copy of v is per query head.
 template <typename T, int D, int C, bool SUB>
@@ -124,7 +122,6 @@ __device__ __forceinline__ void la_body(const LaArgs& a) {
     auto load_x = [&](int tokw) __attribute__((always_inline)) {
       int tok = tokw + r;
       tok = tok < N ? tok : N - 1;
-      tok = tok < 0 ? 0 : tok;
       if constexpr (SUB) {
         carried = a.src[unit * a.N + tok];
         tok = carried >= 0 ? carried : tok;
@@ -136,7 +133,7 @@ __device__ __forceinline__ void la_body(const LaArgs& a) {
     // one word of the chunk's keep mask per 32-token tile; all ones for a chunk that is not routed (nothing of it
     // goes to the state)
     auto load_keep = [&](int tokw) __attribute__((always_inline)) {
-      const int cc = floor_div(tokw, C);
+      const int cc = tokw / C;
       const bool valid = cc < c_end;                     // (c_end never exceeds the number of full chunks)
       if constexpr (SUB) kw = valid ? 0u : 0xffffffffu;  // (which positions carry nothing comes with the rows)
       else kw = valid ? a.kmask[(unit * a.ncf + cc) * (C / 32) + (tokw - cc * C) / 32] : 0xffffffffu;
@@ -285,10 +282,10 @@ __device__ __forceinline__ void la_body(const LaArgs& a) {
   const int NP = R * NPART;                      // parts of the segment
   auto load_v = [&](int gp, VFrag& vf) __attribute__((always_inline)) {
     const int ptok0 = seg_tok0 + gp * PTOK;
-    int cc = floor_div(ptok0, C);
+    int cc = ptok0 / C;
     const int within = ptok0 - cc * C;
     const int cmax = a.Np / C - 1;
-    cc = cc < 0 ? 0 : (cc > cmax ? cmax : cc);   // a chunk that does not exist meets zero features: any finite V will do
+    cc = cc > cmax ? cmax : cc;                  // a chunk that does not exist meets zero features: any finite V will do
     const T* vrow = vfr + vfr_offset(cc * C, 32 * wave, C, D, M::KK, M::KPL) + (within / M::KK) * 64 * M::KPL +
                     (2 * r + g) * M::KPL;
 #pragma unroll
