@@ -438,3 +438,65 @@ def test_backward_makes_no_transposed_copy_of_v(dtype, d):
     L = S.still_fwd_workspace_layout(p)
     untouched = bool((bws[L.vt:L.kret] == 0x5a).all())
     assert untouched
+
+
+@pytest.mark.parametrize("kw", [
+    dict(dtype="f32", N=64 * 6 + 9, Hq=4, Hkv=2), dict(dtype="bf16", d=128, C=128, W=128, N=128 * 5 - 30, Hq=2, Hkv=2),
+    dict(dtype="bf16", N=64 * 5, Hq=8, Hkv=1)], ids=["f32", "bf16-C128", "bf16-d64"])
+def test_backward_and_map_with_strided_tensors(kw):
+    """q, k and v as slices of one packed projection, out and dout head-major, the gate with gaps between its rows: bit for bit
+    the gradients and the map of contiguous tensors (every sum runs in the same order; the parameter gradients are
+    added atomically: 1e-5 of the largest), and nothing between the rows is written."""
+    import torch
+
+    w = small("bwd-strided", **dict(dict(lam=8, B=2), **kw))
+    B, N, Hq, Hkv, d = w.B, w.N, w.Hq, w.Hkv, w.d
+    inp = synth.make_inputs(w, seed=151, with_gate=True)
+    t = {n: synth.to_torch(inp[n], w.dtype, "cuda") for n in ("q", "k", "v", "g", "Wq", "Wk")}
+    t["dout"] = synth.to_torch(make_dy(w, inp, 152), w.dtype, "cuda")
+    dt = t["q"].dtype
+
+    def packed(fill):                                    # [B, N, (Hq + 2 Hkv + 1) d]: q, k, v and a column block of nothing
+        x = torch.full((B, N, Hq + 2 * Hkv + 1, d), fill, dtype=dt, device="cuda")
+        return x, x[:, :, :Hq], x[:, :, Hq:Hq + Hkv], x[:, :, Hq + Hkv:Hq + 2 * Hkv]
+
+    def run(strided):
+        junk = []
+        if strided:
+            _, q, k, v = packed(7.0)
+            grads, dq, dk, dv = packed(5.0)
+            out, dout = (torch.empty(B, Hq, N, d, dtype=dt, device="cuda").permute(0, 2, 1, 3) for _ in range(2))
+            g, dg = (torch.full((B, N, Hq, d + 16), x, dtype=dt, device="cuda") for x in (7.0, 5.0))
+            junk = [grads[:, :, Hq + 2 * Hkv:], dg[..., d:]]
+            g, dg = g[..., :d], dg[..., :d]
+        else:
+            q, k, v, g, dout, out = (torch.empty_like(t[n]) for n in ("q", "k", "v", "g", "dout", "dout"))
+            dq, dk, dv, dg = (torch.empty_like(x) for x in (q, k, v, g))
+        for n, x in (("q", q), ("k", k), ("v", v), ("g", g), ("dout", dout)):
+            x.copy_(t[n])
+        p = S.make_params(B=B, N=N, Hq=Hq, Hkv=Hkv, d=d, C=w.C, W=w.W, lam=w.lam, scale=w.scale, eps=w.eps, dtype=w.dtype, q=q,
+                          k=k, v=v, out=out, g=g)
+        sel = torch.zeros(B, Hq, N // w.C, w.lam, dtype=torch.int32, device="cuda")
+        ws = torch.empty(S.still_fwd_workspace_bytes(p), dtype=torch.uint8, device="cuda")
+        S.still_hybrid_attn_fwd(p, q, k, v, g, t["Wq"], None, t["Wk"], None, out, sel_idx=sel, workspace=ws)
+        off = S.still_fwd_workspace_layout(p).lse
+        lse = ws[off:off + B * Hq * N * 4].view(torch.float32)
+        dWq, dWk, mWq, mWk = (torch.empty(Hq, d, d, dtype=torch.float32, device="cuda") for _ in range(4))
+        bws = torch.empty(S.still_attention_map_bwd_workspace_bytes(p), dtype=torch.uint8, device="cuda")
+        S.still_hybrid_attn_bwd(p, q, k, v, g, t["Wq"], None, t["Wk"], None, out, dout, lse, sel, dq, dk, dv, dg, dWq, None, dWk,
+                                None, bws)
+        amap = torch.empty(B, Hq, N, N, dtype=torch.float32, device="cuda")
+        S.still_attention_map(p, q, k, t["Wq"], None, t["Wk"], None, lse, sel, amap, bws)
+        S.still_attention_map_bwd(p, q, k, t["Wq"], None, t["Wk"], None, lse, sel, amap, amap.square(), mWq, None, mWk, None, bws)
+        return dict(out=out, dq=dq, dk=dk, dv=dv, dg=dg, map=amap), dict(dWq=dWq, dWk=dWk, mWq=mWq, mWk=mWk), junk
+
+    (same, near, _), (same_s, near_s, junk) = run(False), run(True)
+    for n in same:
+        differ = int((same[n] != same_s[n]).sum())
+        assert differ == 0, n
+    for n in near:
+        err = float((near[n] - near_s[n]).abs().max()) / float(near[n].abs().max())
+        assert err <= 1e-5, (n, err)
+    for x in junk:
+        kept = bool((x == 5.0).all())
+        assert kept
