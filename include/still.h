@@ -224,8 +224,9 @@ STILL_API still_status_t still_hybrid_attn_fwd_static(const still_params_t* p,
  * kernels in launch order, the MEAN duration in milliseconds over the calls recorded since
  * still_profile_enable(1) (the last 64 of them if there were more) into the HOST array ms;
  * still_profile_kernel_name(i) names slot i (NULL past the last).  Returns STILL_ERR_STATE if no call was
- * recorded.  A kernel that a call skips (e.g. the score kernel when the selection is an input) shows as a
- * zero-length slot.
+ * recorded.  A kernel that a call skips (the score kernel when the selection is an input, keep_mask when it is not,
+ * la_prefix where the scan has one segment) shows as the few microseconds of an empty event pair; with budget_policy 1
+ * the keep_mask slot times the eviction plan.
  * still_profile_enable(2) records the pair of the last kernel (the sparse-attention + merge kernel) only and
  * reports 0 for the others: every recorded event is a marker in the stream, and sixteen of them per call cost
  * a few per cent of a back-to-back run.
@@ -250,7 +251,7 @@ STILL_API const char* still_profile_kernel_name(int32_t i);
  *                                     (for inspection)
  *   ring dtype [B, Hkv, R, d] x 2     keys and values of the last R = 4*C tokens, slot = token % R
  *   sc   float [B, Hq, R]             Self-Saliency Score of the same tokens
- *   part float [B, Hq, 32, d+2]       split partials of the attention pass
+ *   part float [B, Hq, 32, d+2]       scratch of a step: the splits' partials (at most 31), in slot 31 the linear terms
  *   rsc  float [B, Hq, cap]           budget_policy 1 only: Self-Saliency Score of every retained row
  *   rtok int32 [B, Hq, cap]           budget_policy 1 only: its token index (retained rows are then in no order)
  * The number of tokens seen is NOT stored: the caller passes the index t of the new token to every step.
