@@ -12,7 +12,10 @@
 // state image S^T [x][2 d_f] passes through LDS in slabs of 64 features, and one copy of a slab serves both products:
 // read along its rows for phi S, down its columns (transposing LDS reads) for a S^T.
 // Least traffic: the images (2 d d_f elements per chunk, four times the chunk's rows at C = 64), rows and gradients once.
-// Measured at 16 sequences of 1024 tokens, 32 / 8 heads, d = 128, C = 64, bf16: query side 0.58 ms, key side 0.63 ms, state
+// What bounds it beyond that: two workgroups per CU (registers and LDS) that alternate between products and row-wise vector
+// work at one barrier per slab.  All 256 registers are in use at d = 128 and 26 (query side) / 44 (key side) values spill, 84 on
+// the key side in fp32; none at d = 64 in bf16.
+// Measured at 16 sequences of 1024 tokens, 32 / 8 heads, d = 128, C = 64, bf16: query side 0.58 ms, key side 0.62 ms, state
 // gradient 0.175 ms, parameter gradients 0.12 ms; as batched products through memory (f, u, dphi, phi S and their
 // fp32 sums each written and read) 4.2 ms.
 #include "still_kernels.h"
@@ -543,8 +546,8 @@ __global__ __launch_bounds__(256, 2) void bwd_lin_kernel(BwdLinArgs a) {
 // ---------------------------------------------------------------------------------------------------------
 // The state gradient as a running sum: dS(c) = sum over c' >= c + 2 of A(c')^T phi_q(c'), dz(c) likewise of the rows'
 // E delta.  One workgroup owns 64 channels x BF features of one (batch, head) and walks the chunks from the last one
-// down; after chunk c' its accumulators ARE dS(c' - 2), which is stored in the storage type as [x][2 d_f] (the layout
-// of the forward states).  Token tiles are double-buffered and read down their columns on both sides.
+// down; after chunk c' its accumulators ARE dS(c' - 2), which is stored in the storage type (the layout of the
+// forward states).  Token tiles are double-buffered and read down their columns on both sides.
 // Bound by the images it writes (2 d d_f elements per chunk).
 // ---------------------------------------------------------------------------------------------------------
 template <typename T, int D>

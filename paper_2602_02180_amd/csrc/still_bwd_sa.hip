@@ -10,7 +10,7 @@
 //   dkv : S = Q K^T, dP = dO V^T (32 rows x 32 keys per wave), dv^T += dO^T P, dk^T += Q^T dS.
 // What bounds them: LDS operand bandwidth next to the matrix pipe (every product reads a fresh 1 KB fragment).
 // Measured at 16 sequences of 1024 tokens, 32 / 8 heads, d = 128, C = 64, lambda = 16, bf16: dq 0.75 -> 0.24 ms, dkv of
-// the local span 0.40 -> 0.15 ms, of the retained entries 0.67 -> 0.18 ms, against the same products with every operand
+// the local span 0.40 -> 0.16 ms, of the retained entries 0.67 -> 0.18 ms (four values spilled), against the same products with every operand
 // fetched from global memory in fragment form (32 cache lines per instruction) and P, dS passed through LDS.
 #include "still_kernels.h"
 #include "still_tile.h"

@@ -852,7 +852,8 @@ __device__ __forceinline__ void decode_linear(const DecArgs& a, int hq, int b, L
 
 // ---------------------------------------------------------------- one launch of everything that reads the state
 // Workgroups: the splits of the salient cache (the long ones) first, then linear terms, scores, ring copies, which fill
-// what the splits leave idle.  As launches of their own (score + append, attend, linear terms and merge in the last)
+// what the splits leave idle (with the short ones first: 756 -> 773 us at 64 sequences behind 32 K tokens, 48 -> 53 us at
+// 24 sequences with 896 retained rows).  As launches of their own (score + append, attend, linear terms and merge in the last)
 // each of them paid its own start and tail.  Before -> now: one sequence behind 4 K tokens, 32 heads, d = 128, 27 us
 // (6.0 + 6.2 + 12.7 in the kernels) -> 10.5 us; 24 sequences with 896 retained rows, d = 64, 59 us (5.7 + 32 + 10) -> 48
 // us; 64 sequences behind 32 K tokens 782 (16 + 714 + 54) -> 755 us, 4.69 GB at 6.2 TB/s.

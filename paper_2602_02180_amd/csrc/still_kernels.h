@@ -194,9 +194,9 @@ struct SaArgs {
   const void* g;       // nullable gate [B, N, Hq, d]
   int64_t g_sb, g_st, g_sh;
   int gate_act;        // 1: g is a pre-activation, the gate is its logistic function
-  const void* snap;    // [B, Hq, nc][D][DP]: see LaArgs
+  const void* snap;    // [B, Hq, nc][D][DP] in blocks (state_image_offset): see LaArgs
   const float* zsnap;  // [B, Hq, nc][DP]
-  const void* pimg;    // [B, Hq, nseg][D][DP]
+  const void* pimg;    // [B, Hq, nseg][D][DP] in blocks
   const float* zpre;   // [B, Hq, nseg][DP]
   int seg_chunks, nseg;
   float* n_la_out;     // nullable [B, Hq, N, d]: the gated linear numerator of every row (inspection)
@@ -378,7 +378,7 @@ struct BwdRevscanArgs {
   const void* a_rows;      // [U, N, d]
   const void* phi;         // [U, N, 2d]
   const float* ed;         // [U, N]
-  void* ds;                // [U, nc, d, 2d] storage type: dS(c) as [x][feature], chunks <= nc - 3
+  void* ds;                // [U, nc, d, 2d] storage type (state_image_offset): dS(c), chunks <= nc - 3
   float* dz;               // [U, nc, 2d]
   int N, C, nc;
 };

@@ -186,8 +186,8 @@ def test_backward_with_group_shared_selection_bf16():
 
 def test_backward_twice_on_a_user_stream_gives_the_same_gradients():
     """Nothing in the workspace has to start at zero and nothing survives a call: a second call into the same
-    (dirty) workspace on a non-default stream reproduces the first to rounding (dk, dv and the parameter gradients
-    are summed with atomic adds, so not bit for bit)."""
+    (dirty) workspace on a non-default stream reproduces the first to rounding (the parameter gradients are summed
+    with atomic adds, so not bit for bit)."""
     import torch
 
     w = small("bwd-twice", N=700, Hq=4, Hkv=2, lam=8)
