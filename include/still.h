@@ -119,9 +119,9 @@ typedef struct still_params {
 typedef struct still_ws_layout {
   size_t score;    /* float   [B, Hq, N]                         Self-Saliency Score of every token        */
   size_t sel;      /* int32   [B, Hq, N/C, lambda]               selected tokens per full chunk, ascending */
-  size_t vt;       /* dtype   [B, Hkv, d, Npad]                  v transposed, zero padded                 */
+  size_t vt;       /* dtype   [B, Hkv, Npad/64, d, 64]           v transposed in tiles of 64, zero padded  */
   size_t kret;     /* dtype   [B, Hq, cap, d]                    retained keys in routing order            */
-  size_t vrett;    /* dtype   [B, Hq, d, cap]                    retained values, transposed               */
+  size_t vrett;    /* dtype   [B, Hq, cap/64, d, 64]             retained values, transposed likewise      */
   size_t wqt;      /* dtype   [Hq, d_f, d]                       Wq transposed                             */
   size_t wkf;      /* dtype   [Hq, d_f * d]                      Wk transposed, in matrix-operand order    */
   size_t seg;      /* float   [B, Hq, nseg, 2*d_f*(d+1)]         per-segment totals of the linear-attention state */

@@ -215,6 +215,16 @@ __device__ __forceinline__ void async_copy4(const void* gptr, uint32_t lds_base)
                : "memory", "m0");
 }
 
+// The same with a wave-uniform base and 32-bit byte offsets per lane: no address arithmetic on the vector ALU, and the LDS
+// address (first byte lds_base + LDS_OFF) is formed by the instruction that sets M0.
+template <int LDS_OFF>
+__device__ __forceinline__ void async_copy16_at(const void* base, uint32_t lane_bytes, uint32_t lds_base) {
+  asm volatile("s_add_u32 m0, %1, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %3"
+               :
+               : "v"(lane_bytes), "s"(__builtin_amdgcn_readfirstlane(lds_base)), "n"(LDS_OFF), "s"(base)
+               : "memory", "m0", "scc");
+}
+
 __device__ __forceinline__ void wait_async_copies() { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); }
 
 // f(integral_constant<int, 0>{}), ..., f(integral_constant<int, N-1>{}) in order: a loop whose index is a

@@ -52,10 +52,17 @@ struct GScoreArgs {
   float* score;   // [B, Hq, N]
 };
 
+// Element offset of (token or retained row i, column x) in one head's transposed values: tiles of 64 tokens, [i / 64][x][i % 64],
+// so that a tile of the sparse-attention kernel is one run of memory (like its tile of keys) and the lane offsets of its
+// copies are the same for every tile.
+__host__ __device__ inline int64_t value_tile_offset(int i, int x, int d) {
+  return ((int64_t)(i >> 6) * d + x) * 64 + (i & 63);
+}
+
 struct TransposeVArgs {
   const void* v;
   int64_t v_sb, v_st, v_sh;
-  void* vt;       // nullable [B, Hkv, d, Np]
+  void* vt;       // nullable [B, Hkv, Np/64, d, 64], see value_tile_offset()
   void* vfr;      // nullable: the same values in MFMA-fragment order, see vfr_offset()
   int N, Np, Hkv, d, C;
   const int32_t* seq_len;   // nullable, device [B]: see seq_tokens()
@@ -100,7 +107,7 @@ struct GatherArgs {
   int C, lam, rcap;
   const int32_t* seq_len;   // nullable, device [B]: rows of chunks beyond a sequence's full chunks are zero
   void* kret;          // [B, Hq, cap, d]
-  void* vrett;         // [B, Hq, d, cap]
+  void* vrett;         // [B, Hq, cap/64, d, 64], see value_tile_offset()
 };
 
 // Top-lambda lists -> one bit per token of every full chunk (set = kept by the softmax branch, so the token does
@@ -186,9 +193,9 @@ struct SaArgs {
   const void* q;
   const void* k;
   int64_t q_sb, q_st, q_sh, k_sb, k_st, k_sh;
-  const void* vt;      // [B, Hkv, d, Np]
+  const void* vt;      // [B, Hkv, Np/64, d, 64]
   const void* kret;    // [B, Hq, cap, d]
-  const void* vrett;   // [B, Hq, d, cap]
+  const void* vrett;   // [B, Hq, cap/64, d, 64]
   const void* wqt;     // [Hq, df, d]: Wq^T
   const void* bq;      // nullable [Hq, df]
   const void* g;       // nullable gate [B, N, Hq, d]

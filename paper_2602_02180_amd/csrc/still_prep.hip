@@ -1,6 +1,6 @@
 // Layout preparation: pure data movement, no arithmetic of the method.
 //
-//   transpose_v : v [B,N,Hkv,d] -> vt [B,Hkv,d,Np] (tokens contiguous, zero padded to Np), so that
+//   transpose_v : v [B,N,Hkv,d] -> vt [B,Hkv,Np/64,d,64] (tokens contiguous, zero padded to Np), so that
 //                 the value operand of every "contract over tokens" MFMA is k-contiguous; and a second copy
 //                 in MFMA-fragment order for the kernel that loads that operand straight from global memory.
 //   transpose_w : NP-Map weights [Hq,d,df] -> [Hq,df,d] (feature rows, d contiguous), or the same rows in the
@@ -8,7 +8,7 @@
 //   keep_mask   : the Top-lambda lists as one bit per token (what the state scan tests).
 //   gather      : Index(k, M^SA), Index(v, M^SA) of Algorithm 1: the keys of the selected tokens of
 //                 every full chunk, flattened in chunk order, as rows of kret [B,Hq,cap,d]; the values
-//                 transposed into vrett [B,Hq,d,cap].  Rows beyond the selected count are zero.
+//                 transposed into vrett [B,Hq,cap/64,d,64].  Rows beyond the selected count are zero.
 #include "still_kernels.h"
 
 namespace still {
@@ -44,7 +44,7 @@ __global__ __launch_bounds__(256) void transpose_v_kernel(TransposeVArgs a) {
     E* pe = reinterpret_cast<E*>(&pk);
 #pragma unroll
     for (int e = 0; e < EPV; ++e) pe[e] = tile[t0 + e][i];
-    *reinterpret_cast<Vec16*>(vt + (((int64_t)b * a.Hkv + h) * a.d + d0 + i) * a.Np + tok0 + t0) = pk;
+    *reinterpret_cast<Vec16*>(vt + ((int64_t)b * a.Hkv + h) * a.d * a.Np + value_tile_offset(tok0 + t0, d0 + i, a.d)) = pk;
   }
   // second copy in fragment order: consecutive threads write consecutive elements of one (column block, k-step)
   // piece (the 64 tokens of the tile lie in one chunk: C is a multiple of 64)
@@ -163,7 +163,7 @@ __global__ __launch_bounds__(256) void gather_kernel(GatherArgs a) {
     E* pe = reinterpret_cast<E*>(&pk);
 #pragma unroll
     for (int e = 0; e < EPV; ++e) pe[e] = tile[t0 + e][x];
-    *reinterpret_cast<Vec16*>(vrett + (((int64_t)b * a.Hq + hq) * D + x) * a.cap + r0 + t0) = pk;
+    *reinterpret_cast<Vec16*>(vrett + ((int64_t)b * a.Hq + hq) * D * a.cap + value_tile_offset(r0 + t0, x, D)) = pk;
   }
 }
 

@@ -23,7 +23,9 @@
 // Data movement: K tiles (64 keys x d) and V^T tiles (d x 64 keys) go from global memory straight into LDS
 // (global_load_lds, 16 bytes per lane, no staging registers).  Such a load writes lane L's bytes at
 // base + 16 L, so the tiles are unpadded and bank conflicts are avoided by an XOR swizzle of the 16-byte
-// column index, applied on the global-address side when loading and on the LDS-address side when reading.
+// column index, applied on the global-address side when loading and on the LDS-address side when reading.  Tiles of retained
+// keys and of both kinds of values are runs of memory (value_tile_offset), so that one lane offset per kind serves every
+// request of every tile, on top of a scalar base.
 // Software pipeline inside every wave, per iteration i:
 //   request K(i+2), V(i+1)  |  S(i+1) = K(i+1) Q^T on the matrix core  |  softmax of S(i) on the vector ALU
 //   |  O += V(i) P(i)  |  wait for own requests, barrier
@@ -104,10 +106,12 @@ __device__ __forceinline__ void sa_qk(const T* __restrict__ Ks, const typename M
 // MASK: 0 = every key of the tile is visible to every row of the wave, 1 = retained tile with a ragged end,
 //       2 = local tile (window start and causal limit), 3 = retained tile under a bit mask (bit j = key j of the
 //       tile is retained for the wave's chunk: the budget policy that evicts, still_evict.hip)
-template <typename T, int D, int MASK>
+// HAVE_MAX: the caller has taken this lane's maximum already (under the products of the next tile's logits).
+template <typename T, int D, int MASK, bool HAVE_MAX = false>
 __device__ __forceinline__ void sa_softmax_pv(const T* __restrict__ Vs, floatx16 (&st)[2], floatx16 (&o)[D / 32],
                                               float& m_ref, float& lpart, int kb, int ret_w, int lo_w, int t,
-                                              float sc2, int r, int g, unsigned long long bits = 0ull) {
+                                              float sc2, int r, int g, unsigned long long bits = 0ull,
+                                              float tmax_known = 0.f) {
   typedef Mma<T> M;
   typedef SaCfg<T, D> Cf;
   constexpr int DT = D / 32;
@@ -126,11 +130,14 @@ __device__ __forceinline__ void sa_softmax_pv(const T* __restrict__ Vs, floatx16
         st[mt][i] = valid ? st[mt][i] : -INFINITY;
       }
   }
-  float tmax = st[0][0];
+  float tmax = tmax_known;
+  if (!HAVE_MAX) {
+    tmax = st[0][0];
 #pragma unroll
-  for (int i = 1; i < 16; ++i) tmax = fmaxf(tmax, st[0][i]);
+    for (int i = 1; i < 16; ++i) tmax = fmaxf(tmax, st[0][i]);
 #pragma unroll
-  for (int i = 0; i < 16; ++i) tmax = fmaxf(tmax, st[1][i]);
+    for (int i = 0; i < 16; ++i) tmax = fmaxf(tmax, st[1][i]);
+  }
   tmax = max32(tmax);
   const float tm = tmax * sc2;
   if (__any(tm > m_ref + TAU)) {  // wave-uniform; rare once the references have settled
@@ -144,24 +151,56 @@ __device__ __forceinline__ void sa_softmax_pv(const T* __restrict__ Vs, floatx16
     m_ref = m_new;
   }
   const float m_sub = (MASK != 0 && m_ref == -INFINITY) ? 0.f : m_ref;
-#pragma unroll
-  for (int mt = 0; mt < 2; ++mt)
-#pragma unroll
-    for (int i = 0; i < 16; ++i) st[mt][i] = fast_exp2(fmaf(st[mt][i], sc2, -m_sub));
   // O^T += V^T P^T.  The row sums are taken over the ROUNDED operand values (one dot-with-ones per pair on
   // bf16), so that numerator and normaliser see the same weights: a row dominated by one key then returns
   // that key's value exactly, whatever the reference m is.
   float rs = 0.f;
+  if constexpr (M::KPL == 8) {
+    // One k-step (8 keys per lane) at a time: the weights of step ms + 1 are made under the products of step ms (a product
+    // leaves its wave about five vector instructions of room), and the V fragments are read VDEPTH products ahead (the
+    // scheduling barriers pin that order; left alone the compiler reads each one product ahead and waits for it).  With the
+    // maximum taken under the logits' products and the run-of-memory tiles: 32768 tokens, 32 heads, d = 128, 1.50 -> 1.44 ms;
+    // VDEPTH 2, 4 and 6 are equal, 6 spills at d = 64.
+    constexpr int NPV = 2 * SPT * DT, VDEPTH = 4, EPP = 8 / DT;
+    auto a_at = [&](int idx) {
+      const int ms = idx / DT;
+      return M::load(Vs + Cf::voff(32 * (idx % DT) + r, 16 * ms + g * M::KPL));
+    };
+    auto weight = [&](int ms, int e) { return fast_exp2(fmaf(st[ms >> 1][8 * (ms & 1) + e], sc2, -m_sub)); };
+    typename M::frag af[VDEPTH], pf[2];
 #pragma unroll
-  for (int mt = 0; mt < 2; ++mt)
+    for (int i = 0; i < VDEPTH; ++i) af[i] = a_at(i);
+    __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-    for (int s = 0; s < SPT; ++s) {
-      const typename M::frag pf = M::from_acc(st[mt], s);
-      rs = M::sum_into(pf, rs);
-      const int e = 32 * mt + s * M::KK + g * M::KPL;
+    for (int e = 0; e < 8; ++e) pf[0][e] = static_cast<bf16>(weight(0, e));
+    __builtin_amdgcn_sched_barrier(0);
+    static_for<NPV>([&](auto IDX) __attribute__((always_inline)) {
+      constexpr int idx = decltype(IDX)::value, ms = idx / DT, dt = idx % DT;
+      o[dt] = M::mma(af[idx % VDEPTH], pf[ms & 1], o[dt]);
+      if constexpr (idx + VDEPTH < NPV) af[idx % VDEPTH] = a_at(idx + VDEPTH);
+      if constexpr (ms + 1 < 2 * SPT) {
 #pragma unroll
-      for (int dt = 0; dt < DT; ++dt) o[dt] = M::mma(M::load(Vs + Cf::voff(32 * dt + r, e)), pf, o[dt]);
-    }
+        for (int e = 0; e < EPP; ++e) pf[(ms + 1) & 1][EPP * dt + e] = static_cast<bf16>(weight(ms + 1, EPP * dt + e));
+      }
+      if constexpr (dt == DT - 1) rs = M::sum_into(pf[ms & 1], rs);
+      __builtin_amdgcn_sched_barrier(0);
+    });
+  } else {
+#pragma unroll
+    for (int mt = 0; mt < 2; ++mt)
+#pragma unroll
+      for (int i = 0; i < 16; ++i) st[mt][i] = fast_exp2(fmaf(st[mt][i], sc2, -m_sub));
+#pragma unroll
+    for (int mt = 0; mt < 2; ++mt)
+#pragma unroll
+      for (int s = 0; s < SPT; ++s) {
+        const typename M::frag pf = M::from_acc(st[mt], s);
+        rs = M::sum_into(pf, rs);
+        const int e = 32 * mt + s * M::KK + g * M::KPL;
+#pragma unroll
+        for (int dt = 0; dt < DT; ++dt) o[dt] = M::mma(M::load(Vs + Cf::voff(32 * dt + r, e)), pf, o[dt]);
+      }
+  }
   lpart += rs;
 }
 
@@ -249,61 +288,59 @@ __device__ __forceinline__ void sa_body(const SaArgs& a) {
     lrow = v / Cf::VVR;
     col = ((v % Cf::VVR) ^ Cf::vswz(lrow)) * Cf::EPV;
   };
-  uint32_t k_off_ret[Cf::K_INSTR], v_off_ret[Cf::V_INSTR];
-#pragma unroll
-  for (int j = 0; j < Cf::K_INSTR; ++j) {
-    int key, col;
-    k_lane(lane, j, key, col);
-    k_off_ret[j] = (uint32_t)(key * D + col);
+  // Tiles of retained keys, of values (both kinds) and of W_q^T are runs of memory, and a wave's request j lies 16 NW lanes'
+  // bytes behind its request j - 1, in the tile as in LDS: a multiple of 16 rows (same row order, same swizzle), or, for
+  // the rows of 512 bytes of fp32 at d = 128, 8 rows (bit 3 of the swizzle alternates).
+  constexpr int STEP = Cf::NW * 1024, KROWS = STEP / (D * (int)sizeof(T));
+  static_assert(STEP % (16 * BN * (int)sizeof(T)) == 0 && (KROWS % 16 == 0 || KROWS == 8), "see above");
+  auto k_at = [&](uint32_t off, int j) __attribute__((always_inline)) {
+    return (KROWS == 8 && (j & 1) ? off ^ 128u : off) + (uint32_t)(j * STEP);
+  };
+  uint32_t k_off, v_off;      // bytes
+  {
+    int key, row, col;
+    k_lane(lane, 0, key, col);
+    k_off = (uint32_t)(key * D + col) * (uint32_t)sizeof(T);
+    v_lane(lane, 0, row, col);
+    v_off = (uint32_t)(row * BN + col) * (uint32_t)sizeof(T);
   }
-#pragma unroll
-  for (int j = 0; j < Cf::V_INSTR; ++j) {
-    int lrow, col;
-    v_lane(lane, j, lrow, col);
-    v_off_ret[j] = (uint32_t)(lrow * a.cap + col);
-  }
+  const uint32_t lds_k = lds_address(smem) + wave_s * 1024;               // this wave's first piece of K slot 0
+  const uint32_t lds_v = lds_k + 2 * Cf::K_ELEMS * (uint32_t)sizeof(T);
+  auto copy_k = [&](const T* base, uint32_t dst) __attribute__((always_inline)) {
+    static_for<Cf::K_INSTR>([&](auto J) __attribute__((always_inline)) {
+      constexpr int j = decltype(J)::value;
+      async_copy16_at<j * STEP>(base, k_at(k_off, j), dst);
+    });
+  };
 
   auto tile_kb = [&](int ti) { return ti < n_ret_tiles ? ti * BN : loc_lo + (ti - n_ret_tiles) * BN; };
 
   auto request_k = [&](int ti) {
     const int kb = tile_kb(ti);
-    T* dst = Kl + (ti & 1) * Cf::K_ELEMS + wave_s * 64 * Cf::EPV;
+    const uint32_t dst = lds_k + (ti & 1) * Cf::K_ELEMS * (uint32_t)sizeof(T);
     if (ti < n_ret_tiles) {
-      const T* base = kret + (int64_t)kb * D;
-#pragma unroll
-      for (int j = 0; j < Cf::K_INSTR; ++j)
-        async_copy16(base + k_off_ret[j], lds_address(dst + Cf::NW * j * 64 * Cf::EPV));
+      copy_k(kret + (int64_t)kb * D, dst);
     } else {
       // rows past the end of a ragged sequence re-read the last token (masked later)
       const int lane_now = fresh_lane_id();
-#pragma unroll
-      for (int j = 0; j < Cf::K_INSTR; ++j) {
+      static_for<Cf::K_INSTR>([&](auto J) __attribute__((always_inline)) {
+        constexpr int j = decltype(J)::value;
         int key, col;
         k_lane(lane_now, j, key, col);
         int tok = kb + key;
         tok = tok < N ? tok : N - 1;
-        async_copy16(kloc + ((int64_t)tok * kst + col), lds_address(dst + Cf::NW * j * 64 * Cf::EPV));
-      }
+        async_copy16(kloc + ((int64_t)tok * kst + col), dst + j * STEP);
+      });
     }
   };
   auto request_v = [&](int ti) {
     const int kb = tile_kb(ti);
-    T* dst = Vl + (ti & 1) * Cf::V_ELEMS + wave_s * 64 * Cf::EPV;
-    if (ti < n_ret_tiles) {
-      const T* base = vrett + kb;
-#pragma unroll
-      for (int j = 0; j < Cf::V_INSTR; ++j)
-        async_copy16(base + v_off_ret[j], lds_address(dst + Cf::NW * j * 64 * Cf::EPV));
-    } else {
-      const T* base = vtl + kb;
-      const int lane_now = fresh_lane_id();
-#pragma unroll
-      for (int j = 0; j < Cf::V_INSTR; ++j) {
-        int lrow, col;
-        v_lane(lane_now, j, lrow, col);
-        async_copy16(base + ((int64_t)lrow * a.Np + col), lds_address(dst + Cf::NW * j * 64 * Cf::EPV));
-      }
-    }
+    const T* base = (ti < n_ret_tiles ? vrett : vtl) + (int64_t)kb * D;
+    const uint32_t dst = lds_v + (ti & 1) * Cf::V_ELEMS * (uint32_t)sizeof(T);
+    static_for<Cf::V_INSTR>([&](auto J) __attribute__((always_inline)) {
+      constexpr int j = decltype(J)::value;
+      async_copy16_at<j * STEP>(base, v_off + j * STEP, dst);
+    });
   };
   // wave-uniform: does this wave use tile ti, and with which mask variant
   auto tile_mode = [&](int ti) -> int {   // -1 = skip
@@ -349,11 +386,7 @@ __device__ __forceinline__ void sa_body(const SaArgs& a) {
       const bool mine = wave_active && cw >= 2;                          // this wave has linear terms
       const T* wq_h = static_cast<const T*>(a.wqt) + (int64_t)hq * DF * D;
       auto request_w = [&](int wt, T* slot) {       // W_q^T rows [64 wt, +64): laid out like a tile of retained keys
-        const T* base = wq_h + (int64_t)wt * 64 * D;
-        T* dst = slot + wave_s * 64 * Cf::EPV;
-#pragma unroll
-        for (int j = 0; j < Cf::K_INSTR; ++j)
-          async_copy16(base + k_off_ret[j], lds_address(dst + Cf::NW * j * 64 * Cf::EPV));
+        copy_k(wq_h + (int64_t)wt * 64 * D, lds_address(slot) + wave_s * 1024);
       };
       // columns [64 jt, +64) of a state image: like a V^T tile
       auto request_t = [&](const T* img, int jt, T* slot) {
@@ -645,22 +678,24 @@ __device__ __forceinline__ void sa_body(const SaArgs& a) {
   // may leave this loop at different tiles: both loops execute exactly one barrier per tile.
   auto steady_step = [&](int ti, floatx16 (&st_cur)[2], floatx16 (&st_next)[2]) __attribute__((always_inline)) {
     const T* kbase = kret + (int64_t)(ti + 2) * BN * D;
-    const T* vbase = vrett + (ti + 1) * BN;
-    T* kdst = Kl + (ti & 1) * Cf::K_ELEMS + wave_s * 64 * Cf::EPV;
-    T* vdst = Vl + ((ti + 1) & 1) * Cf::V_ELEMS + wave_s * 64 * Cf::EPV;
-    constexpr int NC = Cf::K_INSTR + Cf::V_INSTR, NP = 2 * KS;
+    const T* vbase = vrett + (int64_t)(ti + 1) * BN * D;
+    const uint32_t kdst = lds_k + (ti & 1) * Cf::K_ELEMS * (uint32_t)sizeof(T);
+    const uint32_t vdst = lds_v + ((ti + 1) & 1) * Cf::V_ELEMS * (uint32_t)sizeof(T);
+    constexpr int NC = Cf::K_INSTR + Cf::V_INSTR, NP = 2 * KS, MPP = 32 / NP;
+    float tmax = st_cur[0][0];
     auto issue = [&](auto IDX) __attribute__((always_inline)) {
       constexpr int idx = decltype(IDX)::value;
       static_for<NC>([&](auto CC) __attribute__((always_inline)) {
-        constexpr int c = decltype(CC)::value;
+        constexpr int c = decltype(CC)::value, j = c < Cf::K_INSTR ? c : c - Cf::K_INSTR;
         if constexpr ((c * NP) / NC == idx) {   // request c follows product floor(c NP / NC)
-          if constexpr (c < Cf::K_INSTR)
-            async_copy16(kbase + k_off_ret[c], lds_address(kdst + Cf::NW * c * 64 * Cf::EPV));
-          else
-            async_copy16(vbase + v_off_ret[c - Cf::K_INSTR],
-                         lds_address(vdst + Cf::NW * (c - Cf::K_INSTR) * 64 * Cf::EPV));
+          if constexpr (c < Cf::K_INSTR) async_copy16_at<j * STEP>(kbase, k_at(k_off, j), kdst);
+          else async_copy16_at<j * STEP>(vbase, v_off + j * STEP, vdst);
         }
       });
+      if constexpr (!EV && MPP > 0) {           // the current tile's maximum, under the products
+#pragma unroll
+        for (int i = MPP * idx; i < MPP * (idx + 1); ++i) tmax = fmaxf(tmax, st_cur[i >> 4][i & 15]);
+      }
     };
     sa_qk<T, D>(Kl + ((ti + 1) & 1) * Cf::K_ELEMS, qf, st_next, r, g, issue);
     if constexpr (EV) {   // every offer of the tile exists for this wave; which of them are retained is in the mask
@@ -669,7 +704,8 @@ __device__ __forceinline__ void sa_body(const SaArgs& a) {
         sa_softmax_pv<T, D, 3>(Vl + (ti & 1) * Cf::V_ELEMS, st_cur, o, m_ref, lpart, ti * BN, ret_w, lo_w, t, sc2, r, g,
                                bits);
     } else {
-      sa_softmax_pv<T, D, 0>(Vl + (ti & 1) * Cf::V_ELEMS, st_cur, o, m_ref, lpart, ti * BN, ret_w, lo_w, t, sc2, r, g);
+      sa_softmax_pv<T, D, 0, (MPP > 0)>(Vl + (ti & 1) * Cf::V_ELEMS, st_cur, o, m_ref, lpart, ti * BN, ret_w, lo_w, t, sc2,
+                                        r, g, 0ull, tmax);
     }
     wait_async_copies();
     lds_barrier();
@@ -743,8 +779,11 @@ __device__ __forceinline__ void sa_body(const SaArgs& a) {
   }
 }
 
+// Three workgroups per CU at d = 64 (bf16, 168 registers): a workgroup spends over a third of its time in latencies (prologue,
+// waits for tiles) that only another one can fill; 4 x 4096 tokens, 32 heads: 229 -> 188 us.  d = 128 needs 236 registers
+// (two), and so does the eviction variant at d = 64 (24 values spill at 168).
 template <typename T, int D, bool EV>
-__global__ __launch_bounds__(kSaRows * 2, kSaRows == 128 ? 2 : 1) void sa_kernel(SaArgs a) {
+__global__ __launch_bounds__(kSaRows * 2, (sizeof(T) == 2 && D == 64 && !EV) ? 3 : 2) void sa_kernel(SaArgs a) {
   sa_body<T, D, EV>(a);
 }
 
