@@ -126,7 +126,8 @@ typedef struct still_ws_layout {
   size_t wkf;      /* dtype   [Hq, d_f * d]                      Wk transposed, in matrix-operand order    */
   size_t seg;      /* float   [B, Hq, nseg, 2*d_f*(d+1)]         per-segment totals of the linear-attention state */
   size_t snap;     /* dtype   [B, Hq, ceil(N/C), d, 2*d_f]       S^T summed inside chunk c's segment, through chunk c-2,
-                      in blocks of 32 rows by 16 features: [d/32][2*d_f/16][32][16]                        */
+                      in blocks of 32 rows by 16 features, [d/32][2*d_f/16], inside a block [2][32][8]: features by
+                      eight, rows, with bit 2 of the row flipped in the second half                        */
   size_t zsnap;    /* float   [B, Hq, ceil(N/C), 2*d_f]          z likewise                                */
   size_t pimg;     /* dtype   [B, Hq, nseg, d, 2*d_f]            S^T through the chunk before the segment (prefix), in blocks */
   size_t zpre;     /* float   [B, Hq, nseg, 2*d_f]               z likewise                                */

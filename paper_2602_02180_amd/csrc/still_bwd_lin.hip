@@ -103,7 +103,7 @@ __global__ __launch_bounds__(256, 2) void bwd_lin_kernel(BwdLinArgs a) {
   typedef Mma<T> M;
   typedef LinCfg<T, D> Cf;
   typedef RowTile<T, D> RX;              // token tiles
-  typedef RowTile<T, 64> RS;             // state slabs
+  typedef StateSlab<T> RS;               // state slabs
   typedef RowTile<T, Cf::DP> RP;         // features of the tokens
   constexpr int DP = Cf::DP, NS = Cf::NS, NF = NS / 2, KS = D / M::KK, SK = 64 / M::KK, NX = D / 64, EPV = RX::EPV;
   static_assert(KS == SK * NX, "a slab's two products have the same number of steps");
@@ -243,16 +243,13 @@ __global__ __launch_bounds__(256, 2) void bwd_lin_kernel(BwdLinArgs a) {
       nx2 = sum32((n4[0] + n4[1]) + (n4[2] + n4[3]));
     }
     lds_barrier();                       // every wave has its fragments: the slabs may be overwritten
-    // (piece j of a wave lies 4 RPI rows, a divisor of 32, behind piece j - 1: the lane's part of the offset and the
-    // swizzle are the same for all of them)
+    // (a slab is a copy of whole blocks: 1 KB pieces, one after the other)
     auto request = [&](const T* im, int f0, T* dst) __attribute__((always_inline)) {
-      constexpr int INSTR = Cf::SE * (int)sizeof(T) / 1024 / 4, RPI = 64 / RS::PPR;
-      static_assert(32 % (4 * RPI) == 0, "no carry between a lane's row and its piece's");
-      const int lane_now = fresh_lane_id(), sr = RPI * wave + lane_now / RS::PPR;
-      const T* src = im + state_image_offset(0, f0, DP) + state_image_offset(sr, ((lane_now % RS::PPR) ^ RS::swz(sr)) * EPV, DP);
-#pragma unroll
-      for (int j = 0; j < INSTR; ++j)
-        async_copy16(src + state_image_offset(4 * RPI * j, 0, DP), lds_address(dst + (wave + 4 * j) * 64 * EPV));
+      const uint32_t lane_off = 16u * (uint32_t)fresh_lane_id(), base = lds_address(dst) + 1024 * wave;
+      static_for<Cf::SE * (int)sizeof(T) / 4096>([&](auto J) __attribute__((always_inline)) {
+        constexpr int j = decltype(J)::value;
+        async_copy16_at<4096 * j>(im + state_slab_source((wave + 4 * j) * 64 * EPV, f0, DP), lane_off, base);
+      });
     };
     request(img0, 0, slab0);
 
@@ -349,7 +346,7 @@ __global__ __launch_bounds__(256, 2) void bwd_lin_kernel(BwdLinArgs a) {
               [&](auto I) __attribute__((always_inline)) {
                 constexpr int i = decltype(I)::value, q = i >> 1;
                 if constexpr ((i & 1) == 0) return RS::down(cur, q * M::KK, 32 * fh, lane_now);
-                else return RS::along(cur, 32 * (fh * NX + q % NX) + rr, q / NX, gg);
+                else return RS::along(cur, fh * NX + q % NX, q / NX, rr, gg);
               },
               [&](auto I, const typename M::frag& f) __attribute__((always_inline)) {
                 constexpr int i = decltype(I)::value, q = i >> 1;

@@ -119,12 +119,19 @@ struct KeepMaskArgs {
   int Hq, ncf, C, lam, rcap;
 };
 
-// Element offset of (x, feature) in a state image S^T [d][2 d_f]: blocks of 32 rows x by 16 features, [x / 32][f / 16][x % 32]
-// [f % 16].  An accumulator tile's store then covers 1 KB of one block instead of 32 bytes in each of 32 rows, and a
-// consumer's piece of 8 rows by 64 features is four runs of 256 bytes.  (Row-major, the scan of 2 x 8192 tokens, 32 heads,
-// d = 128, C = 64, took 180 us; with this order 139; 97 if it stored no images at all.)
+// Element offset of (x, feature) in a state image S^T [d][2 d_f]: blocks of 32 rows x by 16 features, [x / 32][f / 16], and
+// inside a block the order of an MFMA operand over features: [f / 8][x % 32, bit 2 flipped in the second half][f % 8].  An
+// accumulator tile's store covers 1 KB of one block, and a consumer's copy into LDS takes a block as it stands, 64 lanes
+// on 1 KB: blocks of [x % 32][f % 16] that the copy had to spread over rows cost its wave about 300 cycles per KB, a copy of
+// a run 70.  In LDS a block is then read both ways without bank conflicts (the flip is for the transposing reads).
 __host__ __device__ inline int state_image_offset(int x, int f, int DP) {
-  return ((x >> 5) * (DP >> 4) + (f >> 4)) * 512 + (x & 31) * 16 + (f & 15);
+  const int h = (f >> 3) & 1;
+  return ((x >> 5) * (DP >> 4) + (f >> 4)) * 512 + h * 256 + ((x & 31) ^ (h << 2)) * 8 + (f & 7);
+}
+// The piece of an image that a slab of 64 features holds in LDS: [x / 32][f / 16 of 4], blocks as in the image.  Element i of
+// the slab that starts at feature f0 lies here in the image.
+__host__ __device__ inline int state_slab_source(int i, int f0, int DP) {
+  return (i >> 11) * (DP >> 4) * 512 + (f0 >> 4) * 512 + (i & 2047);
 }
 
 struct LaArgs {

@@ -388,17 +388,13 @@ __device__ __forceinline__ void sa_body(const SaArgs& a) {
       auto request_w = [&](int wt, T* slot) {       // W_q^T rows [64 wt, +64): laid out like a tile of retained keys
         copy_k(wq_h + (int64_t)wt * 64 * D, lds_address(slot) + wave_s * 1024);
       };
-      // columns [64 jt, +64) of a state image: like a V^T tile
-      auto request_t = [&](const T* img, int jt, T* slot) {
-        const T* base = img + state_image_offset(0, 64 * jt, DP);
-        T* dst = slot + wave_s * 64 * Cf::EPV;
-        const int lane_now = fresh_lane_id();
-#pragma unroll
-        for (int j = 0; j < Cf::V_INSTR; ++j) {
-          int lrow, col;
-          v_lane(lane_now, j, lrow, col);
-          async_copy16(base + state_image_offset(lrow, col, DP), lds_address(dst + Cf::NW * j * 64 * Cf::EPV));
-        }
+      // columns [64 jt, +64) of a state image: whole blocks (state_image_offset)
+      auto request_t = [&](const T* img, int jt, T* slot) __attribute__((always_inline)) {
+        const uint32_t lane_off = 16u * (uint32_t)fresh_lane_id(), dst = lds_address(slot) + wave_s * 1024;
+        static_for<Cf::V_INSTR>([&](auto J) __attribute__((always_inline)) {
+          constexpr int j = decltype(J)::value;
+          async_copy16_at<j * STEP>(img + state_slab_source((wave_s + Cf::NW * j) * 64 * Cf::EPV, 64 * jt, DP), lane_off, dst);
+        });
       };
       // The state through chunk cc-2 is the sum of two images: the running sums of cc's own segment (operand 0;
       // empty for the first chunk of a segment) and the prefix of that segment (operand 1; empty in segment 0).
@@ -543,6 +539,7 @@ __device__ __forceinline__ void sa_body(const SaArgs& a) {
         dla = sum32((dp4[0] + dp4[1]) + (dp4[2] + dp4[3])) * ip + sum32((dn4[0] + dn4[1]) + (dn4[2] + dn4[3])) * in;
       }
 
+
       // "S^T tile x phi_q^T" into the accumulator, tile jt from its slot (a wave joins only for its own chunk).  The
       // S^T fragments are read PDEPTH products ahead of their use (the scheduling barriers pin that order).
       auto la_pv = [&](int jt_c, const T* Vs) __attribute__((always_inline)) {
@@ -554,7 +551,7 @@ __device__ __forceinline__ void sa_body(const SaArgs& a) {
             constexpr int PDEPTH = NPV < 8 ? NPV : 8;
             auto a_at = [&](int idx) {
               const int ms = idx / DT;
-              return M::load(Vs + Cf::voff(32 * (idx % DT) + r, 32 * (ms / SPT) + (ms % SPT) * M::KK + g * M::KPL));
+              return M::load(Vs + (idx % DT) * 2048 + state_image_offset(r, 32 * (ms / SPT) + (ms % SPT) * M::KK + g * M::KPL, 64));
             };
             typename M::frag af[PDEPTH];
 #pragma unroll

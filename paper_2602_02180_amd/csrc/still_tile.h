@@ -10,7 +10,7 @@
 // conflicts: sixteen consecutive rows at one piece index fall on sixteen different pieces of the 256-byte bank
 // width, and so do four consecutive rows at four consecutive pieces.
 #pragma once
-#include "still_common.h"
+#include "still_kernels.h"
 
 namespace still {
 
@@ -46,6 +46,34 @@ struct RowTile {
       } u;
       u.h[0] = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_shortx4*)(tile + off(row, col)));
       u.h[1] = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_shortx4*)(tile + off(row + 4, col)));
+      return u.f;
+    } else {
+      return tile[off(k0 + (lane >> 5), c0 + M::kappa(lane & 31))];
+    }
+  }
+};
+
+// A slab of 64 features of a state image in LDS (state_image_offset: blocks of 32 rows x by 16 features in operand order), read
+// over its features (rows 32 xb ..) or, transposing, over its rows x (columns = features).
+template <typename T>
+struct StateSlab {
+  typedef Mma<T> M;
+  static __device__ __forceinline__ int off(int x, int f) { return state_image_offset(x, f, 64); }
+  static __device__ __forceinline__ typename M::frag along(const T* tile, int xb, int s, int r, int g) {
+    return M::load(tile + xb * 2048 + off(r, s * M::KK + g * M::KPL));
+  }
+  static __device__ __forceinline__ typename M::frag down(const T* tile, int k0, int c0, int lane) {
+    if constexpr (sizeof(T) == 2) {
+      const int g = lane >> 5, j = (lane >> 2) & 3, b = lane & 3;
+      const int col = 16 * ((lane >> 4) & 1) + 4 * (((b & 1) << 1) | (b >> 1));   // kappa swaps bits 2 and 3
+      const T* base = tile + state_image_offset(k0, c0, 64) + state_image_offset(8 * g + j, col, 64);
+      union {
+        shortx4 h[2];
+        typename M::frag f;
+      } u;
+      // (rows k0 + 8 g + j and + 4: bit 2 of the row is the second read's and the swizzle's, so the offset changes sign)
+      u.h[0] = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_shortx4*)base);
+      u.h[1] = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_shortx4*)(base + ((col >> 3) & 1 ? -32 : 32)));
       return u.f;
     } else {
       return tile[off(k0 + (lane >> 5), c0 + M::kappa(lane & 31))];
