@@ -597,27 +597,40 @@ __device__ __forceinline__ void sa_body(const SaArgs& a) {
       if (mine) {
         la_done = true;
         const int tq = t < N ? t : N - 1;
+        // four consecutive columns per register quad; all gate loads first (one round trip, not one per quad)
+        if (a.g != nullptr) {
+          typedef T Quad __attribute__((ext_vector_type(4)));
+          const T* gp = static_cast<const T*>(a.g) + (int64_t)b * a.g_sb + (int64_t)tq * a.g_st + (int64_t)hq * a.g_sh + 4 * g;
+          Quad gv[DT][4];
 #pragma unroll
-        for (int dt = 0; dt < DT; ++dt)
+          for (int dt = 0; dt < DT; ++dt)
 #pragma unroll
-          for (int i4 = 0; i4 < 4; ++i4) {
-            const int x0 = 32 * dt + 8 * i4 + 4 * g;     // four consecutive columns per register quad
-            float gv[4] = {1.f, 1.f, 1.f, 1.f};
-            if (a.g != nullptr) {
-              const T* gp = static_cast<const T*>(a.g) + (int64_t)b * a.g_sb + (int64_t)tq * a.g_st +
-                            (int64_t)hq * a.g_sh + x0;
+            for (int i4 = 0; i4 < 4; ++i4) gv[dt][i4] = *reinterpret_cast<const Quad*>(gp + 32 * dt + 8 * i4);
+          const bool act = a.gate_act != 0;
 #pragma unroll
-              for (int e = 0; e < 4; ++e) gv[e] = a.gate_act ? fast_sigmoid(to_f32(gp[e])) : to_f32(gp[e]);
+          for (int dt = 0; dt < DT; ++dt)
+#pragma unroll
+            for (int i = 0; i < 16; ++i) {
+              const float x = to_f32(gv[dt][i >> 2][i & 3]);
+              o[dt][i] *= in * (act ? fast_sigmoid(x) : x);
             }
+        } else {
 #pragma unroll
-            for (int e = 0; e < 4; ++e) o[dt][4 * i4 + e] *= in * gv[e];
-            if (a.n_la_out != nullptr && t < N) {
+          for (int dt = 0; dt < DT; ++dt)
+#pragma unroll
+            for (int i = 0; i < 16; ++i) o[dt][i] *= in;
+        }
+        if (a.n_la_out != nullptr && t < N) {
+#pragma unroll
+          for (int dt = 0; dt < DT; ++dt)
+#pragma unroll
+            for (int i4 = 0; i4 < 4; ++i4) {
               floatx4 nv;
 #pragma unroll
               for (int e = 0; e < 4; ++e) nv[e] = o[dt][4 * i4 + e];
-              *reinterpret_cast<floatx4*>(a.n_la_out + (unit * a.N + t) * D + x0) = nv;
+              *reinterpret_cast<floatx4*>(a.n_la_out + (unit * a.N + t) * D + 32 * dt + 8 * i4 + 4 * g) = nv;
             }
-          }
+        }
         if (a.d_la_out != nullptr && t < N && g == 0) a.d_la_out[unit * a.N + t] = dla;
         // one more "key": logit 0, weight D_LA, value N_LA / D_LA (an all-kept context has D_LA = 0: no such key)
         if (dla > 0.f) {
