@@ -11,6 +11,7 @@ struct ScoreArgs {
   int64_t q_sb, q_st, q_sh, k_sb, k_st, k_sh;
   HeadMap map;
   int N, C, W, lam, Hq, ncf;
+  int pass_tiles; // (set by the launch) band tiles that pass through LDS at a time
   int rcap;       // budget on the retained tokens of one (batch, head): see chunk_quota()
   float scale, eps;
   float* score;   // [B, Hq, N]

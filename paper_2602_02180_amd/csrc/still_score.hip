@@ -66,10 +66,8 @@ __global__ __launch_bounds__(256, NT > 5 ? 2 : 3) void score_select_kernel(Score
   // direct-to-LDS copies of whole 1 KB pieces (the 16-byte column index is XOR-ed with the row so that the
   // operand reads meet no bank conflicts); every wave then takes the tiles of the pass that belong to its band.
   constexpr int EPV = 16 / (int)sizeof(T), KVR = D / EPV;                // elements / vectors per K row
-  constexpr int PT_MAX = 32768 / (32 * D * (int)sizeof(T));              // tiles in 32 KB
-  const int NW = C / 32, NB = NT - 1 + NW;
-  constexpr int PT = PT_MAX < 8 ? PT_MAX : 8;
-  __shared__ __attribute__((aligned(16))) unsigned char s_kraw[PT * 32 * D * sizeof(T)];
+  const int NW = C / 32, NB = NT - 1 + NW, PT = a.pass_tiles;            // (PT tiles are what the launch has LDS for)
+  extern __shared__ __attribute__((aligned(16))) unsigned char s_kraw[];
   T* s_k = reinterpret_cast<T*>(s_kraw);
   auto swz = [](int row) { return KVR == 8 ? ((row >> 1) & 7) : (row & 15); };
   const T* kbase = k + (int64_t)b * a.k_sb + (int64_t)kvh * a.k_sh;
@@ -276,15 +274,26 @@ hipError_t launch_group_select(const ScoreArgs& a, int B, int Hkv, hipStream_t s
   return hipGetLastError();
 }
 
+// Band tiles per pass: as few passes as 32 KB of LDS allow, and no more LDS than these passes need.  A chunk of 64 tokens is a
+// workgroup of two waves, and with 32 KB for each four of them fit a CU where the registers allow six (d = 128) to ten
+// (d = 64).  4 x 4096 tokens, d = 64, W = 64: 65 -> 51 us; 2 x 8192 tokens, d = 128, W = 128: 118 -> 103 us.
+template <typename T, int D, int NT>
+static void launch_score_nt(ScoreArgs a, int B, int nc, hipStream_t stream) {
+  constexpr int tile_bytes = 32 * D * (int)sizeof(T), most = 32768 / tile_bytes;
+  const int band = NT - 1 + a.C / 32, passes = (band + most - 1) / most;
+  a.pass_tiles = (band + passes - 1) / passes;
+  dim3 grid(nc * a.Hq, 1, B), block((a.C / 32) * 64);
+  hipLaunchKernelGGL((score_select_kernel<T, D, NT>), grid, block, (size_t)a.pass_tiles * tile_bytes, stream, a);
+}
+
 template <typename T, int D>
 static hipError_t launch_score_t(const ScoreArgs& a, int B, int nc, hipStream_t stream) {
-  dim3 grid(nc * a.Hq, 1, B), block((a.C / 32) * 64);
   if (a.W <= 64)   // the band must be at least 32 keys longer than the window less one: W <= 32 (NT - 1)
-    hipLaunchKernelGGL((score_select_kernel<T, D, 3>), grid, block, 0, stream, a);
+    launch_score_nt<T, D, 3>(a, B, nc, stream);
   else if (a.W <= 128)
-    hipLaunchKernelGGL((score_select_kernel<T, D, 5>), grid, block, 0, stream, a);
+    launch_score_nt<T, D, 5>(a, B, nc, stream);
   else             // up to 256 keys: nine band tiles (two workgroups per CU: 144 accumulator registers)
-    hipLaunchKernelGGL((score_select_kernel<T, D, 9>), grid, block, 0, stream, a);
+    launch_score_nt<T, D, 9>(a, B, nc, stream);
   return hipGetLastError();
 }
 
