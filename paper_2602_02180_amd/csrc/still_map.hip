@@ -13,7 +13,9 @@
 // registers and f, u, dphi and df stay on the chip.
 // Measured at 4 sequences of 1024 tokens, 32 / 8 heads, d = 128, C = 64, bf16 (forward call included): as batched products
 // through memory, with w as a matrix of its own and the operands fetched 32 cache lines per instruction, 2.95 ms; now 1.12
-// ms (features 0.06 twice, map 0.21: 2.6 TB/s of stores, query side 0.34, key side 0.21, parameter gradients 0.07).
+// ms, and 0.91 with no choice per entry and no wait inside the loops' loads (features 0.06 twice; map 0.21 -> 0.19: 2.8 TB/s
+// of stores; query side 0.34 -> 0.24, a third of it the row sums, which read map and gradient at 6 TB/s; key side 0.21 -> 0.125;
+// parameter gradients 0.07).  What is left there is one tile in flight per workgroup and the features' trips through memory.
 #include "still_kernels.h"
 #include "still_tile.h"
 
@@ -46,6 +48,22 @@ __device__ __forceinline__ void request_rows(const T* base, int64_t stride, int 
     const int col = ((piece % RT::PPR) ^ RT::swz(row)) * RT::EPV;
     async_copy16(base + (int64_t)min(row0 + row, n - 1) * stride + col, lds_address(tile + (wave + 4 * j) * 64 * RT::EPV));
   }
+}
+
+// The same for 64 rows that exist and lie one behind the other: a wave's copies are 4 KB apart in memory as in LDS, so one lane
+// offset on a scalar base serves them all (8 rows on, bit 1 of the swizzle alternates).
+template <typename T, int W>
+__device__ __forceinline__ void request_run(const T* base, T* tile, int wave) {
+  typedef RowTile<T, W> RT;
+  constexpr int ROWS = 256 / RT::PPR;
+  static_assert(ROWS == 8 || ROWS == 16, "whole periods of the swizzle, or half of one");
+  const int piece = wave * 64 + fresh_lane_id(), row = piece / RT::PPR;
+  const uint32_t off = (uint32_t)row * (W * sizeof(T)) + 16u * ((piece % RT::PPR) ^ RT::swz(row));
+  const uint32_t dst = lds_address(tile) + 1024 * wave;
+  static_for<64 * W * (int)sizeof(T) / 4096>([&](auto J) __attribute__((always_inline)) {
+    constexpr int j = decltype(J)::value;
+    async_copy16_at<4096 * j>(base, (ROWS == 8 && (j & 1) ? off ^ 32u : off) + 4096 * j, dst);
+  });
 }
 
 // The NP-Map of 64 tokens whose rows are in LDS: wave (rg, fh) has the features 64 j + 32 fh + (0..31) of the tokens
@@ -229,9 +247,11 @@ __global__ __launch_bounds__(256, 2) void attn_map_kernel(MapArgs a) {
 #pragma unroll
     for (int s = 0; s < KP; ++s) pf[s] = M::load(pq + s * M::KK);
   }
-  float l2[16];                          // L_t log2 e of the lane's rows
+  float l2[16], el[16];                  // L_t log2 e and E_t of the lane's rows
 #pragma unroll
   for (int i = 0; i < 16; ++i) l2[i] = a.lse[unit * N + min(r0 + 32 * rg + c_row(i, g), N - 1)] * kLog2e;
+#pragma unroll
+  for (int i = 0; i < 16; ++i) el[i] = fast_exp2(-l2[i]);
   const float sc2 = a.scale * kLog2e;
 #pragma unroll 1
   for (int kt = 0; kt <= rt; ++kt) {
@@ -239,7 +259,7 @@ __global__ __launch_bounds__(256, 2) void attn_map_kernel(MapArgs a) {
     const bool far = cj <= c - 2;        // (chunks <= c-2 are full chunks)
     lds_barrier();                       // everybody is done with the previous tile
     request_rows<T, D>(kb, a.k_st, k0, N, Kl, wave);
-    if (far) request_rows<T, 2 * D>(pk, 2 * D, k0, N, Pl, wave);
+    if (far) request_run<T, 2 * D>(pk + (int64_t)k0 * (2 * D), Pl, wave);
     wait_async_copies();
     lds_barrier();
     const int lane_now = fresh_lane_id(), rr = lane_now & 31, gg = lane_now >> 5;
@@ -253,11 +273,23 @@ __global__ __launch_bounds__(256, 2) void attn_map_kernel(MapArgs a) {
                                      [&](auto I, const typename M::frag& f) __attribute__((always_inline)) { w = M::mma(pf[decltype(I)::value], f, w); });
       kept = kept_token(a.kmask, unit, a.ncf, C, cj, j);
     }
+    // (whole tiles below the diagonal are stored without a test per entry)
+    const bool inner = kt < rt && r0 + 64 <= N;
+    float* op = out + (int64_t)(r0 + 32 * rg + 4 * gg) * N + j;          // row c_row(i, gg) lies 8 (i / 4) + i % 4 rows on
 #pragma unroll
     for (int i = 0; i < 16; ++i) {
-      const int t = r0 + 32 * rg + c_row(i, gg);
-      const float val = kept ? fast_exp2(fmaf(s[i], sc2, -l2[i])) : fast_exp2(-l2[i]) * w[i];
-      if (t < N && j < N) out[(int64_t)t * N + j] = j <= t ? val : 0.f;
+      const float own = fast_exp2(fmaf(s[i], sc2, -l2[i])), lin = el[i] * w[i];
+      s[i] = kept ? own : lin;
+    }
+    if (inner) {
+#pragma unroll
+      for (int i = 0; i < 16; ++i) op[(int64_t)(8 * (i / 4) + i % 4) * N] = s[i];
+    } else {
+#pragma unroll
+      for (int i = 0; i < 16; ++i) {
+        const int t = r0 + 32 * rg + c_row(i, gg);
+        if (t < N && j < N) op[(int64_t)(8 * (i / 4) + i % 4) * N] = j <= t ? s[i] : 0.f;
+      }
     }
   }
   const int z0 = r0 + 64, zn = N - z0;
@@ -284,7 +316,7 @@ __global__ __launch_bounds__(256, 2) void map_bwd_kernel(MapArgs a) {
   T* phi = reinterpret_cast<T*>(smem);   // two tiles of the other side's features
   T* xl = phi + Cf::PE;                  // the token rows, before the loop; df after it
   float* xch = reinterpret_cast<float*>(smem + 2 * Cf::phi_bytes);
-  float* re = xch + 2 * 64 * 4;          // [tile parity][64](rho, E); E < 0: no such row
+  float* re = xch + 2 * 64 * 4;          // [tile parity][rho, E][64]; E = 0: no such row
   const int N = a.N, C = a.C, n_tiles = (N + 63) / 64;
   int64_t unit;
   int tile;
@@ -312,36 +344,51 @@ __global__ __launch_bounds__(256, 2) void map_bwd_kernel(MapArgs a) {
   request_rows<T, 2 * D>(po, 2 * D, 64 * o_beg, N, phi, wave);
 
   float rho = 0.f, E = 0.f;              // query side: of this lane's row
-  if constexpr (!KEY) {                  // rho_t over the keys up to t: four rows of a wave at a time, all their loads in flight
+  if constexpr (!KEY) {                  // rho_t over the keys up to t: eight rows of a wave at a time, all their loads in flight
+    constexpr int RH = 8;
     const float* A = a.map_in + unit * N * (int64_t)N;
 #pragma unroll 1
-    for (int r0 = 16 * wave; r0 < 16 * wave + 16; r0 += 4) {
-      const int t_lo = min(t0 + r0, N - 1), full = (t_lo + 1) & ~255;   // columns all four rows have, in pieces of 256
-      float acc[4] = {0.f, 0.f, 0.f, 0.f};
-      const float *pa[4], *pd[4];
+    for (int r0 = 16 * wave; r0 < 16 * wave + 16; r0 += RH) {
+      const int t_lo = min(t0 + r0, N - 1), full = (t_lo + 1) & ~255;   // columns all the rows have, in pieces of 256
+      float acc[RH];
+      const float *pa[RH], *pd[RH];
 #pragma unroll
-      for (int h = 0; h < 4; ++h) {
+      for (int h = 0; h < RH; ++h) {
+        acc[h] = 0.f;
         const int64_t o = (int64_t)min(t_lo + h, N - 1) * N;
         pa[h] = A + o;
         pd[h] = dA + o;
       }
-#pragma unroll 2
+#pragma unroll 1
       for (int j = 4 * lane; j < full; j += 256)
 #pragma unroll
-        for (int h = 0; h < 4; ++h) {
+        for (int h = 0; h < RH; ++h) {
           const floatx4u xa = *reinterpret_cast<const floatx4u*>(pa[h] + j), xd = *reinterpret_cast<const floatx4u*>(pd[h] + j);
 #pragma unroll
           for (int e = 0; e < 4; ++e) acc[h] = fmaf(xa[e], xd[e], acc[h]);
         }
+      // at most 255 + RH columns are left: two steps of whole pieces whose columns past the diagonal count as nothing.  (No load
+      // sits under a condition: as five steps of single columns, each tested, a row group took 18 K cycles.)
 #pragma unroll
-      for (int e = 0; e < 5; ++e) {      // (at most 255 + 4 columns are left)
-        const int j = full + 64 * e + lane;
+      for (int q = 0; q < 2; ++q) {
+        if (full + 256 * q > t_lo + RH - 1) break;
+        const int j = full + 256 * q + 4 * lane, jc = min(j, min(t_lo + RH - 1, N - 4));   // (rows here have more than 128 columns)
+        floatx4u xa[RH], xd[RH];
 #pragma unroll
-        for (int h = 0; h < 4; ++h)
-          if (j <= min(t_lo + h, N - 1)) acc[h] = fmaf(pa[h][j], pd[h][j], acc[h]);
+        for (int h = 0; h < RH; ++h) {
+          xa[h] = *reinterpret_cast<const floatx4u*>(pa[h] + jc);
+          xd[h] = *reinterpret_cast<const floatx4u*>(pd[h] + jc);
+        }
+#pragma unroll
+        for (int h = 0; h < RH; ++h)
+#pragma unroll
+          for (int e = 0; e < 4; ++e) {
+            const bool on = jc + e >= j && jc + e <= min(t_lo + h, N - 1);
+            acc[h] = fmaf(on ? xa[h][e] : 0.f, on ? xd[h][e] : 0.f, acc[h]);
+          }
       }
 #pragma unroll
-      for (int h = 0; h < 4; ++h) {
+      for (int h = 0; h < RH; ++h) {
 #pragma unroll
         for (int o = 32; o >= 1; o >>= 1) acc[h] += __shfl_xor(acc[h], o, 64);
         if (lane == 0) {
@@ -361,7 +408,7 @@ __global__ __launch_bounds__(256, 2) void map_bwd_kernel(MapArgs a) {
 
   // this lane's 32 entries of dA against a tile of the other side: entry v of step v / KPL
   floatx16 d[2];
-  float rho_n = 0.f, E_n = -1.f;         // key side: of row 64 ot + tid of the next tile
+  float rho_n = 0.f, L_n = 0.f;          // key side: rho and L of row 64 ot + tid of the next tile, as loaded
   auto load_d = [&](int ot) __attribute__((always_inline)) {
     const int lane_now = fresh_lane_id(), rr = lane_now & 31, gg = lane_now >> 5;
     if constexpr (KEY) {
@@ -374,7 +421,7 @@ __global__ __launch_bounds__(256, 2) void map_bwd_kernel(MapArgs a) {
       if (tid < 64) {
         const int to = 64 * ot + tid;
         rho_n = a.rowdot[unit * N + min(to, N - 1)];
-        E_n = to < N ? __expf(-a.lse[unit * N + min(to, N - 1)]) : -1.f;
+        L_n = a.lse[unit * N + min(to, N - 1)];   // (E = exp(-L) is taken when the tile is: here it would wait for every load above)
       }
     } else {
       const float* p = dA + (int64_t)min(t0 + 32 * rg + rr, N - 1) * N + 64 * ot + gg * KPL;   // (full chunks)
@@ -399,27 +446,40 @@ __global__ __launch_bounds__(256, 2) void map_bwd_kernel(MapArgs a) {
   for (int ot = o_beg; ot < o_end; ++ot) {
     const int par = (ot - o_beg) & 1;
     if constexpr (KEY) {
-      if (tid < 64) re[128 * par + 2 * tid] = rho_n, re[128 * par + 2 * tid + 1] = E_n;
+      if (tid < 64) re[128 * par + tid] = rho_n, re[128 * par + 64 + tid] = 64 * ot + tid < N ? __expf(-L_n) : 0.f;
     }
     wait_async_copies();
     lds_barrier();                       // the tile and its (rho, E) are here; everybody is done with its predecessor
     typename M::frag wf[SK];
+    if constexpr (KEY && KPL == 8) {     // (rows past the end weigh nothing through E = 0: no choice per entry, which would be
+#pragma unroll                           // a branch and two dependent LDS reads for each of the 32)
+      for (int s = 0; s < SK; ++s) {
+        const float* ro = re + 128 * par + s * M::KK + g * KPL;
 #pragma unroll
-    for (int v = 0; v < 32; ++v) {
-      float wv;
-      if constexpr (KEY) {
-        const int o = (v / KPL) * M::KK + g * KPL + v % KPL;
-        const float e = re[128 * par + 2 * o + 1];
-        wv = e < 0.f ? 0.f : (d[v / 16][v % 16] - re[128 * par + 2 * o]) * e;
-      } else {
-        wv = (d[v / 16][v % 16] - rho) * E;
+        for (int q = 0; q < 2; ++q) {
+          const floatx4 rh = *reinterpret_cast<const floatx4*>(ro + 4 * q), ev = *reinterpret_cast<const floatx4*>(ro + 64 + 4 * q);
+#pragma unroll
+          for (int e = 0; e < 4; ++e) {
+            const int v = 8 * s + 4 * q + e;
+            wf[s][4 * q + e] = static_cast<bf16>((d[v / 16][v % 16] - rh[e]) * ev[e]);
+          }
+        }
       }
-      if constexpr (KPL == 8) wf[v / KPL][v % KPL] = static_cast<bf16>(wv);
-      else wf[v] = wv;
+    } else {
+#pragma unroll
+      for (int v = 0; v < 32; ++v) {
+        float rv = rho, ev = E;
+        if constexpr (KEY) rv = re[128 * par + v * M::KK + g], ev = re[128 * par + 64 + v * M::KK + g];
+        const float wv = (d[v / 16][v % 16] - rv) * ev;
+        if constexpr (KPL == 8) wf[v / KPL][v % KPL] = static_cast<bf16>(wv);
+        else wf[v] = wv;
+      }
     }
     if (ot + 1 < o_end) {
       load_d(ot + 1);
-      request_rows<T, 2 * D>(po, 2 * D, 64 * (ot + 1), N, phi + (par ^ 1) * Cf::PE, wave);
+      T* next = phi + (par ^ 1) * Cf::PE;
+      if (!KEY || 64 * (ot + 2) <= N) request_run<T, 2 * D>(po + (int64_t)64 * (ot + 1) * (2 * D), next, wave);   // (queries: full chunks)
+      else request_rows<T, 2 * D>(po, 2 * D, 64 * (ot + 1), N, next, wave);
     }
     const T* cur = phi + par * Cf::PE;
     const int lane_now = fresh_lane_id();

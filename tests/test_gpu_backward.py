@@ -500,3 +500,39 @@ def test_backward_and_map_with_strided_tensors(kw):
     for x in junk:
         kept = bool((x == 5.0).all())
         assert kept
+
+
+@pytest.mark.parametrize("kw", [dict(dtype="f32", N=64 * 4 + 3), dict(dtype="bf16", d=128, C=64, N=64 * 8 + 61),
+                                dict(dtype="bf16", d=64, C=128, W=128, N=128 * 5)], ids=["f32-259", "bf16-573", "bf16-640"])
+def test_map_backward_reads_nothing_above_the_diagonal(kw):
+    """The row sums take whole pieces of a row and drop the columns behind the diagonal, the last piece lies inside the
+    row: NaN above the diagonal of both matrices changes no gradient (added atomically: 1e-5 of the largest)."""
+    import torch
+
+    w = small("map-nan", **dict(dict(Hq=3, Hkv=1, lam=8, B=2), **kw))
+    inp = synth.make_inputs(w, seed=171)
+    t = {n: synth.to_torch(inp[n], w.dtype, "cuda") for n in ("q", "k", "v", "Wq", "Wk")}
+    out = torch.empty_like(t["q"])
+    p = S.make_params(B=w.B, N=w.N, Hq=w.Hq, Hkv=w.Hkv, d=w.d, C=w.C, W=w.W, lam=w.lam, scale=w.scale, eps=w.eps,
+                      dtype=w.dtype, q=t["q"], k=t["k"], v=t["v"], out=out)
+    sel = torch.zeros(w.B, w.Hq, w.N // w.C, w.lam, dtype=torch.int32, device="cuda")
+    ws = torch.empty(S.still_fwd_workspace_bytes(p), dtype=torch.uint8, device="cuda")
+    S.still_hybrid_attn_fwd(p, t["q"], t["k"], t["v"], None, t["Wq"], None, t["Wk"], None, out, sel_idx=sel, workspace=ws)
+    L = S.still_fwd_workspace_layout(p)
+    lse = ws[L.lse:L.lse + w.B * w.Hq * w.N * 4].view(torch.float32)
+    amap = torch.empty(w.B, w.Hq, w.N, w.N, device="cuda")
+    bws = torch.empty(S.still_attention_map_bwd_workspace_bytes(p), dtype=torch.uint8, device="cuda")
+    S.still_attention_map(p, t["q"], t["k"], t["Wq"], None, t["Wk"], None, lse, sel, amap, bws)
+    g = torch.Generator(device="cuda")
+    g.manual_seed(172)
+    dmap = torch.randn(amap.shape, generator=g, device="cuda").tril_()
+    upper = torch.ones(w.N, w.N, dtype=torch.bool, device="cuda").triu_(1)
+    grads = []
+    for fill in (0.0, float("nan")):
+        dWq, dWk = torch.empty(w.Hq, w.d, w.d, device="cuda"), torch.empty(w.Hq, w.d, w.d, device="cuda")
+        S.still_attention_map_bwd(p, t["q"], t["k"], t["Wq"], None, t["Wk"], None, lse, sel, amap.masked_fill(upper, fill),
+                                  dmap.masked_fill(upper, fill), dWq, None, dWk, None, bws)
+        grads.append((dWq, dWk))
+    for a_, b_ in zip(*grads):
+        assert torch.isfinite(b_).all() and float(a_.abs().max()) > 0
+        assert float((a_ - b_).abs().max()) <= 1e-5 * float(a_.abs().max())
