@@ -13,10 +13,10 @@
 // read along its rows for phi S, down its columns (transposing LDS reads) for a S^T.
 // Least traffic: the images (2 d d_f elements per chunk, four times the chunk's rows at C = 64), rows and gradients once.
 // What bounds it beyond that: two workgroups per CU (registers and LDS) that alternate between products and row-wise vector
-// work at one barrier per slab.  All 256 registers are in use at d = 128 and 26 (query side) / 44 (key side) values spill, 84 on
+// work at one barrier per slab.  All 256 registers are in use at d = 128 and 13 (query side) / 50 (key side) values spill, 94 on
 // the key side in fp32; none at d = 64 in bf16.
-// Measured at 16 sequences of 1024 tokens, 32 / 8 heads, d = 128, C = 64, bf16: query side 0.58 ms, key side 0.62 ms, state
-// gradient 0.175 ms, parameter gradients 0.12 ms; as batched products through memory (f, u, dphi, phi S and their
+// Measured at 16 sequences of 1024 tokens, 32 / 8 heads, d = 128, C = 64, bf16: query side 0.465 ms, key side 0.455 ms (0.58 and
+// 0.62 with loads that waited for each other and the retained entries looked up per result), state gradient 0.175 ms, parameter gradients 0.12 ms; as batched products through memory (f, u, dphi, phi S and their
 // fp32 sums each written and read) 4.2 ms.
 #include "still_kernels.h"
 #include "still_tile.h"
@@ -37,6 +37,7 @@ struct LinCfg {
   static constexpr size_t work_bytes = 2 * slab_bytes > f32_bytes ? 2 * slab_bytes : f32_bytes;   // slabs, then results
   static constexpr size_t phi_bytes = 64 * DP * sizeof(T);
   static constexpr size_t smem = work_bytes + phi_bytes + DP * 4 + 2 * 64 * 4 * 4 + 64 * 4;
+  static constexpr size_t key_smem(int heads) { return smem + kMaxHq + 64 * (size_t)heads; }   // + the retained entries
 };
 
 // element offset, inside one head's copy, of the operand "row x of W, contraction over features": [x / 32][k-step][lane][k
@@ -96,6 +97,15 @@ __device__ __forceinline__ void store_elems(T* p, const float (&x)[8]) {
   }
 }
 
+// eight elements as loaded: what a loop asks for before it uses any of it
+template <typename T>
+struct Raw8 {
+  typedef T Vec8 __attribute__((ext_vector_type(8), aligned(16)));
+  Vec8 v;
+  __device__ __forceinline__ void load(const T* p) { v = *reinterpret_cast<const Vec8*>(p); }
+  __device__ __forceinline__ float at(int e) const { return to_f32<T>(v[e]); }
+};
+
 // IN_FP32: the results stay fp32, dx and dv over dx32 and dv32, dg in dg32.  (An instance of its own: as a run-time choice it
 // cost the ordinary ones a per cent, 577 -> 582 and 619 -> 626 us at the shape above.)
 template <typename T, int D, bool KEY, bool IN_FP32>
@@ -116,6 +126,8 @@ __global__ __launch_bounds__(256, 2) void bwd_lin_kernel(BwdLinArgs a) {
   float* zl = reinterpret_cast<float*>(smem + Cf::work_bytes + Cf::phi_bytes);
   float* xch = zl + DP;                                               // [2 feature sides][64 tokens][4]
   float* cxl = xch + 2 * 64 * 4;
+  uint8_t* head_of = reinterpret_cast<uint8_t*>(cxl + 64);            // (keys) the query heads of the kv head, and for each
+  uint8_t* entry = head_of + kMaxHq;                                  // the slot of every token in the chunk's list, 255: none
 
   const int n_tiles = (a.N + 63) / 64;
   int bh, tile;                          // (batch, query head) or (batch, kv head)
@@ -142,6 +154,8 @@ __global__ __launch_bounds__(256, 2) void bwd_lin_kernel(BwdLinArgs a) {
 #pragma unroll
   for (int i = 0; i < NX; ++i) dxa[i] = zero16(), ya[i] = zero16();
   float cx = 0.f;
+  int n_heads = 0;                       // (keys) heads walked so far
+  constexpr int NE8 = 64 * D / 8 / 256;  // pieces of eight elements of a tile per thread
 
   for (int hi = 0; hi < (KEY ? a.Hq : 1); ++hi) {
     const int hq = KEY ? hi : hx;
@@ -156,40 +170,76 @@ __global__ __launch_bounds__(256, 2) void bwd_lin_kernel(BwdLinArgs a) {
       continue;
     }
     // ---- the token rows and what they are multiplied with, row by row into LDS
-    for (int i = tid; i < 64 * RX::PPR; i += 256) {
-      const int ri = i / RX::PPR, e0 = (i % RX::PPR) * EPV, tt = min(t0 + ri, N - 1);
-      *reinterpret_cast<Vec16*>(slab0 + RX::off(ri, e0)) = *reinterpret_cast<const Vec16*>(xg + (int64_t)tt * a.x_st + e0);
-      if constexpr (KEY) {
-        *reinterpret_cast<Vec16*>(slab1 + RX::off(ri, e0)) = *reinterpret_cast<const Vec16*>(
-            static_cast<const T*>(a.v) + b * a.v_sb + hx * a.v_sh + (int64_t)tt * a.v_st + e0);
+    // (all loads of a thread first: a loop that loads, waits and stores piece by piece took four round trips, 18 K of the 72 K
+    // cycles of a query workgroup)
+    {
+      constexpr int NPC = 64 * RX::PPR / 256;
+      const int tn = 64 * wave + fresh_lane_id();
+      typedef uint32_t Piece __attribute__((ext_vector_type(4)));
+      Piece xr[NPC], vr[KEY ? NPC : 1];
+#pragma unroll
+      for (int p = 0; p < NPC; ++p) {
+        const int i = tn + 256 * p, e0 = (i % RX::PPR) * EPV, tt = min(t0 + i / RX::PPR, N - 1);
+        xr[p] = *reinterpret_cast<const Piece*>(xg + (int64_t)tt * a.x_st + e0);
+        if constexpr (KEY)
+          vr[p] = *reinterpret_cast<const Piece*>(static_cast<const T*>(a.v) + b * a.v_sb + hx * a.v_sh + (int64_t)tt * a.v_st + e0);
+      }
+      if constexpr (!KEY) {              // A_t = E_t (gate_t * dy_t)
+        Raw8<T> dyr[NE8], gr[NE8];
+        float E[NE8];
+#pragma unroll
+        for (int p = 0; p < NE8; ++p) {
+          const int i = tn + 256 * p, e0 = (i % (D / 8)) * 8, tt = min(t0 + i / (D / 8), N - 1);
+          dyr[p].load(static_cast<const T*>(a.dout) + b * a.o_sb + (int64_t)tt * a.o_st + hx * a.o_sh + e0);
+          E[p] = a.e_row[unit * N + tt];
+          if (a.gate != nullptr) gr[p].load(static_cast<const T*>(a.gate) + b * a.g_sb + (int64_t)tt * a.g_st + hx * a.g_sh + e0);
+        }
+#pragma unroll
+        for (int p = 0; p < NE8; ++p) {
+          const int i = tn + 256 * p, ri = i / (D / 8), e0 = (i % (D / 8)) * 8;
+          float dy[8];
+#pragma unroll
+          for (int e = 0; e < 8; ++e) dy[e] = dyr[p].at(e) * E[p];
+          if (a.gate != nullptr) {
+#pragma unroll
+            for (int e = 0; e < 8; ++e) {
+              const float g = gr[p].at(e);
+              dy[e] = dyr[p].at(e) * (E[p] * (a.gate_act ? 1.f / (1.f + __expf(-g)) : g));
+            }
+          }
+          if constexpr (sizeof(T) == 2) {
+            store_elems<T>(slab1 + RX::off(ri, e0), dy);
+          } else {
+#pragma unroll
+            for (int e = 0; e < 8; ++e) slab1[RX::off(ri, e0 + e)] = dy[e];
+          }
+          if (t0 + ri < N) store_elems<T>(static_cast<T*>(a.a_rows) + (unit * N + t0 + ri) * D + e0, dy);
+        }
+      }
+#pragma unroll
+      for (int p = 0; p < NPC; ++p) {
+        const int i = tn + 256 * p, at = RX::off(i / RX::PPR, (i % RX::PPR) * EPV);
+        *reinterpret_cast<Piece*>(slab0 + at) = xr[p];
+        if constexpr (KEY) *reinterpret_cast<Piece*>(slab1 + at) = vr[p];
       }
     }
-    if constexpr (!KEY) {                // A_t = E_t (gate_t * dy_t)
-      for (int i = tid; i < 64 * D / 8; i += 256) {
-        const int ri = i / (D / 8), e0 = (i % (D / 8)) * 8, tt = min(t0 + ri, N - 1);
-        float dy[8], gate[8];
-        load_elems<T>(dy, static_cast<const T*>(a.dout) + b * a.o_sb + (int64_t)tt * a.o_st + hx * a.o_sh + e0);
-        const float E = a.e_row[unit * N + tt];
-        if (a.gate != nullptr) {
-          load_elems<T>(gate, static_cast<const T*>(a.gate) + b * a.g_sb + (int64_t)tt * a.g_st + hx * a.g_sh + e0);
-          if (a.gate_act) {
-#pragma unroll
-            for (int e = 0; e < 8; ++e) gate[e] = 1.f / (1.f + __expf(-gate[e]));
-          }
-#pragma unroll
-          for (int e = 0; e < 8; ++e) dy[e] *= E * gate[e];
-        } else {
-#pragma unroll
-          for (int e = 0; e < 8; ++e) dy[e] *= E;
+    if constexpr (KEY) {                 // which retained entry each of the tokens is, for the results' sums
+      if (a.dkret != nullptr && wave == (n_heads & 3)) {
+        const int w = t0 - c * C + lane;
+        const uint32_t* m = a.kmask + (unit * a.ncf + c) * (C / 32);
+        int pos = 255;
+        if ((m[w / 32] >> (w & 31)) & 1u) {
+          const int32_t* list = a.sel + unit * a.sel_stride + c * a.lam;
+          pos = __popc(m[w / 32] & ((1u << (w & 31)) - 1u));     // its rank among the list's tokens
+          for (int j = 0; j < w / 32; ++j) pos += __popc(m[j]);
+          if (list[pos] != t0 + lane)    // (a list with foreign or repeated entries, or in another order)
+            for (pos = 0; pos < a.lam && list[pos] != t0 + lane; ++pos) {}
+          if (pos == a.lam || c * a.lam + pos >= a.n_ret) pos = 255;
         }
-        if constexpr (sizeof(T) == 2) {
-          store_elems<T>(slab1 + RX::off(ri, e0), dy);
-        } else {
-#pragma unroll
-          for (int e = 0; e < 8; ++e) slab1[RX::off(ri, e0 + e)] = dy[e];
-        }
-        if (t0 + ri < N) store_elems<T>(static_cast<T*>(a.a_rows) + (unit * N + t0 + ri) * D + e0, dy);
+        entry[64 * n_heads + lane] = (uint8_t)pos;
+        if (lane == 0) head_of[n_heads] = (uint8_t)hq;
       }
+      ++n_heads;
     }
     // the images, and z of the same states
     // (the first chunk of a segment has no local state, the first segment no prefix; never both at c >= 2)
@@ -412,26 +462,32 @@ __global__ __launch_bounds__(256, 2) void bwd_lin_kernel(BwdLinArgs a) {
     if (g == 0) my[2] = dnx;
     if constexpr (!KEY) {                // dg = E_t dy_t * (phi_q S)_t (times the logistic function's slope)
       if (need_y) {
-        for (int i = tid; i < 64 * D / 8; i += 256) {
-          const int ri = i / (D / 8), e0 = (i % (D / 8)) * 8, tt = t0 + ri;
+        const int tn = 64 * wave + fresh_lane_id();
+        Raw8<T> dyr[NE8], gr[NE8];
+        float E[NE8];
+#pragma unroll
+        for (int p = 0; p < NE8; ++p) {
+          const int i = tn + 256 * p, e0 = (i % (D / 8)) * 8, tt = min(t0 + i / (D / 8), N - 1);
+          dyr[p].load(static_cast<const T*>(a.dout) + b * a.o_sb + (int64_t)tt * a.o_st + hx * a.o_sh + e0);
+          E[p] = a.e_row[unit * N + tt];
+          if (a.gate_act) gr[p].load(static_cast<const T*>(a.gate) + b * a.g_sb + (int64_t)tt * a.g_st + hx * a.g_sh + e0);
+        }
+#pragma unroll
+        for (int p = 0; p < NE8; ++p) {
+          const int i = tn + 256 * p, ri = i / (D / 8), e0 = (i % (D / 8)) * 8, tt = t0 + ri;
           if (tt >= N) continue;
           float dy[8];
-          load_elems<T>(dy, static_cast<const T*>(a.dout) + b * a.o_sb + (int64_t)tt * a.o_st + hx * a.o_sh + e0);
-          const float E = a.e_row[unit * N + tt];
-          const int64_t go = b * a.g_sb + (int64_t)tt * a.g_st + hx * a.g_sh + e0;
 #pragma unroll
-          for (int e = 0; e < 8; ++e) dy[e] *= E * res[ri * Cf::FST + e0 + e];
+          for (int e = 0; e < 8; ++e) dy[e] = dyr[p].at(e) * (E[p] * res[ri * Cf::FST + e0 + e]);
           if (a.gate_act) {
-            float gv[8];
-            load_elems<T>(gv, static_cast<const T*>(a.gate) + go);
 #pragma unroll
             for (int e = 0; e < 8; ++e) {
-              const float sg = 1.f / (1.f + __expf(-gv[e]));
+              const float sg = 1.f / (1.f + __expf(-gr[p].at(e)));
               dy[e] *= sg * (1.f - sg);
             }
           }
           if constexpr (IN_FP32) store_elems<float>(a.dg32 + (unit * N + tt) * D + e0, dy);
-          else store_elems<T>(static_cast<T*>(a.dg) + go, dy);
+          else store_elems<T>(static_cast<T*>(a.dg) + b * a.g_sb + (int64_t)tt * a.g_st + hx * a.g_sh + e0, dy);
         }
       }
     }
@@ -481,46 +537,64 @@ __global__ __launch_bounds__(256, 2) void bwd_lin_kernel(BwdLinArgs a) {
       if (with_x && g == 0 && fh == 0) cxl[row] = cx;
       lds_barrier();
     }
-    for (int i = tid; i < 64 * D / 8; i += 256) {
-      const int ri = i / (D / 8), e0 = (i % (D / 8)) * 8, tt = t0 + ri;
-      if (tt >= N) continue;
-      float x[8];
-      load_elems<float>(x, src + ((int64_t)bh * N + tt) * D + e0);
-      if (linear) {
+    // (loads first, as above.  The retained entries: four heads at a time, every load unconditional and dropped where the head
+    // does not keep the token; looked up per piece, three dependent loads per head, they took 120 K cycles of a workgroup
+    // that works 45 K per head)
+    const int tn = 64 * wave + fresh_lane_id();
+    float x[NE8][8];
+    Raw8<T> xr[NE8];
 #pragma unroll
-        for (int e = 0; e < 8; ++e) x[e] += res[ri * Cf::FST + e0 + e];
+    for (int p = 0; p < NE8; ++p) {
+      const int i = tn + 256 * p, e0 = (i % (D / 8)) * 8, tt = min(t0 + i / (D / 8), N - 1);
+      load_elems<float>(x[p], src + ((int64_t)bh * N + tt) * D + e0);
+      if (with_x) xr[p].load(xg + (int64_t)tt * a.x_st + e0);
+    }
+    if (linear) {
+#pragma unroll
+      for (int p = 0; p < NE8; ++p) {
+        const int i = tn + 256 * p, ri = i / (D / 8), e0 = (i % (D / 8)) * 8;
+#pragma unroll
+        for (int e = 0; e < 8; ++e) x[p][e] += res[ri * Cf::FST + e0 + e];
         if (with_x) {
-          float xv[8];
-          load_elems<T>(xv, xg + (int64_t)tt * a.x_st + e0);
 #pragma unroll
-          for (int e = 0; e < 8; ++e) x[e] += cxl[ri] * xv[e];
+          for (int e = 0; e < 8; ++e) x[p][e] += cxl[ri] * xr[p].at(e);
         }
       }
-      if (KEY && dret != nullptr && full_chunk) {
-        // the query heads of the group that retained this token: its entry is its rank among the list's tokens
-        for (int hq = 0; hq < a.Hq; ++hq) {
-          if (a.map.kv[hq] != hx) continue;
-          const int64_t unit = (int64_t)b * a.Hq + hq;
-          const int w = tt - c * C;
-          const uint32_t* m = a.kmask + (unit * a.ncf + c) * (C / 32);
-          if (!((m[w / 32] >> (w & 31)) & 1u)) continue;
-          int en = c * a.lam + __popc(m[w / 32] & ((1u << (w & 31)) - 1u));
-          for (int j = 0; j < w / 32; ++j) en += __popc(m[j]);
-          const int32_t* list = a.sel + unit * a.sel_stride;
-          if (list[en] != tt) {          // (a list with foreign or repeated entries, or in another order)
-            const int end = (c + 1) * a.lam;
-            for (en = c * a.lam; en < end && list[en] != tt; ++en) {}
-            if (en == end) continue;
+      if (KEY && dret != nullptr) {      // (tokens that are in no state are in no retained set either)
+        constexpr int HG = 4;
+#pragma unroll 1
+        for (int g0 = 0; g0 < n_heads; g0 += HG) {
+          const float* base[HG];
+#pragma unroll
+          for (int u = 0; u < HG; ++u) {
+            const int hq = __builtin_amdgcn_readfirstlane(head_of[min(g0 + u, n_heads - 1)]);
+            base[u] = dret + (((int64_t)b * a.Hq + hq) * a.cap + c * a.lam) * D;
           }
-          if (en >= a.n_ret) continue;
-          float xr[8];
-          load_elems<float>(xr, dret + (unit * a.cap + en) * D + e0);
 #pragma unroll
-          for (int k = 0; k < 8; ++k) x[k] += xr[k];
+          for (int p = 0; p < NE8; ++p) {
+            const int i = tn + 256 * p, ri = i / (D / 8), e0 = (i % (D / 8)) * 8;
+            float xd[HG][8];
+            bool on[HG];
+#pragma unroll
+            for (int u = 0; u < HG; ++u) {
+              const int pos = entry[64 * min(g0 + u, n_heads - 1) + ri];
+              on[u] = g0 + u < n_heads && pos != 255;
+              load_elems<float>(xd[u], base[u] + (int64_t)(on[u] ? pos : 0) * D + e0);
+            }
+#pragma unroll
+            for (int u = 0; u < HG; ++u)
+#pragma unroll
+              for (int e = 0; e < 8; ++e) x[p][e] += on[u] ? xd[u][e] : 0.f;
+          }
         }
       }
-      if constexpr (IN_FP32) store_elems<float>(src + ((int64_t)bh * N + tt) * D + e0, x);
-      else store_elems<T>(dst + b * s_b + (int64_t)tt * s_t + hx * s_h + e0, x);
+    }
+#pragma unroll
+    for (int p = 0; p < NE8; ++p) {
+      const int i = tn + 256 * p, e0 = (i % (D / 8)) * 8, tt = t0 + i / (D / 8);
+      if (tt >= N) continue;
+      if constexpr (IN_FP32) store_elems<float>(src + ((int64_t)bh * N + tt) * D + e0, x[p]);
+      else store_elems<T>(dst + b * s_b + (int64_t)tt * s_t + hx * s_h + e0, x[p]);
     }
   };
   if (!KEY && !linear && a.dg != nullptr) {
@@ -779,9 +853,16 @@ template <typename T, int D>
 hipError_t launch_lin_t(const BwdLinArgs& a, bool key, hipStream_t s) {
   auto kern = a.in_fp32 ? (key ? bwd_lin_kernel<T, D, true, true> : bwd_lin_kernel<T, D, false, true>)
                         : (key ? bwd_lin_kernel<T, D, true, false> : bwd_lin_kernel<T, D, false, false>);
-  const hipError_t e = allow_lds(kern, LinCfg<T, D>::smem);
+  int heads = 0;                         // of the widest group
+  for (int kv = 0; kv < (key ? a.Hkv : 0); ++kv) {
+    int n = 0;
+    for (int h = 0; h < a.Hq; ++h) n += a.map.kv[h] == kv;
+    heads = n > heads ? n : heads;
+  }
+  const size_t smem = key ? LinCfg<T, D>::key_smem(heads) : LinCfg<T, D>::smem;
+  const hipError_t e = allow_lds(kern, smem);
   if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(kern, dim3((unsigned)((a.N + 63) / 64) * a.n_units), dim3(256), (LinCfg<T, D>::smem), s, a);
+  hipLaunchKernelGGL(kern, dim3((unsigned)((a.N + 63) / 64) * a.n_units), dim3(256), smem, s, a);
   return hipGetLastError();
 }
 

@@ -536,3 +536,15 @@ def test_map_backward_reads_nothing_above_the_diagonal(kw):
     for a_, b_ in zip(*grads):
         assert torch.isfinite(b_).all() and float(a_.abs().max()) > 0
         assert float((a_ - b_).abs().max()) <= 1e-5 * float(a_.abs().max())
+
+
+@pytest.mark.parametrize("kw,kv_map", [
+    (dict(dtype="bf16", d=64, N=64 * 6 + 9, Hq=11, Hkv=2, lam=16), [0, 1, 0, 0, 1, 0, 0, 0, 0, 0, 0]),   # groups of nine and two, interleaved
+    (dict(dtype="f32", N=64 * 5, Hq=6, Hkv=1, lam=64), None),                                            # every token retained, six heads
+    (dict(dtype="bf16", d=128, C=128, W=128, N=128 * 5 + 70, Hq=5, Hkv=1, lam=128, max_retained=200), None),
+], ids=["bf16-groups-of-9-and-2", "f32-all-kept", "bf16-C128-budget-inside-a-chunk"])
+def test_backward_retained_entries_of_wide_groups(kw, kv_map):
+    """The key side adds the retained entries of four query heads at a time, from a table of one slot per token and head."""
+    w = small("bwd-ret-" + "-".join(f"{k}{v}" for k, v in kw.items()), **kw)
+    inp = synth.make_inputs(w, seed=181, with_gate=True)
+    check_backward(w, inp, 182, kv_map=None if kv_map is None else np.array(kv_map, np.int32))
