@@ -5,12 +5,13 @@
 // span once.  Kernels of a step, all on the caller's stream:
 //   route    : only when t opens chunk c >= 2: Top-lambda of chunk c-2 (ties to the lower index), selected
 //              rows appended to the retained cache, the others folded into (S, z) through the NP-Map
-//   step     : everything that reads the state, as workgroups of one launch that do not depend on each other:
+//   step     : everything that reads the state, as workgroups of one launch that do not wait for each other:
 //     attend : split over the rows of the salient cache: per split an online-softmax partial (m, l, acc)
 //     linear : NP-Map of q_t, N_LA = phi_q S, D_LA = phi_q z
 //     score  : Self-Saliency Score of token t over its window (Sec. 3.1), one thread per window key
 //     append : (k_t, v_t) into the ring of recent tokens (slot = t mod R)
-//   merge    : y = (N_SA + g*N_LA) / (D_SA + D_LA) over the partials, both branches scaled by exp(-max(m, 0))
+//     merge  : y = (N_SA + g*N_LA) / (D_SA + D_LA) over the partials, both branches scaled by exp(-max(m, 0)), by the
+//              workgroup that delivers a head's last partial
 // The token's own key and value are read from the caller's rows, so nobody waits for the ring; its ring slot (that of
 // token t - R) lies outside every window and local span (W <= R, the span is at most 2C rows, R = 4C).
 // Everything is plain vector-ALU code with fp32 accumulation: there is no contraction here that could
@@ -176,7 +177,7 @@ __global__ __launch_bounds__(256, 2) void decode_route_kernel(DecArgs a, int cr_
     int rank = 0;
     for (int jx = 0; jx < C; ++jx) {
       const float sj = s_sc[jx];
-      rank += (sj > si || (sj == si && jx < tid)) ? 1 : 0;
+      rank += (int)(sj > si) | ((int)(sj == si) & (int)(jx < tid));
     }
     chosen = rank < quota;
     s_flag[tid] = chosen ? 1 : 0;
@@ -497,6 +498,82 @@ constexpr size_t decode_route_smem() {
   return part > w ? part : w;
 }
 
+// ---------------------------------------------------------------- merge of the partials
+// The workgroup that delivers the last part of a (sequence, query head) merges them: as a launch of its own behind the step
+// the merge took 4 us of every step (one sequence behind 4 K tokens 10.9 -> 8.2 us, a request of 24 steps for eight sequences
+// 1129 -> 1054 us).
+// The counter holds a mark and the number of parts delivered, and the last delivery leaves the mark with zero.  Anything
+// else in its place (a new state, or one written before this slot was a counter) counts as zero, so that no caller
+// has to prepare it.  The parts come from every XCD, whose L2s do not see each other's writes: parts are written and read by
+// device-scope operations on every value (past the L2s), a wave waits until its writes have arrived before the workgroup counts
+// itself, and the merging workgroup reads after it has seen the full count.  (Ordering plain accesses by an acquire-release
+// operation on the counter instead makes every workgroup write back and drop its XCD's L2: one sequence 10.9 -> 45 us.)
+__device__ __forceinline__ void put_part(float* p, float x) { __hip_atomic_store(p, x, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
+__device__ __forceinline__ float get_part(const float* p) { return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
+constexpr unsigned long long kArrivalMark = 0x5ca1ab1e0ddba11ull << 8;   // 56 bits
+
+// all parts of the unit are there, and this workgroup is the one that delivered last (uniform over the workgroup)
+__device__ __forceinline__ bool last_delivery(const DecArgs& a, int64_t unit, int D, int* s_last) {
+  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // this wave's part has arrived
+  __syncthreads();                                  // and every wave's
+  if (threadIdx.x == 0) {
+    unsigned long long* cnt = reinterpret_cast<unsigned long long*>(a.part + (unit * 32 + kArrivalSlot) * (int64_t)(D + 2));
+    const unsigned total = a.nsplit + 1; // the splits and the linear terms
+    unsigned long long old = __hip_atomic_fetch_add(cnt, 1ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    unsigned n = (unsigned)(old & 255) + 1;
+    if (((old ^ kArrivalMark) >> 8) != 0) {   // no mark: the sum counts nothing; put the mark, or count where somebody has put it
+      old += 1;
+      do {
+        n = ((old ^ kArrivalMark) >> 8) == 0 ? (unsigned)(old & 255) + 1 : 1;
+      } while (!__hip_atomic_compare_exchange_strong(cnt, &old, kArrivalMark | n, __ATOMIC_RELAXED, __ATOMIC_RELAXED,
+                                                     __HIP_MEMORY_SCOPE_AGENT));
+    }
+    if (n == total) __hip_atomic_store(cnt, kArrivalMark, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    *s_last = n == total;
+  }
+  __syncthreads();
+  return *s_last != 0;
+}
+
+template <typename T, int D>
+__device__ __forceinline__ void decode_merge(const DecArgs& a, int64_t unit) {
+  const int tid = threadIdx.x;
+  if (tid >= D) return;
+  const float* part = a.part + unit * 32 * (int64_t)(D + 2);
+  const float* lin = part + kLinearSlot * (D + 2);
+  float nla = get_part(lin + 2 + tid);
+  const float dl = get_part(lin + 1);
+  if (a.g != nullptr) {
+    const float gx = to_f32(static_cast<const T*>(a.g)[unit * D + tid]);
+    nla *= a.gate_act ? fast_sigmoid(gx) : gx;
+  }
+  // lane s of every wave has split s's maximum and sum; the accumulators are asked for before the weights are known
+  const int lane = tid & 63, ns = a.nsplit;
+  const float ms = lane < ns ? get_part(part + lane * (D + 2)) : -INFINITY, ls = lane < ns ? get_part(part + lane * (D + 2) + 1) : 0.f;
+  constexpr int PRE = 8;
+  float pre[PRE];
+#pragma unroll
+  for (int s = 0; s < PRE; ++s) pre[s] = s < ns ? get_part(part + s * (D + 2) + 2 + tid) : 0.f;
+  const float M = wave_max(ms);
+  const float w = ms == -INFINITY ? 0.f : fast_exp2(ms - M);
+  const float L = wave_sum(w * ls);
+  float acc = 0.f;
+#pragma unroll
+  for (int s = 0; s < PRE; ++s) acc = fmaf(__shfl(w, s, 64), pre[s], acc);
+#pragma unroll 8
+  for (int s = PRE; s < ns; ++s) acc = fmaf(__shfl(w, s, 64), get_part(part + s * (D + 2) + 2 + tid), acc);
+  float fs, fl;
+  if (M >= 0.f) {
+    fs = 1.f;
+    fl = fast_exp2(-M);
+  } else {
+    fs = fast_exp2(M);
+    fl = 1.f;
+  }
+  const float y = (fs * acc + fl * nla) / (fs * L + fl * dl);
+  static_cast<T*>(a.out)[unit * D + tid] = from_f32<T>(y);
+}
+
 // ---------------------------------------------------------------- attention over the salient cache (split)
 // LDS tables of the row groups' partials, for GH query heads
 template <typename T, int D, int GH>
@@ -592,7 +669,7 @@ __device__ __forceinline__ void decode_attend(const DecArgs& a, int split, int h
       const float w = s_m[gi] == -INFINITY ? 0.f : fast_exp2(s_m[gi] - M);
       av = fmaf(w, s_acc[gi][tid], av);
     }
-    part[2 + tid] = av;
+    put_part(part + 2 + tid, av);
   }
   if (tid == 0) {
     float L = 0.f;
@@ -600,8 +677,8 @@ __device__ __forceinline__ void decode_attend(const DecArgs& a, int split, int h
       const float w = s_m[gi] == -INFINITY ? 0.f : fast_exp2(s_m[gi] - M);
       L = fmaf(w, s_l[gi], L);
     }
-    part[0] = M;
-    part[1] = L;
+    put_part(part, M);
+    put_part(part + 1, L);
   }
 }
 
@@ -716,7 +793,7 @@ __device__ __forceinline__ void decode_attend_shared(const DecArgs& a, int split
           const float w = s_m[g][gi] == -INFINITY ? 0.f : fast_exp2(s_m[g][gi] - M);
           av = fmaf(w, s_acc[g][gi][tid], av);
         }
-        part[2 + tid] = av;
+        put_part(part + 2 + tid, av);
       }
       if (tid == 128 + g) {
         float L = 0.f;
@@ -724,8 +801,8 @@ __device__ __forceinline__ void decode_attend_shared(const DecArgs& a, int split
           const float w = s_m[g][gi] == -INFINITY ? 0.f : fast_exp2(s_m[g][gi] - M);
           L = fmaf(w, s_l[g][gi], L);
         }
-        part[0] = M;
-        part[1] = L;
+        put_part(part, M);
+        put_part(part + 1, L);
       }
     }
     __syncthreads();   // the partial tables are reused by the next pass
@@ -839,14 +916,14 @@ __device__ __forceinline__ void decode_linear(const DecArgs& a, int hq, int b, L
     }
     *reinterpret_cast<floatx4*>(&lds.red[rp][4 * cg]) = n4;
     __syncthreads();
-    float* part = a.part + (unit * 32 + kMaxSplits) * (int64_t)(D + 2);
+    float* part = a.part + (unit * 32 + kLinearSlot) * (int64_t)(D + 2);
     if (tid < D) {
       float nla = 0.f;
 #pragma unroll
       for (int i = 0; i < L::RP; ++i) nla += lds.red[i][tid];
-      part[2 + tid] = nla;
+      put_part(part + 2 + tid, nla);
     }
-    if (tid == 0) part[1] = dl;
+    if (tid == 0) put_part(part + 1, dl);
   }
 }
 
@@ -855,7 +932,7 @@ __device__ __forceinline__ void decode_linear(const DecArgs& a, int hq, int b, L
 // what the splits leave idle (with the short ones first: 756 -> 773 us at 64 sequences behind 32 K tokens, 48 -> 53 us at
 // 24 sequences with 896 retained rows).  As launches of their own (score + append, attend, linear terms and merge in the last)
 // each of them paid its own start and tail.  Before -> now: one sequence behind 4 K tokens, 32 heads, d = 128, 27 us
-// (6.0 + 6.2 + 12.7 in the kernels) -> 10.5 us; 24 sequences with 896 retained rows, d = 64, 59 us (5.7 + 32 + 10) -> 48
+// (6.0 + 6.2 + 12.7 in the kernels) -> 8.2 us; 24 sequences with 896 retained rows, d = 64, 59 us (5.7 + 32 + 10) -> 48
 // us; 64 sequences behind 32 K tokens 782 (16 + 714 + 54) -> 755 us, 4.69 GB at 6.2 TB/s.
 template <typename T, int D, bool SHARED>
 __device__ __forceinline__ void decode_step_body(const DecArgs& a) {
@@ -864,14 +941,24 @@ __device__ __forceinline__ void decode_step_body(const DecArgs& a) {
     LinearLds<T, D> lin;
     float sh[16];
   } lds;
+  __shared__ int s_last;
+  auto deliver = [&](int64_t unit) __attribute__((always_inline)) {
+    if (last_delivery(a, unit, D, &s_last)) decode_merge<T, D>(a, unit);
+  };
   int i = blockIdx.x;
   const int heads = SHARED ? a.Hkv : a.Hq, n_att = a.nsplit * heads * a.B, n_q = a.Hq * a.B;
   if (i < n_att) {
     const int split = i % a.nsplit, h = (i / a.nsplit) % heads, b = i / (a.nsplit * heads);
     const int t = step_index(a, b);
     if (t < 0) return;
-    if constexpr (SHARED) decode_attend_shared<T, D>(a, split, h, b, t, lds.att);
-    else decode_attend<T, D>(a, split, h, b, t, lds.att);
+    if constexpr (SHARED) {
+      decode_attend_shared<T, D>(a, split, h, b, t, lds.att);
+      for (int hq = 0; hq < a.Hq; ++hq)
+        if (a.map.kv[hq] == h) deliver((int64_t)b * a.Hq + hq);
+    } else {
+      decode_attend<T, D>(a, split, h, b, t, lds.att);
+      deliver((int64_t)b * a.Hq + h);
+    }
     return;
   }
   i -= n_att;
@@ -880,8 +967,10 @@ __device__ __forceinline__ void decode_step_body(const DecArgs& a) {
   const int nh = kind == 2 ? a.Hkv : a.Hq, h = i % nh, b = i / nh;
   const int t = step_index(a, b);
   if (t < 0) return;
-  if (kind == 0) decode_linear<T, D>(a, h, b, lds.lin);
-  else if (kind == 1) decode_score<T, D>(a, h, b, t, lds.sh);
+  if (kind == 0) {
+    decode_linear<T, D>(a, h, b, lds.lin);
+    deliver((int64_t)b * a.Hq + h);
+  } else if (kind == 1) decode_score<T, D>(a, h, b, t, lds.sh);
   else decode_append<T>(a, h, b, t, D);
 }
 
@@ -896,47 +985,6 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4, 4))) voi
 template <typename T, int D>
 __global__ __launch_bounds__(256) void decode_step_shared_kernel(DecArgs a) {
   decode_step_body<T, D, true>(a);
-}
-
-// ---------------------------------------------------------------- merge of the partials
-template <typename T, int D>
-__global__ __launch_bounds__(D) void decode_merge_kernel(DecArgs a) {
-  const int hq = blockIdx.x, b = blockIdx.y, tid = threadIdx.x;
-  if (step_index(a, b) < 0) return;
-  const int64_t unit = (int64_t)b * a.Hq + hq;
-  const float* part = a.part + unit * 32 * (int64_t)(D + 2);
-  const float* lin = part + kMaxSplits * (D + 2);
-  float nla = lin[2 + tid];
-  const float dl = lin[1];
-  if (a.g != nullptr) {
-    const float gx = to_f32(static_cast<const T*>(a.g)[unit * D + tid]);
-    nla *= a.gate_act ? fast_sigmoid(gx) : gx;
-  }
-  // lane s of every wave has split s's maximum and sum; the accumulators are asked for before the weights are known
-  const int lane = tid & 63, ns = a.nsplit;
-  const float ms = lane < ns ? part[lane * (D + 2)] : -INFINITY, ls = lane < ns ? part[lane * (D + 2) + 1] : 0.f;
-  constexpr int PRE = 8;
-  float pre[PRE];
-#pragma unroll
-  for (int s = 0; s < PRE; ++s) pre[s] = s < ns ? part[s * (D + 2) + 2 + tid] : 0.f;
-  const float M = wave_max(ms);
-  const float w = ms == -INFINITY ? 0.f : fast_exp2(ms - M);
-  const float L = wave_sum(w * ls);
-  float acc = 0.f;
-#pragma unroll
-  for (int s = 0; s < PRE; ++s) acc = fmaf(__shfl(w, s, 64), pre[s], acc);
-#pragma unroll 8
-  for (int s = PRE; s < ns; ++s) acc = fmaf(__shfl(w, s, 64), part[s * (D + 2) + 2 + tid], acc);
-  float fs, fl;
-  if (M >= 0.f) {
-    fs = 1.f;
-    fl = fast_exp2(-M);
-  } else {
-    fs = fast_exp2(M);
-    fl = 1.f;
-  }
-  const float y = (fs * acc + fl * nla) / (fs * L + fl * dl);
-  static_cast<T*>(a.out)[unit * D + tid] = from_f32<T>(y);
 }
 
 // ---------------------------------------------------------------- state export from the prefill
@@ -1019,8 +1067,6 @@ hipError_t launch_decode_step(const DecArgs& a, int dtype, int d, bool route, hi
   } else {
     STILL_DISPATCH(dtype, d, CALL_STEP)
   }
-#define CALL_MERGE(TT, DD) hipLaunchKernelGGL((decode_merge_kernel<TT, DD>), dim3(a.Hq, a.B), dim3(DD), 0, stream, a);
-  STILL_DISPATCH(dtype, d, CALL_MERGE)
   return hipGetLastError();
 }
 

@@ -227,7 +227,9 @@ struct SaArgs {
   int AW;              //   all offers, each under its chunk's mask; AW = words per row = cap / 64)
 };
 
-constexpr int kMaxSplits = 31;   // of the salient cache in a decode step
+// Slots of a decode step's scratch, 32 per unit: the splits of the salient cache, the counter of the workgroups that have
+// delivered their part (first eight bytes), the linear terms.
+constexpr int kMaxSplits = 30, kArrivalSlot = 30, kLinearSlot = 31;
 struct DecArgs {
   float* S;            // [B, Hq, DP*(D+1)]
   void* kret;          // [B, Hq, cap, d]
@@ -236,7 +238,7 @@ struct DecArgs {
   void* kring;         // [B, Hkv, R, d]
   void* vring;
   float* score;        // [B, Hq, R]
-  float* part;         // [B, Hq, 32, d+2]: (m, l, acc) of every split, in the last slot (-, D_LA, N_LA)
+  float* part;         // [B, Hq, 32, d+2]: (m, l, acc) of every split, kArrivalSlot, kLinearSlot: (-, D_LA, N_LA)
   const void* q;       // [B, Hq, d]
   const void* k;       // [B, Hkv, d]
   const void* v;

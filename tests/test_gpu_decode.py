@@ -594,3 +594,47 @@ def test_a_step_equals_the_last_row_of_a_longer_prefill(d, dtype, shared, N):
         err, err_p = (float(np.max(np.abs(got - x)) / np.max(np.abs(ref))) for x in (ref, other))
         print(f"[step d={d} {dtype} shared={shared} N={N} head {h}] against the oracle {err:.2e}, against the prefill {err_p:.2e}")
         assert err <= tol and err_p <= tol, (err, err_p)
+
+
+@pytest.mark.parametrize("dtype,d,shared", [("f32", 64, 0), ("bf16", 128, 0), ("bf16", 64, 1), ("f32", 128, 1)])
+def test_the_scratch_of_a_step_may_hold_anything(dtype, d, shared):
+    """The last workgroup to deliver its part of a head merges them, and counts on a slot of the scratch region that nobody
+    prepares: whatever the region holds before a step (a state in memory that was used for something else, or one
+    written before that slot was a counter) gives the same bits, for consecutive steps, with a sequence that sits one out."""
+    import torch
+
+    w = synth.Workload("dec-scratch", B=3, N=520, Hq=4, Hkv=2, d=d, C=64, W=64, lam=8, dtype=dtype)
+    inp = synth.make_inputs(w, seed=191)
+    dev = "cuda"
+    full = {n: synth.to_torch(inp[n], dtype, dev) for n in ("q", "k", "v", "Wq", "Wk")}
+    n0 = 500
+    base = dict(B=3, Hq=4, Hkv=2, d=d, C=w.C, W=w.W, lam=8, scale=w.scale, eps=w.eps, dtype=dtype, max_tokens=520, shared_selection=shared)
+    ps = S.make_params(N=1, **base)
+    L = S.still_state_layout(ps)
+    q0, k0, v0 = (full[n][:, :n0].contiguous() for n in ("q", "k", "v"))
+    o0 = torch.empty_like(q0)
+    p0 = S.make_params(N=n0, q=q0, k=k0, v=v0, out=o0, **base)
+    ws = torch.empty(S.still_fwd_workspace_bytes(p0), dtype=torch.uint8, device=dev)
+    gen = torch.Generator(device=dev)
+    gen.manual_seed(192)
+    size = 3 * 4 * 32 * (d + 2) * 4
+    fills = {"zeros": None, "ones": lambda: torch.full((size,), 255, dtype=torch.uint8, device=dev),
+             "bytes": lambda: torch.randint(0, 256, (size,), generator=gen, dtype=torch.uint8, device=dev),
+             "floats": lambda: torch.randn(size // 4, generator=gen, device=dev).view(torch.uint8)}
+    got = {}
+    for name, fill in fills.items():
+        state = torch.zeros(S.still_state_bytes(ps), dtype=torch.uint8, device=dev)
+        S.still_hybrid_attn_fwd(p0, q0, k0, v0, None, full["Wq"], None, full["Wk"], None, o0, state_out=state, workspace=ws)
+        outs = []
+        for s in range(4):
+            if fill is not None and s in (0, 2):         # (steps 1 and 3 find what the step before them left)
+                state[L.part:L.part + size] = fill()
+            pos = torch.tensor([n0 + s, -1 if s == 1 else n0 + s - (s > 1), n0 + s], dtype=torch.int32, device=dev)
+            rows = [torch.stack([full[n][b, max(int(pos[b]), 0)] for b in range(3)]) for n in ("q", "k", "v")]
+            o = torch.zeros(3, 4, d, dtype=full["q"].dtype, device=dev)
+            S.still_hybrid_attn_decode_step_at(ps, state, pos, n0 + s, *rows, None, full["Wq"], None, full["Wk"], None, o)
+            outs.append(o)
+        got[name] = torch.stack(outs)
+    assert torch.isfinite(got["zeros"]).all() and float(got["zeros"].abs().max()) > 0
+    for name in ("ones", "bytes", "floats"):
+        assert torch.equal(got[name], got["zeros"]), name
