@@ -61,12 +61,13 @@ void prof_end(int slot, hipStream_t stream) {
 // The layout kernels (transposes of v and of the projection weights) do not depend on the scores and are bound by
 // memory, the score kernel by the vector ALU: they run side by side, the layout kernels on a second stream of
 // default priority that forks from the caller's stream at the start of the call and joins it again before the
-// first kernel that reads their output.  One side stream and one event pair per host thread and device.
+// first kernel that reads their output.  The backward pass runs its softmax branch there.  One side stream and its events
+// per host thread and device.
 struct SideStream {
   bool ok = false;
   int dev = -1;
   hipStream_t s = nullptr;
-  hipEvent_t fork = nullptr, join = nullptr;
+  hipEvent_t fork = nullptr, join = nullptr, mid = nullptr;
 };
 thread_local SideStream g_side;
 
@@ -77,6 +78,7 @@ SideStream* side_stream() {
   if (g_side.ok) {   // the thread moved to another device: drop the old objects
     (void)hipEventDestroy(g_side.fork);
     (void)hipEventDestroy(g_side.join);
+    (void)hipEventDestroy(g_side.mid);
     (void)hipStreamDestroy(g_side.s);
     g_side.ok = false;
   }
@@ -87,6 +89,12 @@ SideStream* side_stream() {
   }
   if (hipEventCreateWithFlags(&g_side.join, hipEventDisableTiming) != hipSuccess) {
     (void)hipEventDestroy(g_side.fork);
+    (void)hipStreamDestroy(g_side.s);
+    return nullptr;
+  }
+  if (hipEventCreateWithFlags(&g_side.mid, hipEventDisableTiming) != hipSuccess) {
+    (void)hipEventDestroy(g_side.fork);
+    (void)hipEventDestroy(g_side.join);
     (void)hipStreamDestroy(g_side.s);
     return nullptr;
   }
@@ -938,7 +946,16 @@ still_status_t bwd_impl(const still_params_t* p, const void* q, const void* k, c
   const int dt = p->dtype;
   const int budget = retained_budget(p);
   hipError_t e;
+  SideStream* side = nullptr;            // joined back into the caller's stream on every path
+  auto join_side = [&]() -> hipError_t {
+    if (side == nullptr) return hipSuccess;
+    hipError_t je = hipEventRecord(side->join, side->s);
+    if (je == hipSuccess) je = hipStreamWaitEvent(stream, side->join, 0);
+    side = nullptr;
+    return je;
+  };
   auto hip_fail = [&](const char* what, hipError_t err) -> still_status_t {
+    (void)join_side();
     return fail(STILL_ERR_HIP, "%s: %s", what, hipGetErrorString(err));
   };
   auto f32p = [&](size_t off) { return reinterpret_cast<float*>(bws + off); };
@@ -961,6 +978,23 @@ still_status_t bwd_impl(const still_params_t* p, const void* q, const void* k, c
   bool over = false;
   for (const Span& r : results)
     for (const Span& i : inputs) over = over || (meet(r, i) && !(g != nullptr && dg == g && r.lo == in_g.lo && i.lo == in_g.lo));
+
+  // The softmax branch (row scalars, retained rows, dq, then dk and dv) and the forward pass's states need nothing of each
+  // other, and the linear branch's query side and state gradient need only dq of it: two queues.  Small steps are chains
+  // of launches that leave most of the chip idle (3 x 777 tokens, d = 64: 342 -> 280); at 16 x 1024 tokens both queues fill
+  // the chip (2571 -> 2502 us).  Results that lie over lse, which dk and dv still read when dq is written, take one queue after
+  // the other, as they did.
+  bool over_lse = false;
+  const Span in_lse = flat(lse, (size_t)U * N * 4);
+  for (const Span& r : results) over_lse = over_lse || meet(r, in_lse);
+  hipStream_t s2 = stream;
+  side = side_stream();
+  if (side != nullptr) {
+    if (hipEventRecord(side->fork, stream) == hipSuccess && hipStreamWaitEvent(side->s, side->fork, 0) == hipSuccess)
+      s2 = side->s;
+    else
+      side = nullptr;
+  }
 
   // ---- the weights in operand order, the parameter gradients (sums are added into them) cleared
   still::BwdWeightsArgs wa{Wq, Wk, ws + L.wqt, ws + L.wkf, bws + BL.wqr, bws + BL.wkr, dWq, dWk, dbq, dbk, d};
@@ -995,7 +1029,7 @@ still_status_t bwd_impl(const still_params_t* p, const void* q, const void* k, c
   ra.out = out; ra.dout = dout; ra.o_sb = p->o_sb; ra.o_st = p->o_st; ra.o_sh = p->o_sh;
   ra.lse = lse; ra.e_row = f32p(BL.e_row); ra.delta = f32p(BL.delta); ra.ed = f32p(BL.ed);
   ra.U = U; ra.N = N; ra.Hq = Hq; ra.d = d;
-  if ((e = still::launch_bwd_row_prep(ra, dt, stream)) != hipSuccess) return hip_fail("bwd_row_prep", e);
+  if ((e = still::launch_bwd_row_prep(ra, dt, s2)) != hipSuccess) return hip_fail("bwd_row_prep", e);
 
   // ---- softmax branch: dq (owned rows), dk / dv (the local span's, and the retained entries' in routing order)
   still::BwdGatherArgs ga{};
@@ -1009,7 +1043,7 @@ still_status_t bwd_impl(const still_params_t* p, const void* q, const void* k, c
   ga.kret = bws + BL.kret; ga.vret = bws + BL.vret;
   ga.rvalid = reinterpret_cast<unsigned long long*>(bws + BL.rvalid);
   ga.times = reinterpret_cast<int32_t*>(ga.rvalid + (size_t)U * (BL.cap_t / 64));
-  if ((e = still::launch_bwd_gather(ga, dt, U, stream)) != hipSuccess) return hip_fail("bwd gather", e);
+  if ((e = still::launch_bwd_gather(ga, dt, U, s2)) != hipSuccess) return hip_fail("bwd gather", e);
   still::BwdSaArgs sa{};
   sa.kret = ga.kret; sa.vret = ga.vret; sa.rvalid = ga.rvalid; sa.times = ga.times;
   sa.cap = BL.cap_t;
@@ -1026,7 +1060,11 @@ still_status_t bwd_impl(const still_params_t* p, const void* q, const void* k, c
   sa.n_row_tiles = (N + 127) / 128;
   sa.n_ret_tiles = (still::retained_rows(nc >= 2 ? nc - 2 : 0, sa.lam, budget) + 127) / 128;
   sa.scale = p->scale;
-  if ((e = still::launch_bwd_sa(sa, dt, d, B, stream)) != hipSuccess) return hip_fail("bwd_sparse_attention", e);
+  if ((e = still::launch_bwd_sa_dq(sa, dt, d, s2)) != hipSuccess) return hip_fail("bwd_sparse_attention (dq)", e);
+  if (side != nullptr && ((e = hipEventRecord(side->mid, s2)) != hipSuccess || (e = hipStreamWaitEvent(stream, side->mid, 0)) != hipSuccess))
+    return hip_fail("side stream", e);
+  if ((e = still::launch_bwd_sa_dkv(sa, dt, d, B, s2)) != hipSuccess) return hip_fail("bwd_sparse_attention (dk, dv)", e);
+  if (over_lse && (e = join_side()) != hipSuccess) return hip_fail("side stream", e);
 
   // ---- linear branch: query side (dq, dg, and what the state gradient is made of), state gradient, key side, then the
   // parameter gradients
@@ -1058,6 +1096,7 @@ still_status_t bwd_impl(const still_params_t* p, const void* q, const void* k, c
   if (lk.n_ret > 0) lk.dkret = sa.dkret, lk.dvret = sa.dvret;
   lk.map = map; lk.n_units = B * Hkv;
   lk.N = N; lk.C = C; lk.Hq = Hq; lk.Hkv = Hkv; lk.nc = nc; lk.ncf = ncf;
+  if ((e = join_side()) != hipSuccess) return hip_fail("side stream", e);
   if ((e = still::launch_bwd_lin(lk, dt, d, true, stream)) != hipSuccess) return hip_fail("bwd_lin (keys)", e);
   still::BwdDwArgs dw{};
   dw.q = q; dw.q_sb = p->q_sb; dw.q_st = p->q_st; dw.q_sh = p->q_sh;

@@ -476,15 +476,20 @@ hipError_t allow_lds(K kern, size_t smem) {
 }
 
 template <typename T, int D>
-hipError_t launch_sa_t(const BwdSaArgs& a, int B, hipStream_t s) {
+hipError_t launch_dq_t(const BwdSaArgs& a, hipStream_t s) {
   auto kq = bwd_sa_dq_kernel<T, D>;
-  hipError_t e = allow_lds(kq, DqCfg<T, D>::smem);
+  const hipError_t e = allow_lds(kq, DqCfg<T, D>::smem);
   if (e != hipSuccess) return e;
   hipLaunchKernelGGL(kq, dim3((unsigned)a.n_row_tiles * a.U), dim3(256), (DqCfg<T, D>::smem), s, a);
-  if ((e = hipGetLastError()) != hipSuccess) return e;
+  return hipGetLastError();
+}
+
+template <typename T, int D>
+hipError_t launch_dkv_t(const BwdSaArgs& a, int B, hipStream_t s) {
   constexpr size_t smem = DkvCfg<T, D>::smem;
   auto kl = bwd_sa_dkv_kernel<T, D, true>;
-  if ((e = allow_lds(kl, smem)) != hipSuccess) return e;
+  hipError_t e = allow_lds(kl, smem);
+  if (e != hipSuccess) return e;
   hipLaunchKernelGGL(kl, dim3((a.N + 127) / 128, B * a.Hkv), dim3(256), smem, s, a);
   if ((e = hipGetLastError()) != hipSuccess || a.n_ret_tiles == 0) return e;
   auto kr = bwd_sa_dkv_kernel<T, D, false>;
@@ -507,10 +512,15 @@ hipError_t launch_bwd_gather(const BwdGatherArgs& a, int dtype, int U, hipStream
   return hipGetLastError();
 }
 
-hipError_t launch_bwd_sa(const BwdSaArgs& a, int dtype, int d, int B, hipStream_t s) {
-  if (dtype == 1) return d == 128 ? launch_sa_t<bf16, 128>(a, B, s) : launch_sa_t<bf16, 64>(a, B, s);
-  if (d == 64) return launch_sa_t<float, 64>(a, B, s);
-  return hipErrorInvalidValue;   // fp32 is built for d = 64 only (refused by the host checks)
+// (fp32 is built for d = 64 only; the host checks refuse the rest)
+hipError_t launch_bwd_sa_dq(const BwdSaArgs& a, int dtype, int d, hipStream_t s) {
+  if (dtype == 1) return d == 128 ? launch_dq_t<bf16, 128>(a, s) : launch_dq_t<bf16, 64>(a, s);
+  return d == 64 ? launch_dq_t<float, 64>(a, s) : hipErrorInvalidValue;
+}
+
+hipError_t launch_bwd_sa_dkv(const BwdSaArgs& a, int dtype, int d, int B, hipStream_t s) {
+  if (dtype == 1) return d == 128 ? launch_dkv_t<bf16, 128>(a, B, s) : launch_dkv_t<bf16, 64>(a, B, s);
+  return d == 64 ? launch_dkv_t<float, 64>(a, B, s) : hipErrorInvalidValue;
 }
 
 }  // namespace still

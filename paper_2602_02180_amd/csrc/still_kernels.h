@@ -464,7 +464,8 @@ hipError_t launch_rope(const RopeArgs& a, int dtype, hipStream_t stream);
 hipError_t launch_bwd_row_prep(const BwdRowArgs& a, int dtype, hipStream_t stream);
 hipError_t launch_bwd_round(const BwdRoundArgs& a, int dtype, hipStream_t stream);
 hipError_t launch_bwd_gather(const BwdGatherArgs& a, int dtype, int U, hipStream_t stream);
-hipError_t launch_bwd_sa(const BwdSaArgs& a, int dtype, int d, int B, hipStream_t stream);
+hipError_t launch_bwd_sa_dq(const BwdSaArgs& a, int dtype, int d, hipStream_t stream);
+hipError_t launch_bwd_sa_dkv(const BwdSaArgs& a, int dtype, int d, int B, hipStream_t stream);   // local span, then retained entries
 // attention map and its backward pass (still_map.hip)
 struct MapArgs {
   const void* q;

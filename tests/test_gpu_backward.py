@@ -548,3 +548,68 @@ def test_backward_retained_entries_of_wide_groups(kw, kv_map):
     w = small("bwd-ret-" + "-".join(f"{k}{v}" for k, v in kw.items()), **kw)
     inp = synth.make_inputs(w, seed=181, with_gate=True)
     check_backward(w, inp, 182, kv_map=None if kv_map is None else np.array(kv_map, np.int32))
+
+
+@pytest.mark.parametrize("kw", [dict(dtype="f32", N=64 * 9 + 5), dict(dtype="bf16", d=128, C=128, W=128, N=128 * 6 + 40)],
+                         ids=["f32", "bf16-C128"])
+@pytest.mark.parametrize("how", ["dq_over_lse", "dg_over_lse", "graph"])
+def test_backward_on_two_queues(kw, how):
+    """The softmax branch runs beside the states and the linear branch.  Results may lie over lse, which its last kernels still
+    read when the first results are written; and a captured call replays with both queues.  dq, dk, dv and dg bit for
+    bit those of a plain call (the parameter gradients are added atomically: 1e-5 of the largest)."""
+    import torch
+
+    w = small("bwd-queues", **dict(dict(Hq=4, Hkv=2, lam=8, B=2), **kw))
+    inp = synth.make_inputs(w, seed=201, with_gate=True)
+    t = {n: synth.to_torch(inp[n], w.dtype, "cuda") for n in ("q", "k", "v", "g", "Wq", "Wk")}
+    dout, out = synth.to_torch(make_dy(w, inp, 202), w.dtype, "cuda"), torch.empty_like(t["q"])
+    p = S.make_params(B=w.B, N=w.N, Hq=w.Hq, Hkv=w.Hkv, d=w.d, C=w.C, W=w.W, lam=w.lam, scale=w.scale, eps=w.eps,
+                      dtype=w.dtype, q=t["q"], k=t["k"], v=t["v"], out=out, g=t["g"])
+    sel = torch.zeros(w.B, w.Hq, w.N // w.C, w.lam, dtype=torch.int32, device="cuda")
+    ws = torch.empty(S.still_fwd_workspace_bytes(p), dtype=torch.uint8, device="cuda")
+    S.still_hybrid_attn_fwd(p, t["q"], t["k"], t["v"], t["g"], t["Wq"], None, t["Wk"], None, out, sel_idx=sel, workspace=ws)
+    L = S.still_fwd_workspace_layout(p)
+    lse = ws[L.lse:L.lse + w.B * w.Hq * w.N * 4].view(torch.float32).clone()
+    bws = torch.empty(S.still_bwd_workspace_bytes(p), dtype=torch.uint8, device="cuda")
+
+    def grads():
+        return {n: torch.zeros_like(t[n[1:]]) for n in ("dq", "dk", "dv", "dg")}, \
+               [torch.zeros(w.Hq, w.d, w.d, device="cuda") for _ in range(2)]
+
+    def call(g, dw, l):
+        S.still_hybrid_attn_bwd(p, t["q"], t["k"], t["v"], t["g"], t["Wq"], None, t["Wk"], None, out, dout, l, sel,
+                                g["dq"], g["dk"], g["dv"], g["dg"], dw[0], None, dw[1], None, bws)
+
+    def check(g, dw):
+        for n in g:
+            assert torch.equal(g[n], ref[n]), n
+        for a_, b_ in zip(dw, dw_ref):
+            assert float((a_ - b_).abs().max()) <= 1e-5 * float(b_.abs().max())
+
+    ref, dw_ref = grads()
+    call(ref, dw_ref, lse)
+    torch.cuda.synchronize()
+    assert float(ref["dk"].abs().max()) > 0
+    g, dw = grads()
+    if how == "graph":
+        side = torch.cuda.Stream()
+        with torch.cuda.stream(side):
+            call(g, dw, lse)
+        torch.cuda.synchronize()
+        graph = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(graph, stream=side):
+            call(g, dw, lse)
+        for _ in range(4):
+            for x in list(g.values()) + dw:
+                x.fill_(7.0)
+            bws.fill_(0x5a)
+            graph.replay()
+            torch.cuda.synchronize()
+            check(g, dw)
+    else:
+        n = how[:2]
+        over = g[n].view(torch.uint8).flatten()[:lse.numel() * 4].view(torch.float32)    # the result's own memory
+        over.copy_(lse)
+        call(g, dw, over)
+        torch.cuda.synchronize()
+        check(g, dw)
