@@ -31,7 +31,7 @@ PEAK_HBM = 8.0e12
 # HBM bytes per launch of the dominant prefill kernel (sparse_attn_merge), measured with rocprofv3 --pmc FETCH_SIZE /
 # WRITE_SIZE and scaled by the plain-copy calibration (two counter runs plus two --calibrate-copy runs; FETCH_SIZE
 # counts 2 KiB and WRITE_SIZE 1 KiB per unit on this machine).  Other configs: null.
-MEASURED_TRAFFIC = {"c4": 1.871e9}
+MEASURED_TRAFFIC = {"c4": 1.889e9}
 
 
 def sparse_branch_flops(w: synth.Workload, N: int) -> float:
@@ -441,7 +441,8 @@ def decode_record(args, steps: int, with_cpu: bool):
                    "median_ordinary_step_ms": ordinary,
                    "routing_step_ms": [float(x) for x in lat[routing]],
                    "prefill_of_contexts_s": t_prefill, "state_gb": state.numel() / 1e9},
-        "roofline": {"bound": "hbm", "kernel": "decode step (one launch + merge)", "achieved": bytes_step / (ordinary * 1e-3) / 1e9,
+        "roofline": {"bound": "hbm", "kernel": "decode step (one launch)" + (" + merge" if args.shared_selection else ""),
+                     "achieved": bytes_step / (ordinary * 1e-3) / 1e9,
                      "peak": PEAK_HBM / 1e9, "unit": "GB/s", "frac": bytes_step / (ordinary * 1e-3) / PEAK_HBM,
                      "traffic": args.traffic_bytes, "algorithmic_bytes_per_step": bytes_step},
     }
