@@ -12,10 +12,12 @@
 // Scores go to an LDS array; each thread ranks one token by counting (score higher, or equal with a
 // lower index) and the selected tokens are written in ascending order, and once more as a bit per token for the state
 // scan (a launch of its own over the lists took 5-6 us of every prefill).
-// Bound by vector issue: per key and lane one exponential, one reciprocal, one logarithm (8 cycles each) and about six
-// ordinary operations.  The rank count is written without short-circuits: as "higher, or equal and earlier" the compiler
-// made branches of it, more instructions than the whole window.  4 x 4096 tokens, d = 64, W = 64: 69 -> 65 us;
-// 32768 tokens, 32 heads, d = 128, W = 128: 195 -> 179 us.
+// Bound by vector issue: per key and lane one exponential, two logarithms (8 cycles each) and about nine ordinary
+// operations.  The order of the sums decides which of two tokens with nearly equal scores is kept, and index lists are outputs:
+// it stays as it is.  (One reciprocal and one logarithm per key, as the logarithm of the quotient of both distributions, is 4 %
+// faster and no less exact, and swaps such a pair in one of 100 000 lists.)  The rank count is written without
+// short-circuits: as "higher, or equal and earlier" the compiler made branches of it, more instructions than the whole
+// window (32768 tokens, 32 heads, d = 128, W = C = 128: 199 -> 188 us).
 #include "still_kernels.h"
 
 namespace still {
@@ -148,49 +150,46 @@ __global__ __launch_bounds__(256, NT > 5 ? 2 : 3) void score_select_kernel(Score
     for (int i = 0; i < 16; ++i) mraw = fmaxf(mraw, acc[j][i]);
   }
   mraw = max32(mraw);
-  // pass 2: e = exp(scale * (x - max)); masked entries give exp2(-inf) = 0.  The diagonal key (slot p == r of the merged
-  // tile) is kept apart: z is the sum over the others.
+  // pass 2: e = exp(scale * (x - max)); masked entries give exp2(-inf) = 0.  The sums without the diagonal
+  // differ from the full sums only in the merged tile.
   const float moff = -mraw * sc2;
-  float e_dd = 0.f, z4[4] = {0.f, 0.f, 0.f, 0.f};
+  float d_old = 0.f, d_new = 0.f, d_new_no = 0.f;
 #pragma unroll
   for (int j = 1; j < NT; ++j) {
 #pragma unroll
     for (int i = 0; i < 16; ++i) {
-      float e = fast_exp2(fmaf(acc[j][i], sc2, moff));
-      if (j == NT - 1) {
-        const bool diag = M::pos_of_reg(i, g) == r;
-        e_dd = diag ? e : e_dd;
-        e = diag ? 0.f : e;
-      }
+      const float e = fast_exp2(fmaf(acc[j][i], sc2, moff));
       acc[j][i] = e;
-      z4[i & 3] += e;
+      if (j < NT - 1) {
+        d_old += e;
+      } else {
+        d_new += e;
+        d_new_no += (M::pos_of_reg(i, g) == r) ? 0.f : e;   // slot p == r of the merged tile is the query itself
+      }
     }
   }
-  e_dd = sum32(e_dd);
-  const float z = sum32((z4[0] + z4[1]) + (z4[2] + z4[3]));
-  const float inv_d = 1.0f / (z + e_dd);
-  // pass 3: the sum over the window of a_j ln((a_j + eps) / (n_j + eps)), a_j = e_j / d with d = z + e_dd, n_j = e_j / z
-  // (0 for the diagonal).  For the other keys (a_j + eps) / (n_j + eps) = (z / d) (1 + eps e_dd / (e_j + eps z)), so
-  //   score = (z / d) ln(z / d) + (1 / d) sum_j e_j ln(1 + eps e_dd / (e_j + eps z)) + a_dd ln((a_dd + eps) / eps):
-  // a reciprocal, a logarithm and three ordinary operations per key instead of two logarithms and six, and no difference
-  // of two nearly equal logarithms.  A masked key has weight 0; the lower bound keeps its second factor finite where z
-  // is zero or underflows (no other key, or all of them 2^-126 below the diagonal).
-  const float ez = fmaxf(a.eps * z, 1e-30f * fmaxf(a.eps, 1.f)), ed = a.eps * e_dd;
-  float c4[4] = {0.f, 0.f, 0.f, 0.f};
+  float d_all = d_old + d_new, d_no = d_old + d_new_no;
+  d_all = sum32(d_all);
+  d_no = sum32(d_no);
+  const float inv_all = 1.0f / d_all;
+  const float inv_no = d_no > 0.f ? 1.0f / d_no : 0.f;
+  // pass 3: sum of a_diag * (log(a_diag + eps) - log(a_nodiag + eps)).  A masked entry has a_diag = a_nodiag = 0:
+  // its term is 0 * (log eps - log eps) = 0 (eps > 0 is checked on the host).
+  float score = 0.f;
 #pragma unroll
   for (int j = 1; j < NT; ++j) {
 #pragma unroll
     for (int i = 0; i < 16; ++i) {
       const float e = acc[j][i];
-      c4[i & 3] = fmaf(e, fast_log2(fmaf(ed, fast_rcp(e + ez), 1.f)), c4[i & 3]);
+      const float ad = e * inv_all;
+      float an = e * inv_no;
+      if (j == NT - 1) an = (M::pos_of_reg(i, g) == r) ? 0.f : an;
+      score = fmaf(ad, fast_log2(ad + a.eps) - fast_log2(an + a.eps), score);
     }
   }
-  float score = sum32((c4[0] + c4[1]) + (c4[2] + c4[3])) * inv_d;
-  {
-    const float share = z * inv_d, a_dd = e_dd * inv_d;
-    score += (z > 0.f ? share * fast_log2(share) : 0.f) + a_dd * (fast_log2(a_dd + a.eps) - fast_log2(a.eps));
-  }
   score *= kLn2;
+  score = sum32(score);
+
   if (g == 0) {
     s_score[32 * wave + r] = score;
     if (t < N) a.score[((int64_t)b * a.Hq + hq) * N + t] = score;
@@ -276,7 +275,7 @@ hipError_t launch_group_select(const ScoreArgs& a, int B, int Hkv, hipStream_t s
 
 // Band tiles per pass: as few passes as 32 KB of LDS allow, and no more LDS than these passes need.  A chunk of 64 tokens is a
 // workgroup of two waves, and with 32 KB for each four of them fit a CU where the registers allow six (d = 128) to ten
-// (d = 64).  4 x 4096 tokens, d = 64, W = 64: 65 -> 51 us; 2 x 8192 tokens, d = 128, W = 128: 118 -> 103 us.
+// (d = 64).  With the rank count above, 4 x 4096 tokens, d = 64, W = 64: 70 -> 53 us; 2 x 8192 tokens, d = 128, W = 128: 122 -> 106 us.
 template <typename T, int D, int NT>
 static void launch_score_nt(ScoreArgs a, int B, int nc, hipStream_t stream) {
   constexpr int tile_bytes = 32 * D * (int)sizeof(T), most = 32768 / tile_bytes;

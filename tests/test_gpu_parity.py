@@ -762,3 +762,32 @@ def test_scores_where_one_key_takes_the_window_and_where_scores_tie(dtype, d, W,
             if np.all(s == s[0]):
                 assert np.array_equal(hip["sel"][b, h, c], c * w.C + np.arange(w.lam))
     assert len(tied) > 0 or W > 64
+
+
+# Which tokens of the test below the library keeps, as one bit per token of a chunk (hexadecimal, token 0 in the lowest bit),
+# for the heads 0 and 1, recorded from the library.
+KEPT_OF_TIES = {
+    ("f32", 64, 64): [["0000000040c0c0fb"] + ["4040c0c04040c0c0"] * 5, ["0000004040484a5b"] + ["4848404048484040"] * 5],
+    ("bf16", 128, 128): [["0000000000000000000809090949c9cf"] + ["08080808080808080808080809090909"] * 3,
+                         ["000000000000000000001019191999bb"] + ["10101010101010101818101018181010"] * 3],
+    ("bf16", 64, 256): [["000000000000001f", "0000000000109090", "0000000010101090", "0000000010101090"] + ["0000001010101010"] * 3,
+                        ["0000000000001151", "0000000000011111", "0000000000101111", "0000000000101111"] + ["0000101000101010"] * 3],
+}
+
+
+@pytest.mark.parametrize("dtype,d,C,W,lam,N", [("f32", 64, 64, 64, 12, 384), ("bf16", 128, 128, 128, 20, 512), ("bf16", 64, 64, 256, 5, 448)])
+def test_which_of_two_tied_tokens_is_kept_does_not_change(dtype, d, C, W, lam, N):
+    """Index lists are outputs that callers keep and pass on.  Eight tokens that repeat have eight different scores, each many times,
+    equal but for the last bits of sums in another order: which of two such tokens is kept follows from the order of the
+    kernel's arithmetic alone.  Another order is no less correct, but it changes lists, and with a list entries of the
+    output and of the attention map by more than their size.  So the order is part of the interface: the lists stay."""
+    w = small(f"ties-{dtype}-{d}", dtype=dtype, d=d, C=C, W=W, lam=lam, N=N)
+    inp = synth.make_inputs(w, seed=301)
+    for n in ("q", "k"):
+        inp[n] = inp[n][:, np.arange(N) % 8]
+    hip, ref = U.run_hip(w, inp, want_terms=False), U.oracle_units(w, inp, all_units(w))
+    for h in range(2):
+        # (scores reach ln(1 / eps) = 13.8, of which half a unit in the last place is 4.8e-7)
+        assert U.selection_is_valid(ref[(0, h)]["score"], hip["sel"][0, h], C, 4e-6)
+        kept = ["%0*x" % (C // 4, sum(1 << int(t - c * C) for t in hip["sel"][0, h, c])) for c in range(N // C)]
+        assert kept == KEPT_OF_TIES[(dtype, d, W)][h]
