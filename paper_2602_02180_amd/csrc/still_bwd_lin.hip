@@ -234,7 +234,7 @@ __global__ __launch_bounds__(256, 2) void bwd_lin_kernel(BwdLinArgs a) {
           for (int j = 0; j < w / 32; ++j) pos += __popc(m[j]);
           if (list[pos] != t0 + lane)    // (a list with foreign or repeated entries, or in another order)
             for (pos = 0; pos < a.lam && list[pos] != t0 + lane; ++pos) {}
-          if (pos == a.lam || c * a.lam + pos >= a.n_ret) pos = 255;
+          if (pos == a.lam || retained_row(c, a.lam, pos, a.n_ret) < 0) pos = 255;
         }
         entry[64 * n_heads + lane] = (uint8_t)pos;
         if (lane == 0) head_of[n_heads] = (uint8_t)hq;
@@ -539,7 +539,8 @@ __global__ __launch_bounds__(256, 2) void bwd_lin_kernel(BwdLinArgs a) {
     }
     // (loads first, as above.  The retained entries: four heads at a time, every load unconditional and dropped where the head
     // does not keep the token; looked up per piece, three dependent loads per head, they took 120 K cycles of a workgroup
-    // that works 45 K per head)
+    // that works 45 K per head.  A load that is dropped reads the chunk's first row, so a chunk that the budget leaves
+    // nothing, whose first row would lie behind the buffer, is left out)
     const int tn = 64 * wave + fresh_lane_id();
     float x[NE8][8];
     Raw8<T> xr[NE8];
@@ -560,7 +561,8 @@ __global__ __launch_bounds__(256, 2) void bwd_lin_kernel(BwdLinArgs a) {
           for (int e = 0; e < 8; ++e) x[p][e] += cxl[ri] * xr[p].at(e);
         }
       }
-      if (KEY && dret != nullptr) {      // (tokens that are in no state are in no retained set either)
+      const int first = KEY ? retained_row(c, a.lam, 0, a.n_ret) : -1;
+      if (KEY && dret != nullptr && first >= 0) {      // (tokens that are in no state are in no retained set either)
         constexpr int HG = 4;
 #pragma unroll 1
         for (int g0 = 0; g0 < n_heads; g0 += HG) {
@@ -568,7 +570,7 @@ __global__ __launch_bounds__(256, 2) void bwd_lin_kernel(BwdLinArgs a) {
 #pragma unroll
           for (int u = 0; u < HG; ++u) {
             const int hq = __builtin_amdgcn_readfirstlane(head_of[min(g0 + u, n_heads - 1)]);
-            base[u] = dret + (((int64_t)b * a.Hq + hq) * a.cap + c * a.lam) * D;
+            base[u] = dret + (((int64_t)b * a.Hq + hq) * a.cap + first) * D;
           }
 #pragma unroll
           for (int p = 0; p < NE8; ++p) {

@@ -32,6 +32,12 @@ __host__ __device__ inline int retained_rows(int chunks, int lam, int rcap) {
   return r < rcap ? r : rcap;
 }
 constexpr int kNoBudget = 1 << 30;
+// Retained row of slot pos of chunk c, or -1 where it is none of the n_ret rows that a buffer is sure to hold.  (Under a budget
+// c * lam alone leaves the buffer, whose size no longer grows with the chunks.)
+__host__ __device__ inline int retained_row(int c, int lam, int pos, int n_ret) {
+  const int row = c * lam + pos;
+  return row < n_ret ? row : -1;
+}
 constexpr int kMaxEvictBudget = 4096;   // the plan and the routing step hold the retained set in LDS
 
 // Tokens of sequence b: N for every sequence, or, for a right-padded batch, the caller's per-sequence count

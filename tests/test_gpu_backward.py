@@ -542,7 +542,8 @@ def test_map_backward_reads_nothing_above_the_diagonal(kw):
     (dict(dtype="bf16", d=64, N=64 * 6 + 9, Hq=11, Hkv=2, lam=16), [0, 1, 0, 0, 1, 0, 0, 0, 0, 0, 0]),   # groups of nine and two, interleaved
     (dict(dtype="f32", N=64 * 5, Hq=6, Hkv=1, lam=64), None),                                            # every token retained, six heads
     (dict(dtype="bf16", d=128, C=128, W=128, N=128 * 5 + 70, Hq=5, Hkv=1, lam=128, max_retained=200), None),
-], ids=["bf16-groups-of-9-and-2", "f32-all-kept", "bf16-C128-budget-inside-a-chunk"])
+    (dict(dtype="bf16", d=64, N=64 * 24 + 5, Hq=6, Hkv=1, lam=32, max_retained=64), None),               # most chunks keep nothing
+], ids=["bf16-groups-of-9-and-2", "f32-all-kept", "bf16-C128-budget-inside-a-chunk", "bf16-budget-of-two-chunks"])
 def test_backward_retained_entries_of_wide_groups(kw, kv_map):
     """The key side adds the retained entries of four query heads at a time, from a table of one slot per token and head."""
     w = small("bwd-ret-" + "-".join(f"{k}{v}" for k, v in kw.items()), **kw)

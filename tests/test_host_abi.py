@@ -257,3 +257,42 @@ def test_the_backward_workspace_holds_what_the_kernels_use_and_no_more():
         + entries // 8 + 4 * Hq * d * d
     assert want <= S.still_bwd_workspace_bytes(p) <= want + 64 * 256
     assert S.still_attention_map_bwd_workspace_bytes(p) <= S.still_bwd_workspace_bytes(p) + 4 * rows + 256
+
+
+def test_the_backward_pass_reads_no_retained_row_behind_its_buffers(tmp_path):
+    """The key side of the linear branch reads, for every chunk that has retained entries, rows from the chunk's first to the last
+    slot that counts, whether a token is retained or not.  Under a budget the buffers stop growing with the chunks: the
+    rows of every chunk, by the kernel's own rule, lie inside what the workspace layout gives a head."""
+    import random
+    import subprocess
+
+    from paper_2602_02180_amd import build
+
+    src, exe = tmp_path / "rows.hip", tmp_path / "rows"
+    src.write_text('#include <cstdio>\n#include "still_kernels.h"\n'
+                   'int main() {\n  int nc, lam, n_ret;\n'
+                   '  while (std::scanf("%d %d %d", &nc, &lam, &n_ret) == 3) {\n    int last = -1;\n'
+                   '    for (int c = 0; c + 2 < nc; ++c) {\n      if (still::retained_row(c, lam, 0, n_ret) < 0) continue;\n'
+                   '      for (int pos = 0; pos < lam; ++pos) {\n        const int row = still::retained_row(c, lam, pos, n_ret);\n'
+                   '        last = row > last ? row : last;\n      }\n    }\n    std::printf("%d\\n", last);\n  }\n  return 0;\n}\n')
+    subprocess.run([build.HIPCC, "-x", "hip", "--cuda-host-only", "--offload-arch=gfx950", "-O1", "-std=c++17", "-w",
+                    "-I", build.CSRC, str(src), "-o", str(exe)], check=True)
+    rng, calls = random.Random(5), []
+    for _ in range(400):
+        kw = dict(B=rng.randint(1, 3), Hq=rng.choice([1, 4, 8]), d=rng.choice([64, 128]), C=rng.choice([64, 128]),
+                  N=rng.randint(1, 32768), max_retained=rng.choice([0, 1, 5, 64, 128, 200, 896, rng.randint(1, 4000)]))
+        kw.update(Hkv=1, lam=rng.choice([1, 7, 16, 32, kw["C"]]))
+        nc = -(-kw["N"] // kw["C"])
+        n_ret = max(0, nc - 2) * kw["lam"]
+        if kw["max_retained"]:
+            n_ret = min(n_ret, kw["max_retained"])
+        calls.append((kw, nc, n_ret))
+    text = "".join(f"{nc} {kw['lam']} {n_ret}\n" for kw, nc, n_ret in calls)
+    out = subprocess.run([str(exe)], input=text, check=True, capture_output=True, text=True).stdout.split()
+    short = 0
+    for (kw, nc, n_ret), last in zip(calls, map(int, out)):
+        L = S.still_bwd_workspace_layout(params(**kw))
+        assert last == n_ret - 1 and last < max(L.cap_t, 1), (kw, last)
+        assert L.dvret - L.dkret >= kw["B"] * kw["Hq"] * L.cap_t * kw["d"] * 4
+        short += (nc - 3) * kw["lam"] >= L.cap_t       # the first row of the last such chunk would lie behind the buffer
+    assert short > 50
