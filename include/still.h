@@ -281,6 +281,7 @@ STILL_API still_status_t still_state_init(const still_params_t* p, void* state, 
  *   - y_t = (N_SA + N_LA) / (D_SA + D_LA) over the retained cache, the local span and the state.
  *
  *   q_t [B, Hq, d], k_t, v_t [B, Hkv, d], g_t [B, Hq, d] or NULL, out_t [B, Hq, d]: device, dtype, contiguous.
+ *   out_t may lie over q_t, k_t or v_t (the step then takes one launch more) and may be g_t.
  *   Wq, Wk, bq, bk as for the prefill.
  * Returns STILL_ERR_STATE when t < 0 or t >= p->max_tokens.
  */

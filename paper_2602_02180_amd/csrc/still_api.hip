@@ -105,6 +105,15 @@ SideStream* side_stream() {
 
 inline size_t align_up(size_t x, size_t a) { return (x + a - 1) / a * a; }
 inline size_t esize(int dtype) { return dtype == STILL_BF16 ? 2 : 4; }
+// A range of memory (empty for a null pointer), and whether two of them meet.
+struct Span {
+  uintptr_t lo, hi;
+};
+inline Span flat_span(const void* x, size_t bytes) {
+  const uintptr_t lo = reinterpret_cast<uintptr_t>(x);
+  return {lo, x != nullptr ? lo + bytes : lo};
+}
+inline bool meet(const Span& a, const Span& b) { return a.lo < b.hi && b.lo < a.hi; }
 inline bool aligned16(const void* p) { return (reinterpret_cast<uintptr_t>(p) & 15) == 0; }
 inline int retained_budget(const still_params_t* p) { return p->max_retained > 0 ? p->max_retained : still::kNoBudget; }
 
@@ -768,6 +777,15 @@ still_status_t decode_step(const still_params_t* p, void* state, int32_t t, cons
   if (nsplit > (rows + 63) / 64) nsplit = (rows + 63) / 64;
   if (nsplit < 1) nsplit = 1;
   a.nsplit = nsplit;
+  // The step merges a head as soon as its parts are there, while other workgroups still read the token's rows (the score, the
+  // ring copy, other heads).  Where out_t lies over what they read, the merge is a launch behind them.  (Not g_t: only the
+  // merge reads it, each element by the thread that writes the output's.)
+  const size_t es = esize(p->dtype), rows_q = (size_t)p->B * p->Hq * p->d * es, rows_kv = (size_t)p->B * p->Hkv * p->d * es;
+  const Span read[] = {flat_span(q_t, rows_q), flat_span(k_t, rows_kv), flat_span(v_t, rows_kv),
+                       flat_span(Wq, (size_t)p->Hq * p->d * p->d_f * es), flat_span(bq, (size_t)p->Hq * p->d_f * es),
+                       flat_span(t_dev, (size_t)p->B * sizeof(int32_t))};
+  for (const Span& x : read) a.merge_apart = a.merge_apart || meet(flat_span(out_t, rows_q), x);
+  a.merge_apart = a.merge_apart || a.shared;
   // with per-sequence positions any sequence at a chunk start >= 2C routes; the others leave the kernel at once
   const bool route = t_dev != nullptr ? c >= 2 : ((t % p->C == 0) && c >= 2);
   hipError_t e = still::launch_decode_step(a, p->dtype, p->d, route, static_cast<hipStream_t>(stream_v));
@@ -897,16 +915,12 @@ void compute_bwd_layout(const still_params_t* p, still_bwd_ws_layout_t* L) {
   L->total = off;
 }
 
-// The bytes from a tensor's first element to its last (strides are never negative), and whether two such ranges meet.
-struct Span {
-  uintptr_t lo, hi;
-};
+// The bytes from a tensor's first element to its last (strides are never negative).
 Span strided_span(const still_params_t* p, const void* x, int64_t s_b, int64_t s_t, int64_t s_h, int H) {
   const int64_t elems = (p->B - 1) * s_b + (int64_t)(p->N - 1) * s_t + (H - 1) * s_h + p->d;
   const uintptr_t lo = reinterpret_cast<uintptr_t>(x);
   return {lo, x != nullptr ? lo + (uintptr_t)elems * esize(p->dtype) : lo};
 }
-bool meet(const Span& a, const Span& b) { return a.lo < b.hi && b.lo < a.hi; }
 
 still_status_t bwd_impl(const still_params_t* p, const void* q, const void* k, const void* v, const void* g,
                         const void* Wq, const void* bq, const void* Wk, const void* bk, const void* out,
@@ -966,13 +980,9 @@ still_status_t bwd_impl(const still_params_t* p, const void* q, const void* k, c
   const Span in_q = strided_span(p, q, p->q_sb, p->q_st, p->q_sh, Hq), in_k = strided_span(p, k, p->k_sb, p->k_st, p->k_sh, Hkv),
              in_v = strided_span(p, v, p->v_sb, p->v_st, p->v_sh, Hkv), in_g = strided_span(p, g, p->g_sb, p->g_st, p->g_sh, Hq),
              in_do = strided_span(p, dout, p->o_sb, p->o_st, p->o_sh, Hq);
-  auto flat = [](const void* x, size_t bytes) -> Span {
-    const uintptr_t lo = reinterpret_cast<uintptr_t>(x);
-    return {lo, x != nullptr ? lo + bytes : lo};
-  };
   const size_t bias_bytes = (size_t)Hq * p->d_f * esize(p->dtype);
-  const Span inputs[] = {in_q, in_k, in_v, in_g, in_do, flat(bq, bias_bytes), flat(bk, bias_bytes),
-                         flat(sel_idx, (size_t)U * ncf * p->lambda * 4)};
+  const Span inputs[] = {in_q, in_k, in_v, in_g, in_do, flat_span(bq, bias_bytes), flat_span(bk, bias_bytes),
+                         flat_span(sel_idx, (size_t)U * ncf * p->lambda * 4)};
   const Span results[] = {strided_span(p, dq, p->q_sb, p->q_st, p->q_sh, Hq), strided_span(p, dk, p->k_sb, p->k_st, p->k_sh, Hkv),
                           strided_span(p, dv, p->v_sb, p->v_st, p->v_sh, Hkv), strided_span(p, dg, p->g_sb, p->g_st, p->g_sh, Hq)};
   bool over = false;
@@ -987,7 +997,7 @@ still_status_t bwd_impl(const still_params_t* p, const void* q, const void* k, c
   // C = 64, 8 heads: 260 -> 217).  Results that lie over lse, which dk and dv still read when dq is written, take one
   // queue after the other, as they did.
   bool over_lse = false;
-  const Span in_lse = flat(lse, (size_t)U * N * 4);
+  const Span in_lse = flat_span(lse, (size_t)U * N * 4);
   for (const Span& r : results) over_lse = over_lse || meet(r, in_lse);
   hipStream_t s2 = stream;
   if (nc >= 4) side = side_stream();

@@ -11,7 +11,8 @@
 //     score  : Self-Saliency Score of token t over its window (Sec. 3.1), one thread per window key
 //     append : (k_t, v_t) into the ring of recent tokens (slot = t mod R)
 //     merge  : y = (N_SA + g*N_LA) / (D_SA + D_LA) over the partials, both branches scaled by exp(-max(m, 0)), by the
-//              workgroup that delivers a head's last partial (group-shared selection: in a launch of its own)
+//              workgroup that delivers a head's last partial (group-shared selection, or an output that lies over what
+//              others read: in a launch of its own)
 // The token's own key and value are read from the caller's rows, so nobody waits for the ring; its ring slot (that of
 // token t - R) lies outside every window and local span (W <= R, the span is at most 2C rows, R = 4C).
 // Everything is plain vector-ALU code with fp32 accumulation: there is no contraction here that could
@@ -944,7 +945,7 @@ __device__ __forceinline__ void decode_step_body(const DecArgs& a) {
   __shared__ int s_last;
   auto deliver = [&](int64_t unit) __attribute__((always_inline)) {
     if constexpr (!SHARED) {
-      if (last_delivery(a, unit, D, &s_last)) decode_merge<T, D>(a, unit);
+      if (a.merge_apart == 0 && last_delivery(a, unit, D, &s_last)) decode_merge<T, D>(a, unit);
     }
   };
   int i = blockIdx.x;
@@ -987,7 +988,8 @@ __global__ __launch_bounds__(256) void decode_step_shared_kernel(DecArgs a) {
   decode_step_body<T, D, true>(a);
 }
 
-// Group-shared selection merges in a launch of its own: there a workgroup has a part of every head of the group, and the last one
+// An output that lies over the token's rows is written when nobody reads them any more (merge_apart).  And group-shared selection
+// merges in a launch of its own: there a workgroup has a part of every head of the group, and the last one
 // would merge them all.  Merged in the step (heads counted at once, 256 / D merged at a time): 2 sequences behind 9000 tokens, 32 / 8
 // heads, d = 128, 16.9 -> 20.4 us, 40 behind 20000 136 -> 139, 1 behind 700 12.9 -> 12.8.
 template <typename T, int D>
@@ -1073,9 +1075,11 @@ hipError_t launch_decode_step(const DecArgs& a, int dtype, int d, bool route, hi
 #define CALL_MERGE(TT, DD) hipLaunchKernelGGL((decode_merge_kernel<TT, DD>), dim3(a.Hq, a.B), dim3(DD), 0, stream, a);
   if (a.shared) {
     STILL_DISPATCH(dtype, d, CALL_STEP_SHARED)
-    STILL_DISPATCH(dtype, d, CALL_MERGE)
   } else {
     STILL_DISPATCH(dtype, d, CALL_STEP)
+  }
+  if (a.merge_apart) {
+    STILL_DISPATCH(dtype, d, CALL_MERGE)
   }
   return hipGetLastError();
 }

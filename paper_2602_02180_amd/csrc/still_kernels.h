@@ -257,6 +257,7 @@ struct DecArgs {
   HeadMap map;
   int B, Hq, Hkv, C, W, lam, cap, R, nchunks, t, nsplit, rcap;
   int shared;              // 1: the query heads of one kv head rank by their summed score (one list per group)
+  int merge_apart;         // 1: the parts are merged by a launch of their own (always with shared)
   int gate_act;            // 1: g is a pre-activation, the gate is its logistic function
   int evict;               // 1: the budget is held by evicting the lowest score (ret_score, ret_tok are then kept)
   float* ret_score;        // [B, Hq, cap] score of every retained row

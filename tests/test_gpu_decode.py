@@ -638,3 +638,55 @@ def test_the_scratch_of_a_step_may_hold_anything(dtype, d, shared):
     assert torch.isfinite(got["zeros"]).all() and float(got["zeros"].abs().max()) > 0
     for name in ("ones", "bytes", "floats"):
         assert torch.equal(got[name], got["zeros"]), name
+
+
+@pytest.mark.parametrize("dtype,d,shared", [("f32", 64, 0), ("bf16", 128, 0), ("bf16", 64, 1)])
+@pytest.mark.parametrize("at", [False, True], ids=["step", "step_at"])
+def test_the_output_of_a_step_may_lie_over_its_inputs(dtype, d, shared, at):
+    """A serving loop may write y_t over q_t, k_t, v_t or the gate: output, scores and ring rows are those of a step with tensors of
+    its own, bit for bit, over steps with and without a routing (fifteen sequences: more workgroups than run at once)."""
+    import torch
+
+    B, Hq, Hkv, C, lam, T = 15, 32, 8, 64, 8, 70
+    dev, dt = "cuda", torch.float32 if dtype == "f32" else torch.bfloat16
+    gen = torch.Generator(device=dev)
+    gen.manual_seed(211)
+    rn = lambda *s: torch.randn(*s, generator=gen, device=dev).to(dt)
+    Wq, Wk = (rn(Hq, d, d) / d ** 0.5 for _ in range(2))
+    rows = [(rn(B, Hq, d), rn(B, Hkv, d), rn(B, Hkv, d), rn(B, Hq, d)) for _ in range(T)]
+    p = S.make_params(B=B, N=1, Hq=Hq, Hkv=Hkv, d=d, C=C, W=C, lam=lam, scale=d ** -0.5, eps=1e-6, dtype=dtype, max_tokens=4 * C,
+                      shared_selection=shared, gate_activation=1)
+    L, size = S.still_state_layout(p), S.still_state_bytes(p)
+    es = dt.itemsize
+    regions = [(L.score, B * Hq * L.R * 4), (L.kring, B * Hkv * L.R * d * es), (L.vring, B * Hkv * L.R * d * es)]
+    n_q, n_kv = B * Hq * d, B * Hkv * d
+
+    def walk(over):
+        state = torch.zeros(size, dtype=torch.uint8, device=dev)
+        S.still_state_init(p, state)
+        got = []
+        for i, (q, k, v, g) in enumerate(rows):
+            t = C + 1 + i                                        # (the tokens before it are zeros: the ring is all the same)
+            buf = torch.zeros(n_q + 2 * n_kv + n_q, dtype=dt, device=dev)   # q | k | v | gate, in one allocation
+            parts = buf[:n_q], buf[n_q:n_q + n_kv], buf[n_q + n_kv:n_q + 2 * n_kv], buf[n_q + 2 * n_kv:]
+            for x, y in zip(parts, (q, k, v, g)):
+                x.copy_(y.flatten())
+            o = {"none": torch.zeros(n_q, dtype=dt, device=dev), "q": parts[0], "k": buf[n_q:2 * n_q], "v": buf[n_q + n_kv - 64:2 * n_q + n_kv - 64],
+                 "g": parts[3]}[over]
+            if over in ("k", "v"):                               # (the gate would lie under the output's end: it has its own)
+                parts = parts[:3] + (g.flatten().clone(),)
+            if at:
+                pos = torch.full((B,), t, dtype=torch.int32, device=dev)
+                S.still_hybrid_attn_decode_step_at(p, state, pos, t, parts[0], parts[1], parts[2], parts[3], Wq, None, Wk, None, o)
+            else:
+                S.still_hybrid_attn_decode_step(p, state, t, parts[0], parts[1], parts[2], parts[3], Wq, None, Wk, None, o)
+            got.append(o.clone())
+        return torch.stack(got), [state[a:a + n].clone() for a, n in regions]
+
+    ref = walk("none")
+    assert torch.isfinite(ref[0]).all() and float(ref[0].abs().max()) > 0
+    for over in ("q", "k", "v", "g"):
+        out, seen = walk(over)
+        assert torch.equal(out, ref[0]), over
+        for x, y in zip(seen, ref[1]):
+            assert torch.equal(x, y), over
