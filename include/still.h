@@ -252,12 +252,12 @@ STILL_API const char* still_profile_kernel_name(int32_t i);
  *                                     (for inspection)
  *   ring dtype [B, Hkv, R, d] x 2     keys and values of the last R = 4*C tokens, slot = token % R
  *   sc   float [B, Hq, R]             Self-Saliency Score of the same tokens
- *   part float [B, Hq, 32, d+2]       scratch of a step: the splits' partials (at most 30), in slot 30 the count of
+ *   part float [B, Hq, 32, d+2]       scratch of a step: the splits' partials (at most 30), in slot 30 counts of
  *                                     delivered parts, in slot 31 the linear terms; need not be prepared
  *   rsc  float [B, Hq, cap]           budget_policy 1 only: Self-Saliency Score of every retained row
  *   rtok int32 [B, Hq, cap]           budget_policy 1 only: its token index (retained rows are then in no order)
  * The number of tokens seen is NOT stored: the caller passes the index t of the new token to every step.
- * The buffer can be copied or saved with plain memcpy.  p->N is ignored by the state functions.
+ * The buffer can be copied or saved with plain memcpy, not while a step runs on it.  p->N is ignored by the state functions.
  */
 STILL_API size_t still_state_bytes(const still_params_t* p);
 

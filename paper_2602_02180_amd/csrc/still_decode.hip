@@ -503,9 +503,10 @@ constexpr size_t decode_route_smem() {
 // The workgroup that delivers the last part of a (sequence, query head) merges them: as a launch of its own behind the step
 // the merge took 4 us of every step (one sequence behind 4 K tokens 10.9 -> 8.2 us, a request of 24 steps for eight sequences
 // 1129 -> 1054 us).
-// The counter holds a mark and the number of parts delivered, and the last delivery leaves the mark with zero.  Anything
-// else in its place (a new state, or one written before this slot was a counter) counts as zero, so that no caller
-// has to prepare it.  The parts come from every XCD, whose L2s do not see each other's writes: parts are written and read by
+// A counter holds a mark and the number of parts delivered, and the last delivery leaves the mark with zero.  Anything else in
+// its place (a new state, or one written before this slot held counters) counts as zero, so that no caller has to
+// prepare it.  Even and odd token indices have a counter each, and a step that completes clears both: what a step that never
+// completed has left (in a copy of the state taken while it ran) is gone after the next one.  The parts come from every XCD, whose L2s do not see each other's writes: parts are written and read by
 // device-scope operations on every value (past the L2s), a wave waits until its writes have arrived before the workgroup counts
 // itself, and the merging workgroup reads after it has seen the full count.  (Ordering plain accesses by an acquire-release
 // operation on the counter instead makes every workgroup write back and drop its XCD's L2: one sequence 10.9 -> 45 us.)
@@ -514,11 +515,12 @@ __device__ __forceinline__ float get_part(const float* p) { return __hip_atomic_
 constexpr unsigned long long kArrivalMark = 0x5ca1ab1e0ddba11ull << 8;   // 56 bits
 
 // all parts of the unit are there, and this workgroup is the one that delivered last (uniform over the workgroup)
-__device__ __forceinline__ bool last_delivery(const DecArgs& a, int64_t unit, int D, int* s_last) {
+__device__ __forceinline__ bool last_delivery(const DecArgs& a, int64_t unit, int t, int D, int* s_last) {
   asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // this wave's part has arrived
   __syncthreads();                                  // and every wave's
   if (threadIdx.x == 0) {
-    unsigned long long* cnt = reinterpret_cast<unsigned long long*>(a.part + (unit * 32 + kArrivalSlot) * (int64_t)(D + 2));
+    unsigned long long* slot = reinterpret_cast<unsigned long long*>(a.part + (unit * 32 + kArrivalSlot) * (int64_t)(D + 2));
+    unsigned long long* cnt = slot + (t & 1);
     const unsigned total = a.nsplit + 1; // the splits and the linear terms
     unsigned long long old = __hip_atomic_fetch_add(cnt, 1ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     unsigned n = (unsigned)(old & 255) + 1;
@@ -529,7 +531,10 @@ __device__ __forceinline__ bool last_delivery(const DecArgs& a, int64_t unit, in
       } while (!__hip_atomic_compare_exchange_strong(cnt, &old, kArrivalMark | n, __ATOMIC_RELAXED, __ATOMIC_RELAXED,
                                                      __HIP_MEMORY_SCOPE_AGENT));
     }
-    if (n == total) __hip_atomic_store(cnt, kArrivalMark, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    if (n == total) {
+      __hip_atomic_store(cnt, kArrivalMark, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      __hip_atomic_store(slot + (~t & 1), kArrivalMark, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    }
     *s_last = n == total;
   }
   __syncthreads();
@@ -943,9 +948,9 @@ __device__ __forceinline__ void decode_step_body(const DecArgs& a) {
     float sh[16];
   } lds;
   __shared__ int s_last;
-  auto deliver = [&](int64_t unit) __attribute__((always_inline)) {
+  auto deliver = [&](int64_t unit, int t) __attribute__((always_inline)) {
     if constexpr (!SHARED) {
-      if (a.merge_apart == 0 && last_delivery(a, unit, D, &s_last)) decode_merge<T, D>(a, unit);
+      if (a.merge_apart == 0 && last_delivery(a, unit, t, D, &s_last)) decode_merge<T, D>(a, unit);
     }
   };
   int i = blockIdx.x;
@@ -958,7 +963,7 @@ __device__ __forceinline__ void decode_step_body(const DecArgs& a) {
       decode_attend_shared<T, D>(a, split, h, b, t, lds.att);
     } else {
       decode_attend<T, D>(a, split, h, b, t, lds.att);
-      deliver((int64_t)b * a.Hq + h);
+      deliver((int64_t)b * a.Hq + h, t);
     }
     return;
   }
@@ -970,7 +975,7 @@ __device__ __forceinline__ void decode_step_body(const DecArgs& a) {
   if (t < 0) return;
   if (kind == 0) {
     decode_linear<T, D>(a, h, b, lds.lin);
-    deliver((int64_t)b * a.Hq + h);
+    deliver((int64_t)b * a.Hq + h, t);
   } else if (kind == 1) decode_score<T, D>(a, h, b, t, lds.sh);
   else decode_append<T>(a, h, b, t, D);
 }

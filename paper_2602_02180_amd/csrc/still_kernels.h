@@ -233,8 +233,8 @@ struct SaArgs {
   int AW;              //   all offers, each under its chunk's mask; AW = words per row = cap / 64)
 };
 
-// Slots of a decode step's scratch, 32 per unit: the splits of the salient cache, the counter of the workgroups that have
-// delivered their part (first eight bytes), the linear terms.
+// Slots of a decode step's scratch, 32 per unit, d + 2 words each: the splits of the salient cache, the counters of the
+// workgroups that have delivered their part (eight bytes each, for even and odd token indices), the linear terms.
 constexpr int kMaxSplits = 30, kArrivalSlot = 30, kLinearSlot = 31;
 struct DecArgs {
   float* S;            // [B, Hq, DP*(D+1)]

@@ -640,6 +640,40 @@ def test_the_scratch_of_a_step_may_hold_anything(dtype, d, shared):
         assert torch.equal(got[name], got["zeros"]), name
 
 
+@pytest.mark.parametrize("dtype,d", [("f32", 64), ("bf16", 128)])
+def test_what_an_unfinished_step_left_in_the_counters_is_harmless(dtype, d):
+    """A counter that holds the mark and a count is that of a step which never completed.  The steps after it give the same bits, also
+    those whose turn it is again (even and odd token indices have a counter each)."""
+    import torch
+
+    B, Hq, Hkv, C, T, n0 = 2, 4, 2, 64, 6, 150
+    dev, dt = "cuda", torch.float32 if dtype == "f32" else torch.bfloat16
+    gen = torch.Generator(device=dev)
+    gen.manual_seed(221)
+    rn = lambda *s: torch.randn(*s, generator=gen, device=dev).to(dt)
+    Wq, Wk = (rn(Hq, d, d) / d ** 0.5 for _ in range(2))
+    rows = [(rn(B, Hq, d), rn(B, Hkv, d), rn(B, Hkv, d)) for _ in range(T)]
+    p = S.make_params(B=B, N=1, Hq=Hq, Hkv=Hkv, d=d, C=C, W=C, lam=8, scale=d ** -0.5, eps=1e-6, dtype=dtype, max_tokens=4 * C)
+    L = S.still_state_layout(p)
+    got = []
+    for spoil in (False, True):
+        state = torch.zeros(S.still_state_bytes(p), dtype=torch.uint8, device=dev)
+        S.still_state_init(p, state)
+        outs = []
+        for i, (q, k, v) in enumerate(rows):
+            o = torch.zeros_like(q)
+            S.still_hybrid_attn_decode_step(p, state, n0 + i, q, k, v, None, Wq, None, Wk, None, o)
+            outs.append(o)
+            if spoil and i < 4:
+                counters = state[L.part:L.part + B * Hq * 32 * (d + 2) * 4].view(B * Hq, 32, (d + 2) * 4)[:, 30, :16].view(torch.int64)
+                mark = int(counters[0, 0])
+                assert mark & 255 == 0 and bool((counters == mark).all())
+                counters[:, (n0 + i) % 2] = mark + 1 + i % 3
+        got.append(torch.stack(outs))
+    assert torch.isfinite(got[0]).all() and float(got[0].abs().max()) > 0
+    assert torch.equal(got[0], got[1])
+
+
 @pytest.mark.parametrize("dtype,d,shared", [("f32", 64, 0), ("bf16", 128, 0), ("bf16", 64, 1)])
 @pytest.mark.parametrize("at", [False, True], ids=["step", "step_at"])
 def test_the_output_of_a_step_may_lie_over_its_inputs(dtype, d, shared, at):
