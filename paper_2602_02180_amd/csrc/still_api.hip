@@ -71,10 +71,22 @@ struct SideStream {
 };
 thread_local SideStream g_side;
 
-SideStream* side_stream() {
+// Between a captured call and the end of its capture the helper stream belongs to that capture: a call on a stream outside it
+// (eager, or in a capture of its own) that waited for the helper would be drawn into it, and the capture end unjoined.  Such
+// a call takes its own stream alone.
+bool in_another_capture(hipStream_t helper, hipStream_t stream) {
+  hipStreamCaptureStatus own = hipStreamCaptureStatusNone, his = hipStreamCaptureStatusNone;
+  unsigned long long own_id = 0, his_id = 0;
+  if (hipStreamGetCaptureInfo(helper, &own, &own_id) != hipSuccess) return true;
+  if (own == hipStreamCaptureStatusNone) return false;
+  return hipStreamGetCaptureInfo(stream, &his, &his_id) != hipSuccess || his != own || his_id != own_id;
+}
+
+// the helper stream for a call on `stream`, or nullptr
+SideStream* side_stream(hipStream_t stream) {
   int dev = -1;
   if (hipGetDevice(&dev) != hipSuccess) return nullptr;
-  if (g_side.ok && g_side.dev == dev) return &g_side;
+  if (g_side.ok && g_side.dev == dev) return in_another_capture(g_side.s, stream) ? nullptr : &g_side;
   if (g_side.ok) {   // the thread moved to another device: drop the old objects
     (void)hipEventDestroy(g_side.fork);
     (void)hipEventDestroy(g_side.join);
@@ -439,7 +451,7 @@ still_status_t fwd_impl(const still_params_t* p, const void* q, const void* k, c
   hipError_t e;
 
   // layout preparation, on the side stream (the caller's stream if it could not be created)
-  SideStream* side = two_streams ? side_stream() : nullptr;
+  SideStream* side = two_streams ? side_stream(stream) : nullptr;
   hipStream_t s2 = stream;
   if (side != nullptr) {
     if (hipEventRecord(side->fork, stream) == hipSuccess && hipStreamWaitEvent(side->s, side->fork, 0) == hipSuccess)
@@ -1000,7 +1012,7 @@ still_status_t bwd_impl(const still_params_t* p, const void* q, const void* k, c
   const Span in_lse = flat_span(lse, (size_t)U * N * 4);
   for (const Span& r : results) over_lse = over_lse || meet(r, in_lse);
   hipStream_t s2 = stream;
-  if (nc >= 4) side = side_stream();
+  if (nc >= 4) side = side_stream(stream);
   if (side != nullptr) {
     if (hipEventRecord(side->fork, stream) == hipSuccess && hipStreamWaitEvent(side->s, side->fork, 0) == hipSuccess)
       s2 = side->s;

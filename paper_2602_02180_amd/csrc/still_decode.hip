@@ -501,7 +501,7 @@ constexpr size_t decode_route_smem() {
 
 // ---------------------------------------------------------------- merge of the partials
 // The workgroup that delivers the last part of a (sequence, query head) merges them: as a launch of its own behind the step
-// the merge took 4 us of every step (one sequence behind 4 K tokens 10.9 -> 8.2 us, a request of 24 steps for eight sequences
+// the merge took 4 us of every step (one sequence behind 4 K tokens 10.6 -> 8.8 us, a request of 24 steps for eight sequences
 // 1129 -> 1054 us).
 // A counter holds a mark and the number of parts delivered, and the last delivery leaves the mark with zero.  Anything else in
 // its place (a new state, or one written before this slot held counters) counts as zero, so that no caller has to
@@ -509,7 +509,9 @@ constexpr size_t decode_route_smem() {
 // completed has left (in a copy of the state taken while it ran) is gone after the next one.  The parts come from every XCD, whose L2s do not see each other's writes: parts are written and read by
 // device-scope operations on every value (past the L2s), a wave waits until its writes have arrived before the workgroup counts
 // itself, and the merging workgroup reads after it has seen the full count.  (Ordering plain accesses by an acquire-release
-// operation on the counter instead makes every workgroup write back and drop its XCD's L2: one sequence 10.9 -> 45 us.)
+// operation on the counter instead makes every workgroup write back and drop its XCD's L2: one sequence 10.6 -> 45 us.  Where
+// the merge is always a launch of its own, with group-shared selection, plain accesses are no faster: 8 sequences behind 3000
+// tokens, d = 64, 14.5 us so and 14.8 with plain ones.)
 __device__ __forceinline__ void put_part(float* p, float x) { __hip_atomic_store(p, x, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
 __device__ __forceinline__ float get_part(const float* p) { return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
 constexpr unsigned long long kArrivalMark = 0x5ca1ab1e0ddba11ull << 8;   // 56 bits
@@ -938,7 +940,7 @@ __device__ __forceinline__ void decode_linear(const DecArgs& a, int hq, int b, L
 // what the splits leave idle (with the short ones first: 756 -> 773 us at 64 sequences behind 32 K tokens, 48 -> 53 us at
 // 24 sequences with 896 retained rows).  As launches of their own (score + append, attend, linear terms and merge in the last)
 // each of them paid its own start and tail.  Before -> now: one sequence behind 4 K tokens, 32 heads, d = 128, 27 us
-// (6.0 + 6.2 + 12.7 in the kernels) -> 8.2 us; 24 sequences with 896 retained rows, d = 64, 59 us (5.7 + 32 + 10) -> 48
+// (6.0 + 6.2 + 12.7 in the kernels) -> 8.8 us; 24 sequences with 896 retained rows, d = 64, 59 us (5.7 + 32 + 10) -> 48
 // us; 64 sequences behind 32 K tokens 782 (16 + 714 + 54) -> 755 us, 4.69 GB at 6.2 TB/s.
 template <typename T, int D, bool SHARED>
 __device__ __forceinline__ void decode_step_body(const DecArgs& a) {

@@ -614,3 +614,64 @@ def test_backward_on_two_queues(kw, how):
         call(g, dw, over)
         torch.cuda.synchronize()
         check(g, dw)
+
+
+@pytest.mark.parametrize("eager", ["backward", "forward"])
+def test_a_call_on_another_stream_stays_out_of_a_capture(eager):
+    """A thread that captures a backward pass on one stream may call the library eagerly on another before the capture ends: the
+    helper stream is part of the capture then, so the eager call does without it.  Its results are there at once, the
+    captured call's after a replay."""
+    import torch
+
+    w = small("capture", dtype="bf16", B=2, N=64 * 9 + 5, Hq=4, Hkv=2, lam=8)
+    sides = []
+    for seed in (231, 232):
+        inp = synth.make_inputs(w, seed=seed)
+        t = {n: synth.to_torch(inp[n], w.dtype, "cuda") for n in ("q", "k", "v", "Wq", "Wk")}
+        t["dout"], t["out"] = synth.to_torch(make_dy(w, inp, seed + 10), w.dtype, "cuda"), torch.empty_like(t["q"])
+        p = S.make_params(B=w.B, N=w.N, Hq=w.Hq, Hkv=w.Hkv, d=w.d, C=w.C, W=w.W, lam=w.lam, scale=w.scale, eps=w.eps,
+                          dtype=w.dtype, q=t["q"], k=t["k"], v=t["v"], out=t["out"])
+        t.update(sel=torch.zeros(w.B, w.Hq, w.N // w.C, w.lam, dtype=torch.int32, device="cuda"),
+                 ws=torch.empty(S.still_fwd_workspace_bytes(p), dtype=torch.uint8, device="cuda"),
+                 bws=torch.empty(S.still_bwd_workspace_bytes(p), dtype=torch.uint8, device="cuda"),
+                 dW=[torch.zeros(w.Hq, w.d, w.d, device="cuda") for _ in range(2)])
+        t.update({"d" + n: torch.zeros_like(t[n]) for n in ("q", "k", "v")})
+        L = S.still_fwd_workspace_layout(p)
+        t["lse"] = t["ws"][L.lse:L.lse + w.B * w.Hq * w.N * 4].view(torch.float32)
+        sides.append((p, t))
+
+    def forward(p, t, stream):
+        S.still_hybrid_attn_fwd(p, t["q"], t["k"], t["v"], None, t["Wq"], None, t["Wk"], None, t["out"], sel_idx=t["sel"],
+                                workspace=t["ws"], stream=stream)
+
+    def backward(p, t, stream):
+        S.still_hybrid_attn_bwd(p, t["q"], t["k"], t["v"], None, t["Wq"], None, t["Wk"], None, t["out"], t["dout"], t["lse"], t["sel"],
+                                t["dq"], t["dk"], t["dv"], None, t["dW"][0], None, t["dW"][1], None, t["bws"], stream=stream)
+
+    names = {"backward": ("dq", "dk", "dv"), "forward": ("out",)}
+    ref = []
+    for p, t in sides:
+        for call in (forward, backward):
+            call(p, t, torch.cuda.current_stream())
+        torch.cuda.synchronize()
+        ref.append({n: t[n].clone() for n in ("dq", "dk", "dv", "out")})
+        for n in names["backward"]:
+            t[n].fill_(7.0)
+    if eager == "forward":
+        sides[1][1]["out"].fill_(7.0)
+    torch.cuda.synchronize()
+    one, two, graph = torch.cuda.Stream(), torch.cuda.Stream(), torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph, stream=one):
+        backward(*sides[0], one)
+        (backward if eager == "backward" else forward)(*sides[1], two)
+    torch.cuda.synchronize()
+    for n in names[eager]:
+        assert torch.equal(sides[1][1][n], ref[1][n]), n
+    for n in names["backward"]:
+        assert bool((sides[0][1][n] == 7.0).all()), n            # captured, not run
+    for _ in range(3):
+        graph.replay()
+        torch.cuda.synchronize()
+        for n in names["backward"]:
+            assert torch.equal(sides[0][1][n], ref[0][n]), n
+            sides[0][1][n].fill_(7.0)
