@@ -1004,15 +1004,18 @@ still_status_t bwd_impl(const still_params_t* p, const void* q, const void* k, c
   // The softmax branch (row scalars, retained rows, dq, then dk and dv) and the forward pass's states need nothing of each
   // other, and the linear branch's query side and state gradient need only dq of it: two queues.  Small steps are chains
   // of launches that leave most of the chip idle (3 x 777 tokens, d = 64: 342 -> 280 us); at 16 x 1024 tokens both queues
-  // fill the chip (2571 -> 2502 us).  Below four chunks the linear branch has the rows of one chunk at most and the call is
-  // bound by the host, which pays about 40 us for the events (2 x 129 tokens, C = 128: 67 -> 104 us on two queues; 1 x 512,
-  // C = 64, 8 heads: 260 -> 217).  Results that lie over lse, which dk and dv still read when dq is written, take one
-  // queue after the other, as they did.
+  // fill the chip (2571 -> 2502 us).  The host pays for the events, which must hide behind the chain.  In bf16 at d = 64 that
+  // takes more than 512 tokens, whatever the heads and the batch: 8 / 8 heads, C = 64, on one queue and on two, calls in a row
+  // 92 / 104 us at 256 tokens, 102 / 107 at 384, 112 / 105 at 512, waited for one by one 110 / 120, 123 / 128, 133 / 132 (C = 128,
+  // 512 tokens: 124 / 129; 640: 135 / 136, in a row 116 / 103).  The longer products of d = 128 (256 tokens 139 / 120,
+  // waited for 154 / 150) and of fp32 (247 / 204, 266 / 239) hide them from four chunks on.  Below four chunks the linear branch
+  // has the rows of one chunk at most (2 x 129 tokens, C = 128: 67 / 104).  Results that lie over lse, which dk and dv still
+  // read when dq is written, take one queue after the other, as they did.
   bool over_lse = false;
   const Span in_lse = flat_span(lse, (size_t)U * N * 4);
   for (const Span& r : results) over_lse = over_lse || meet(r, in_lse);
   hipStream_t s2 = stream;
-  if (nc >= 4) side = side_stream(stream);
+  if (nc >= 4 && (N > 512 || d == 128 || dt == STILL_F32)) side = side_stream(stream);
   if (side != nullptr) {
     if (hipEventRecord(side->fork, stream) == hipSuccess && hipStreamWaitEvent(side->s, side->fork, 0) == hipSuccess)
       s2 = side->s;
