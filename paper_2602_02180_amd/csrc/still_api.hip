@@ -332,7 +332,9 @@ extern "C" {
 
 // 0.3.0: budget_policy in the params, more regions in both layouts
 // 0.4.0: backward pass, attention map, rotary pre-pass
-int32_t still_version(void) { return 500; }   // 0.5.0: state images in blocks, other regions in the backward workspace
+// 0.5.0: state images in blocks, other regions in the backward workspace
+// 0.5.1: values in tiles of 64 tokens, the blocks of the images in operand order, counters in the decode scratch
+int32_t still_version(void) { return 501; }
 
 const char* still_last_error(void) { return g_err; }
 

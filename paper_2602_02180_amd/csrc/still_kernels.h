@@ -130,7 +130,7 @@ struct KeepMaskArgs {
 // inside a block the order of an MFMA operand over features: [f / 8][x % 32, bit 2 flipped in the second half][f % 8].  An
 // accumulator tile's store covers 1 KB of one block, and a consumer's copy into LDS takes a block as it stands, 64 lanes
 // on 1 KB: blocks of [x % 32][f % 16] that the copy had to spread over rows cost its wave about 300 cycles per KB, a copy of
-// a run 70.  In LDS a block is then read both ways without bank conflicts (the flip is for the transposing reads).
+// a run about 100.  In LDS a block is then read both ways without bank conflicts (the flip is for the transposing reads).
 __host__ __device__ inline int state_image_offset(int x, int f, int DP) {
   const int h = (f >> 3) & 1;
   return ((x >> 5) * (DP >> 4) + (f >> 4)) * 512 + h * 256 + ((x & 31) ^ (h << 2)) * 8 + (f & 7);

@@ -272,10 +272,11 @@ __device__ __forceinline__ void sa_body(const SaArgs& a) {
   // Per-lane constants of the direct-to-LDS requests.  Request j of this wave fills the 1 KB LDS segment
   // number (wave + NW j) of a tile; lane L lands at segment + 16 L, i.e. at LDS (row, slot); it therefore
   // fetches the global 16-byte column  slot ^ swizzle(row)  of the key (K) or feature row (V^T) that LDS row
-  // holds.  Every request is "tile base (wave-uniform) + constant per-lane element offset".  Only the offsets
-  // into the retained buffers (the steady-state loop's) are kept in registers for the whole kernel; the few
-  // general steps of a workgroup rebuild theirs from the lane id, which costs a handful of integer operations
-  // per request and keeps eight to sixteen registers out of the loop's allocation.
+  // holds.  Tiles of retained keys, of values (both kinds) and of W_q^T are runs of memory: a wave's request j lies 16 NW
+  // lanes' bytes behind its request j - 1, in the tile as in LDS, i.e. a multiple of 16 rows (same row order, same swizzle) or,
+  // for the rows of 512 bytes of fp32 at d = 128, 8 rows (bit 3 of the swizzle alternates).  So one lane offset for keys and
+  // one for values, kept for the whole kernel, serve every request on top of a scalar base.  Local keys lie at the
+  // caller's strides: their few requests rebuild the lane's row and column.
   const int wave_s = __builtin_amdgcn_readfirstlane(wave);
   auto k_lane = [&](int lane_now, int j, int& key, int& col) __attribute__((always_inline)) {
     const int v = (wave_s + Cf::NW * j) * 64 + lane_now;     // 16-byte vector index inside the tile
@@ -288,11 +289,8 @@ __device__ __forceinline__ void sa_body(const SaArgs& a) {
     lrow = v / Cf::VVR;
     col = ((v % Cf::VVR) ^ Cf::vswz(lrow)) * Cf::EPV;
   };
-  // Tiles of retained keys, of values (both kinds) and of W_q^T are runs of memory, and a wave's request j lies 16 NW lanes'
-  // bytes behind its request j - 1, in the tile as in LDS: a multiple of 16 rows (same row order, same swizzle), or, for
-  // the rows of 512 bytes of fp32 at d = 128, 8 rows (bit 3 of the swizzle alternates).
   constexpr int STEP = Cf::NW * 1024, KROWS = STEP / (D * (int)sizeof(T));
-  static_assert(STEP % (16 * BN * (int)sizeof(T)) == 0 && (KROWS % 16 == 0 || KROWS == 8), "see above");
+  static_assert(STEP % (16 * BN * (int)sizeof(T)) == 0 && (KROWS % 16 == 0 || KROWS == 8), "a request keeps the row order and the swizzle, or flips one bit of it");
   auto k_at = [&](uint32_t off, int j) __attribute__((always_inline)) {
     return (KROWS == 8 && (j & 1) ? off ^ 128u : off) + (uint32_t)(j * STEP);
   };
