@@ -634,7 +634,7 @@ template <typename T, int D>
 __global__ __launch_bounds__(256, 2) void bwd_revscan_kernel(BwdRevscanArgs a) {
   typedef Mma<T> M;
   typedef RevCfg<T, D> Cf;
-  constexpr int BF = Cf::BF, DP = 2 * D, SK = 64 / M::KK, NT = BF / 64, SPT = M::STEPS_PER_TILE;
+  constexpr int BF = Cf::BF, DP = 2 * D, SK = 64 / M::KK, NT = BF / 64;
   typedef RowTile<T, 64> RA;
   typedef RowTile<T, BF> RP;
   constexpr int EPV = RA::EPV;
@@ -681,11 +681,7 @@ __global__ __launch_bounds__(256, 2) void bwd_revscan_kernel(BwdRevscanArgs a) {
 #pragma unroll
     for (int j = 0; j < NT; ++j) {
       const int x = 64 * xt + 32 * (NT == 2 ? j : xw) + M::kappa(r), f0 = BF * ft + 32 * fw;
-#pragma unroll
-      for (int s = 0; s < SPT; ++s) {
-        const int f = f0 + (M::KPL == 1 ? M::pos_of_reg(s, g) : s * M::KK + g * M::KPL);
-        *reinterpret_cast<typename M::frag*>(cp + state_image_offset(x, f, DP)) = M::from_acc(acc[j], s);
-      }
+      store_image_tile<M>(cp, x, f0, DP, g, acc[j]);
     }
     if (xt == 0 && 2 * pair < BF) {
       float z0 = dz0 + __shfl_xor(dz0, 16, 64), z1 = dz1 + __shfl_xor(dz1, 16, 64);

@@ -135,6 +135,22 @@ __host__ __device__ inline int state_image_offset(int x, int f, int DP) {
   const int h = (f >> 3) & 1;
   return ((x >> 5) * (DP >> 4) + (f >> 4)) * 512 + h * 256 + ((x & 31) ^ (h << 2)) * 8 + (f & 7);
 }
+// A lane's 16 entries of a product "32 features from f0 (rows) x rows x (columns)" into the image of row x: one address per half of
+// a block and constant offsets from it.  (With an offset per entry the fp32 instances held 16 addresses per product in
+// registers: la_kernel at d = 128, C = 64 spilled 2458 values instead of 448, and a call of 2 x 2048 tokens, 32 / 8 heads, took
+// 3.09 ms instead of 2.65.)
+template <typename M, typename T>
+__device__ __forceinline__ void store_image_tile(T* img, int x, int f0, int DP, int g, const floatx16& acc) {
+  if constexpr (M::KPL == 1) {             // entry s is feature f0 + 2 s + g
+    T* half[2] = {img + state_image_offset(x, f0, DP) + g, img + state_image_offset(x, f0 + 8, DP) + g};
+#pragma unroll
+    for (int s = 0; s < 16; ++s) half[(s >> 2) & 1][512 * (s >> 3) + ((2 * s) & 7)] = acc[s];
+  } else {                                 // entries 8 s .. 8 s + 7 are features f0 + 16 s + 8 g ..
+    T* p = img + state_image_offset(x, f0 + 8 * g, DP);
+#pragma unroll
+    for (int s = 0; s < 2; ++s) *reinterpret_cast<typename M::frag*>(p + 512 * s) = M::from_acc(acc, s);
+  }
+}
 // The piece of an image that a slab of 64 features holds in LDS: [x / 32][f / 16 of 4], blocks as in the image.  Element i of
 // the slab that starts at feature f0 lies here in the image.
 __host__ __device__ inline int state_slab_source(int i, int f0, int DP) {

@@ -74,7 +74,6 @@ __device__ __forceinline__ void la_body(const LaArgs& a) {
   typedef LaCfg<T, D, C> L;
   constexpr int DF = L::DF, DP = L::DP, RT = L::RT, NCW = L::NCW, FT = L::FT, PT = L::PT, KS = L::KS;
   constexpr int PTOK = L::PTOK, NPART = L::NPART, HS = L::HS;
-  constexpr int SPT = M::STEPS_PER_TILE;
 
   extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
   T* wl = reinterpret_cast<T*>(smem + 2 * L::phi_bytes);      // W_k^T in operand order (when it fits)
@@ -300,12 +299,7 @@ __device__ __forceinline__ void la_body(const LaArgs& a) {
     if (oc % G != 0 && oc >= 2) {
       T* sp = static_cast<T*>(a.snap) + (unit * a.nc + oc) * (int64_t)(D * DP);
 #pragma unroll
-      for (int ft = 0; ft < PT; ++ft)
-#pragma unroll
-        for (int s = 0; s < SPT; ++s) {
-          const int f = 32 * ft + (M::KPL == 1 ? M::pos_of_reg(s, gg) : s * M::KK + gg * M::KPL);
-          *reinterpret_cast<typename M::frag*>(sp + state_image_offset(32 * wave + rr, f, DP)) = M::from_acc(S[ft], s);
-        }
+      for (int ft = 0; ft < PT; ++ft) store_image_tile<M>(sp, 32 * wave + rr, 32 * ft, DP, gg, S[ft]);
     }
     a.zsnap[(unit * a.nc + oc) * DP + 64 * wave + lane_now] = z;
     if (a.s_final != nullptr && oc == nc_b - 1) {

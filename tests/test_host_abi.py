@@ -296,3 +296,20 @@ def test_the_backward_pass_reads_no_retained_row_behind_its_buffers(tmp_path):
         assert L.dvret - L.dkret >= kw["B"] * kw["Hq"] * L.cap_t * kw["d"] * 4
         short += (nc - 3) * kw["lam"] >= L.cap_t       # the first row of the last such chunk would lie behind the buffer
     assert short > 50
+
+
+def test_the_state_scan_spills_no_addresses(tmp_path):
+    """Registers of every instance of the scan, as the compiler reports them: its image store must not hold an address per entry
+    (in fp32 at d = 128, whose accumulators alone fill the register file, that was 2458 spilled values and a kernel
+    1.8 times as slow)."""
+    import subprocess
+
+    from paper_2602_02180_amd import build
+
+    run = subprocess.run([build.HIPCC, *build.FLAGS, "--cuda-device-only", "-c", os.path.join(build.CSRC, "still_la.hip"), "-o",
+                          str(tmp_path / "la.o"), "-Rpass-analysis=kernel-resource-usage"], check=True, capture_output=True, text=True)
+    found = re.findall(r"Function Name: (\S*la_kernel\S*)(?:.|\n)*?VGPRs Spill: (\d+)", run.stderr)
+    spills = {name: int(n) for name, n in found}
+    assert len(spills) == 16
+    for name, n in spills.items():
+        assert n <= (460 if "la_kernelIfLi128" in name else 0), (name, n)
